@@ -58,25 +58,6 @@ __device__ __forceinline__ float sum_across_rows16(float x) {
     return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
-// Multiplier 1/sqrt(mean(x^2) + eps) of one q row whose D channels are read by the four lanes (i, 0..3), lane
-// row g taking the 16-byte chunks 4 ks + g.
-template <int D>
-__device__ __forceinline__ float q_row_rstd16(const NormArgs& n, const void* q, int64_t base, int in_f32, int g,
-                                              int64_t stat) {
-    if (n.mode == 2) return n.rstd[stat];
-    float ss = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) {
-        float x[8];
-        load8(q, base + 8 * (4 * ks + g), in_f32, x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
-    }
-    ss += __shfl_xor(ss, 16);
-    ss += __shfl_xor(ss, 32);
-    return 1.0f / sqrtf(ss * (1.0f / D) + n.eps);
-}
-
 // NW = wavefronts per workgroup (4 or 8); a wavefront owns 32 query rows (two blocks of 16), the workgroup's
 // NW * 32 rows share every K/V tile in LDS.
 // The chained form keeps, behind the tile buffers, one area per wavefront the size of its 32 query rows in 16
@@ -123,10 +104,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     rg.Hg = pv.Hg;
     rg.Wg = pv.Wg;
 
-    // Query rows (16-bit inputs) are requested before anything else; they are converted after the first
-    // tiles have been requested.
     u32x4 Qf[2][NKS];
-    u32x4 qraw[2][NKS];
     int qrow[2];
     uint8_t* const qarea = smem + 4 * G::K_BYTES + wave * chain_stage_bytes<D>();  // chained form only
     constexpr int QPR = D / 8;  // 16-byte pieces per 16-bit query row
@@ -153,23 +131,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, 0);
         }
     };
-    auto request_q = [&](int qtile) {
-        if constexpr (CHAIN) {
-            request_q_lds(qtile);
-        } else if (!a.in_f32) {
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                const int row = qtile * BQ + wave * 32 + qb * 16 + i16;
-                const int qr = row < pv.Lq ? row : pv.Lq - 1;
-                const int64_t base = pv.q_off + (int64_t)qr * a.sq_t;
-#pragma unroll
-                for (int ks = 0; ks < NKS; ++ks)
-                    qraw[qb][ks] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.q) + base +
-                                                                  8 * (4 * ks + g4));
-            }
-        }
-    };
-    request_q(qt);
+    if constexpr (CHAIN) request_q_lds(qt);
 
     // ---- tile streaming (as in attn_pipe_body): a tile part is PART_KIB pieces of 1 KiB; wavefront w moves
     // pieces w, w+NW, ... of both parts; the two odd pieces of the K part go to wavefronts 0 and 1, those of
@@ -192,15 +154,11 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         else return (j == last && tail < kBK) ? ((1ull << tail) - 1ull) : ~0ull;
     };
     constexpr int NDMA = 2 * NI + 1;
-    auto dma_piece = [&](int i, int tk, int kb_, int tv, int vb_) {
+    auto dma_piece = [&](int i, int tk, int kb_, int tv, int vb_, uint32_t lane_off) {
         const uint8_t* ksrc = tiles + (size_t)tk * G::TILE_BYTES;
         const uint8_t* vsrc = tiles + (size_t)tv * G::TILE_BYTES + G::K_BYTES;
         uint8_t* kdst = kbuf + kb_ * G::K_BYTES;
         uint8_t* vdst = vbuf + vb_ * G::V_BYTES;
-        // (chained form: the empty statement keeps the compiler from carrying per-lane 64-bit addresses through
-        // the loop, two registers each, which it spilled there; uniform base + 32-bit lane offset instead)
-        uint32_t lane_off = lane * 16;
-        if constexpr (CHAIN) asm volatile("" : "+v"(lane_off));
         if (i < 2 * NI) {
             const int c = (wave + NW * (i >> 1)) * 1024;
             if ((i & 1) == 0) {
@@ -216,8 +174,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         }
     };
     auto dma_tiles = [&](int tk, int kb_, int tv, int vb_) {
+        // (the empty statement keeps the lane's offset a 32-bit value of this block: known ahead of the loop it is
+        // widened there, and every load then adds it to its uniform base on the vector ALU, two registers each)
+        uint32_t lane_off = lane * 16;
+        asm volatile("" : "+v"(lane_off));
 #pragma unroll
-        for (int i = 0; i < NDMA; ++i) dma_piece(i, tk, kb_, tv, vb_);
+        for (int i = 0; i < NDMA; ++i) dma_piece(i, tk, kb_, tv, vb_, lane_off);
     };
     auto dma_wait_and_sync = [&]() {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -501,10 +463,124 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     };
 
     // ---- prologue: tiles 0 (K, V) and 1 (K) start streaming, then Q is converted while they fly ----
-    if (n_steps > 0) {
-        const int t1 = last > 0 ? 1 : 0;
-        dma_tiles(0, 0, 0, 0);
-        dma_tiles(t1, 1, 0, 1);  // K'(1); its V part lands in a buffer iteration 0 refills anyway
+    auto first_tiles = [&]() {
+        if (n_steps > 0) {
+            const int t1 = last > 0 ? 1 : 0;
+            dma_tiles(0, 0, 0, 0);
+            dma_tiles(t1, 1, 0, 1);  // K'(1); its V part lands in a buffer iteration 0 refills anyway
+        }
+    };
+    // Query rows -> operand registers: normalise, rotate, fold scale*log2(e), round once (not the chained form, see
+    // convert_q_area).  Rows, rotation entries and the per-token factor are requested before the first tiles, in one
+    // go, and the arithmetic is one straight line per input type.  What bounds this stage is instructions and gathers
+    // (two wavefronts per SIMD, four clocks an instruction, and some thirty clocks of the address unit a gather): with
+    // a test of the input type, the normalisation and the rotation around every 16 bytes and a compare-and-select
+    // saturation a workgroup of 8 wavefronts took 17,800 clocks from its start to its first scores (21,000 with the
+    // normalisation), now 15,300 (16,700); 123.3 -> 119.5 us at 6,240 tokens x 4 heads, 333 -> 328 us at
+    // 3,600 tokens x 40 heads, long sequences level.
+    auto start_q = [&](auto f32_tag) {
+        constexpr bool F32 = decltype(f32_tag)::value;
+        u32x4 raw[2][NKS][F32 ? 2 : 1];
+        float2 cs[2][NKS][4];  // (cos, sin) of the lane's channel pairs at the row's position
+        float rs[2] = {1.f, 1.f};
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const int row = qt * BQ + wave * 32 + qb * 16 + i16;
+            const int qr = row < pv.Lq ? row : pv.Lq - 1;
+            const int64_t base = pv.q_off + (int64_t)qr * a.sq_t + 8 * g4;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                if constexpr (F32) {
+                    const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.q) + base + 32 * ks);
+                    raw[qb][ks][0] = src[0];
+                    raw[qb][ks][1] = src[1];
+                } else {
+                    raw[qb][ks][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.q) + base + 32 * ks);
+                }
+            }
+            int pt, ph, pw;
+            token_pos(qr, rg, pt, ph, pw);
+            const int h0 = rg.hd[0], h01 = rg.hd[0] + rg.hd[1];
+            const int bt = rg.off[0] + pt * rg.hd[0];
+            const int bh = rg.off[1] + ph * rg.hd[1] - h0;
+            const int bw = rg.off[2] + pw * rg.hd[2] - h01;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) {
+                    const int ip = 16 * ks + 4 * g4 + pp;
+                    const uint32_t idx = ip + (ip < h0 ? bt : ip < h01 ? bh : bw);
+                    cs[qb][ks][pp] = a.tab[idx];
+                }
+            if (a.qn.mode == 2) rs[qb] = a.qn.rstd[pv.stat_off + qr];
+        }
+        first_tiles();
+        float x[2][NKS][8];
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                if constexpr (F32) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[qb][ks][e] = __uint_as_float(raw[qb][ks][e >> 2][e & 3]);
+                } else {
+                    widen8(raw[qb][ks][0], x[qb][ks]);
+                }
+            }
+        if (a.qn.mode) {
+            if (a.qn.mode == 1) {  // a row's channels are read by the four lanes (i, 0..3)
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    float ss = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) ss = fmaf(x[qb][ks][e], x[qb][ks][e], ss);
+                    rs[qb] = 1.0f / sqrtf(sum_across_rows16(ss) * (1.0f / D) + a.qn.eps);
+                }
+            }
+            float4 g[NKS][2];
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) g[ks][0] = g[ks][1] = make_float4(1.f, 1.f, 1.f, 1.f);
+            if (a.qn.gamma) {
+                const float4* const src = reinterpret_cast<const float4*>(a.qn.gamma + (int64_t)pv.h * D + 8 * g4);
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    g[ks][0] = src[8 * ks];
+                    g[ks][1] = src[8 * ks + 1];
+                }
+            }
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float4 ge = g[ks][e >> 2];
+                        const float w = (e & 3) == 0 ? ge.x : (e & 3) == 1 ? ge.y : (e & 3) == 2 ? ge.z : ge.w;
+                        x[qb][ks][e] *= rs[qb] * w;
+                    }
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                float y[8];
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) {
+                    const float2 c = cs[qb][ks][pp];
+                    const float x0 = x[qb][ks][2 * pp], x1 = x[qb][ks][2 * pp + 1];
+                    y[2 * pp] = (x0 * c.x - x1 * c.y) * a.qscale;
+                    y[2 * pp + 1] = (x0 * c.y + x1 * c.x) * a.qscale;
+                }
+                Qf[qb][ks] = pack8<QK_OP>(y);
+            }
+    };
+    if constexpr (CHAIN) {
+        first_tiles();
+    } else {
+        if (a.in_f32) start_q(std::true_type{});
+        else start_q(std::false_type{});
     }
 
     int vs_run = 0;  // chained: the V^T buffer of the stream's current step
@@ -559,33 +635,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         // the rows of the next one, which arrive while this one is in its loop
         if (it == 0) convert_q_area(qt);
         else reset_state();
-        if (it + 1 < n_qt) request_q(qt + 1);
+        if (it + 1 < n_qt) request_q_lds(qt + 1);
     }
-    // ---- Q: rotate, fold scale*log2(e), round once, keep as B operands ----
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        qrow[qb] = qt * BQ + wave * 32 + qb * 16 + i16;
-        const int qr = qrow[qb] < pv.Lq ? qrow[qb] : pv.Lq - 1;
-        const int64_t base = pv.q_off + (int64_t)qr * a.sq_t;
-        if constexpr (!CHAIN) {
-            int pt = 0, ph = 0, pw = 0;
-            if (a.tab) token_pos(qr, rg, pt, ph, pw);
-            float rs = 1.f;
-            if (a.qn.mode) rs = q_row_rstd16<D>(a.qn, a.q, base, a.in_f32, g4, pv.stat_off + qr);
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                const int c = 4 * ks + g4;
-                float x[8];
-                if (a.in_f32) load8(a.q, base + 8 * c, 1, x);
-                else widen8(qraw[qb][ks], x);
-                if (a.qn.mode) norm8(x, a.qn, rs, pv.h, D, c);
-                if (a.tab) rope8(x, c, rg, a.tab, pt, ph, pw);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] *= a.qscale;
-                Qf[qb][ks] = pack8<QK_OP>(x);
-            }
-        }
-    }
+    for (int qb = 0; qb < 2; ++qb) qrow[qb] = qt * BQ + wave * 32 + qb * 16 + i16;
 
     if (n_steps > 0) {
         // scores of tile 0 become the first running maximum

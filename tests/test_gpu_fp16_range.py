@@ -102,3 +102,24 @@ def test_cross_attention_keys_beyond_fp16():
     out = B.dit_cross_attn_forward(qd, kd, vd, md, out_dtype=torch.float32, flags=BF16_ALL)
     torch.cuda.synchronize()
     compare(to_f64(out), ref_exact, what="k beyond fp16, bf16 operands: full range")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_infinities_saturate_and_nan_stays(dtype):
+    """v holds +-infinity and values past the range in either half of a pair of neighbouring channels: they count as
+    +-65504, and the other channel of the pair is untouched.  A NaN in v makes its channel NaN and no other."""
+    import torch
+
+    cfg = dict(B=1, grid=(2, 5, 9), H=1, D=64, split=(22, 20, 22), dtype=dtype, seed=79)
+    q, k, v = wl.self_attn_inputs(cfg)
+    widen = wl.bf16_bits_to_f32 if dtype == "bf16" else np.asarray
+    vf = widen(v).copy()
+    vf[0, 3, 0, 6], vf[0, 11, 0, 9], vf[0, 40, 0, 20], vf[0, 41, 0, 21] = np.inf, -np.inf, BIG, -BIG
+    ref = oracle.self_attn(widen(q), widen(k), np.clip(vf, -F16_MAX, F16_MAX), cfg["grid"], cfg["split"])
+    vf[0, 17, 0, 33] = np.nan
+    v_in = wl.f32_to_bf16_bits(vf) if dtype == "bf16" else vf
+    out = B.dit_attn_forward(to_dev(q), to_dev(k), to_dev(v_in), cfg["grid"], cfg["split"], out_dtype=torch.float32)
+    got = to_f64(out)
+    assert np.all(np.isnan(got[..., 33]))
+    keep = [c for c in range(64) if c != 33]
+    compare(got[..., keep], ref[..., keep], what="infinities in v (%s)" % dtype)
