@@ -84,8 +84,9 @@ enum {
     DIT_FLAG_SIMPLE_SCHEDULE = 1u << 7,
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
-     * rows, two workgroups per CU.  Neither flag: BIG when that still gives every CU at least
-     * two workgroups, else SMALL. */
+     * rows, two workgroups per CU.  Neither flag: the one whose rounds of workgroups fill the chip
+     * better; dit_attn_forward may then (or with BIG) also compute the query tiles of a partly filled
+     * last round in pieces along the keys. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,
     DIT_FLAG_SMALL_WORKGROUP = 1u << 9,
     /* Cross-attention runs the plain kernel by default: with a dozen key tiles per query tile its
@@ -174,7 +175,9 @@ typedef struct {
     dit_qk_norm norm;      /* zero = off */
 } dit_self_attn_params;
 
-/* Bytes of workspace dit_attn_forward needs for these params (0 on invalid params). */
+/* Bytes of workspace dit_attn_forward needs for these params (0 on invalid params).  Where the call would compute some
+ * query tiles in pieces along the keys this includes room for the pieces (at most 135 MB); a workspace that holds
+ * everything but them is accepted too, and the tiles are then computed whole. */
 size_t dit_attn_workspace_bytes(const dit_self_attn_params *p);
 
 /*

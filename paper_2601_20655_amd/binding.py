@@ -319,6 +319,16 @@ def _check_workspace(what, workspace, need, device):
             what, workspace.numel() * workspace.element_size(), need))
 
 
+def _workspace_floor(workspace, params, need, query):
+    """Bytes below which the self-attention entry points refuse a workspace: `need` less the room for pieces of query
+    tiles, which 4-wavefront workgroups never use."""
+    if workspace.numel() * workspace.element_size() >= need:
+        return need
+    p = type(params).from_buffer_copy(params)
+    p.flags = (p.flags & ~DIT_FLAG_BIG_WORKGROUP) | DIT_FLAG_SMALL_WORKGROUP
+    return query(p)
+
+
 def _workspace(nbytes, device):
     import torch
 
@@ -352,7 +362,7 @@ def dit_attn_forward(q, k, v, grid, split, out=None, lse=None, origin=(0, 0, 0),
     need = dit_attn_workspace_bytes(p)
     if workspace is None:
         workspace = _workspace(need, q.device)
-    _check_workspace("dit_attn_forward", workspace, need, q.device)
+    _check_workspace("dit_attn_forward", workspace, _workspace_floor(workspace, p, need, dit_attn_workspace_bytes), q.device)
     st = lib().dit_attn_forward(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                 lse.data_ptr() if lse is not None else None, ctypes.byref(p),
                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -496,7 +506,8 @@ def dit_attn_varlen_forward(q, k, v, grids, split, out=None, lse=None, origin=(0
     need = dit_attn_varlen_workspace_bytes(p)
     if workspace is None:
         workspace = _workspace(need, q.device)
-    _check_workspace("dit_attn_varlen_forward", workspace, need, q.device)
+    _check_workspace("dit_attn_varlen_forward", workspace,
+                     _workspace_floor(workspace, p, need, dit_attn_varlen_workspace_bytes), q.device)
     st = lib().dit_attn_varlen_forward(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                        lse.data_ptr() if lse is not None else None, ctypes.byref(p),
                                        workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -567,7 +578,7 @@ def dit_qkv_proj_forward(x, w, bias, grid, split, H, q_out=None, origin=(0, 0, 0
     need = dit_attn_workspace_bytes(ap)
     if workspace is None:
         workspace = _workspace(need, x.device)
-    _check_workspace("dit_qkv_proj_forward", workspace, need, x.device)
+    _check_workspace("dit_qkv_proj_forward", workspace, _workspace_floor(workspace, ap, need, dit_attn_workspace_bytes), x.device)
     st = lib().dit_qkv_proj_forward(x.data_ptr(), w.data_ptr(), bias.data_ptr() if bias is not None else None,
                                     q_out.data_ptr(), ctypes.byref(lp), ctypes.byref(ap), workspace.data_ptr(),
                                     workspace.numel() * workspace.element_size(), _stream_ptr(stream))

@@ -110,6 +110,8 @@ dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused,
         e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (chain16) {
         e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, s);
+    } else if (mfma16 && aa.split.n_tail > 0) {
+        e = dit::launch_attn_pipe16_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (mfma16) {
         e = dit::launch_attn_pipe16(aa, D, fl.qk_op, fl.pv_op, fl.nw, s);
     } else if (!fused && !fl.simple) {
@@ -197,8 +199,55 @@ struct SelfPlan {
     int64_t L;
     int nKT, nQT;
     int table_entries;
-    size_t tab_off, tiles_off, rstd_off, total;
+    size_t tab_off, tiles_off, rstd_off;
+    size_t base;  // bytes without which the call is refused
+    // Query tiles of the last round computed in pieces, where that pays: 8 wavefronts (split_nQT query tiles a head)
+    // and this much more workspace, from base on.  A workspace of fewer than `total` bytes gets the whole-tile form.
+    dit::SplitPlan split;
+    int split_nQT;
+    size_t total;
 };
+
+// How the self-attention kernel on 16x16x32 MFMAs is laid over the chip.  Estimates of its time in key-tile steps of an
+// 8-wavefront workgroup (one per compute unit, 256 query rows; 1.2 to 1.45 us a step at head_dim 128), from runs over
+// 21 shapes of 320 to 75,600 tokens and 2 to 40 heads, both head dimensions:
+//   - a workgroup's start and end cost 7.5 steps, the end of a piece one more;
+//   - with 4 wavefronts (128 rows) a compute unit holds two workgroups, which together take 1.04 of the 8-wavefront
+//     step; one alone takes 0.83 of it;
+//   - combining P pieces costs a launch and 2 x 256 rows of fp32 each: 3 + 0.037 P steps.
+// The measured order of the forms follows these numbers wherever they are more than a few per cent apart: e.g. (tokens,
+// heads) 3,600 x 3: 62.7 us in whole tiles, 40.1 in 5 pieces each; 6,240 x 4: 101.8 and 86.6 (2 pieces); 3,600 x 40:
+// 262 and 258 (last 88 of 600 tiles in 2 pieces); 75,600 x 2: 5,294 and 4,395 (last 80 of 592 in 3 pieces); level or
+// slower in pieces, and left whole: 1,560 x 12 (33.1 and 37.2), 6,307 x 20 (336 and 357), 20,280 x 3 (497 and 518).
+constexpr int kCUs = 256;  // compute units of the chip
+constexpr double kEnds = 7.5;
+constexpr int kMaxPieces = 1024;  // 134 MB of workspace at head_dim 128
+
+double whole_tile_steps(int64_t tiles, int nKT, int nw) {  // tiles of 32 nw query rows
+    if (nw == 8) return (double)((tiles + kCUs - 1) / kCUs) * (nKT + kEnds);
+    const int64_t pairs = tiles / (2 * kCUs), rest = tiles - pairs * 2 * kCUs;
+    return (nKT + kEnds) * (1.04 * pairs + (rest == 0 ? 0.0 : rest <= kCUs ? 0.83 : 1.04));
+}
+
+// nw: the form that runs the tiles whole; tiles, tiles_nw: query tiles of 256 and of 32 nw rows
+dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int nKT, int nw) {
+    dit::SplitPlan best{0, 0, 1};
+    double best_steps = 0.97 * whole_tile_steps(tiles_nw, nKT, nw);
+    const int64_t rounds = tiles / kCUs;
+    if (tiles % kCUs == 0 || tiles > (1 << 20)) return best;
+    for (int64_t r = rounds; r >= 0 && r >= rounds - 1; --r) {  // rounds of whole tiles
+        const int64_t tail = tiles - r * kCUs;
+        for (int np = 2; np <= 16 && tail * np <= kMaxPieces && nKT / np >= 6; ++np) {
+            const double steps = r * (nKT + kEnds) + (double)((tail * np + kCUs - 1) / kCUs) * ((double)nKT / np + kEnds + 1) +
+                                 3.0 + 0.037 * (double)(tail * np);
+            if (steps < best_steps) {
+                best_steps = steps;
+                best = dit::SplitPlan{(int)(r * kCUs), (int)tail, np};
+            }
+        }
+    }
+    return best;
+}
 
 dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -233,8 +282,11 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     if (pl->fl.fused || pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;  // only the pipelined 32-rows-per-wavefront kernel has the 8-wavefront form
     } else if (pl->fl.nw == 0) {
-        // 8 wavefronts when 256-row workgroups still cover the 256 CUs at least twice over
-        pl->fl.nw = ((L + 255) / 256) * p->B * p->H >= 512 ? 8 : 4;
+        const int64_t t8 = ((L + 255) / 256) * p->B * p->H, t4 = ((L + 127) / 128) * p->B * p->H;
+        if (self_attn_uses_mfma16(pl->fl))
+            pl->fl.nw = whole_tile_steps(t8, pl->nKT, 8) <= whole_tile_steps(t4, pl->nKT, 4) ? 8 : 4;
+        else  // 8 wavefronts when 256-row workgroups still cover the 256 CUs at least twice over
+            pl->fl.nw = t8 >= 512 ? 8 : 4;
     }
     const int bq = 32 * pl->fl.nw * pl->fl.qb;
     pl->nQT = (int)((L + bq - 1) / bq);
@@ -245,9 +297,30 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     pl->tiles_off = round_up((size_t)pl->table_entries * sizeof(float2), kAlign);
     size_t tiles = pl->fl.fused ? 0 : (size_t)p->B * p->H * pl->nKT * dit::tile_bytes(p->D);
     pl->rstd_off = pl->tiles_off + round_up(tiles, kAlign);
-    pl->total = pl->rstd_off + rstd_bytes(p->norm, (int64_t)p->B * L, (int64_t)p->B * L);
-    if (pl->total == 0) pl->total = kAlign;
+    pl->base = pl->rstd_off + rstd_bytes(p->norm, (int64_t)p->B * L, (int64_t)p->B * L);
+    if (pl->base == 0) pl->base = kAlign;
+    pl->total = pl->base;
+    pl->split = dit::SplitPlan{0, 0, 1};
+    if (self_attn_uses_mfma16(pl->fl) && !(p->flags & DIT_FLAG_SMALL_WORKGROUP)) {
+        pl->split_nQT = (int)((L + 255) / 256);
+        pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H, pl->nKT, pl->fl.nw);
+        if (pl->split.n_tail > 0)
+            pl->total = pl->base + round_up(dit::part_o_bytes((int64_t)pl->split.n_tail * pl->split.n_piece, p->D), kAlign) +
+                        round_up(dit::part_ml_bytes((int64_t)pl->split.n_tail * pl->split.n_piece), kAlign);
+    }
     return DIT_OK;
+}
+
+// The split of a plan, if the workspace holds its pieces: fills the kernel's arguments and switches the plan to it.
+void apply_split(SelfPlan* pl, int D, uint8_t* ws, size_t workspace_bytes, dit::AttnArgs* aa) {
+    if (pl->split.n_tail == 0 || workspace_bytes < pl->total) return;
+    pl->fl.nw = 8;
+    pl->nQT = pl->split_nQT;
+    aa->nQT = pl->nQT;
+    aa->split = pl->split;
+    aa->part_o = reinterpret_cast<float*>(ws + pl->base);
+    aa->part_ml = reinterpret_cast<float2*>(
+        ws + pl->base + round_up(dit::part_o_bytes((int64_t)pl->split.n_tail * pl->split.n_piece, D), kAlign));
 }
 
 struct VarlenPlan {
@@ -255,10 +328,116 @@ struct VarlenPlan {
     dit::VarlenTable vt;
     int maxT, maxHg, maxWg;
     int table_entries;
-    size_t tab_off, tiles_off, rstd_off, total;
+    size_t tab_off, tiles_off, rstd_off;
+    size_t base, total;     // as in SelfPlan
+    size_t part_ml_off;     // with pieces: their row statistics (their outputs start at base)
+    dit::SplitPlan single;  // one request: its split as dit_attn_forward would have it
 };
 
-dit_status plan_varlen(const dit_varlen_attn_params* p, VarlenPlan* pl) {
+// Time, in the steps of whole_tile_steps, until `slots` workgroups at a time have worked off the classes of equal
+// workgroups in the order given (longest first); *half: until half of the slots have nothing left to do.
+struct PackedClass {
+    int64_t count;
+    double steps;
+};
+double work_off(const PackedClass* c, int n, int64_t slots, double* half = nullptr) {
+    struct Group {
+        double at;
+        int64_t slots;
+    } g[2 * DIT_MAX_REQUESTS + 8];
+    int ng = 1;
+    g[0] = Group{0.0, slots};  // ascending in time
+    for (int i = 0; i < n; ++i) {
+        int64_t left = c[i].count;
+        while (left > 0) {
+            const int64_t k = left < g[0].slots ? left : g[0].slots;
+            const double end = g[0].at + c[i].steps;
+            left -= k;
+            g[0].slots -= k;
+            if (g[0].slots == 0) {
+                --ng;
+                for (int j = 0; j < ng; ++j) g[j] = g[j + 1];
+            }
+            int j = ng;
+            while (j > 0 && g[j - 1].at > end) --j;
+            if (j > 0 && g[j - 1].at == end) {
+                g[j - 1].slots += k;
+            } else if (ng < (int)(sizeof(g) / sizeof(g[0]))) {
+                for (int m = ng; m > j; --m) g[m] = g[m - 1];
+                g[j] = Group{end, k};
+                ++ng;
+            } else {
+                g[j < ng ? j : ng - 1].slots += k;
+            }
+        }
+    }
+    if (half) {
+        int64_t done = 0;
+        int i = 0;
+        for (; i < ng - 1 && done + g[i].slots < slots / 2; ++i) done += g[i].slots;
+        *half = g[i].at;
+    }
+    return g[ng - 1].at;
+}
+
+// Several packed requests: wavefronts per workgroup, and pieces per query tile of each request, by the numbers that
+// choose_split goes by.  A request is cut into pieces of at most one length common to all; batches of more than six
+// rounds of workgroups are left whole (their last round is a small part of them).
+void choose_packed(const dit::VarlenTable& vt, int H, uint32_t flags, int* nw, int* pieces) {
+    PackedClass c8[DIT_MAX_REQUESTS], c4[DIT_MAX_REQUESTS];
+    int64_t n8 = 0, n4 = 0;
+    for (int r = 0; r < vt.n; ++r) {
+        const dit::ReqDesc& d = vt.r[r];
+        c8[r] = PackedClass{(int64_t)H * ((d.L + 255) / 256), d.nKT + kEnds};
+        c4[r] = PackedClass{(int64_t)H * ((d.L + 127) / 128), d.nKT + kEnds};
+        n8 += c8[r].count;
+        n4 += c4[r].count;
+    }
+    if (n8 > 6 * kCUs) {
+        if (*nw == 0) *nw = 8;
+        return;
+    }
+    const double t8 = work_off(c8, vt.n, kCUs);
+    double half4 = 0.0;  // from here on at most one workgroup per compute unit is left
+    const double all4 = work_off(c4, vt.n, 2 * kCUs, &half4);
+    const double t4 = 1.04 * half4 + 0.83 * (all4 - half4);
+    if (*nw == 0) *nw = t8 <= t4 ? 8 : 4;
+    if (flags & DIT_FLAG_SMALL_WORKGROUP) return;
+    double best = 0.97 * (*nw == 8 ? t8 : t4);
+    int best_len = 0;
+    const int longest = vt.r[0].nKT;
+    auto pieces_of = [](int nKT, int len) {
+        int np = (nKT + len - 1) / len;
+        if (np > nKT / 6) np = nKT / 6;
+        return np > 16 ? 16 : np < 1 ? 1 : np;
+    };
+    for (int cut : {2, 3, 4, 5, 6, 8, 12, 16}) {
+        const int len = (longest + cut - 1) / cut;
+        if (len < 6) break;
+        PackedClass c[DIT_MAX_REQUESTS];
+        int64_t total = 0;
+        for (int r = 0; r < vt.n; ++r) {
+            const int np = pieces_of(vt.r[r].nKT, len);
+            PackedClass k{c8[r].count * np, (double)vt.r[r].nKT / np + kEnds + (np > 1 ? 1 : 0)};
+            if (np > 1) total += k.count;
+            int j = r;
+            for (; j > 0 && c[j - 1].steps < k.steps; --j) c[j] = c[j - 1];
+            c[j] = k;
+        }
+        if (total > kMaxPieces) break;
+        const double t = work_off(c, vt.n, kCUs) + 3.0 + 0.037 * (double)total;
+        if (t < best) {
+            best = t;
+            best_len = len;
+        }
+    }
+    if (best_len == 0) return;
+    *nw = 8;
+    for (int r = 0; r < vt.n; ++r) pieces[r] = pieces_of(vt.r[r].nKT, best_len);
+}
+
+// workspace_bytes: what the call has (the plan of a workspace query assumes that everything fits)
+dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, VarlenPlan* pl) {
     if (!p || !p->grids) return DIT_ERR_INVALID_ARG;
     if (p->n_requests < 1 || p->H < 1 || p->D < 1) return DIT_ERR_INVALID_ARG;
     if (p->n_requests > DIT_MAX_REQUESTS) return DIT_ERR_UNSUPPORTED;
@@ -297,8 +476,6 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, VarlenPlan* pl) {
         order[i] = i;
     }
     if (total > (1 << 24)) return DIT_ERR_UNSUPPORTED;  // token indices are 32-bit with room for tile padding
-    if (pl->fl.nw == 0) pl->fl.nw = big_blocks >= 512 ? 8 : 4;
-    const int bq = 32 * pl->fl.nw;
     // longest request first (stable, so equal lengths keep the caller's order)
     for (int i = 1; i < n; ++i) {
         const int o = order[i];
@@ -311,7 +488,6 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, VarlenPlan* pl) {
     vt.n = n;
     vt.total_tokens = (int)total;
     int tile0 = 0;
-    int64_t queue[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int r = 0; r < n; ++r) {
         const int i = order[r];
         dit::ReqDesc& d = vt.r[r];
@@ -320,27 +496,76 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, VarlenPlan* pl) {
         d.Hg = p->grids[i].Hg;
         d.Wg = p->grids[i].Wg;
         d.nKT = (int)((Ls[i] + dit::kBK - 1) / dit::kBK);
-        d.nQT = (int)((Ls[i] + bq - 1) / bq);
         d.tile0 = tile0;
         tile0 += d.nKT;
-        // the kernel's rule: XCD x takes heads h with (r*H + h) % 8 == x
-        for (int x = 0; x < 8; ++x) {
-            const int h_first = (x - r * p->H) & 7;
-            const int heads = h_first < p->H ? (p->H - h_first + 7) >> 3 : 0;
-            queue[x] += (int64_t)heads * d.nQT;
-        }
     }
     vt.total_tiles = tile0;
-    int64_t qmax = 0;
-    for (int x = 0; x < 8; ++x) qmax = queue[x] > qmax ? queue[x] : qmax;
-    if (8 * qmax > 0x7fffffffLL || (int64_t)tile0 * p->H > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
-    vt.queue_len = (int)qmax;
+    if ((int64_t)tile0 * p->H > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
 
     pl->table_entries = pl->maxT * (p->d_t / 2) + pl->maxHg * (p->d_h / 2) + pl->maxWg * (p->d_w / 2);
     pl->tab_off = 0;
     pl->tiles_off = round_up((size_t)pl->table_entries * sizeof(float2), kAlign);
     pl->rstd_off = pl->tiles_off + round_up((size_t)tile0 * p->H * dit::tile_bytes(p->D), kAlign);
-    pl->total = pl->rstd_off + rstd_bytes(p->norm, total, total);
+    pl->base = pl->rstd_off + rstd_bytes(p->norm, total, total);
+    pl->total = pl->base;
+    pl->single = dit::SplitPlan{0, 0, 1};
+    int pieces[DIT_MAX_REQUESTS];
+    for (int r = 0; r < n; ++r) pieces[r] = 1;
+    if (!self_attn_uses_mfma16(pl->fl)) {
+        if (pl->fl.nw == 0) pl->fl.nw = big_blocks >= 512 ? 8 : 4;
+    } else if (n == 1) {
+        // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit
+        const int64_t t8 = ((total + 255) / 256) * p->H, t4 = ((total + 127) / 128) * p->H;
+        const int nKT = vt.r[0].nKT;
+        if (pl->fl.nw == 0) pl->fl.nw = whole_tile_steps(t8, nKT, 8) <= whole_tile_steps(t4, nKT, 4) ? 8 : 4;
+        if (!(p->flags & DIT_FLAG_SMALL_WORKGROUP)) pl->single = choose_split(t8, pl->fl.nw == 8 ? t8 : t4, nKT, pl->fl.nw);
+    } else {
+        choose_packed(vt, p->H, p->flags, &pl->fl.nw, pieces);
+    }
+    int64_t n_pieces = (int64_t)pl->single.n_tail * pl->single.n_piece;
+    for (int r = 0; r < n; ++r)
+        if (pieces[r] > 1) n_pieces += (int64_t)pieces[r] * p->H * ((vt.r[r].L + 255) / 256);
+    if (n_pieces > 0)
+        pl->total = pl->base + round_up(dit::part_o_bytes(n_pieces, p->D), kAlign) + round_up(dit::part_ml_bytes(n_pieces), kAlign);
+    pl->part_ml_off = pl->base + round_up(dit::part_o_bytes(n_pieces, p->D), kAlign);
+    if (n_pieces > 0 && workspace_bytes < pl->total) {  // no room for the pieces: whole tiles
+        for (int r = 0; r < n; ++r) pieces[r] = 1;
+        pl->single = dit::SplitPlan{0, 0, 1};
+    }
+    if (pl->single.n_tail > 0) pl->fl.nw = 8;
+
+    // query tiles, pieces, and the order the workgroups are handed out in: longest first
+    const int bq = 32 * pl->fl.nw;
+    int64_t queue[8] = {0, 0, 0, 0, 0, 0, 0, 0}, piece0 = 0;
+    vt.split_tiles = 0;
+    for (int r = 0; r < n; ++r) {
+        dit::ReqDesc& d = vt.r[r];
+        d.nQT = (d.L + bq - 1) / bq;
+        d.n_piece = pieces[r];
+        d.piece0 = (int)piece0;
+        if (d.n_piece > 1) {
+            piece0 += (int64_t)p->H * d.nQT * d.n_piece;
+            vt.split_tiles += p->H * d.nQT;
+        }
+        int j = r;
+        for (; j > 0; --j) {
+            const dit::ReqDesc& o = vt.r[vt.order[j - 1]];
+            if ((int64_t)o.nKT * d.n_piece >= (int64_t)d.nKT * o.n_piece) break;
+            vt.order[j] = vt.order[j - 1];
+        }
+        vt.order[j] = r;
+    }
+    for (int i = 0; i < n; ++i) {
+        const dit::ReqDesc& d = vt.r[vt.order[i]];
+        const int64_t blocks = (int64_t)p->H * d.n_piece * d.nQT;
+        if (blocks > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
+        // the kernel's rule: XCD x takes range (x + i) % 8 of the eight the request's workgroups are cut into
+        for (int x = 0; x < 8; ++x) queue[x] += (blocks >> 3) + (((x + i) & 7) < (blocks & 7) ? 1 : 0);
+    }
+    int64_t qmax = 0;
+    for (int x = 0; x < 8; ++x) qmax = queue[x] > qmax ? queue[x] : qmax;
+    if (8 * qmax > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
+    vt.queue_len = (int)qmax;
     return DIT_OK;
 }
 
@@ -434,7 +659,7 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     if (!pl.fl.resident && (!aligned16(k, p->sk, p->in_dtype) || !aligned16(v, p->sv, p->in_dtype)))
         return DIT_ERR_ALIGNMENT;
     if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return DIT_ERR_ALIGNMENT;
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.total)
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.base)
         return DIT_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -499,6 +724,7 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     aa.rg = rg;
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
+    apply_split(&pl, p->D, ws, workspace_bytes, &aa);
     return run_attn(aa, p->D, pl.fl, pl.fl.fused, self_attn_uses_mfma16(pl.fl), s);
 }
 
@@ -608,14 +834,14 @@ dit_status dit_cross_attn_forward_lengths(const void* q, const void* k, const vo
 
 size_t dit_attn_varlen_workspace_bytes(const dit_varlen_attn_params* p) {
     VarlenPlan pl;
-    return plan_varlen(p, &pl) == DIT_OK ? pl.total : 0;
+    return plan_varlen(p, SIZE_MAX, &pl) == DIT_OK ? pl.total : 0;
 }
 
 dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, void* out, float* lse,
                                    const dit_varlen_attn_params* p, void* workspace, size_t workspace_bytes,
                                    void* stream) {
     VarlenPlan pl;
-    dit_status st = plan_varlen(p, &pl);
+    dit_status st = plan_varlen(p, workspace_bytes, &pl);
     if (st != DIT_OK) return st;
     if (!q || !out) return DIT_ERR_INVALID_ARG;
     if (!pl.fl.resident && (!k || !v)) return DIT_ERR_INVALID_ARG;
@@ -623,7 +849,7 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     if (!pl.fl.resident && (!aligned16(k, p->sk, p->in_dtype) || !aligned16(v, p->sv, p->in_dtype)))
         return DIT_ERR_ALIGNMENT;
     if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return DIT_ERR_ALIGNMENT;
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.total)
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.base)
         return DIT_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -680,7 +906,10 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     aa.tiles = pa.tiles;
     aa.tab = ta.tab;
     aa.B = 1; aa.H = p->H; aa.Lq = pl.vt.total_tokens; aa.Lk = pl.vt.total_tokens;
-    aa.nKT = pl.vt.total_tiles; aa.nQT = 0;
+    aa.nKT = pl.vt.total_tiles; aa.nQT = pl.vt.r[0].nQT;  // (one request: as in dit_attn_forward)
+    aa.split = pl.single;
+    aa.part_o = reinterpret_cast<float*>(ws + pl.base);
+    aa.part_ml = reinterpret_cast<float2*>(ws + pl.part_ml_off);
     aa.in_f32 = p->in_dtype == DIT_F32; aa.out_f32 = p->out_dtype == DIT_F32;
     aa.sq_t = p->sq.token; aa.sq_h = p->sq.head;
     aa.so_t = p->so.token; aa.so_h = p->so.head;
@@ -692,6 +921,7 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     e = pl.fl.qk_op == dit::OP_FP8
             ? dit::launch_attn_pipe_varlen_fp8(aa, pl.vt, p->D, pl.fl.pv_op, pl.fl.nw, s)
+            : pl.single.n_tail > 0 ? dit::launch_attn_pipe16_split(aa, p->D, pl.fl.qk_op, pl.fl.pv_op, s)
             : self_attn_uses_mfma16(pl.fl)
                   ? dit::launch_attn_pipe16_varlen(aa, pl.vt, p->D, pl.fl.qk_op, pl.fl.pv_op, pl.fl.nw, s)
                   : dit::launch_attn_pipe_varlen(aa, pl.vt, p->D, pl.fl.qk_op, pl.fl.pv_op, pl.fl.nw, s);
@@ -760,7 +990,7 @@ dit_status dit_qkv_proj_forward(const void* x, const void* w, const void* bias, 
     if ((uintptr_t)x % 16 || (uintptr_t)w % 16 || (lp->ldx * 2) % 16 || (lp->ldw * 2) % 16 || (uintptr_t)bias % 8)
         return DIT_ERR_ALIGNMENT;
     if (!aligned16(q_out, ap->sq, DIT_BF16)) return DIT_ERR_ALIGNMENT;
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.total)
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.base)
         return DIT_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);

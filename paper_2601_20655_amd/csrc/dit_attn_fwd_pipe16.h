@@ -77,7 +77,10 @@ constexpr int chain_lds_bytes() { return 4 * TileGeom<D>::PART_KIB * 1024 + NW *
 // first score tile.  For sequences of a few key tiles (cross-attention: 8 to 13) the start-up of a workgroup
 // -- query rows and first tiles from memory, one after the other -- is otherwise as long as its loop.  The
 // chained form keeps every wavefront on the same side of the barrier (no stagger).
-template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false>
+//
+// PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
+// leaves its unnormalised output, running maxima and row sums in piece pv.piece of a.part_o / a.part_ml.
+template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
     constexpr int NKS = D / 32;        // MFMAs of one score chain
@@ -105,7 +108,6 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     rg.Wg = pv.Wg;
 
     u32x4 Qf[2][NKS];
-    int qrow[2];
     uint8_t* const qarea = smem + 4 * G::K_BYTES + wave * chain_stage_bytes<D>();  // chained form only
     constexpr int QPR = D / 8;  // 16-byte pieces per 16-bit query row
     // chained form: this wavefront's 32 rows of query tile `qtile` -> its area, piece p of row r in slot
@@ -637,9 +639,6 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         else reset_state();
         if (it + 1 < n_qt) request_q_lds(qt + 1);
     }
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) qrow[qb] = qt * BQ + wave * 32 + qb * 16 + i16;
-
     if (n_steps > 0) {
         // scores of tile 0 become the first running maximum
         // (chained, later query tiles: the tiles are there, and the barrier that ended the step before has been passed)
@@ -655,6 +654,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             m_run[qb] = mx_new[qb];
+            // (bf16 score operands can overflow to -inf for a whole tile; a piece may START with such a tile)
+            if constexpr (PIECES && QK_OP == OP_BF16) m_run[qb] = fmaxf(m_run[qb], -3.0e38f);
 #pragma unroll
             for (int r = 0; r < 4; ++r) negm[qb][r] = -m_run[qb];
 #pragma unroll
@@ -779,17 +780,34 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
         else stage_and_store(std::integral_constant<int, 2>());
     } else {
+    const int ln = opaque_lane();  // (nothing of the epilogue's addresses is held through the key loop)
+    const int li = ln & 15, lg = ln >> 4;
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
+        const int row = qt * BQ + wave * 32 + qb * 16 + li;
         float l = l_run[qb];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
+        if constexpr (PIECES) {
+            if (pv.piece >= 0) {  // in the lanes' own order: 1 KiB of consecutive bytes per store
+                const int64_t blk = ((int64_t)pv.piece * NW + wave) * 2 + qb;
+                float4* const dst = reinterpret_cast<float4*>(a.part_o) + blk * NCB * 64 + ln;
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) {
+                    const int e = 4 * (cb % 4);
+                    dst[cb * 64] = make_float4(O[cb / 4][qb][e], O[cb / 4][qb][e + 1], O[cb / 4][qb][e + 2],
+                                               O[cb / 4][qb][e + 3]);
+                }
+                if (lg == 0) a.part_ml[blk * 16 + li] = make_float2(m_run[qb], l);
+                continue;
+            }
+        }
         const float inv = l > 0.f ? 1.0f / l : 0.f;
-        if (qrow[qb] < pv.Lq) {
-            const int64_t obase = pv.o_off + (int64_t)qrow[qb] * a.so_t;
+        if (row < pv.Lq) {
+            const int64_t obase = pv.o_off + (int64_t)row * a.so_t;
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
-                const int d0 = 16 * cb + 4 * g4;
+                const int d0 = 16 * cb + 4 * lg;
                 const int e = 4 * (cb % 4);
                 const float o0 = O[cb / 4][qb][e] * inv, o1 = O[cb / 4][qb][e + 1] * inv;
                 const float o2 = O[cb / 4][qb][e + 2] * inv, o3 = O[cb / 4][qb][e + 3] * inv;
@@ -800,9 +818,9 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                         make_uint2(pack2<OP_BF16>(o0, o1), pack2<OP_BF16>(o2, o3));
                 }
             }
-            if (a.lse && g4 == 0) {
+            if (a.lse && lg == 0) {
                 const float v = l > 0.f ? (m_run[qb] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
-                a.lse[pv.lse_off + qrow[qb]] = v;
+                a.lse[pv.lse_off + row] = v;
             }
         }
     }
@@ -836,36 +854,119 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_kernel(const AttnA
     attn_pipe16_body<D, QK_OP, PV_OP, NW>(a, pv);
 }
 
-// Packed requests of different lengths: work distribution as attn_fwd_pipe_varlen_kernel.
-template <int D, int QK_OP, int PV_OP, int NW>
-__global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(const AttnArgs a, const VarlenTable vt) {
-    const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3;
-    int r = 0, h_first = 0;
-    for (; r < vt.n; ++r) {
-        h_first = (xcd - r * a.H) & 7;
-        const int heads = h_first < a.H ? (a.H - h_first + 7) >> 3 : 0;
-        const int nblk = heads * vt.r[r].nQT;
-        if (idx < nblk) break;
-        idx -= nblk;
-    }
-    if (r == vt.n) return;  // uniform over the workgroup, before any barrier
-    const ReqDesc& rq = vt.r[r];
+// The same with the query tiles of the last, partly filled round cut into pieces along the keys (AttnArgs::split):
+// the first n_full workgroups take whole query tiles, the others one piece each, all pieces of one key range before
+// those of the next so that neighbouring workgroups stream the same key tiles.
+template <int D, int QK_OP, int PV_OP>
+__global__ void __launch_bounds__(512, 2) attn_fwd_pipe16_split_kernel(const AttnArgs a) {
+    const int n_full = a.split.n_full, n_tail = a.split.n_tail, n_piece = a.split.n_piece;
+    const bool whole = (int)blockIdx.x < n_full;
+    // (n_full is a multiple of 8: a workgroup's XCD is its index modulo 8 on both sides)
+    const int logical = whole ? xcd_contiguous(blockIdx.x, n_full) : xcd_contiguous(blockIdx.x - n_full, n_tail * n_piece);
     PipeView pv;
-    pv.qt = idx % rq.nQT;
-    pv.h = h_first + 8 * (idx / rq.nQT);
-    pv.b = 0;
-    pv.Lq = rq.L;
-    pv.Lk = rq.L;
-    pv.nKT = rq.nKT;
-    pv.tiles = a.tiles + ((size_t)rq.tile0 * a.H + (size_t)pv.h * rq.nKT) * TileGeom<D>::TILE_BYTES;
-    pv.q_off = (int64_t)rq.tok0 * a.sq_t + (int64_t)pv.h * a.sq_h;
-    pv.o_off = (int64_t)rq.tok0 * a.so_t + (int64_t)pv.h * a.so_h;
-    pv.lse_off = (int64_t)pv.h * vt.total_tokens + rq.tok0;
-    pv.stat_off = rq.tok0;
-    pv.Hg = rq.Hg;
-    pv.Wg = rq.Wg;
-    attn_pipe16_body<D, QK_OP, PV_OP, NW>(a, pv);
+    pv.piece = whole ? -1 : logical;
+    const int tile = whole ? logical : n_full + logical % n_tail;
+    const int bh = tile / a.nQT;
+    pv.qt = tile % a.nQT;
+    pv.b = bh / a.H;
+    pv.h = bh - pv.b * a.H;
+    // key tiles [k0, k1) of the sequence; n_piece <= nKT
+    const int s = whole ? 0 : logical / n_tail, ns = whole ? 1 : n_piece;
+    const int k0 = (int)((int64_t)a.nKT * s / ns), k1 = (int)((int64_t)a.nKT * (s + 1) / ns);
+    pv.Lq = a.Lq;
+    pv.nKT = k1 - k0;
+    pv.Lk = (a.Lk < k1 * kBK ? a.Lk : k1 * kBK) - k0 * kBK;
+    pv.tiles = a.tiles + ((size_t)bh * a.nKT + k0) * TileGeom<D>::TILE_BYTES;
+    pv.q_off = (int64_t)pv.b * a.sq_b + (int64_t)pv.h * a.sq_h;
+    pv.o_off = (int64_t)pv.b * a.so_b + (int64_t)pv.h * a.so_h;
+    pv.lse_off = ((int64_t)pv.b * a.H + pv.h) * a.Lq;
+    pv.stat_off = (int64_t)pv.b * a.Lq;
+    pv.Hg = a.rg.Hg;
+    pv.Wg = a.rg.Wg;
+    attn_pipe16_body<D, QK_OP, PV_OP, 8, false, true>(a, pv);
+}
+
+// Puts the pieces of a query tile together: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, M = max_s m_s.  A
+// wavefront takes 16 rows (block rb of the tile), in the layout the pieces were left in; memory-bound (it reads every
+// piece once; writing, reading and the launch together cost what 3 + 0.037 key-tile steps a piece would, see
+// choose_split).  6,240 tokens x 4 heads, whole call: 120 -> 101 us.  Pieces: first, first + stride, ...
+template <int D>
+__device__ __forceinline__ void combine_rows(const AttnArgs& a, int64_t first, int stride, int n_piece, int rb, int row,
+                                             int Lq, int64_t o_off, int64_t lse_off) {
+    constexpr int NCB = D / 16;
+    const int lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
+    float m = -INFINITY;
+    for (int s = 0; s < n_piece; ++s) m = fmaxf(m, a.part_ml[((first + (int64_t)s * stride) * 16 + rb) * 16 + i16].x);
+    float l = 0.f;
+    float4 o[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) o[cb] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s = 0; s < n_piece; ++s) {
+        const int64_t blk = (first + (int64_t)s * stride) * 16 + rb;
+        const float2 ml = a.part_ml[blk * 16 + i16];
+        const float4* const src = reinterpret_cast<const float4*>(a.part_o) + blk * NCB * 64 + lane;
+        float4 x[NCB];
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) x[cb] = src[cb * 64];
+        const float w = __builtin_amdgcn_exp2f(ml.x - m);
+        l = fmaf(w, ml.y, l);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) {
+            o[cb].x = fmaf(w, x[cb].x, o[cb].x);
+            o[cb].y = fmaf(w, x[cb].y, o[cb].y);
+            o[cb].z = fmaf(w, x[cb].z, o[cb].z);
+            o[cb].w = fmaf(w, x[cb].w, o[cb].w);
+        }
+    }
+    if (row >= Lq) return;
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    const int64_t obase = o_off + (int64_t)row * a.so_t + 4 * g4;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+        const float o0 = o[cb].x * inv, o1 = o[cb].y * inv, o2 = o[cb].z * inv, o3 = o[cb].w * inv;
+        if (a.out_f32)
+            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + obase + 16 * cb) = make_float4(o0, o1, o2, o3);
+        else
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + obase + 16 * cb) =
+                make_uint2(pack2<OP_BF16>(o0, o1), pack2<OP_BF16>(o2, o3));
+    }
+    if (a.lse && g4 == 0)
+        a.lse[lse_off + row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a) {
+    const int rb = (blockIdx.x & 3) * 4 + (threadIdx.x >> 6);
+    const int t = blockIdx.x >> 2, tile = a.split.n_full + t;
+    const int bh = tile / a.nQT, qt = tile % a.nQT, b = bh / a.H, h = bh - b * a.H;
+    combine_rows<D>(a, t, a.split.n_tail, a.split.n_piece, rb, qt * 256 + rb * 16 + (threadIdx.x & 15), a.Lq,
+                    (int64_t)b * a.so_b + (int64_t)h * a.so_h, (int64_t)bh * a.Lq);
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) attn_combine_varlen_kernel(const AttnArgs a, const VarlenTable vt) {
+    const int rb = (blockIdx.x & 3) * 4 + (threadIdx.x >> 6);
+    int t = blockIdx.x >> 2, r = 0;
+    for (; r < vt.n; ++r) {
+        const int tiles = vt.r[r].n_piece > 1 ? a.H * vt.r[r].nQT : 0;
+        if (t < tiles) break;
+        t -= tiles;
+    }
+    if (r == vt.n) return;
+    const ReqDesc& rq = vt.r[r];
+    const int h = t / rq.nQT, qt = t - h * rq.nQT;
+    combine_rows<D>(a, rq.piece0 + h * rq.n_piece * rq.nQT + qt, rq.nQT, rq.n_piece, rb,
+                    qt * 256 + rb * 16 + (threadIdx.x & 15), rq.L, (int64_t)rq.tok0 * a.so_t + (int64_t)h * a.so_h,
+                    (int64_t)h * vt.total_tokens + rq.tok0);
+}
+
+// Packed requests of different lengths: work distribution in varlen_view.  PIECES: some requests' tiles are computed
+// in pieces (8 wavefronts only).
+template <int D, int QK_OP, int PV_OP, int NW, bool PIECES>
+__global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(const AttnArgs a, const VarlenTable vt) {
+    PipeView pv;
+    if (!varlen_view<D>(a, vt, pv)) return;  // uniform over the workgroup, before any barrier
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, false, PIECES>(a, pv);
 }
 
 // Cross-attention with one joint softmax per request: workgroups chain `qch` query tiles of one (request, head).
@@ -939,15 +1040,34 @@ hipError_t launch_attn_pipe16_inst(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int D, int QK_OP, int PV_OP, int NW>
+template <int D, int QK_OP, int PV_OP>
+hipError_t launch_attn_pipe16_split_inst(const AttnArgs& a, hipStream_t s) {
+    auto kern = attn_fwd_pipe16_split_kernel<D, QK_OP, PV_OP>;
+    constexpr int smem = pipe_lds_bytes<D, 8>();
+    static std::atomic<uint64_t> attr_set{0};
+    hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.split.n_full + a.split.n_tail * a.split.n_piece)), dim3(512), smem, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_combine_kernel<D>, dim3((unsigned)(4 * a.split.n_tail)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int D, int QK_OP, int PV_OP, int NW, bool PIECES>
 hipError_t launch_attn_pipe16_varlen_inst(const AttnArgs& a, const VarlenTable& vt, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_varlen_kernel<D, QK_OP, PV_OP, NW>;
+    auto kern = attn_fwd_pipe16_varlen_kernel<D, QK_OP, PV_OP, NW, PIECES>;
     constexpr int smem = pipe_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(8 * vt.queue_len)), dim3(64 * NW), smem, s, a, vt);
-    return hipGetLastError();
+    e = hipGetLastError();
+    if constexpr (PIECES) {
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(attn_combine_varlen_kernel<D>, dim3((unsigned)(4 * vt.split_tiles)), dim3(256), 0, s, a, vt);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace dit

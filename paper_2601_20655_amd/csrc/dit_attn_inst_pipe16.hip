@@ -23,6 +23,14 @@ hipError_t launch_attn_pipe16(const AttnArgs& a, int D, int qk_op, int pv_op, in
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_op, hipStream_t s) {
+#define DIT_CASE(DD, QK, PV) \
+    if (D == DD && qk_op == QK && pv_op == PV) return launch_attn_pipe16_split_inst<DD, QK, PV>(a, s);
+    DIT_PIPE16_CASES(DIT_CASE)
+#undef DIT_CASE
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, hipStream_t s) {
 #define DIT_CASE(DD, QK, PV)                                 \
     if (D == DD && qk_op == QK && pv_op == PV)                \
@@ -37,8 +45,9 @@ hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, i
                                      hipStream_t s) {
 #define DIT_CASE(DD, QK, PV)                                                            \
     if (D == DD && qk_op == QK && pv_op == PV)                                           \
-        return nw == 8 ? launch_attn_pipe16_varlen_inst<DD, QK, PV, 8>(a, vt, s)         \
-                       : launch_attn_pipe16_varlen_inst<DD, QK, PV, 4>(a, vt, s);
+        return vt.split_tiles > 0 ? launch_attn_pipe16_varlen_inst<DD, QK, PV, 8, true>(a, vt, s)   \
+               : nw == 8          ? launch_attn_pipe16_varlen_inst<DD, QK, PV, 8, false>(a, vt, s)  \
+                                  : launch_attn_pipe16_varlen_inst<DD, QK, PV, 4, false>(a, vt, s);
     DIT_PIPE16_CASES(DIT_CASE)
 #undef DIT_CASE
     return hipErrorInvalidValue;

@@ -96,6 +96,16 @@ struct PackArgs {
     NormArgs kn;  // normalisation of k rows (rstd indexed by b*Lk + key, packed requests: by token)
 };
 
+// Self-attention in 256-row query tiles, one workgroup per compute unit at a time: the last round of workgroups is
+// rarely full.  The query tiles [n_full, n_full + n_tail) are computed in n_piece pieces each, every piece a range of
+// the key tiles, and put together by attn_combine_kernel.  n_tail = 0: no tile is.
+struct SplitPlan {
+    int n_full, n_tail, n_piece;
+};
+// room for the outputs and for the row statistics of `pieces` pieces
+inline size_t part_o_bytes(int64_t pieces, int D) { return (size_t)pieces * 256 * D * sizeof(float); }
+inline size_t part_ml_bytes(int64_t pieces) { return (size_t)pieces * 256 * sizeof(float) * 2; }
+
 struct AttnArgs {
     const void* q;
     void* out;
@@ -116,6 +126,9 @@ struct AttnArgs {
     RopeGeom rg;
     float qscale;  // softmax scale * log2(e), folded into q'
     NormArgs qn;   // normalisation of q rows (rstd indexed by b*Lq + row, packed requests: by token)
+    SplitPlan split;  // self-attention, 8 wavefronts: which query tiles are computed in pieces
+    float* part_o;    // the pieces' unnormalised outputs, [piece][16-row block][channel block][lane] of float4
+    float2* part_ml;  // their running maxima (base 2) and row sums, [piece][row]
 };
 
 // Several requests with their own latent grids packed back to back along the token axis
@@ -128,14 +141,18 @@ struct ReqDesc {
     int nKT;     // key tiles
     int nQT;     // query tiles
     int tile0;   // key tiles of all earlier table entries (per head)
-    int pad_;
+    int n_piece;  // > 1: every query tile is computed in this many pieces along the keys
+    int piece0;   // with pieces: index of the request's first one; piece s of (head, query tile) is
+                  // piece0 + (head * n_piece + s) * nQT + query tile
 };
-// Table order is the order workgroups are handed out in (longest request first), not token order.
+// Table order (which is the order of the tile images) is by length, longest request first.
 struct VarlenTable {
     int n;             // requests
     int total_tokens;  // sum of L
     int total_tiles;   // sum of nKT
     int queue_len;     // workgroups per XCD queue; the grid is 8 * queue_len
+    int split_tiles;   // query tiles, over all heads, of the requests that are computed in pieces (0: none is)
+    int order[kMaxRequests];  // table entries in the order their workgroups are handed out: longest workgroups first
     ReqDesc r[kMaxRequests];
 };
 
@@ -164,6 +181,8 @@ hipError_t launch_attn_pipe_varlen(const AttnArgs& a, const VarlenTable& vt, int
 hipError_t launch_prepack(const PackArgs& a, int D, int qk_op, int pv_op, hipStream_t s);
 // pipelined self-attention on 16x16x32 MFMAs (16-bit operands, 32 rows per wavefront, tiles packed with v_layout 1)
 hipError_t launch_attn_pipe16(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, hipStream_t s);
+// the same with a.split.n_tail > 0 (8 wavefronts only): the pieces, then their combination
+hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_op, hipStream_t s);
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, hipStream_t s);

@@ -1,0 +1,87 @@
+"""Self-attention whose query tiles are computed in pieces along the keys and put together afterwards: shapes in which
+every tile is (fewer tiles than compute units) and in which only those of the last round are, ragged on both sides
+(last key tile, last query tile), both head dimensions, both output types; against the oracle, and against the
+whole-tile form that a workspace without room for the pieces gets."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_20655_amd import binding as B
+from paper_2601_20655_amd import workloads as wl
+from gpu_util import compare, to_dev, to_f64
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # batch, grid, heads, head_dim, dtype of the inputs, flags
+    (1, (1, 45, 77), 3, 128, "bf16", 0),                      # all tiles, 55 key tiles, last one of 9 keys
+    (2, (3, 31, 33), 12, 128, "f32", 0),                      # 256 of 288 tiles whole
+    (1, (1, 45, 77), 3, 64, "bf16", B.DIT_FLAG_BIG_WORKGROUP),
+    (1, (2, 40, 40), 2, 128, "bf16", B.DIT_FLAG_QK_BF16 | B.DIT_FLAG_PV_BF16),
+]
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "%dx%s-H%d-D%d-%s-%d" % (c[0], "x".join(map(str, c[1])), c[2], c[3], c[4], c[5]))
+def test_pieces_against_oracle_and_whole_tiles(case):
+    import torch
+
+    nb, grid, H, D, dtype, flags = case
+    split = (44, 42, 42) if D == 128 else (22, 20, 22)
+    L = grid[0] * grid[1] * grid[2]
+    cfg = dict(B=nb, grid=grid, H=H, D=D, split=split, dtype=dtype, seed=91)
+    qn, kn, vn = wl.self_attn_inputs(cfg)
+    q, k, v = to_dev(qn), to_dev(kn), to_dev(vn)
+    out = torch.empty((nb, L, H, D), dtype=torch.float32, device="cuda")
+    lse = torch.empty((nb, H, L), dtype=torch.float32, device="cuda")
+    need = B.dit_attn_workspace_bytes(B.self_attn_params(q, k, v, out, grid, split, flags=flags))
+    up = lambda x: (x + 255) // 256 * 256
+    table = 8 * (grid[0] * split[0] + grid[1] * split[1] + grid[2] * split[2]) // 2
+    whole = up(table) + nb * H * ((L + 63) // 64) * 2 * (18 if D == 128 else 10) * 1024
+    assert need > whole, "this shape is meant to be computed in pieces"
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    ws.view(torch.float32).fill_(float("nan"))  # every piece that is read must have been written
+    B.dit_attn_forward(q, k, v, grid, split, out=out, lse=lse, flags=flags, workspace=ws)
+    got, got_lse = to_f64(out), to_f64(lse)
+    # 16-bit output of the same call is the same numbers rounded
+    out16 = B.dit_attn_forward(q, k, v, grid, split, out_dtype=torch.bfloat16, flags=flags, workspace=ws)
+    assert torch.equal(out16, out.to(torch.bfloat16))
+    # whole tiles: the same scores and probabilities, summed in fewer parts; what differs is the reference maximum of
+    # a row's probabilities, which changes their rounding to 11 (bf16 operands: 8) significant bits
+    out_w, lse_w = B.dit_attn_forward(q, k, v, grid, split, out_dtype=torch.float32, want_lse=True, flags=flags,
+                                      workspace=ws[:whole].clone())
+    rms = float(np.sqrt(np.mean(got ** 2)))
+    bf16_ops = bool(flags & B.DIT_FLAG_PV_BF16)
+    assert np.abs(to_f64(out_w) - got).max() <= (4e-2 if bf16_ops else 1e-2) * rms
+    assert np.abs(to_f64(lse_w) - got_lse).max() < (1e-2 if bf16_ops else 1e-3)
+
+    compare(got, oracle.self_attn(qn, kn, vn, grid, split), tol=4e-2 if bf16_ops else 2e-2, what="pieces %s" % (case,))
+
+
+@pytest.mark.parametrize("grids,H,D", [(((2, 9, 17), (1, 45, 77), (1, 40, 60)), 3, 128), (((1, 50, 61), (1, 1, 5)), 5, 64),
+                                       (((1, 45, 77),), 3, 128)], ids=["three", "long-and-short-d64", "one"])
+def test_packed_requests_in_pieces(grids, H, D):
+    import torch
+
+    split = (44, 42, 42) if D == 128 else (22, 20, 22)
+    cfg = dict(grids=grids, H=H, D=D, split=split, dtype="bf16", seed=92)
+    qn, kn, vn = wl.varlen_attn_inputs(cfg)
+    q, k, v = to_dev(qn), to_dev(kn), to_dev(vn)
+    n = q.shape[0]
+    out = torch.empty((n, H, D), dtype=torch.float32, device="cuda")
+    lse = torch.empty((H, n), dtype=torch.float32, device="cuda")
+    need = B.dit_attn_varlen_workspace_bytes(B.varlen_attn_params(q, k, v, out, grids, split))
+    whole = B.dit_attn_varlen_workspace_bytes(
+        B.varlen_attn_params(q, k, v, out, grids, split, flags=B.DIT_FLAG_SMALL_WORKGROUP))
+    assert need > whole, "this batch is meant to be computed in pieces"
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    ws.view(torch.float32).fill_(float("nan"))
+    B.dit_attn_varlen_forward(q, k, v, grids, split, out=out, lse=lse, workspace=ws)
+    out_w, lse_w = B.dit_attn_varlen_forward(q, k, v, grids, split, out_dtype=torch.float32, want_lse=True,
+                                             workspace=ws[:whole].clone())
+    assert (lse_w - lse).abs().max().item() < 1e-3
+    first = 0
+    for g in grids:
+        rows = slice(first, first + g[0] * g[1] * g[2])
+        first = rows.stop
+        ref = oracle.self_attn(qn[None, rows], kn[None, rows], vn[None, rows], g, split)[0]
+        compare(to_f64(out[rows]), ref, what="request %s in pieces" % (g,))
+        compare(to_f64(out_w[rows]), ref, what="request %s whole" % (g,))
