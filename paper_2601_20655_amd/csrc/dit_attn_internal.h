@@ -227,6 +227,9 @@ struct LinearArgs {
     const float* qkv_kgamma;     // nullable [H*128]
 };
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
+// plain projections that 256 x 256 tiles would leave most of the chip idle for (dit_linear_small.hip): which tile, 0 = none
+int choose_linear_form(int M, int N, int K);
+hipError_t launch_linear_small(const LinearArgs& a, int form, hipStream_t s);
 
 // Second half of the per-token normalisation of the fused q/k/v projection: the projection's epilogue left, in the
 // spare bytes behind the K' rows of every tile image, one float per key slot = the sum of squares of that token's k

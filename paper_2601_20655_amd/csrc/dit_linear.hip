@@ -679,6 +679,7 @@ hipError_t launch_linear(const LinearArgs& a, hipStream_t s) {
         if (a.qkv_norm == 2) return launch_linear_inst<false, 3>(a, s);
         return a.qkv_norm ? launch_linear_inst<false, 2>(a, s) : launch_linear_inst<false, 1>(a, s);
     }
+    if (const int form = choose_linear_form(a.M, a.N, a.K)) return launch_linear_small(a, form, s);
     return a.out_f32 ? launch_linear_inst<true, false>(a, s) : launch_linear_inst<false, false>(a, s);
 }
 

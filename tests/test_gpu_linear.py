@@ -139,3 +139,29 @@ def test_several_tiles_per_workgroup_exact(K, out):
     torch.cuda.synchronize()
     assert np.array_equal(to_f64(y[:M, :N]), ref)
     assert torch.all(y[M] == -77.0) and torch.all(y[:, N:] == -77.0)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (33, 72, 64),        # 32 x 64 tiles, one step, fewer steps than stages
+    (1, 4104, 448),      # the same: one row, ragged features
+    (2783, 144, 64),     # 64 x 64
+    (130, 3664, 704),    # the same, more steps than stages
+    (1031, 3592, 64),    # 64 x 128
+    (977, 1336, 704),    # the same, more steps than stages
+    (1025, 3080, 320),   # 128 x 128
+    (1250, 4104, 256),   # 96 x 256 (half a chunk of loads per wavefront)
+    (3502, 1560, 64),    # 128 x 256
+    (2500, 3336, 576),   # 160 x 256 (half a chunk)
+])
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_small_tiles(M, N, K, out):
+    """Shapes at which tiles smaller than 256 x 256 are taken, ragged on both sides, from one step to more steps than
+    LDS stages; all elements."""
+    import torch
+
+    cfg = dict(M=M, N=N, K=K, seed=61 + M)
+    x, w, b = wl.linear_inputs(cfg)
+    y = torch.full((M, N + 8), 7.0, dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda")
+    B.dit_linear_forward(to_dev(x), to_dev(w), to_dev(b), out=y[:, :N])
+    compare(to_f64(y[:, :N]), oracle.linear(x, w, b), bf16_out=out == "bf16", tol=tol(K), what="M=%d N=%d K=%d" % (M, N, K))
+    assert torch.all(y[:, N:] == 7.0)
