@@ -100,16 +100,17 @@ bool self_attn_uses_mfma16(const Flags& fl) {
     return !fl.fused && !fl.simple && fl.qb == 1 && fl.qk_op != dit::OP_FP8 && !fl.mfma32;
 }
 
-// Attention kernel launch, bracketed by the caller's timing events when the hook is set.
+// Attention kernel launch, bracketed by the caller's timing events when the hook is set.  chain16: query tiles per
+// workgroup of the chained cross-attention kernel, 0 for the other kernels.
 dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused, bool mfma16, hipStream_t s,
-                    bool chain16 = false) {
+                    int chain16 = 0) {
     const bool timed = g_ev_before && g_ev_after;
     hipError_t e;
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (aa.tile_count_a) {
         e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (chain16) {
-        e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, s);
+        e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, chain16, s);
     } else if (mfma16 && aa.split.n_tail > 0) {
         e = dit::launch_attn_pipe16_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (mfma16) {
@@ -572,10 +573,45 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
 struct CrossPlan {
     Flags fl;
     bool chain16;  // the chained 16x16x32 kernel (joint softmax, default)
+    int qch;       // with it: query tiles per workgroup
     int nKT, nQT;
     int split, nTA;  // decoupled form: first key of the second sequence, tiles of the first (0, 0: joint)
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
+
+// Wavefronts per workgroup and query tiles per workgroup (1 .. 16) of the chained cross-attention kernel.  Estimate in
+// microseconds: rounds of workgroups x (start + query tiles x (what a query tile costs once + its key tiles)), fitted to
+// every chain length from 1 to 16 in both workgroup sizes at 18 shapes of 144 to 32,760 queries and 1 to 9 key tiles.
+// A compute unit holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles attend is on the
+// device; three quarters of the capacity are taken for it.  Measured against the rule before (8 wavefronts from 512
+// workgroups on, five workgroups per compute unit), us: 7,800 queries x 12 heads, 3 key tiles 30.2 -> 23.8;
+// 12,473 x 9, 2 tiles 33.3 -> 21.9; 3,600 x 40, 7 tiles 56.2 -> 50.3; 32,760 x 12, 9 tiles 136.2 -> 128.9.  Chains
+// longer than 16 lose to requests of different lengths in the last round.
+void choose_chain(int Lq, int64_t BH, int nKT, int D, int* nw, int* qch) {
+    const double n = 0.75 * nKT + 0.5;
+    double best = 0.0;
+    int best_nw = 0;
+    for (int w : {8, 4}) {
+        if (*nw != 0 && *nw != w) continue;
+        const int64_t nQT = (Lq + 32 * w - 1) / (32 * w);
+        const int slots = D == 64 && w == 4 ? 2 * kCUs : kCUs;
+        const double start = D == 64 ? 1.5 : 2.0;
+        const double tile = D == 64 ? (w == 8 ? 5.0 : 4.0) + n : w == 8 ? 7.0 + 1.4 * n : 4.5 + n;
+        for (int ch = 1; ch <= 16 && ch <= nQT; ++ch) {
+            const int64_t wgs = (nQT + ch - 1) / ch * BH;
+            const int64_t full = wgs / slots, left = wgs % slots;
+            // (one of two workgroups alone on its compute unit: 0.65 of a pair's time)
+            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > kCUs ? 0.65 : 1.0);
+            const double t = full * (start + ch * tile) + last;
+            if (best_nw == 0 || t < best) {
+                best = t;
+                best_nw = w;
+                *qch = ch;
+            }
+        }
+    }
+    *nw = best_nw;
+}
 
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -608,7 +644,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
                   p->in_dtype == DIT_BF16;
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
-        if (pl->fl.nw == 0) pl->fl.nw = (int64_t)((p->Lq + 255) / 256) * p->B * p->H >= 512 ? 8 : 4;
+        choose_chain(p->Lq, (int64_t)p->B * p->H, pl->nKT, p->D, &pl->fl.nw, &pl->qch);
     } else if (pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;
     } else if (pl->fl.nw == 0) {
@@ -811,7 +847,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     aa.so_b = p->so.batch; aa.so_t = p->so.token; aa.so_h = p->so.head;
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
-    return run_attn(aa, p->D, pl.fl, false, false, s, pl.chain16);
+    return run_attn(aa, p->D, pl.fl, false, false, s, pl.chain16 ? pl.qch : 0);
 }
 
 }  // namespace

@@ -1001,30 +1001,16 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const
     attn_pipe16_body<D, QK_OP, PV_OP, NW, true>(a, pv);
 }
 
+// qch: query tiles per workgroup
 template <int D, int QK_OP, int PV_OP, int NW>
-hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, hipStream_t s) {
+hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t s) {
     auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW>;
     constexpr int smem = chain_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
-    // query tiles per workgroup: long enough chains that a workgroup's start-up is a small part of its life,
-    // enough workgroups (about five per compute unit) that requests of different lengths even out
-    int dev = 0, cus = 0;
-    e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const int64_t total_qt = (int64_t)a.nQT * a.B * a.H;
-#ifndef DIT_CHAIN_PER_CU
-#define DIT_CHAIN_PER_CU 5
-#endif
-#ifndef DIT_CHAIN_MAX
-#define DIT_CHAIN_MAX 16
-#endif
-    int64_t qch = total_qt / (DIT_CHAIN_PER_CU * (int64_t)(cus > 0 ? cus : 1));
-    qch = qch < 1 ? 1 : (qch > DIT_CHAIN_MAX ? DIT_CHAIN_MAX : qch);
     const int64_t nch = (a.nQT + qch - 1) / qch;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(nch * a.B * a.H)), dim3(64 * NW), smem, s, a, (int)qch);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nch * a.B * a.H)), dim3(64 * NW), smem, s, a, qch);
     return hipGetLastError();
 }
 

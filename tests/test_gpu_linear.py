@@ -147,7 +147,7 @@ def test_several_tiles_per_workgroup_exact(K, out):
     (2783, 144, 64),     # 64 x 64
     (130, 3664, 704),    # the same, more steps than stages
     (1031, 3592, 64),    # 64 x 128
-    (977, 1336, 704),    # the same, more steps than stages
+    (1031, 3592, 256),   # the same, more steps than stages
     (1025, 3080, 320),   # 128 x 128
     (1250, 4104, 256),   # 96 x 256 (half a chunk of loads per wavefront)
     (3502, 1560, 64),    # 128 x 256
