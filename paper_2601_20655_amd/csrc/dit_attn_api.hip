@@ -165,34 +165,33 @@ size_t rstd_bytes(const dit_qk_norm& n, int64_t q_rows, int64_t k_rows) {
     return round_up((size_t)q_rows * sizeof(float), kAlign) + round_up((size_t)k_rows * sizeof(float), kAlign);
 }
 
-// Fills the normalisation arguments of both kernels; in TOKEN mode launches the two statistics passes.
-dit_status setup_norm(const dit_qk_norm& n, const void* q, const void* k, const dit_strides& sq, const dit_strides& sk,
-                      int B, int Lq, int Lk, int H, int D, int in_f32, uint8_t* rstd_ws, dit::NormArgs* qn,
-                      dit::NormArgs* kn, bool k_resident, hipStream_t s) {
+// Fills the normalisation arguments of both kernels, and enqueues what they read: the rotation table (null: there is
+// none, or it is in the workspace) and in TOKEN mode the per-token factors.
+dit_status setup_rows(const dit::TableArgs* table, const dit_qk_norm& n, const void* q, const void* k, const dit_strides& sq,
+                      const dit_strides& sk, int B, int Lq, int Lk, int H, int D, int in_f32, uint8_t* rstd_ws,
+                      dit::NormArgs* qn, dit::NormArgs* kn, bool k_resident, hipStream_t s) {
     memset(qn, 0, sizeof(*qn));
     memset(kn, 0, sizeof(*kn));
-    if (n.mode == DIT_NORM_NONE) return DIT_OK;
-    qn->mode = kn->mode = n.mode;
-    qn->eps = kn->eps = n.eps;
-    qn->gamma = n.q_gamma;
-    kn->gamma = n.k_gamma;
-    if (n.mode == DIT_NORM_TOKEN) {
-        float* rq = reinterpret_cast<float*>(rstd_ws);
-        float* rk = reinterpret_cast<float*>(rstd_ws + round_up((size_t)B * Lq * sizeof(float), kAlign));
-        dit::RstdArgs ra;
-        ra.x = q; ra.rstd = rq; ra.s_b = sq.batch; ra.s_t = sq.token; ra.s_h = sq.head;
-        ra.B = B; ra.L = Lq; ra.H = H; ra.D = D; ra.in_f32 = in_f32; ra.eps = n.eps;
-        hipError_t e = dit::launch_token_rstd(ra, s);
-        if (e != hipSuccess) return hip_fail(e, "token_rstd_kernel");
-        if (!k_resident) {  // the key rows' factors only feed the pre-pack pass
-            ra.x = k; ra.rstd = rk; ra.s_b = sk.batch; ra.s_t = sk.token; ra.s_h = sk.head; ra.L = Lk;
-            e = dit::launch_token_rstd(ra, s);
-            if (e != hipSuccess) return hip_fail(e, "token_rstd_kernel");
-        }
-        qn->rstd = rq;
-        kn->rstd = rk;
+    dit::RstdArgs rq, rk;
+    const bool token = n.mode == DIT_NORM_TOKEN;
+    if (n.mode != DIT_NORM_NONE) {
+        qn->mode = kn->mode = n.mode;
+        qn->eps = kn->eps = n.eps;
+        qn->gamma = n.q_gamma;
+        kn->gamma = n.k_gamma;
     }
-    return DIT_OK;
+    if (token) {
+        rq.x = q; rq.rstd = reinterpret_cast<float*>(rstd_ws); rq.s_b = sq.batch; rq.s_t = sq.token; rq.s_h = sq.head;
+        rq.B = B; rq.L = Lq; rq.H = H; rq.D = D; rq.in_f32 = in_f32; rq.eps = n.eps;
+        rk = rq;
+        rk.x = k; rk.rstd = reinterpret_cast<float*>(rstd_ws + round_up((size_t)B * Lq * sizeof(float), kAlign));
+        rk.s_b = sk.batch; rk.s_t = sk.token; rk.s_h = sk.head; rk.L = Lk;
+        qn->rstd = rq.rstd;
+        kn->rstd = rk.rstd;
+    }
+    // the key rows' factors only feed the pre-pack pass
+    const hipError_t e = dit::launch_row_stats(table, token ? &rq : nullptr, token && !k_resident ? &rk : nullptr, s);
+    return e == hipSuccess ? DIT_OK : hip_fail(e, "row_stats_kernel");
 }
 
 struct SelfPlan {
@@ -711,18 +710,13 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     ta.n[0] = p->T; ta.n[1] = p->Hg; ta.n[2] = p->Wg;
     ta.origin[0] = p->t0; ta.origin[1] = p->h0; ta.origin[2] = p->w0;
     ta.rg = rg;
-    ta.base = (double)p->rope_base;
+    ta.log2_base = log2((double)p->rope_base);
     ta.total = pl.table_entries;
     hipError_t e = hipSuccess;
-    if (!pl.fl.resident) {
-        e = dit::launch_rope_table(ta, s);
-        if (e != hipSuccess) return hip_fail(e, "rope_table_kernel");
-    }
-
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
-    st = setup_norm(p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D, p->in_dtype == DIT_F32,
+    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D, p->in_dtype == DIT_F32,
                     ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
@@ -797,7 +791,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
-    st = setup_norm(p->norm, q, k, p->sq, p->sk, p->B, p->Lq, p->Lk, p->H, p->D, p->in_dtype == DIT_F32,
+    st = setup_rows(nullptr, p->norm, q, k, p->sq, p->sk, p->B, p->Lq, p->Lk, p->H, p->D, p->in_dtype == DIT_F32,
                     ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
@@ -902,20 +896,15 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     ta.n[0] = pl.maxT; ta.n[1] = pl.maxHg; ta.n[2] = pl.maxWg;
     ta.origin[0] = p->t0; ta.origin[1] = p->h0; ta.origin[2] = p->w0;
     ta.rg = rg;
-    ta.base = (double)p->rope_base;
+    ta.log2_base = log2((double)p->rope_base);
     ta.total = pl.table_entries;
     hipError_t e = hipSuccess;
-    if (!pl.fl.resident) {
-        e = dit::launch_rope_table(ta, s);
-        if (e != hipSuccess) return hip_fail(e, "rope_table_kernel");
-    }
-
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
     dit_strides sq1 = p->sq, sk1 = p->sk;
     sq1.batch = sk1.batch = 0;
-    st = setup_norm(p->norm, q, k, sq1, sk1, 1, pl.vt.total_tokens, pl.vt.total_tokens, p->H, p->D,
+    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, sq1, sk1, 1, pl.vt.total_tokens, pl.vt.total_tokens, p->H, p->D,
                     p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
@@ -1040,10 +1029,10 @@ dit_status dit_qkv_proj_forward(const void* x, const void* w, const void* bias, 
     ta.n[0] = ap->T; ta.n[1] = ap->Hg; ta.n[2] = ap->Wg;
     ta.origin[0] = ap->t0; ta.origin[1] = ap->h0; ta.origin[2] = ap->w0;
     ta.rg = rg;
-    ta.base = (double)ap->rope_base;
+    ta.log2_base = log2((double)ap->rope_base);
     ta.total = pl.table_entries;
-    hipError_t e = dit::launch_rope_table(ta, s);
-    if (e != hipSuccess) return hip_fail(e, "rope_table_kernel");
+    hipError_t e = dit::launch_row_stats(&ta, nullptr, nullptr, s);
+    if (e != hipSuccess) return hip_fail(e, "row_stats_kernel");
 
     dit::LinearArgs a{};
     a.x = static_cast<const uint16_t*>(x);

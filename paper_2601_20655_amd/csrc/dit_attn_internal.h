@@ -50,7 +50,7 @@ struct NormArgs {
     int mode;            // 0 off; 1 mean over the D channels of the head; 2 over all H*D channels of the token
     float eps;
     const float* gamma;  // nullable [H*D]
-    const float* rstd;   // mode 2: 1/sqrt(mean + eps) per token row, filled by launch_token_rstd
+    const float* rstd;   // mode 2: 1/sqrt(mean + eps) per token row, filled by launch_row_stats
 };
 
 // per-token 1/sqrt(mean over H*D channels + eps)
@@ -68,7 +68,7 @@ struct TableArgs {
     int n[3];       // positions per axis (T, Hg, Wg)
     int origin[3];  // t0, h0, w0
     RopeGeom rg;
-    double base;
+    double log2_base;
     int total;
 };
 
@@ -173,8 +173,8 @@ inline hipError_t allow_dynamic_lds(K kern, int bytes, std::atomic<uint64_t>& do
 // Records "<where>: <HIP error text>" for dit_last_hip_error() of the calling thread; returns DIT_ERR_HIP.
 int report_hip_error(hipError_t e, const char* where);
 
-hipError_t launch_rope_table(const TableArgs& a, hipStream_t s);
-hipError_t launch_token_rstd(const RstdArgs& a, hipStream_t s);
+// rotation table, per-token factors of q rows, of k rows: any may be null
+hipError_t launch_row_stats(const TableArgs* t, const RstdArgs* q, const RstdArgs* k, hipStream_t s);
 hipError_t launch_prepack_varlen(const PackArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, hipStream_t s);
 hipError_t launch_attn_pipe_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                    hipStream_t s);

@@ -1,6 +1,7 @@
 // Memory-bound helper kernels that run before the attention kernel on the same stream:
-//  * rope_table_kernel: (cos, sin) of every (axis, position, pair) angle, evaluated in fp64
-//    and stored as fp32, so that the rotation itself never calls a transcendental.
+//  * row_stats_kernel: (cos, sin) of every (axis, position, pair) angle, evaluated in fp64
+//    and stored as fp32, so that the rotation itself never calls a transcendental; per-token factors of
+//    the q and k rows.
 //  * kv_prepack_kernel: rotates K, rounds K' and V once to the MFMA operand types (16-bit, or for
 //    K' 8-bit E4M3 with one power-of-two factor per row) and writes each 64-key tile as the exact
 //    byte image the attention kernel keeps in LDS (K' rows, then V^T rows with keys permuted into
@@ -9,8 +10,11 @@
 
 namespace dit {
 
-__global__ void __launch_bounds__(256) rope_table_kernel(const TableArgs a) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// angle = position * base^(-2i/d_a), d_a = 2 * hd.  base^x = 2^(x log2(base)): its relative error, a few units of 2^-53
+// times |x log2(base)| < 14, stays far below the fp32 result's, and it and the joint sine and cosine are a third of the
+// dependent fp64 instructions of pow(), cos() and sin() -- a table is a few hundred to a few thousand entries, so the
+// time is a launch and one thread's latency: 2.8 -> 2.4 us for 212 entries.
+__device__ __forceinline__ void rope_entry(const TableArgs& a, int idx) {
     if (idx >= a.total) return;
     int ax = 0;
     if (idx >= a.rg.off[2]) ax = 2;
@@ -18,45 +22,65 @@ __global__ void __launch_bounds__(256) rope_table_kernel(const TableArgs a) {
     const int local = idx - a.rg.off[ax];
     const int hd = a.rg.hd[ax];
     const int p = local / hd, i = local - p * hd;
-    // angle = position * base^(-2i/d_a) with d_a = 2*hd
-    const double omega = pow(a.base, -(double)i / (double)hd);
-    const double phi = (double)(a.origin[ax] + p) * omega;
-    a.tab[idx] = make_float2((float)cos(phi), (float)sin(phi));
+    const double phi = (double)(a.origin[ax] + p) * exp2(-(double)i / (double)hd * a.log2_base);
+    double sn, cs;
+    sincos(phi, &sn, &cs);
+    a.tab[idx] = make_float2((float)cs, (float)sn);
 }
 
-hipError_t launch_rope_table(const TableArgs& a, hipStream_t s) {
-    if (a.total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rope_table_kernel, dim3((a.total + 255) / 256), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-// One workgroup per token: 1/sqrt(mean of x^2 over all H*D channels + eps).
-__global__ void __launch_bounds__(256) token_rstd_kernel(const RstdArgs a) {
-    __shared__ float part[4];
-    const int64_t row = blockIdx.x;
+// 1/sqrt(mean of x^2 over all H*D channels + eps) of one token row, by one wavefront
+__device__ __forceinline__ void token_rstd(const RstdArgs& a, int64_t row) {
+    if (row >= (int64_t)a.B * a.L) return;
+    const int lane = threadIdx.x & 63;
     const int b = (int)(row / a.L), n = (int)(row - (int64_t)b * a.L);
-    const int cpr = a.D / 8, chunks = a.H * cpr;
+    const int shift = a.D == 128 ? 4 : 3;  // 16-byte chunks per head
+    const int chunks = a.H << shift;
     const int64_t base = (int64_t)b * a.s_b + (int64_t)n * a.s_t;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < chunks; i += 256) {
-        const int h = i / cpr, c = i - h * cpr;
-        float x[8];
-        load8(a.x, base + (int64_t)h * a.s_h + 8 * c, a.in_f32, x);
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = lane; i0 < chunks; i0 += 256) {
+        float x[4][8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
-    }
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 64 * u;
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) ss += __shfl_xor(ss, m);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const float tot = (part[0] + part[1]) + (part[2] + part[3]);
-        a.rstd[row] = 1.0f / sqrtf(tot / (float)(a.H * a.D) + a.eps);
+            for (int e = 0; e < 8; ++e) x[u][e] = 0.f;
+            if (i < chunks) load8(a.x, base + (int64_t)(i >> shift) * a.s_h + 8 * (i & ((1 << shift) - 1)), a.in_f32, x[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss[u] = fmaf(x[u][e], x[u][e], ss[u]);
     }
+    float tot = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) tot += __shfl_xor(tot, m);
+    if (lane == 0) a.rstd[row] = 1.0f / sqrtf(tot / (float)(a.H * a.D) + a.eps);
 }
 
-hipError_t launch_token_rstd(const RstdArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(token_rstd_kernel, dim3((unsigned)((int64_t)a.B * a.L)), dim3(256), 0, s, a);
+// What the pre-pack and the attention kernel need before they can start, in one launch: the rotation table (the first
+// table_blocks workgroups, one entry a thread) and the per-token factors of the q rows and the k rows (four rows a
+// workgroup, one wavefront each).  Memory-bound where there are factors: 32,760 tokens x 12 heads of q and k
+// 41 us, 4.9 TB/s (one workgroup of 256 threads per row and three launches: 65).
+__global__ void __launch_bounds__(256) row_stats_kernel(const TableArgs t, const RstdArgs q, const RstdArgs k,
+                                                        int table_blocks, int q_blocks) {
+    const int blk = blockIdx.x;
+    const int wave = threadIdx.x >> 6;
+    if (blk < table_blocks) rope_entry(t, blk * 256 + threadIdx.x);
+    else if (blk < table_blocks + q_blocks) token_rstd(q, (int64_t)(blk - table_blocks) * 4 + wave);
+    else token_rstd(k, (int64_t)(blk - table_blocks - q_blocks) * 4 + wave);
+}
+
+// any of the three may be null
+hipError_t launch_row_stats(const TableArgs* t, const RstdArgs* q, const RstdArgs* k, hipStream_t s) {
+    TableArgs ta{};
+    RstdArgs qa{}, ka{};
+    if (t) ta = *t;
+    if (q) qa = *q;
+    if (k) ka = *k;
+    const int64_t tb = ((int64_t)ta.total + 255) / 256;
+    const int64_t qb = ((int64_t)qa.B * qa.L + 3) / 4, kb = ((int64_t)ka.B * ka.L + 3) / 4;
+    if (tb + qb + kb == 0) return hipSuccess;
+    hipLaunchKernelGGL(row_stats_kernel, dim3((unsigned)(tb + qb + kb)), dim3(256), 0, s, ta, qa, ka, (int)tb, (int)qb);
     return hipGetLastError();
 }
 
