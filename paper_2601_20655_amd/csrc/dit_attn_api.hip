@@ -804,7 +804,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     pa.tile_list = reinterpret_cast<int*>(ws + pl.list_off);
     pa.tile_count = reinterpret_cast<int*>(ws + pl.count_off);
     pa.tile_count_a = pl.split > 0 ? reinterpret_cast<int*>(ws + pl.count_a_off) : nullptr;
-    pa.key_src = kv_valid ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
+    pa.key_src = kv_valid && dit::mask_needs_key_list(p->Lk) ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
     pa.kv_len = use_len ? kv_len : nullptr;
     pa.second_start = second_start;
     pa.split = pl.split;
@@ -820,7 +820,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
         if (pa.key_src && (e = dit::launch_key_compact(pa, s)) != hipSuccess) return hip_fail(e, "key_compact_kernel");
         e = dit::launch_prepack(pa, p->D, pl.fl.qk_op, pl.fl.pv_op, s);
         if (e != hipSuccess) return hip_fail(e, "kv_prepack_kernel");
-        if (!pa.kv_len) {  // (with key counts the pre-pack writes the tile list itself)
+        if (pa.key_src) {  // (otherwise the pre-pack writes the tile list itself)
             e = dit::launch_tile_compact(pa, s);
             if (e != hipSuccess) return hip_fail(e, "tile_compact_kernel");
         }

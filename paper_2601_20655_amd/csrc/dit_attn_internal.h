@@ -76,7 +76,7 @@ struct PackArgs {
     const void* k;
     const void* v;
     const uint8_t* valid;  // nullable [B, Lk]
-    int* key_src;          // with valid: [B, nKT, 64] source key of every tile slot, -1 = empty (launch_key_compact)
+    int* key_src;          // with valid, long masks: [B, nKT, 64] source key of every tile slot, -1 = empty (launch_key_compact)
     const int* kv_len;     // nullable [B, 2] (instead of valid): the keys that attend are the first kv_len[b][0] of
                            // [0, ...) and the first kv_len[b][1] of [second_start, Lk); the pre-pack works out every
                            // slot's source key, the tile masks, the tile list and its counts from the two numbers
@@ -186,10 +186,12 @@ hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s);
-// before launch_prepack when a.valid is set: the valid keys of every batch entry (of each key group) in
+// a mask of this many keys is listed beforehand (the next two passes); launch_prepack sorts out shorter ones by itself
+bool mask_needs_key_list(int Lk);
+// before launch_prepack when a.valid and a.key_src are set: the valid keys of every batch entry (of each key group) in
 // ascending order, densely over the tile slots
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s);
-// after launch_prepack: compact the non-empty tiles of every batch entry into tile_list / tile_count
+// after launch_prepack when a.key_src is set: compact the non-empty tiles of every batch entry into tile_list / tile_count
 hipError_t launch_tile_compact(const PackArgs& a, hipStream_t s);
 // qb = 32-row query blocks per wavefront (1 or 2)
 hipError_t launch_attn(const AttnArgs& a, int D, int qb, int qk_op, int pv_op, bool fused,

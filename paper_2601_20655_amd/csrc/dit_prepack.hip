@@ -264,11 +264,49 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
     }
 }
 
+// Key padding masks.  Attention does not depend on the order of its keys, so the keys that attend, in ascending order,
+// are packed densely into the tiles of their group: padded keys cost no tile, wherever they sit.  Every workgroup finds
+// the keys of its own tile: slot r holds the valid key of rank rank0 + r among mask bytes [k0, k1) (src[r], -1: none).
+// Returns the number of valid keys.  cnt: one count per 64 keys of the range.  (Two small passes ahead of this one, one
+// that listed the keys and one that listed the tiles, cost 11 us and two launches whatever the size of the call.)
+constexpr int kMaskKeys = 4096;  // the counts are summed up by one wavefront; longer masks are listed beforehand
+__device__ __forceinline__ int find_keys(const uint8_t* valid, int k0, int k1, int rank0, int* src, int* cnt) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int r = tid; r < kBK; r += kThreads) src[r] = -1;
+    for (int key0 = k0 + (tid & ~63); key0 < k1; key0 += kThreads) {
+        const uint64_t m = __ballot(key0 + lane < k1 && valid[key0 + lane] != 0);
+        if (lane == 0) cnt[(key0 - k0) >> 6] = __popcll(m);
+    }
+    __syncthreads();
+    const int groups = (k1 - k0 + 63) >> 6;
+    int c = lane < groups ? cnt[lane] : 0, upto = c;  // every wavefront sums up all counts for itself
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const int o = __shfl_up(upto, m);
+        if (lane >= m) upto += o;
+    }
+    const int total = __shfl(upto, 63);
+    if (rank0 < total) {
+        for (int key0 = k0 + (tid & ~63); key0 < k1; key0 += kThreads) {
+            const int g = (key0 - k0) >> 6;
+            const int first = __shfl(upto - c, g) - rank0, n = __shfl(c, g);
+            if (first >= kBK || first + n <= 0) continue;  // uniform over the wavefront
+            const bool ok = key0 + lane < k1 && valid[key0 + lane] != 0;
+            const uint64_t m = __ballot(ok);
+            const int slot = first + __popcll(m & ((1ull << lane) - 1ull));
+            if (ok && slot >= 0 && slot < kBK) src[slot] = key0 + lane;
+        }
+    }
+    __syncthreads();
+    return total;
+}
+
 // One workgroup per (tile, head, batch).
 template <int D, int QK_OP, int PV_OP>
 __global__ void __launch_bounds__(kThreads) kv_prepack_kernel(const PackArgs a) {
     using G = TileGeom<D>;
     __shared__ __attribute__((aligned(16))) uint16_t vs[kBK * (D + 2)];
+    __shared__ int src[kBK], cnt[kMaskKeys / 64];
     const int tid = threadIdx.x;
     // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of the same 64 tokens
     const int h = blockIdx.x % a.H, jb = blockIdx.x / a.H, j = jb % a.nKT, b = jb / a.nKT;
@@ -283,7 +321,23 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_kernel(const PackArgs a) 
     t.key_src = a.key_src ? a.key_src + ((size_t)b * a.nKT + j) * kBK : nullptr;
     t.ranges = a.kv_len != nullptr;
     t.slot0 = t.la = t.sa = t.lb = t.sb = 0;
-    int ca = 0, cb = 0;  // ranges: tiles that hold a key, first and second key group (decoupled) or all (joint: ca)
+    int ca = 0, cb = 0;  // tiles that hold a key, first and second key group (decoupled) or all (joint: ca)
+    const bool find = a.valid && !a.key_src;
+    if (find) {
+        const uint8_t* const valid = a.valid + (size_t)b * a.Lk;
+        // whoever writes list entries and counts below needs the other group's number of keys too
+        if (h == 0 && a.split > 0) {
+            const int other = second ? find_keys(valid, 0, a.split, 0x3fffffff, src, cnt)
+                                     : find_keys(valid, a.split, a.Lk, 0x3fffffff, src, cnt);
+            (second ? ca : cb) = (other + kBK - 1) / kBK;
+        }
+        const int mine = find_keys(valid, second ? a.split : 0, t.key_end, (second ? j - a.nTA : j) * kBK, src, cnt);
+        (second ? cb : ca) = (mine + kBK - 1) / kBK;
+        t.key_src = src;
+    } else if (a.tile_mask && !a.key_src && !t.ranges) {  // no mask: all keys
+        ca = a.split > 0 ? a.nTA : a.nKT;
+        cb = a.nKT - ca;
+    }
     if (t.ranges) {
         // counts are clamped to the ranges they count in: whatever the caller wrote, every key index stays inside k, v
         const int end0 = a.split > 0 ? a.split : a.second_start;
@@ -314,7 +368,7 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_kernel(const PackArgs a) 
         const uint64_t m = __ballot(ok);
         if (tid == 0) {
             a.tile_mask[(size_t)b * a.nKT + j] = m;
-            if (t.ranges) {
+            if (!a.key_src) {
                 // the list of tiles that hold a key and its counts, which tile_compact_kernel otherwise derives from the masks
                 const int jj = second ? j - a.nTA : j;
                 if (m != 0ull) a.tile_list[(size_t)b * a.nKT + (second ? ca + jj : jj)] = j;
@@ -353,10 +407,8 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_varlen_kernel(const PackA
     pack_tile<D, QK_OP, PV_OP>(a, t, vs);
 }
 
-// Key padding masks: one wavefront per (batch entry, key group) writes the group's valid keys, in
-// ascending order, densely into the slots of the group's tiles; the slots left over get -1.  Attention
-// does not depend on the order of the keys, so the padded keys cost no tile: a request keeps
-// ceil(valid keys / 64) tiles per group whatever the positions of its padding.
+// Masks of more than kMaskKeys keys: one wavefront per (batch entry, key group) writes the group's valid keys, in
+// ascending order, densely into the slots of the group's tiles; the slots left over get -1.
 __global__ void __launch_bounds__(64) key_compact_kernel(const uint8_t* valid, int* key_src, int Lk, int nKT,
                                                          int split, int nTA) {
     const int b = blockIdx.x, g = blockIdx.y, lane = threadIdx.x;
@@ -373,6 +425,8 @@ __global__ void __launch_bounds__(64) key_compact_kernel(const uint8_t* valid, i
     }
     for (int i = count + lane; i < (t1 - t0) * kBK; i += 64) out[i] = -1;
 }
+
+bool mask_needs_key_list(int Lk) { return Lk > kMaskKeys; }
 
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(key_compact_kernel, dim3(a.B, a.split > 0 ? 2 : 1), dim3(64), 0, s, a.valid, a.key_src, a.Lk,

@@ -278,3 +278,27 @@ def test_key_counts_decoupled_and_resident(D):
                                             flags=B.DIT_FLAG_KV_RESIDENT, out_dtype=torch.float32)
     torch.cuda.synchronize()
     compare(to_f64(out2), oracle.cross_attn_decoupled(q2, k, v, n_text, valid), what="resident tiles from key counts")
+
+
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("Lk", [63, 65, 1000, 4096, 4097, 4500])
+def test_scattered_masks_short_and_long(Lk, split):
+    """Valid keys anywhere: masks that the pre-pack sorts out by itself (up to 4,096 keys) and longer ones that are listed
+    beforehand; all, none, one and about half of the keys valid; huge values under the mask."""
+    import torch
+
+    cut = (Lk // 3) if split else 0
+    cfg = dict(B=4, Lq=65, n_text=Lk - 1, n_image=1, H=2, D=64, dtype="bf16", min_text=1, seed=500 + Lk)
+    q, k, v, _, _ = wl.cross_attn_inputs(cfg)
+    valid = (np.random.default_rng(Lk).random((4, Lk)) < 0.5).astype(np.uint8)
+    valid[1], valid[2] = 1, 0
+    valid[3] = 0
+    valid[3, Lk - 1] = 1
+    v = v.copy()
+    v[valid == 0] = wl.f32_to_bf16_bits(np.float32(3.0e38))
+    ref = oracle.cross_attn_decoupled(q, k, v, cut, valid) if split else oracle.cross_attn(q, k, v, valid)
+    out = B.dit_cross_attn_forward(to_dev(q), to_dev(k), to_dev(v), torch.from_numpy(valid).cuda(),
+                                   out_dtype=torch.float32, split=cut)
+    got = to_f64(out)
+    assert np.all(got[2] == 0.0)
+    compare(got, ref, what="scattered mask Lk=%d split=%d" % (Lk, cut))
