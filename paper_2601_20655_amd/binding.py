@@ -8,6 +8,8 @@ there is no fallback path.
 import ctypes
 import os
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdit_attn.so")
 
@@ -200,28 +202,29 @@ def dit_attn_version():
     return int(lib().dit_attn_version())
 
 
-def _dtype_code(t):
-    import torch
+_DTYPE_CODES = {torch.bfloat16: DIT_BF16, torch.float32: DIT_F32}
 
-    if t.dtype == torch.bfloat16:
-        return DIT_BF16
-    if t.dtype == torch.float32:
-        return DIT_F32
-    raise TypeError("tensors must be bfloat16 or float32, got %s" % t.dtype)
+
+def _dtype_code(t):
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("tensors must be bfloat16 or float32, got %s" % t.dtype)
+    return code
 
 
 def _strides(t):
     """[B, L, H, D] tensor (any permutation underneath) -> dit_strides; channel stride must be 1."""
-    if t.dim() != 4 or t.stride(3) != 1:
+    s = t.stride()
+    if len(s) != 4 or s[3] != 1:
         raise ValueError("expected a [B, L, H, D] tensor with contiguous channels")
-    return dit_strides(t.stride(0), t.stride(1), t.stride(2))
+    return dit_strides(s[0], s[1], s[2])
 
 
 def _stream_ptr(stream):
-    import torch
-
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # (the raw handle: building the Stream object around it took 2.5 us, a seventh of what a small call takes the host)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def qk_norm(norm, H, D):
@@ -229,8 +232,6 @@ def qk_norm(norm, H, D):
     device float32 tensors of H*D elements (or None)."""
     if norm is None:
         return dit_qk_norm()
-    import torch
-
     mode, eps, gq, gk = norm
     ptrs = []
     for g in (gq, gk):
@@ -257,9 +258,10 @@ def cross_attn_params(q, k, v, out, scale=0.0, flags=0, split=0, norm=None):
 
 def _strides3(t):
     """[N, H, D] tensor (packed requests) -> dit_strides with batch stride 0."""
-    if t.dim() != 3 or t.stride(2) != 1:
+    s = t.stride()
+    if len(s) != 3 or s[2] != 1:
         raise ValueError("expected a [tokens, H, D] tensor with contiguous channels")
-    return dit_strides(0, t.stride(0), t.stride(1))
+    return dit_strides(0, s[0], s[1])
 
 
 def varlen_attn_params(q, k, v, out, grids, split, origin=(0, 0, 0), rope_base=10000.0, scale=0.0, flags=0,
@@ -291,8 +293,6 @@ def _check_tensors(what, q, k, v, out, lse, kv_shape, lse_shape, resident=False)
     """The C side addresses memory from the shapes in the params struct alone, so every tensor handed over
     must really have the extent those shapes imply: raise instead of letting a kernel run past an allocation.
     Shapes and dtypes are checked first, devices last."""
-    import torch
-
     qshape = tuple(q.shape)
     kv = () if resident else (("k", k), ("v", v))
     for name, t in kv:
@@ -330,8 +330,6 @@ def _workspace_floor(workspace, params, need, query):
 
 
 def _workspace(nbytes, device):
-    import torch
-
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
@@ -343,8 +341,6 @@ def dit_attn_forward(q, k, v, grid, split, out=None, lse=None, origin=(0, 0, 0),
     Allocates `out` (and `lse`, `workspace`) with torch when not given; returns out, or
     (out, lse) when an lse buffer is requested.  Asynchronous on the stream.
     """
-    import torch
-
     if q.dim() != 4:
         raise ValueError("dit_attn_forward: q must be [B, L, H, D]")
     B, L, H, D = q.shape
@@ -374,8 +370,6 @@ def dit_attn_forward(q, k, v, grid, split, out=None, lse=None, origin=(0, 0, 0),
 
 def _check_kv_valid(kv_valid, q, B, Lk, device_too=False):
     """Shape and dtype of the key mask; with device_too (after the other tensors' shapes are known good) its device."""
-    import torch
-
     if kv_valid is None:
         return
     if kv_valid.dtype != torch.uint8 or not kv_valid.is_contiguous() or tuple(kv_valid.shape) != (B, Lk):
@@ -388,8 +382,6 @@ def dit_cross_attn_forward(q, k, v, kv_valid=None, out=None, lse=None, scale=0.0
                            workspace=None, stream=None, want_lse=False, split=0, norm=None):
     """Cross-attention: q [B, Lq, H, D]; k, v [B, Lk, H, D]; kv_valid uint8 [B, Lk] or None.
     split > 0 selects the decoupled form (separate softmax over keys [0, split) and [split, Lk))."""
-    import torch
-
     if q.dim() != 4 or k.dim() != 4:
         raise ValueError("dit_cross_attn_forward: q must be [B, Lq, H, D] and k, v [B, Lk, H, D]")
     B, Lq, H, D = q.shape
@@ -420,8 +412,6 @@ def dit_cross_attn_forward_lengths(q, k, v, kv_len, second_start, out=None, lse=
                                    out_dtype=None, workspace=None, stream=None, want_lse=False, split=0, norm=None):
     """Cross-attention with per-request key counts: kv_len int32 [B, 2] on the device; the keys that attend are
     the first kv_len[b, 0] of [0, second_start) and the first kv_len[b, 1] of [second_start, Lk)."""
-    import torch
-
     if q.dim() != 4 or k.dim() != 4:
         raise ValueError("dit_cross_attn_forward_lengths: q must be [B, Lq, H, D] and k, v [B, Lk, H, D]")
     B, Lq, H, D = q.shape
@@ -463,8 +453,6 @@ def dit_cross_attn_forward_static(q, k, v, kv_valid=None, out=None, lse=None, sc
                                   stream=None, norm=None):
     """dit_cross_attn_forward on the library's own static device workspace.  `out` (and `lse`) must be
     given: this wrapper allocates nothing either."""
-    import torch
-
     if out is None:
         raise ValueError("dit_cross_attn_forward_static needs a caller-provided out")
     if q.dim() != 4 or k.dim() != 4:
@@ -489,8 +477,6 @@ def dit_attn_varlen_forward(q, k, v, grids, split, out=None, lse=None, origin=(0
                             norm=None):
     """Self-attention of several requests packed along the token axis: q, k, v [sum L_i, H, D],
     grids = [(T, Hg, Wg), ...] with L_i = T*Hg*Wg.  Returns out (and lse [H, sum L_i] if asked)."""
-    import torch
-
     if q.dim() != 3:
         raise ValueError("dit_attn_varlen_forward: q must be [tokens, H, D]")
     N, H, D = q.shape
@@ -528,8 +514,6 @@ def linear_params(x, w, y, flags=0):
 
 def dit_linear_forward(x, w, bias=None, out=None, out_dtype=None, stream=None):
     """y = x w^T + bias: x [M, K] bf16, w [N, K] bf16, bias [N] bf16 or None; y [M, N] bf16 or fp32."""
-    import torch
-
     if not x.is_cuda:
         raise ValueError("dit_linear_forward needs device tensors")
     if x.dtype != torch.bfloat16 or w.dtype != torch.bfloat16 or (bias is not None and bias.dtype != torch.bfloat16):
@@ -554,8 +538,6 @@ def dit_qkv_proj_forward(x, w, bias, grid, split, H, q_out=None, origin=(0, 0, 0
         dit_attn_forward(q_out, k=None, v=None, grid, split, flags=flags | DIT_FLAG_KV_RESIDENT, workspace=workspace)
     completes the attention (k and v are not read).  norm: None or (mode, eps, q_gamma, k_gamma): the k rows are
     normalised here; pass the same norm to dit_attn_forward, which normalises the q rows as it reads them."""
-    import torch
-
     D = 128
     if x.dim() != 2 or w.dim() != 2 or x.stride(1) != 1 or w.stride(1) != 1:
         raise ValueError("x and w must be 2-D with contiguous rows")
