@@ -7,7 +7,7 @@
 //
 // What bounds it: the LDS.  A step of a 128 x 256 tile reads 128 KiB of fragments (a wavefront's 64 x 64 corner takes
 // 8 fragments for 16 MFMAs) and writes 48 KiB, 1,410 clocks at 128 bytes a clock, against 1,024 clocks of MFMAs on
-// each SIMD and 1,530 measured; the big kernel's tile needs as many clocks of either.  So a small tile costs more per
+// each SIMD and 1,530 measured (one workgroup on an idle chip); the big kernel's tile needs as many clocks of either.  So a small tile costs more per
 // flop, and is taken only where it fills the chip better (choose_linear_form).
 #include <type_traits>
 
@@ -20,6 +20,14 @@ namespace {
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<I + 1, N>(f);
+    }
+}
 
 // 2 x 4 wavefronts (tokens x features), TB and FB 16-token and 16-feature blocks per wavefront
 template <int TB, int FB>
@@ -85,18 +93,12 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     const int sw = (lr >> 1) & 7;
     const int wread = (wf * 16 * FB + lr) * 128;
     const int xread = (T::BN + wt * 16 * TB + lr) * 128;
-    auto read_slice = [&](u32x4 (&W)[FB], u32x4 (&X)[TB], int stage, int ks) __attribute__((always_inline)) {
+    // fragment i of a slice of 32 contraction indices: first the FB of w, then the TB of x
+    auto read_fragment = [&](u32x4 (&W)[FB], u32x4 (&X)[TB], auto i, int stage, int ks) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
         const uint8_t* const base = smem + stage * T::STAGE + (((4 * ks + lg) ^ sw) * 16);
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) W[fb] = *reinterpret_cast<const u32x4*>(base + wread + fb * 2048);
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) X[tb] = *reinterpret_cast<const u32x4*>(base + xread + tb * 2048);
-    };
-    auto multiply = [&](const u32x4 (&W)[FB], const u32x4 (&X)[TB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-            for (int fb = 0; fb < FB; ++fb) acc[fb][tb] = mfma16<OP_BF16>(W[fb], X[tb], acc[fb][tb]);
+        if constexpr (I < FB) W[I] = *reinterpret_cast<const u32x4*>(base + wread + I * 2048);
+        else X[I - FB] = *reinterpret_cast<const u32x4*>(base + xread + (I - FB) * 2048);
     };
     // All but the youngest S - 2 stages requested have arrived, and every wavefront has got as far.  (The bare barrier:
     // __syncthreads() would drain the loads that are meant to stay in flight.)
@@ -110,35 +112,63 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     // S - 1 stages are requested ahead; past the end of K the last step is requested again (into a stage nobody reads
     // any more), so that the number of loads in flight stays the constant the waits count on
     int requested = 0;
-    auto request = [&](int stage) __attribute__((always_inline)) {
+    auto request_piece = [&](auto i, int stage) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
         uint8_t* const dst = smem + stage * T::STAGE;
-        const int step = requested > 0 && requested < nK ? 128 : 0;  // bytes on from the step requested before
-#pragma unroll
-        for (int i = 0; i < T::LOADS; ++i) src[i] += step;
-#pragma unroll
-        for (int i = 0; i < FULL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)src[i], (lptr_t)(dst + (wave + 8 * i) * 1024), 16, 0, 0);
-        if constexpr (TB & 1) {
+        src[I] += requested > 0 && requested < nK ? 128 : 0;  // on from the step requested before
+        if constexpr (I < FULL) {
+            __builtin_amdgcn_global_load_lds((gptr_t)src[I], (lptr_t)(dst + (wave + 8 * I) * 1024), 16, 0, 0);
+        } else {
             if ((lane >> 5) == (wave & 1))
-                __builtin_amdgcn_global_load_lds((gptr_t)src[FULL], (lptr_t)(dst + (8 * FULL + (wave >> 1)) * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gptr_t)src[I], (lptr_t)(dst + (8 * FULL + (wave >> 1)) * 1024), 16, 0, 0);
         }
-        ++requested;
     };
 #pragma unroll
-    for (int s = 0; s < S - 1; ++s) request(s);
+    for (int s = 0; s < S - 1; ++s) {
+        static_for<0, T::LOADS>([&](auto i) __attribute__((always_inline)) { request_piece(i, s); });
+        ++requested;
+    }
     sync_stage();
     u32x4 W0[FB], X0[TB], W1[FB], X1[TB];
-    read_slice(W0, X0, 0, 0);
+    constexpr int R = FB + TB;  // fragments of a slice
+    static_for<0, R>([&](auto i) __attribute__((always_inline)) { read_fragment(W0, X0, i, 0, 0); });
+    // While one slice is multiplied, token block by token block, the next one is read: nothing ahead of the first block
+    // (the wait for its own fragments would wait for what was just asked for too) nor of the last one (whose MFMAs
+    // cover the youngest reads), PER fragments ahead of each block between.  (Left to the compiler the reads sank
+    // behind the MFMAs and were waited for there: 641 x 3,320 x 1,664 14.6 -> 12.8 us, 3,600 x 5,120 x 5,120 166 -> 159.)
+    constexpr int GAPS = TB > 2 ? TB - 2 : 1, PER = (R + GAPS - 1) / GAPS, LPER = (T::LOADS + GAPS - 1) / GAPS;
     int stage = 0, free_stage = S - 1;
     for (int k = 0; k < nK; ++k) {
         const int next = stage + 1 == S ? 0 : stage + 1;
-        // the stage read one step ago is free: every wavefront passed a barrier behind its last read of it
-        request(free_stage);
-        read_slice(W1, X1, stage, 1);
-        multiply(W0, X0);
-        sync_stage();                 // step k + 1 has arrived, everybody has read step k
-        read_slice(W0, X0, next, 0);  // (behind the last step: a stage that holds the last step again, unused)
-        multiply(W1, X1);
+        auto slice = [&](u32x4 (&W)[FB], u32x4 (&X)[TB], u32x4 (&Wn)[FB], u32x4 (&Xn)[TB], int nstage, auto ksn) __attribute__((always_inline)) {
+            constexpr int KSN = decltype(ksn)::value;  // slice being read: 1 of this step, or 0 of the next
+            static_for<0, TB>([&](auto tbc) __attribute__((always_inline)) {
+                constexpr int tb = decltype(tbc)::value, gap = tb - 1;
+                if constexpr (gap >= 0 && gap < GAPS) {
+                    constexpr int r0 = gap * PER < R ? gap * PER : R, r1 = r0 + PER < R ? r0 + PER : R;
+                    static_for<r0, r1>([&](auto i) __attribute__((always_inline)) { read_fragment(Wn, Xn, i, nstage, KSN); });
+                    constexpr int l0 = gap * LPER < T::LOADS ? gap * LPER : T::LOADS;
+                    constexpr int l1 = l0 + LPER < T::LOADS ? l0 + LPER : T::LOADS;
+                    // the stage read one step ago is free: every wavefront passed a barrier behind its last read of it
+                    if constexpr (KSN == 1)
+                        static_for<l0, l1>([&](auto i) __attribute__((always_inline)) { request_piece(i, free_stage); });
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int fb = 0; fb < FB; ++fb) acc[fb][tb] = mfma16<OP_BF16>(W[fb], X[tb], acc[fb][tb]);
+                __builtin_amdgcn_sched_barrier(0);
+                // step k + 1 has arrived, everybody has read step k (its fragments have been waited for)
+                if constexpr (KSN == 0 && tb == 0) sync_stage();
+            });
+            if constexpr (TB == 1) {
+                static_for<0, R>([&](auto i) __attribute__((always_inline)) { read_fragment(Wn, Xn, i, nstage, KSN); });
+                if constexpr (KSN == 1)
+                    static_for<0, T::LOADS>([&](auto i) __attribute__((always_inline)) { request_piece(i, free_stage); });
+            }
+        };
+        slice(W0, X0, W1, X1, stage, std::integral_constant<int, 1>());
+        ++requested;
+        slice(W1, X1, W0, X0, next, std::integral_constant<int, 0>());  // (behind the last step: unused)
         free_stage = stage;
         stage = next;
     }
