@@ -6,6 +6,8 @@
 //    K' 8-bit E4M3 with one power-of-two factor per row) and writes each 64-key tile as the exact
 //    byte image the attention kernel keeps in LDS (K' rows, then V^T rows with keys permuted into
 //    the order the PV product consumes).
+#include <type_traits>
+
 #include "dit_attn_device.h"
 
 namespace dit {
@@ -163,76 +165,106 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
     const int tid = threadIdx.x;
     const int c = tid % CPR;
 
+    // All rows of the tile are requested before the first is used: at sizes that leave the chip to a few workgroups
+    // each, row by row, was four trips to memory one after the other (4 heads of 6,240 tokens 10.4 -> 9.1 us; 12 heads
+    // of 32,760 99 -> 90, 40 heads 284 -> 270).
+    auto rows = [&](auto f32_tag) __attribute__((always_inline)) {
+        constexpr bool F32 = decltype(f32_tag)::value;
+        u32x4 rk[NI][F32 ? 2 : 1], rv[NI][F32 ? 2 : 1];
+        int keys[NI];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int r = tid / CPR + i * ROWS_PER_PASS;
-        int key;
-        bool ok;
-        if (t.ranges) {
-            const int i_ = t.slot0 + r;
-            key = i_ < t.la ? t.sa + i_ : (i_ - t.la < t.lb ? t.sb + (i_ - t.la) : -1);
-            ok = key >= 0;
-        } else {
-            key = t.key_src ? t.key_src[r] : t.key0 + r;
-            ok = t.key_src ? key >= 0 : key < t.key_end;
-        }
-        float xk[8], xv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) xk[e] = xv[e] = 0.f;
-        if (ok) {
-            load8(a.k, t.k_off + (int64_t)key * a.sk_t + 8 * c, a.in_f32, xk);
-            load8(a.v, t.v_off + (int64_t)key * a.sv_t + 8 * c, a.in_f32, xv);
-        }
-        if (a.kn.mode) {  // the CPR neighbouring lanes that share a row add up its squares
-            float rs;
-            if (a.kn.mode == 2) {
-                rs = ok ? a.kn.rstd[t.stat_off + key] : 0.f;
+        for (int i = 0; i < NI; ++i) {
+            const int r = tid / CPR + i * ROWS_PER_PASS;
+            int key;
+            if (t.ranges) {
+                const int i_ = t.slot0 + r;
+                key = i_ < t.la ? t.sa + i_ : (i_ - t.la < t.lb ? t.sb + (i_ - t.la) : -1);
             } else {
-                float ss = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ss = fmaf(xk[e], xk[e], ss);
-#pragma unroll
-                for (int m = 1; m < CPR; m <<= 1) ss += __shfl_xor(ss, m);
-                rs = 1.0f / sqrtf(ss * (1.0f / D) + a.kn.eps);
+                key = t.key_src ? t.key_src[r] : t.key0 + r < t.key_end ? t.key0 + r : -1;
             }
-            if (ok) norm8(xk, a.kn, rs, t.h, D, c);
-        }
-        if (ok) {
-            if (a.tab) {
-                int pt, ph, pw;
-                token_pos(key, t.rg, pt, ph, pw);
-                rope8(xk, c, t.rg, a.tab, pt, ph, pw);
+            keys[i] = key;
+#pragma unroll
+            for (int w = 0; w < (F32 ? 2 : 1); ++w) rk[i][w] = rv[i][w] = mk4(0u, 0u, 0u, 0u);
+            if (key >= 0) {
+                const int64_t ko = t.k_off + (int64_t)key * a.sk_t + 8 * c, vo = t.v_off + (int64_t)key * a.sv_t + 8 * c;
+                const u32x4* const ks = reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(a.k) + ko * (F32 ? 4 : 2));
+                const u32x4* const vsrc = reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(a.v) + vo * (F32 ? 4 : 2));
+#pragma unroll
+                for (int w = 0; w < (F32 ? 2 : 1); ++w) {
+                    rk[i][w] = ks[w];
+                    rv[i][w] = vsrc[w];
+                }
             }
         }
-        if constexpr (QK_OP == OP_FP8) {
-            // one power-of-two factor per key row brings its largest magnitude into [128, 256)
-            float am = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) am = fmaxf(am, fabsf(xk[e]));
+        for (int i = 0; i < NI; ++i) {
+            const int r = tid / CPR + i * ROWS_PER_PASS;
+            const int key = keys[i];
+            const bool ok = key >= 0;
+            float xk[8], xv[8];
+            if constexpr (F32) {
 #pragma unroll
-            for (int m = 1; m < CPR; m <<= 1) am = fmaxf(am, __shfl_xor(am, m));
-            const int ex = fp8_row_exponent(am);
-            const float sc = pow2i(ex);
+                for (int e = 0; e < 8; ++e) {
+                    xk[e] = __uint_as_float(rk[i][e >> 2][e & 3]);
+                    xv[e] = __uint_as_float(rv[i][e >> 2][e & 3]);
+                }
+            } else {
+                widen8(rk[i][0], xk);
+                widen8(rv[i][0], xv);
+            }
+            if (a.kn.mode) {  // the CPR neighbouring lanes that share a row add up its squares
+                float rs;
+                if (a.kn.mode == 2) {
+                    rs = ok ? a.kn.rstd[t.stat_off + key] : 0.f;
+                } else {
+                    float ss = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xk[e] *= sc;
-            // chunk c = channels [8c, 8c+8) goes where the lane that multiplies it against the same
-            // channels of q' finds it: contraction step c / 8, lane half c % 2, slot (c / 2) % 4
-            const int off = (c >> 3) * 64 + (c & 1) * 32 + ((c >> 1) & 3) * 8;
-            *reinterpret_cast<uint2*>(t.dst + r * G::KROW8 + off) = pack8_fp8(xk);
-            if (c == CPR - 1) *reinterpret_cast<u32x4*>(t.dst + r * G::KROW8 + D) = mk4(0u, 0u, 0u, 0u);  // the pad, see below
-            if (c == 0) t.dst[G::KSCALE_OFF + r] = (uint8_t)(127 - ex);
-        } else {
-            // (layout 1: rows 4..11 of every 16 keep their 16-byte chunks in swapped pairs, see below)
-            const int cs = a.v_layout ? c ^ (((r >> 2) ^ (r >> 3)) & 1) : c;
-            *reinterpret_cast<u32x4*>(t.dst + r * G::KROW + cs * 16) = pack8<QK_OP>(xk);
-            // the 16 pad bytes behind the row are written too (zeros): a part is then a run of fully written
-            // 32-byte sectors, and none of them has to be read back from memory to be completed
-            if (c == CPR - 1) *reinterpret_cast<u32x4*>(t.dst + r * G::KROW + D * 2) = mk4(0u, 0u, 0u, 0u);
+                    for (int e = 0; e < 8; ++e) ss = fmaf(xk[e], xk[e], ss);
+#pragma unroll
+                    for (int m = 1; m < CPR; m <<= 1) ss += __shfl_xor(ss, m);
+                    rs = 1.0f / sqrtf(ss * (1.0f / D) + a.kn.eps);
+                }
+                if (ok) norm8(xk, a.kn, rs, t.h, D, c);
+            }
+            if (ok) {
+                if (a.tab) {
+                    int pt, ph, pw;
+                    token_pos(key, t.rg, pt, ph, pw);
+                    rope8(xk, c, t.rg, a.tab, pt, ph, pw);
+                }
+            }
+            if constexpr (QK_OP == OP_FP8) {
+                // one power-of-two factor per key row brings its largest magnitude into [128, 256)
+                float am = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) am = fmaxf(am, fabsf(xk[e]));
+#pragma unroll
+                for (int m = 1; m < CPR; m <<= 1) am = fmaxf(am, __shfl_xor(am, m));
+                const int ex = fp8_row_exponent(am);
+                const float sc = pow2i(ex);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xk[e] *= sc;
+                // chunk c = channels [8c, 8c+8) goes where the lane that multiplies it against the same
+                // channels of q' finds it: contraction step c / 8, lane half c % 2, slot (c / 2) % 4
+                const int off = (c >> 3) * 64 + (c & 1) * 32 + ((c >> 1) & 3) * 8;
+                *reinterpret_cast<uint2*>(t.dst + r * G::KROW8 + off) = pack8_fp8(xk);
+                if (c == CPR - 1) *reinterpret_cast<u32x4*>(t.dst + r * G::KROW8 + D) = mk4(0u, 0u, 0u, 0u);  // the pad, see below
+                if (c == 0) t.dst[G::KSCALE_OFF + r] = (uint8_t)(127 - ex);
+            } else {
+                // (layout 1: rows 4..11 of every 16 keep their 16-byte chunks in swapped pairs, see below)
+                const int cs = a.v_layout ? c ^ (((r >> 2) ^ (r >> 3)) & 1) : c;
+                *reinterpret_cast<u32x4*>(t.dst + r * G::KROW + cs * 16) = pack8<QK_OP>(xk);
+                // the 16 pad bytes behind the row are written too (zeros): a part is then a run of fully written
+                // 32-byte sectors, and none of them has to be read back from memory to be completed
+                if (c == CPR - 1) *reinterpret_cast<u32x4*>(t.dst + r * G::KROW + D * 2) = mk4(0u, 0u, 0u, 0u);
+            }
+            const u32x4 pv = pack8<PV_OP>(xv);
+            uint32_t* row = reinterpret_cast<uint32_t*>(vs + r * VS + 8 * c);
+            row[0] = pv.x; row[1] = pv.y; row[2] = pv.z; row[3] = pv.w;
         }
-        const u32x4 pv = pack8<PV_OP>(xv);
-        uint32_t* row = reinterpret_cast<uint32_t*>(vs + r * VS + 8 * c);
-        row[0] = pv.x; row[1] = pv.y; row[2] = pv.z; row[3] = pv.w;
-    }
+    };
+    if (a.in_f32) rows(std::true_type{});
+    else rows(std::false_type{});
     __syncthreads();
 
     // V^T chunk (d, kc) = eight key slots, in the order the attention kernel's PV operand wants its keys:
