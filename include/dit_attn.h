@@ -305,6 +305,7 @@ typedef struct {
     dit_qk_norm norm; /* zero = off */
 } dit_varlen_attn_params;
 
+/* As dit_attn_workspace_bytes: includes room for pieces of query tiles, without which the tiles are computed whole. */
 size_t dit_attn_varlen_workspace_bytes(const dit_varlen_attn_params *p);
 
 dit_status dit_attn_varlen_forward(const void *q, const void *k, const void *v, void *out,
