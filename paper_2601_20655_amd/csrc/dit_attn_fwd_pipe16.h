@@ -970,8 +970,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(cons
 }
 
 // Cross-attention with one joint softmax per request: workgroups chain `qch` query tiles of one (request, head).
-// The pre-pack leaves a request's attending keys densely in its tiles 0 .. count-1 (key_compact_kernel; without a
-// byte mask all keys attend), so only the last of them is partial; count and that tile's mask come from the
+// The pre-pack leaves a request's attending keys densely in its tiles 0 .. count-1 (without a mask or counts all keys
+// attend), so only the last of them is partial; count and that tile's mask come from the
 // workspace.  Workgroup order: request fastest, then chunk, then head, so that the workgroups an XCD holds at a
 // time share a handful of (request, head) tile sets in its L2 and requests of different lengths are interleaved.
 template <int D, int QK_OP, int PV_OP, int NW>

@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_kernel(const PackArgs a) 
         if (tid == 0) {
             a.tile_mask[(size_t)b * a.nKT + j] = m;
             if (!a.key_src) {
-                // the list of tiles that hold a key and its counts, which tile_compact_kernel otherwise derives from the masks
+                // the list of tiles that hold a key and its counts (long masks: tile_compact_kernel derives them)
                 const int jj = second ? j - a.nTA : j;
                 if (m != 0ull) a.tile_list[(size_t)b * a.nKT + (second ? ca + jj : jj)] = j;
                 if (j == 0) {
