@@ -80,6 +80,10 @@ constexpr int chain_lds_bytes() { return 4 * TileGeom<D>::PART_KIB * 1024 + NW *
 //
 // PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
 // leaves its unnormalised output, running maxima and row sums in piece pv.piece of a.part_o / a.part_ml.
+// bf16 score operands can make a score -inf, which a row passes over wherever it has a maximum already; a piece may
+// START with a tile of nothing else.  Such a row is `empty` until a tile has a score for it: its scores are taken as
+// they are (relative to 0: probabilities, sums and output stay 0) and its first finite maximum, above or below 0,
+// moves them whatever the threshold (empty_thr).
 template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
@@ -193,6 +197,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     f32x16 O[NOG][2];
     f32x4 negm[2];  // every element = -m_run: the accumulator a score MFMA chain starts from
     float m_run[2], l_run[2];
+    constexpr bool EMPTY_ROWS = PIECES && QK_OP == OP_BF16;
+    float empty_thr[2] = {kRescaleThr, kRescaleThr};  // EMPTY_ROWS: -inf while the row is empty
     auto reset_state = [&]() {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -273,14 +279,19 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         const u32x4 ones = mk4(kOnes, kOnes, kOnes, kOnes);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            const float want = mx_new[qb] > kRescaleThr ? mx_new[qb] : 0.f;
+            const float thr = EMPTY_ROWS ? empty_thr[qb] : kRescaleThr;
+            const float want = mx_new[qb] > thr ? mx_new[qb] : 0.f;
             // hi + lo in the score operand type; what is applied is their exact fp32 sum
             const uint32_t hi_bits = pack2<QK_OP>(want, 0.f) & 0xffffu;
             const float hi = QK_OP == OP_F16 ? (float)__builtin_bit_cast(f16x2, hi_bits)[0] : bf16_lo(hi_bits);
             const uint32_t lo_bits = pack2<QK_OP>(want - hi, 0.f) & 0xffffu;
             const float lo = QK_OP == OP_F16 ? (float)__builtin_bit_cast(f16x2, lo_bits)[0] : bf16_lo(lo_bits);
             const float shift = hi + lo;
-            const float alpha = __builtin_amdgcn_exp2f(-shift);
+            float alpha = __builtin_amdgcn_exp2f(-shift);
+            if constexpr (EMPTY_ROWS) {
+                if (empty_thr[qb] != kRescaleThr) alpha = 1.f;  // (nothing to rescale; exp2 may be infinite)
+                if (mx_new[qb] > thr) empty_thr[qb] = kRescaleThr;
+            }
             m_run[qb] += shift;
             l_run[qb] *= alpha;
             // B operand: contraction slots 0 and 1 (lanes of row g = 0) = -hi, -lo
@@ -441,7 +452,11 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         }
         // Common case: no score of the pending tile tops the threshold in ANY lane, which needs no exchange
         // between lanes at all; the full row maxima are only formed on the rare paths below.
-        bool need = __any(fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) > kRescaleThr);
+        bool need;
+        if constexpr (EMPTY_ROWS)  // (pm[0], pm[1]: query block 0)
+            need = __any(fmaxf(pm[0], pm[1]) > empty_thr[0] || fmaxf(pm[2], pm[3]) > empty_thr[1]);
+        else
+            need = __any(fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) > kRescaleThr);
         if constexpr (!LATE) dma_wait_and_sync();
         if constexpr (MASKED) {
             const uint64_t mnext = mask_of(j + 1);
@@ -654,8 +669,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             m_run[qb] = mx_new[qb];
-            // (bf16 score operands can overflow to -inf for a whole tile; a piece may START with such a tile)
-            if constexpr (PIECES && QK_OP == OP_BF16) m_run[qb] = fmaxf(m_run[qb], -3.0e38f);
+            if constexpr (EMPTY_ROWS) {
+                if (mx_new[qb] == -INFINITY) {
+                    m_run[qb] = 0.f;
+                    empty_thr[qb] = -INFINITY;
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) negm[qb][r] = -m_run[qb];
 #pragma unroll
@@ -798,7 +817,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                     dst[cb * 64] = make_float4(O[cb / 4][qb][e], O[cb / 4][qb][e + 1], O[cb / 4][qb][e + 2],
                                                O[cb / 4][qb][e + 3]);
                 }
-                if (lg == 0) a.part_ml[blk * 16 + li] = make_float2(m_run[qb], l);
+                const bool empty = EMPTY_ROWS && empty_thr[qb] != kRescaleThr;
+                if (lg == 0) a.part_ml[blk * 16 + li] = make_float2(empty ? -INFINITY : m_run[qb], l);
                 continue;
             }
         }
@@ -908,7 +928,8 @@ __device__ __forceinline__ void combine_rows(const AttnArgs& a, int64_t first, i
         float4 x[NCB];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) x[cb] = src[cb * 64];
-        const float w = __builtin_amdgcn_exp2f(ml.x - m);
+        // (a piece of -inf scores only, bf16 score operands, weighs nothing, also where there is no other)
+        const float w = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - m);
         l = fmaf(w, ml.y, l);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {

@@ -85,3 +85,52 @@ def test_packed_requests_in_pieces(grids, H, D):
         ref = oracle.self_attn(qn[None, rows], kn[None, rows], vn[None, rows], g, split)[0]
         compare(to_f64(out[rows]), ref, what="request %s in pieces" % (g,))
         compare(to_f64(out_w[rows]), ref, what="request %s whole" % (g,))
+
+
+@pytest.mark.parametrize("packed", [False, True], ids=["one-sequence", "packed"])
+def test_bf16_scores_that_overflow_in_some_tiles(packed):
+    """bf16 score operands can make a score -inf in fp32: such a key has no weight, and its row's result is that of the
+    other keys, also where a piece of the keys starts with a tile of nothing else (whichever tiles the pieces start at:
+    row i overflows in tile i only, rows 43 to 86 in one or several thirds of the sequence, which then hold whole
+    pieces).  The latent grid has one frame, so the channels of the first rotary section are not rotated."""
+    import torch
+
+    grid, H, D, split = (1, 45, 77), 3, 128, (44, 42, 42)
+    L = grid[1] * grid[2]
+    n_tiles = (L + 63) // 64
+    flags = B.DIT_FLAG_QK_BF16
+    cfg = dict(B=1, grid=grid, H=H, D=D, split=split, dtype="f32", seed=93)
+    q, k, v = wl.self_attn_inputs(cfg)
+    q[..., :44] = 0.0
+    k[..., :44] = 0.0
+    for t in range(1, 43):  # (tile 0 stays ordinary: every row has a finite score in the first tile)
+        q[:, t, :, t] = 1e30
+        k[:, 64 * t:64 * (t + 1), :, t] = -1e30
+    k[:, 64 * 18:64 * 37, :, 43] = -1e30
+    q[:, 43:65, :, 43] = 1e30
+    k[:, 64 * 37:, :, 0] = -1e30
+    q[:, 65:87, :, 0] = 1e30
+    q[:, 76:87, :, 43] = 1e30
+    qn, kn, vn = (wl.f32_to_bf16_bits(a) for a in (q, k, v))
+    ref, ref_lse = oracle.self_attn(qn, kn, vn, grid, split, rows=np.arange(128), want_lse=True)
+    qd, kd, vd = to_dev(qn), to_dev(kn), to_dev(vn)
+    if packed:
+        short = (1, 3, 7)  # (a second request makes it a packed call; its rows repeat the first ones)
+        n = L + 21
+        qd, kd, vd = (torch.cat([t[0], t[0, :21]]) for t in (qd, kd, vd))
+        p = B.varlen_attn_params(qd, kd, vd, qd, [grid, short], split, flags=flags)
+        need = B.dit_attn_varlen_workspace_bytes(p)
+        p.flags |= B.DIT_FLAG_SMALL_WORKGROUP
+        assert need > B.dit_attn_varlen_workspace_bytes(p), "this batch is meant to be computed in pieces"
+        out, lse = B.dit_attn_varlen_forward(qd, kd, vd, [grid, short], split, out_dtype=torch.float32, want_lse=True,
+                                             flags=flags)
+        out, lse = out[None, :L], lse[None, :, :L]
+    else:
+        assert n_tiles == 55
+        p = B.self_attn_params(qd, kd, vd, qd, grid, split, flags=flags)
+        need = B.dit_attn_workspace_bytes(p)
+        p.flags |= B.DIT_FLAG_SMALL_WORKGROUP
+        assert need > B.dit_attn_workspace_bytes(p), "this shape is meant to be computed in pieces"
+        out, lse = B.dit_attn_forward(qd, kd, vd, grid, split, out_dtype=torch.float32, want_lse=True, flags=flags)
+    compare(to_f64(out[:, :128]), ref, tol=4e-2, what="rows whose scores overflow")  # (8-bit score operands)
+    assert np.abs(to_f64(lse[..., :128]) - ref_lse).max() < 1e-1
