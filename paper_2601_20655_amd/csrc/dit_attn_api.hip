@@ -382,7 +382,8 @@ double work_off(const PackedClass* c, int n, int64_t slots, double* half = nullp
 
 // Several packed requests: wavefronts per workgroup, and pieces per query tile of each request, by the numbers that
 // choose_split goes by.  A request is cut into pieces of at most one length common to all; batches of more than six
-// rounds of workgroups are left whole (their last round is a small part of them).
+// rounds of workgroups are left whole (their last round is a small part of them).  *nw is for whole tiles; pieces, where
+// a request gets more than one, are computed by 8 wavefronts.
 void choose_packed(const dit::VarlenTable& vt, int H, uint32_t flags, int* nw, int* pieces) {
     PackedClass c8[DIT_MAX_REQUESTS], c4[DIT_MAX_REQUESTS];
     int64_t n8 = 0, n4 = 0;
@@ -432,7 +433,6 @@ void choose_packed(const dit::VarlenTable& vt, int H, uint32_t flags, int* nw, i
         }
     }
     if (best_len == 0) return;
-    *nw = 8;
     for (int r = 0; r < vt.n; ++r) pieces[r] = pieces_of(vt.r[r].nKT, best_len);
 }
 
@@ -531,8 +531,9 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
     if (n_pieces > 0 && workspace_bytes < pl->total) {  // no room for the pieces: whole tiles
         for (int r = 0; r < n; ++r) pieces[r] = 1;
         pl->single = dit::SplitPlan{0, 0, 1};
+        n_pieces = 0;
     }
-    if (pl->single.n_tail > 0) pl->fl.nw = 8;
+    if (n_pieces > 0) pl->fl.nw = 8;
 
     // query tiles, pieces, and the order the workgroups are handed out in: longest first
     const int bq = 32 * pl->fl.nw;
@@ -669,6 +670,13 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
 }
 
 }  // namespace
+
+int dit::packed_layout(const void* params, size_t workspace_bytes, int* split_tiles) {
+    VarlenPlan pl;
+    if (plan_varlen(static_cast<const dit_varlen_attn_params*>(params), workspace_bytes, &pl) != DIT_OK) return 0;
+    *split_tiles = pl.vt.split_tiles + pl.single.n_tail;
+    return pl.fl.nw;
+}
 
 extern "C" {
 

@@ -170,6 +170,10 @@ inline hipError_t allow_dynamic_lds(K kern, int bytes, std::atomic<uint64_t>& do
     return e;
 }
 
+// How a packed call (params: dit_varlen_attn_params) with this workspace is laid over the chip: wavefronts per workgroup
+// (0: it is refused) and query tiles computed in pieces.  No device is touched; the host tests read it.
+int packed_layout(const void* params, size_t workspace_bytes, int* split_tiles);
+
 // Records "<where>: <HIP error text>" for dit_last_hip_error() of the calling thread; returns DIT_ERR_HIP.
 int report_hip_error(hipError_t e, const char* where);
 

@@ -1,0 +1,38 @@
+"""Host-side checks of how calls are laid over the chip: the library's own rules, called without a GPU (functions inside
+the library, by their C++ symbols)."""
+import ctypes
+
+import pytest
+
+from paper_2601_20655_amd import binding as B
+from test_abi_host import varlen_params
+
+
+def packed_layout(p, nbytes):
+    f = B.lib()._ZN3dit13packed_layoutEPKvmPi
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+    tiles = ctypes.c_int(-1)
+    return f(ctypes.byref(p), nbytes, ctypes.byref(tiles)), tiles.value
+
+
+@pytest.mark.parametrize("grids,H,nw", [
+    (((1, 55, 63), (1, 40, 60), (1, 17, 18)), 3, 4),  # pieces pay, and whole tiles are faster with 4 wavefronts
+    (((4, 30, 52), (1, 45, 80), (1, 30, 52)), 2, 4),
+    (((1, 45, 80), (1, 40, 60)), 40, 8),
+    (((1, 45, 77),), 3, 4),                           # one request: as in dit_attn_forward
+])
+def test_packed_call_without_room_for_pieces_takes_the_whole_tile_form(grids, H, nw):
+    p = varlen_params(grids, H=H)
+    room = B.dit_attn_varlen_workspace_bytes(p)
+    p.flags = B.DIT_FLAG_SMALL_WORKGROUP
+    whole = B.dit_attn_varlen_workspace_bytes(p)
+    p.flags = 0
+    assert whole <= room
+    if whole < room:
+        assert packed_layout(p, room) == (8, packed_layout(p, room)[1]) and packed_layout(p, room)[1] > 0
+    assert packed_layout(p, whole) == (nw, 0)
+    p.flags = B.DIT_FLAG_BIG_WORKGROUP
+    assert packed_layout(p, whole) == (8, 0)
+    p.flags = B.DIT_FLAG_SMALL_WORKGROUP
+    assert packed_layout(p, room) == (4, 0)
