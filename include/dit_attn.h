@@ -240,7 +240,7 @@ dit_status dit_cross_attn_forward(const void *q, const void *k, const void *v,
  *                 else DIT_ERR_INVALID_ARG.
  * Everything else -- q, k, v, out, lse, params, flags, workspace (same size: dit_cross_attn_workspace_bytes),
  * errors -- as dit_cross_attn_forward.  No mask is read and no key list is built: the pre-pack pass places each
- * key from the two counts, so two small passes of the mask form (key compaction, tile list) do not run.
+ * key from the two counts (the mask form needs two more small passes for long masks of many heads).
  * A request with both counts 0 gets out = 0 and lse = -inf.  Ownership: the caller keeps kv_len alive and
  * unchanged until the work enqueued on `stream` has finished. */
 dit_status dit_cross_attn_forward_lengths(const void *q, const void *k, const void *v,

@@ -812,7 +812,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     pa.tile_list = reinterpret_cast<int*>(ws + pl.list_off);
     pa.tile_count = reinterpret_cast<int*>(ws + pl.count_off);
     pa.tile_count_a = pl.split > 0 ? reinterpret_cast<int*>(ws + pl.count_a_off) : nullptr;
-    pa.key_src = kv_valid && dit::mask_needs_key_list(p->Lk) ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
+    pa.key_src = kv_valid && dit::mask_needs_key_list(p->B, p->H, p->Lk, pl.split) ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
     pa.kv_len = use_len ? kv_len : nullptr;
     pa.second_start = second_start;
     pa.split = pl.split;

@@ -76,14 +76,14 @@ struct PackArgs {
     const void* k;
     const void* v;
     const uint8_t* valid;  // nullable [B, Lk]
-    int* key_src;          // with valid, long masks: [B, nKT, 64] source key of every tile slot, -1 = empty (launch_key_compact)
+    int* key_src;          // with valid, listed masks: [B, nKT, 64] source key of every tile slot, -1 = empty (launch_key_compact)
     const int* kv_len;     // nullable [B, 2] (instead of valid): the keys that attend are the first kv_len[b][0] of
                            // [0, ...) and the first kv_len[b][1] of [second_start, Lk); the pre-pack works out every
                            // slot's source key, the tile masks, the tile list and its counts from the two numbers
     int second_start;      // with kv_len: first key of the second range (decoupled form: = split)
     uint8_t* tiles;        // [B*H, nKT, TILE_BYTES]
     uint64_t* tile_mask;   // nullable [B, nKT]
-    int* tile_list;        // nullable [B, nKT], filled by launch_tile_compact
+    int* tile_list;        // nullable [B, nKT], filled by the pre-pack, with key_src by launch_tile_compact
     int* tile_count;       // nullable [B]
     int* tile_count_a;     // nullable [B]: listed tiles that belong to the first key group
     int split, nTA;        // split > 0: keys [0, split) fill tiles [0, nTA), keys [split, Lk) the rest
@@ -190,8 +190,9 @@ hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s);
-// a mask of this many keys is listed beforehand (the next two passes); launch_prepack sorts out shorter ones by itself
-bool mask_needs_key_list(int Lk);
+// whether the masks of such a call (split: first key of the second group, 0 = one group) are listed beforehand (the next
+// two passes); launch_prepack sorts out the others by itself
+bool mask_needs_key_list(int B, int H, int Lk, int split);
 // before launch_prepack when a.valid and a.key_src are set: the valid keys of every batch entry (of each key group) in
 // ascending order, densely over the tile slots
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s);

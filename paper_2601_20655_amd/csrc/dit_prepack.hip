@@ -299,9 +299,10 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
 // Key padding masks.  Attention does not depend on the order of its keys, so the keys that attend, in ascending order,
 // are packed densely into the tiles of their group: padded keys cost no tile, wherever they sit.  Every workgroup finds
 // the keys of its own tile: slot r holds the valid key of rank rank0 + r among mask bytes [k0, k1) (src[r], -1: none).
-// Returns the number of valid keys.  cnt: one count per 64 keys of the range.  (Two small passes ahead of this one, one
-// that listed the keys and one that listed the tiles, cost 11 us and two launches whatever the size of the call.)
-constexpr int kMaskKeys = 4096;  // the counts are summed up by one wavefront; longer masks are listed beforehand
+// Returns the number of valid keys.  cnt: one count per 64 keys of the range.  Two small passes ahead of this one, one
+// that lists the keys and one that lists the tiles, take 4 to 9 us a call longer where the masks are short or the
+// workgroups few; see mask_needs_key_list for where they are the better way.
+constexpr int kMaskKeys = 4096;  // the counts are summed up by one wavefront
 __device__ __forceinline__ int find_keys(const uint8_t* valid, int k0, int k1, int rank0, int* src, int* cnt) {
     const int tid = threadIdx.x, lane = tid & 63;
     for (int r = tid; r < kBK; r += kThreads) src[r] = -1;
@@ -401,7 +402,7 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_kernel(const PackArgs a) 
         if (tid == 0) {
             a.tile_mask[(size_t)b * a.nKT + j] = m;
             if (!a.key_src) {
-                // the list of tiles that hold a key and its counts (long masks: tile_compact_kernel derives them)
+                // the list of tiles that hold a key and its counts (listed masks: tile_compact_kernel derives them)
                 const int jj = second ? j - a.nTA : j;
                 if (m != 0ull) a.tile_list[(size_t)b * a.nKT + (second ? ca + jj : jj)] = j;
                 if (j == 0) {
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(kThreads) kv_prepack_varlen_kernel(const PackA
     pack_tile<D, QK_OP, PV_OP>(a, t, vs);
 }
 
-// Masks of more than kMaskKeys keys: one wavefront per (batch entry, key group) writes the group's valid keys, in
+// Where mask_needs_key_list says so: one wavefront per (batch entry, key group) writes the group's valid keys, in
 // ascending order, densely into the slots of the group's tiles; the slots left over get -1.
 __global__ void __launch_bounds__(64) key_compact_kernel(const uint8_t* valid, int* key_src, int Lk, int nKT,
                                                          int split, int nTA) {
@@ -458,7 +459,15 @@ __global__ void __launch_bounds__(64) key_compact_kernel(const uint8_t* valid, i
     for (int i = count + lane; i < (t1 - t0) * kBK; i += 64) out[i] = -1;
 }
 
-bool mask_needs_key_list(int Lk) { return Lk > kMaskKeys; }
+// Every workgroup (one per request, head and tile) reads the mask of its key group; past 20 MiB in all that takes
+// longer than listing the keys once does.  Whole calls with 64 queries, us, each tile by itself and from the list
+// (requests x heads x keys): 1 x 12 x 512 18 and 23, 4 x 12 x 4,096 (12.6 MB read) 85 and 93, 4 x 40 x 2,048 (10.5 MB)
+// 96 and 99; at the line 2 x 40 x 4,096 124 and 127, 8 x 40 x 2,048 201 and 199; 16 x 12 x 3,072 (28 MB) 175 and 172,
+// 4 x 40 x 4,096 (42 MB) 225 and 210, head_dim 64 16 x 12 x 4,096 (50 MB) 150 and 134.
+bool mask_needs_key_list(int B, int H, int Lk, int split) {
+    const auto read = [](int64_t keys) { return (keys + kBK - 1) / kBK * keys; };
+    return Lk > kMaskKeys || (int64_t)B * H * (read(split) + read(Lk - split)) > (20 << 20);
+}
 
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(key_compact_kernel, dim3(a.B, a.split > 0 ? 2 : 1), dim3(64), 0, s, a.valid, a.key_src, a.Lk,

@@ -302,3 +302,22 @@ def test_scattered_masks_short_and_long(Lk, split):
     got = to_f64(out)
     assert np.all(got[2] == 0.0)
     compare(got, ref, what="scattered mask Lk=%d split=%d" % (Lk, cut))
+
+
+@pytest.mark.parametrize("split", [0, 700])
+def test_many_heads_with_listed_masks_of_moderate_length(split):
+    """Masks of fewer than 4,096 keys that are listed ahead of the pre-pack because many heads would read them: the same
+    bits as the first heads alone, whose tiles find their keys by themselves, and the oracle's numbers."""
+    import torch
+
+    Lk, H, few = 3300, 200, 2
+    cfg = dict(B=1, Lq=33, n_text=Lk - 1, n_image=1, H=few, D=64, dtype="bf16", min_text=1, seed=611)
+    q, k, v, _, _ = wl.cross_attn_inputs(cfg)
+    valid = (np.random.default_rng(611).random((1, Lk)) < 0.4).astype(np.uint8)
+    ref = oracle.cross_attn_decoupled(q, k, v, split, valid) if split else oracle.cross_attn(q, k, v, valid)
+    qd, kd, vd, vald = to_dev(q), to_dev(k), to_dev(v), torch.from_numpy(valid).cuda()
+    alone = B.dit_cross_attn_forward(qd, kd, vd, vald, out_dtype=torch.float32, split=split)
+    compare(to_f64(alone), ref, what="two heads, split=%d" % split)
+    many = [t.repeat(1, 1, H // few, 1) for t in (qd, kd, vd)]
+    out = B.dit_cross_attn_forward(*many, vald, out_dtype=torch.float32, split=split)
+    assert torch.equal(out, alone.repeat(1, 1, H // few, 1))

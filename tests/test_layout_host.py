@@ -36,3 +36,14 @@ def test_packed_call_without_room_for_pieces_takes_the_whole_tile_form(grids, H,
     assert packed_layout(p, whole) == (8, 0)
     p.flags = B.DIT_FLAG_SMALL_WORKGROUP
     assert packed_layout(p, room) == (4, 0)
+
+
+@pytest.mark.parametrize("nb,H,Lk,split,listed", [
+    (4, 40, 769, 0, False), (1, 3, 4096, 0, False), (4, 12, 4096, 0, False), (4, 40, 2048, 0, False),
+    (8, 40, 2048, 0, False), (2, 40, 4096, 0, False), (16, 12, 3072, 0, True), (4, 40, 4096, 0, True), (8, 40, 4096, 2048, True),
+    (2, 40, 4096, 2048, False), (1, 1, 4097, 0, True), (1, 1, 4097, 1, True), (1 << 20, 1 << 10, 4096, 0, True),
+])
+def test_masks_are_listed_where_the_tiles_would_read_them_too_often(nb, H, Lk, split, listed):
+    f = B.lib()._ZN3dit19mask_needs_key_listEiiii
+    f.restype = ctypes.c_bool
+    assert f(nb, H, Lk, split) == listed
