@@ -194,6 +194,12 @@ dit_status setup_rows(const dit::TableArgs* table, const dit_qk_norm& n, const v
     return e == hipSuccess ? DIT_OK : hip_fail(e, "row_stats_kernel");
 }
 
+void set_base(dit::TableArgs* ta, float base) {
+    const long double l = log2l((long double)base);
+    ta->log2_base = (double)l;
+    ta->log2_base_lo = (double)(l - (long double)ta->log2_base);
+}
+
 struct SelfPlan {
     Flags fl;
     int64_t L;
@@ -718,7 +724,7 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     ta.n[0] = p->T; ta.n[1] = p->Hg; ta.n[2] = p->Wg;
     ta.origin[0] = p->t0; ta.origin[1] = p->h0; ta.origin[2] = p->w0;
     ta.rg = rg;
-    ta.log2_base = log2((double)p->rope_base);
+    set_base(&ta, p->rope_base);
     ta.total = pl.table_entries;
     hipError_t e = hipSuccess;
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
@@ -904,7 +910,7 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     ta.n[0] = pl.maxT; ta.n[1] = pl.maxHg; ta.n[2] = pl.maxWg;
     ta.origin[0] = p->t0; ta.origin[1] = p->h0; ta.origin[2] = p->w0;
     ta.rg = rg;
-    ta.log2_base = log2((double)p->rope_base);
+    set_base(&ta, p->rope_base);
     ta.total = pl.table_entries;
     hipError_t e = hipSuccess;
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
@@ -1037,7 +1043,7 @@ dit_status dit_qkv_proj_forward(const void* x, const void* w, const void* bias, 
     ta.n[0] = ap->T; ta.n[1] = ap->Hg; ta.n[2] = ap->Wg;
     ta.origin[0] = ap->t0; ta.origin[1] = ap->h0; ta.origin[2] = ap->w0;
     ta.rg = rg;
-    ta.log2_base = log2((double)ap->rope_base);
+    set_base(&ta, ap->rope_base);
     ta.total = pl.table_entries;
     hipError_t e = dit::launch_row_stats(&ta, nullptr, nullptr, s);
     if (e != hipSuccess) return hip_fail(e, "row_stats_kernel");

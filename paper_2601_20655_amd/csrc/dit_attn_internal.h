@@ -68,7 +68,7 @@ struct TableArgs {
     int n[3];       // positions per axis (T, Hg, Wg)
     int origin[3];  // t0, h0, w0
     RopeGeom rg;
-    double log2_base;
+    double log2_base, log2_base_lo;  // log2(base) as the sum of two doubles
     int total;
 };
 

@@ -193,3 +193,27 @@ def test_full_size_sampled_rows(name):
     del out
     out = run_self(cfg, q, k, v)
     compare(to_f64(out[:, torch.from_numpy(rows).cuda()]), ref, bf16_out=True, what="%s bf16 out" % name)
+
+
+@pytest.mark.parametrize("base,origin", [(10000.0, 0), (10000.0, 1 << 20), (1e-10, 3), (3e38, 1 << 20)])
+def test_rotation_table_against_extended_precision(base, origin):
+    """The table sits at the start of the workspace: fp32 (cos, sin) of fp64 angles.  An entry may be off by its own
+    rounding (2^-25 at most) and by the fp64 error of the angle: the power and the product with the position, an ulp
+    each and a half for good measure.  (The exponent -2i/d is taken as the double that it rounds to.)"""
+    import torch
+
+    grid, split = (5, 3, 4), (44, 42, 42)
+    q = torch.zeros((1, 60, 1, 128), dtype=torch.bfloat16, device="cuda")
+    p = B.self_attn_params(q, q, q, q, grid, split)
+    ws = torch.empty(B.dit_attn_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    B.dit_attn_forward(q, q, q, grid, split, origin=(origin,) * 3, rope_base=base, workspace=ws)
+    n = sum(g * d // 2 for g, d in zip(grid, split))
+    tab = ws[:8 * n].view(torch.float32).cpu().numpy().reshape(n, 2)
+    ext = np.longdouble
+    base = ext(np.float32(base))
+    phi = np.concatenate([(np.arange(g) + origin).astype(ext)[:, None] * np.power(base, (-(np.arange(d // 2) / np.float64(d // 2))).astype(ext))
+                          for g, d in zip(grid, split)], axis=None)
+    allow = 2.0 ** -25 + np.abs(phi) * ext(2.5 * 2.0 ** -53)
+    for got, want in ((tab[:, 0], np.cos(phi)), (tab[:, 1], np.sin(phi))):
+        err = np.abs(got.astype(ext) - want)
+        assert np.all(err <= allow), "entry %d: off by %g, allowed %g" % (int(np.argmax(err / allow)), err.max(), allow[np.argmax(err / allow)])
