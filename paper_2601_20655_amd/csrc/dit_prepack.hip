@@ -35,7 +35,9 @@ __device__ __forceinline__ void rope_entry(const TableArgs& a, int idx) {
     a.tab[idx] = make_float2((float)cs, (float)sn);
 }
 
-// 1/sqrt(mean of x^2 over all H*D channels + eps) of one token row, by one wavefront
+// 1/sqrt(mean of x^2 over all H*D channels + eps) of one token row, by one wavefront.  The order of the sum is fixed:
+// chunk i (16 bytes of 16-bit rows) belongs to column i % 256, the columns 64 u .. 64 u + 63 are added up pairwise by
+// the distances 1, 2, 4 .. 32, then the four sums (0 + 1) + (2 + 3); a lane holds one column of each u.
 __device__ __forceinline__ void token_rstd(const RstdArgs& a, int64_t row) {
     if (row >= (int64_t)a.B * a.L) return;
     const int lane = threadIdx.x & 63;
@@ -58,9 +60,17 @@ __device__ __forceinline__ void token_rstd(const RstdArgs& a, int64_t row) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss[u] = fmaf(x[u][e], x[u][e], ss[u]);
     }
-    float tot = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    // lane l ends up with the sum of u = l % 4: two exchanges, then one, where every lane keeps half of what it has
+    const bool odd = lane & 1, high = lane & 2;
+    float lo = odd ? ss[1] : ss[0], hi = odd ? ss[3] : ss[2];
+    lo += __shfl_xor(odd ? ss[0] : ss[1], 1);
+    hi += __shfl_xor(odd ? ss[2] : ss[3], 1);
+    float tot = high ? hi : lo;
+    tot += __shfl_xor(high ? lo : hi, 2);
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) tot += __shfl_xor(tot, m);
+    for (int m = 4; m < 64; m <<= 1) tot += __shfl_xor(tot, m);
+    tot += __shfl_xor(tot, 1);
+    tot += __shfl_xor(tot, 2);
     if (lane == 0) a.rstd[row] = 1.0f / sqrtf(tot / (float)(a.H * a.D) + a.eps);
 }
 

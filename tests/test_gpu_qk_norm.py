@@ -132,3 +132,36 @@ def test_full_size_normed_sampled_rows(mode):
     torch.cuda.synchronize()
     got = to_f64(out[:, torch.from_numpy(np.asarray(rows, dtype=np.int64)).cuda()])
     compare(got, ref, what="dit_14b normed %s, %d sampled rows" % (mode, len(rows)))
+
+
+@pytest.mark.parametrize("H,D", [(12, 128), (40, 128), (3, 64), (17, 64)])
+def test_per_token_factors_are_the_fp32_sum_in_its_order(H, D):
+    """1/sqrt(mean x^2 + eps) of every q and k row, read from the workspace, bit for bit: the squares (exact in fp32 for
+    bf16 rows) are added up per 16-byte chunk column, then pairwise (the order stated at token_rstd).  Results with a
+    per-token normalisation therefore do not change with the way the factors are computed."""
+    import torch
+
+    grid, split = (2, 5, 13), ((44, 42, 42) if D == 128 else (22, 20, 22))
+    cfg = dict(B=1, grid=grid, H=H, D=D, split=split, dtype="bf16", seed=71 + H)
+    q, k, v = wl.self_attn_inputs(cfg)
+    L = q.shape[1]
+    qd, kd, vd = to_dev(q), to_dev(k), to_dev(v)
+    norm = ("token", EPS, None, None)
+    p = B.self_attn_params(qd, kd, vd, qd, grid, split, norm=norm)
+    ws = torch.empty(B.dit_attn_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    B.dit_attn_forward(qd, kd, vd, grid, split, norm=norm, workspace=ws)
+    up = lambda x: (x + 255) // 256 * 256
+    off = up(8 * sum(g * d // 2 for g, d in zip(grid, split))) + H * ((L + 63) // 64) * 2 * (18 if D == 128 else 10) * 1024
+    for x, at in ((q, off), (k, off + up(4 * L))):
+        sq = wl.bf16_bits_to_f32(x[0]).reshape(L, H * D // 8, 8) ** 2
+        col = np.zeros((L, 256), dtype=np.float32)
+        for c in range(sq.shape[1]):
+            for e in range(8):
+                col[:, c % 256] += sq[:, c, e]
+        s = col.reshape(L, 4, 64)
+        while s.shape[2] > 1:
+            s = s[:, :, 0::2] + s[:, :, 1::2]
+        tot = (s[:, 0, 0] + s[:, 1, 0]) + (s[:, 2, 0] + s[:, 3, 0])
+        want = np.float32(1) / np.sqrt(tot / np.float32(H * D) + np.float32(EPS))
+        got = ws[at:at + 4 * L].view(torch.float32).cpu().numpy()
+        np.testing.assert_array_equal(got, want)
