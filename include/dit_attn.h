@@ -25,6 +25,12 @@
  *  - Rows may not overlap: every token and head stride is at least D, and the larger of the two
  *    clears all rows the smaller one steps over (token >= H*head or head >= L*token); with
  *    B > 1 the batch stride is at least D.  Else DIT_ERR_INVALID_ARG.
+ *  - Results are deterministic: the same parameters, inputs and workspace size give the same bits.  A row of
+ *    cross-attention, and of self-attention with DIT_FLAG_SMALL_WORKGROUP, depends on nothing else than its own
+ *    sequence and head (DIT_NORM_TOKEN: all heads of its tokens).  Without that flag a self-attention call (also of packed requests) may compute some query tiles
+ *    in pieces along the keys; which ones depends on the number of tiles of the whole call, so the bits of a row (not
+ *    its error against the definition) may then differ with the batch size, the number of heads, the other packed
+ *    requests (their grids, not their order or values) and with whether the workspace has room for the pieces.
  *  - Arithmetic: inputs bf16 (or fp32), q and k rotated and scaled in fp32, then rounded
  *    once (nearest-even) to the 16-bit MFMA operand type chosen by `flags`; scores,
  *    softmax statistics and the output accumulator are fp32; output bf16 or fp32.
@@ -85,8 +91,8 @@ enum {
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
      * rows, two workgroups per CU.  Neither flag: the one whose rounds of workgroups fill the chip
-     * better; dit_attn_forward may then (or with BIG) also compute the query tiles of a partly filled
-     * last round in pieces along the keys. */
+     * better; dit_attn_forward and dit_attn_varlen_forward may then (or with BIG) also compute the query tiles
+     * of a partly filled last round, or of whole requests, in pieces along the keys.  SMALL: never in pieces. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,
     DIT_FLAG_SMALL_WORKGROUP = 1u << 9,
     /* Cross-attention runs the plain kernel by default: with a dozen key tiles per query tile its
@@ -176,7 +182,7 @@ typedef struct {
 } dit_self_attn_params;
 
 /* Bytes of workspace dit_attn_forward needs for these params (0 on invalid params).  Where the call would compute some
- * query tiles in pieces along the keys this includes room for the pieces (at most 135 MB); a workspace that holds
+ * query tiles in pieces along the keys this includes room for the pieces (at most 137 MB); a workspace that holds
  * everything but them is accepted too, and the tiles are then computed whole. */
 size_t dit_attn_workspace_bytes(const dit_self_attn_params *p);
 

@@ -227,7 +227,7 @@ struct SelfPlan {
 // slower in pieces, and left whole: 1,560 x 12 (33.1 and 37.2), 6,307 x 20 (336 and 357), 20,280 x 3 (497 and 518).
 constexpr int kCUs = 256;  // compute units of the chip
 constexpr double kEnds = 7.5;
-constexpr int kMaxPieces = 1024;  // 134 MB of workspace at head_dim 128
+constexpr int kMaxPieces = 1024;  // 136.3 MB of workspace at head_dim 128
 
 double whole_tile_steps(int64_t tiles, int nKT, int nw) {  // tiles of 32 nw query rows
     if (nw == 8) return (double)((tiles + kCUs - 1) / kCUs) * (nKT + kEnds);

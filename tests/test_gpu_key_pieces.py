@@ -134,3 +134,23 @@ def test_bf16_scores_that_overflow_in_some_tiles(packed):
         out, lse = B.dit_attn_forward(qd, kd, vd, grid, split, out_dtype=torch.float32, want_lse=True, flags=flags)
     compare(to_f64(out[:, :128]), ref, tol=4e-2, what="rows whose scores overflow")  # (8-bit score operands)
     assert np.abs(to_f64(lse[..., :128]) - ref_lse).max() < 1e-1
+
+
+def test_small_workgroups_make_rows_independent_of_the_rest_of_the_call():
+    """What the header promises for SMALL_WORKGROUP, in a shape that is cut into pieces without it: a sequence's rows keep
+    their bits next to another batch entry, with fewer heads, among packed requests and in a larger workspace."""
+    import torch
+
+    grid, other, H, D, split = (1, 45, 77), (2, 9, 17), 3, 128, (44, 42, 42)
+    L = grid[1] * grid[2]
+    q, k, v = (to_dev(a) for a in wl.self_attn_inputs(dict(B=2, grid=grid, H=H, D=D, split=split, dtype="bf16", seed=94)))
+    flags = B.DIT_FLAG_SMALL_WORKGROUP
+    both = B.dit_attn_forward(q, k, v, grid, split, flags=flags)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    one = B.dit_attn_forward(q[1:], k[1:], v[1:], grid, split, flags=flags, workspace=ws)
+    assert torch.equal(one[0], both[1])
+    two = B.dit_attn_forward(q[1:, :, 1:], k[1:, :, 1:], v[1:, :, 1:], grid, split, flags=flags)
+    assert torch.equal(two[0], both[1, :, 1:])
+    n = other[0] * other[1] * other[2]
+    packed = [torch.cat([t[0, :n], t[1]]) for t in (q, k, v)]
+    assert torch.equal(B.dit_attn_varlen_forward(*packed, [other, grid], split, flags=flags)[n:], both[1])
