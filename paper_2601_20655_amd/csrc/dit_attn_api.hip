@@ -225,7 +225,7 @@ struct SelfPlan {
 // heads) 3,600 x 3: 62.7 us in whole tiles, 40.1 in 5 pieces each; 6,240 x 4: 101.8 and 86.6 (2 pieces); 3,600 x 40:
 // 262 and 258 (last 88 of 600 tiles in 2 pieces); 75,600 x 2: 5,294 and 4,395 (last 80 of 592 in 3 pieces); level or
 // slower in pieces, and left whole: 1,560 x 12 (33.1 and 37.2), 6,307 x 20 (336 and 357), 20,280 x 3 (497 and 518).
-constexpr int kCUs = 256;  // compute units of the chip
+constexpr int kCUs = 256;  // compute units of the chip (workspace sizes go by them, whatever device is current, if any)
 constexpr double kEnds = 7.5;
 constexpr int kMaxPieces = 1024;  // 136.3 MB of workspace at head_dim 128
 
@@ -576,38 +576,31 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
     return DIT_OK;
 }
 
-struct CrossPlan {
-    Flags fl;
-    bool chain16;  // the chained 16x16x32 kernel (joint softmax, default)
-    int qch;       // with it: query tiles per workgroup
-    int nKT, nQT;
-    int split, nTA;  // decoupled form: first key of the second sequence, tiles of the first (0, 0: joint)
-    size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
-};
+}  // namespace
 
 // Wavefronts per workgroup and query tiles per workgroup (1 .. 16) of the chained cross-attention kernel.  Estimate in
 // microseconds: rounds of workgroups x (start + query tiles x (what a query tile costs once + its key tiles)), fitted to
 // every chain length from 1 to 16 in both workgroup sizes at 18 shapes of 144 to 32,760 queries and 1 to 9 key tiles.
-// A compute unit holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles attend is on the
+// A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles attend is on the
 // device; three quarters of the capacity are taken for it.  Measured against the rule before (8 wavefronts from 512
 // workgroups on, five workgroups per compute unit), us: 7,800 queries x 12 heads, 3 key tiles 30.2 -> 23.8;
 // 12,473 x 9, 2 tiles 33.3 -> 21.9; 3,600 x 40, 7 tiles 56.2 -> 50.3; 32,760 x 12, 9 tiles 136.2 -> 128.9.  Chains
 // longer than 16 lose to requests of different lengths in the last round.
-void choose_chain(int Lq, int64_t BH, int nKT, int D, int* nw, int* qch) {
+void dit::choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int* qch) {
     const double n = 0.75 * nKT + 0.5;
     double best = 0.0;
     int best_nw = 0;
     for (int w : {8, 4}) {
         if (*nw != 0 && *nw != w) continue;
         const int64_t nQT = (Lq + 32 * w - 1) / (32 * w);
-        const int slots = D == 64 && w == 4 ? 2 * kCUs : kCUs;
+        const int slots = D == 64 && w == 4 ? 2 * cus : cus;
         const double start = D == 64 ? 1.5 : 2.0;
         const double tile = D == 64 ? (w == 8 ? 5.0 : 4.0) + n : w == 8 ? 7.0 + 1.4 * n : 4.5 + n;
         for (int ch = 1; ch <= 16 && ch <= nQT; ++ch) {
             const int64_t wgs = (nQT + ch - 1) / ch * BH;
             const int64_t full = wgs / slots, left = wgs % slots;
             // (one of two workgroups alone on its compute unit: 0.65 of a pair's time)
-            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > kCUs ? 0.65 : 1.0);
+            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > cus ? 0.65 : 1.0);
             const double t = full * (start + ch * tile) + last;
             if (best_nw == 0 || t < best) {
                 best = t;
@@ -618,6 +611,17 @@ void choose_chain(int Lq, int64_t BH, int nKT, int D, int* nw, int* qch) {
     }
     *nw = best_nw;
 }
+
+namespace {
+
+struct CrossPlan {
+    Flags fl;
+    bool chain16;  // the chained 16x16x32 kernel (joint softmax, default)
+    int qch;       // with it: query tiles per workgroup
+    int nKT, nQT;
+    int split, nTA;  // decoupled form: first key of the second sequence, tiles of the first (0, 0: joint)
+    size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
+};
 
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -650,7 +654,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
                   p->in_dtype == DIT_BF16;
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
-        choose_chain(p->Lq, (int64_t)p->B * p->H, pl->nKT, p->D, &pl->fl.nw, &pl->qch);
+        dit::choose_chain(p->Lq, (int64_t)p->B * p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
     } else if (pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;
     } else if (pl->fl.nw == 0) {
@@ -799,6 +803,17 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     if (lse && pl.split > 0) return DIT_ERR_UNSUPPORTED;  // two softmaxes have no single log-sum-exp
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.total)
         return DIT_ERR_WORKSPACE;
+
+    if (pl.chain16) {  // a partition of the chip has fewer compute units
+        int cus = 0;
+        const hipError_t e = dit::compute_units(&cus);
+        if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+        if (cus != kCUs) {
+            pl.fl.nw = (p->flags & DIT_FLAG_BIG_WORKGROUP) ? 8 : (p->flags & DIT_FLAG_SMALL_WORKGROUP) ? 4 : 0;
+            dit::choose_chain(p->Lq, (int64_t)p->B * p->H, pl.nKT, p->D, cus, &pl.fl.nw, &pl.qch);
+            pl.nQT = (p->Lq + 32 * pl.fl.nw - 1) / (32 * pl.fl.nw);
+        }
+    }
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);

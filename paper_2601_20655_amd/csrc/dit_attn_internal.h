@@ -170,6 +170,16 @@ inline hipError_t allow_dynamic_lds(K kern, int bytes, std::atomic<uint64_t>& do
     return e;
 }
 
+// Compute units of the current device.
+inline hipError_t compute_units(int* n) {
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    return e == hipSuccess ? hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev) : e;
+}
+
+// Layout of the chained cross-attention kernel on `cus` compute units.  *nw: 4 or 8 if asked for, 0 to choose.
+void choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int* qch);
+
 // How a packed call (params: dit_varlen_attn_params) with this workspace is laid over the chip: wavefronts per workgroup
 // (0: it is refused) and query tiles computed in pieces.  No device is touched; the host tests read it.
 int packed_layout(const void* params, size_t workspace_bytes, int* split_tiles);
@@ -235,7 +245,7 @@ struct LinearArgs {
 };
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
 // plain projections that 256 x 256 tiles would leave most of the chip idle for (dit_linear_small.hip): which tile, 0 = none
-int choose_linear_form(int M, int N, int K);
+int choose_linear_form(int M, int N, int K, int cus);
 hipError_t launch_linear_small(const LinearArgs& a, int form, hipStream_t s);
 
 // Second half of the per-token normalisation of the fused q/k/v projection: the projection's epilogue left, in the

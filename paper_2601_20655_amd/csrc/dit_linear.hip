@@ -655,17 +655,13 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
 }
 
 template <bool OUT_F32, int QKV>
-hipError_t launch_linear_inst(const LinearArgs& a, hipStream_t s) {
+hipError_t launch_linear_inst(const LinearArgs& a, int cus, hipStream_t s) {
     auto kern = linear_kernel<OUT_F32, QKV>;
     constexpr int smem = (kLinSX + kLinSW) * kLinTileBytes;
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
     // one workgroup per compute unit (a workgroup takes all of a unit's LDS), fewer if there are fewer tiles
-    int dev = 0, cus = 0;
-    e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
     const int64_t ntiles = (int64_t)a.nTM * a.nTN;
     const unsigned grid = (unsigned)(ntiles < cus ? ntiles : cus);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kLinWaves), smem, s, a);
@@ -675,12 +671,15 @@ hipError_t launch_linear_inst(const LinearArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s) {
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
     if (a.qkv) {
-        if (a.qkv_norm == 2) return launch_linear_inst<false, 3>(a, s);
-        return a.qkv_norm ? launch_linear_inst<false, 2>(a, s) : launch_linear_inst<false, 1>(a, s);
+        if (a.qkv_norm == 2) return launch_linear_inst<false, 3>(a, cus, s);
+        return a.qkv_norm ? launch_linear_inst<false, 2>(a, cus, s) : launch_linear_inst<false, 1>(a, cus, s);
     }
-    if (const int form = choose_linear_form(a.M, a.N, a.K)) return launch_linear_small(a, form, s);
-    return a.out_f32 ? launch_linear_inst<true, false>(a, s) : launch_linear_inst<false, false>(a, s);
+    if (const int form = choose_linear_form(a.M, a.N, a.K, cus)) return launch_linear_small(a, form, s);
+    return a.out_f32 ? launch_linear_inst<true, false>(a, cus, s) : launch_linear_inst<false, false>(a, cus, s);
 }
 
 }  // namespace dit

@@ -248,7 +248,6 @@ struct Form {
 };
 constexpr Form kForms[] = {{1, 1, 0.20, 0.35, 2.5}, {2, 1, 0.215, 0.36, 2.5}, {2, 2, 0.33, 0.55, 3.0}, {4, 2, 0.47, 0.0, 3.0},
                            {3, 4, 0.74, 0.0, 3.5},  {4, 4, 0.76, 0.0, 4.0},   {5, 4, 1.05, 0.0, 4.0}};
-constexpr int kCUs = 256;
 
 }  // namespace
 
@@ -257,19 +256,19 @@ constexpr int kCUs = 256;
 // 769 x 5,120 x 5,120: 82 and 55 (96 x 256); 512 x 3,072 x 1,536: 28 and 10 (64 x 128); 172 x 3,664 x 3,072: 51 and 12
 // (64 x 64); 1 x 15,360 x 5,120: 97 and 26; 3,600 x 5,120 x 5,120: 191 and 174 (160 x 256); kept:
 // 14,040 x 1,536 x 1,536 (66 against 70), 3,600 x 15,360 x 5,120 (440 against 519).
-int choose_linear_form(int M, int N, int K) {
+int choose_linear_form(int M, int N, int K, int cus) {
     const double nK = K / kLinBK;
     auto tiles_of = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const int64_t big = tiles_of(kLinBM, kLinBN), full = big / kCUs, rest = big % kCUs;
-    double best = 0.95 * (7.0 + full * (1.2 * nK + 3.5) + (rest == 0 ? 0.0 : (rest <= kCUs / 2 ? 1.0 : 1.2) * nK + 3.5));
+    const int64_t big = tiles_of(kLinBM, kLinBN), full = big / cus, rest = big % cus;
+    double best = 0.95 * (7.0 + full * (1.2 * nK + 3.5) + (rest == 0 ? 0.0 : (rest <= cus / 2 ? 1.0 : 1.2) * nK + 3.5));
     int form = 0;
     for (const Form& f : kForms) {
         const int64_t tiles = tiles_of(32 * f.tb, 64 * f.fb);
-        const int slots = f.step2 > 0.0 ? 2 * kCUs : kCUs;
+        const int slots = f.step2 > 0.0 ? 2 * cus : cus;
         const int64_t rounds = tiles / slots, left = tiles % slots;
         const double full_step = f.step2 > 0.0 ? f.step2 : f.step;
         const double t = 3.0 + rounds * (full_step * nK + f.ends) +
-                         (left == 0 ? 0.0 : (left <= kCUs ? f.step : full_step) * nK + f.ends);
+                         (left == 0 ? 0.0 : (left <= cus ? f.step : full_step) * nK + f.ends);
         if (t < best) {
             best = t;
             form = 10 * f.tb + f.fb;

@@ -47,3 +47,25 @@ def test_masks_are_listed_where_the_tiles_would_read_them_too_often(nb, H, Lk, s
     f = B.lib()._ZN3dit19mask_needs_key_listEiiii
     f.restype = ctypes.c_bool
     assert f(nb, H, Lk, split) == listed
+
+
+def linear_form(M, N, K, cus=256):
+    """Ten times the 32-row blocks plus the 64-feature blocks of the tile a projection runs on, 0: 256 x 256 tiles."""
+    f = B.lib()._ZN3dit18choose_linear_formEiiii
+    f.restype = ctypes.c_int
+    return f(M, N, K, cus)
+
+
+def test_layouts_follow_the_compute_units_of_the_device():
+    """A partition of the chip has fewer compute units: 256 x 256 tiles fill it earlier, and cross-attention chains more
+    query tiles per workgroup on it."""
+    assert linear_form(769, 10240, 5120) == 54 and linear_form(769, 10240, 5120, cus=32) == 0
+    f = B.lib()._ZN3dit12choose_chainEiliiiPiS0_
+    f.argtypes = [ctypes.c_int, ctypes.c_int64] + 3 * [ctypes.c_int] + 2 * [ctypes.POINTER(ctypes.c_int)]
+    lengths = []
+    for cus in (256, 32):
+        nw, chain = ctypes.c_int(8), ctypes.c_int(0)
+        f(7800, 12, 3, 128, cus, ctypes.byref(nw), ctypes.byref(chain))
+        assert nw.value == 8
+        lengths.append(chain.value)
+    assert 1 <= lengths[0] < lengths[1] <= 16
