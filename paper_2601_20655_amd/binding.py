@@ -8,7 +8,18 @@ there is no fallback path.
 import ctypes
 import os
 
-import torch
+
+class _Torch:
+    """Stands for torch until it is first used (constants, structs, the library and its queries do without it)."""
+
+    def __getattr__(self, name):
+        global torch
+        import torch
+
+        return getattr(torch, name)
+
+
+torch = _Torch()
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdit_attn.so")
@@ -202,10 +213,12 @@ def dit_attn_version():
     return int(lib().dit_attn_version())
 
 
-_DTYPE_CODES = {torch.bfloat16: DIT_BF16, torch.float32: DIT_F32}
+_DTYPE_CODES = {}
 
 
 def _dtype_code(t):
+    if not _DTYPE_CODES:
+        _DTYPE_CODES.update({torch.bfloat16: DIT_BF16, torch.float32: DIT_F32})
     code = _DTYPE_CODES.get(t.dtype)
     if code is None:
         raise TypeError("tensors must be bfloat16 or float32, got %s" % t.dtype)
@@ -221,10 +234,13 @@ def _strides(t):
 
 
 def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
     # (the raw handle: building the Stream object around it took 2.5 us, a seventh of what a small call takes the host)
-    if stream is None:
+    try:
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    except AttributeError:  # not a public function: this torch may not have it
+        return torch.cuda.current_stream().cuda_stream
 
 
 def qk_norm(norm, H, D):

@@ -468,3 +468,30 @@ def test_counter_summary_is_of_this_library_version():
     traffic = bench.traffic_bytes_for(B.dit_attn_version())
     assert traffic is not None and 1e9 < traffic < 1e10
     assert bench.traffic_bytes_for(B.dit_attn_version() + 1) is None
+
+
+def test_binding_loads_without_torch():
+    """Constants, structs, the library and its queries need no torch: importing the binding neither requires nor loads it."""
+    import subprocess
+    import sys
+
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "from paper_2601_20655_amd import binding as B\n"
+            "s = B.dit_strides(24 * 256, 256, 128)\n"
+            "p = B.dit_self_attn_params(1, 2, 128, 2, 3, 4, 0, 0, 0, 44, 42, 42, 10000.0, 0.0, 0, 0, 0, s, s, s, s)\n"
+            "assert B.dit_attn_workspace_bytes(p) > 0 and B.dit_attn_version() >= 10500 and B.dit_strerror(0) == 'ok'\n"
+            "del sys.modules['torch']\n"
+            "assert not [m for m in sys.modules if m.split('.')[0] == 'torch']\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stdout
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    from types import SimpleNamespace as N
+
+    cuda = N(current_device=lambda: 0, current_stream=lambda: N(cuda_stream=123))
+    monkeypatch.setattr(B, "torch", N(_C=N(), cuda=cuda))
+    assert B._stream_ptr(None) == 123 and B._stream_ptr(N(cuda_stream=5)) == 5
+    monkeypatch.setattr(B, "torch", N(_C=N(_cuda_getCurrentRawStream=lambda d: 7 + d), cuda=cuda))
+    assert B._stream_ptr(None) == 7
