@@ -119,3 +119,46 @@ def test_graph_replay_of_the_other_entry_points_and_flags():
         assert torch.equal(out8, ref8), "8-bit scores, replay %d" % rep
         assert torch.equal(cout, cref), "resident cross-attention, replay %d" % rep
         assert torch.equal(lout, lref), "projection, replay %d" % rep
+
+
+def test_graph_replay_of_calls_in_pieces():
+    """Self-attention and packed requests whose query tiles are computed in pieces along the keys and combined by a second
+    kernel: captured into one graph, replayed on soiled workspaces, bit for bit the eager results."""
+    import torch
+
+    grid, H, split = (1, 45, 77), 3, (44, 42, 42)
+    cfg = dict(B=1, grid=grid, H=H, D=128, split=split, dtype="bf16", seed=323)
+    q, k, v = (to_dev(a) for a in wl.self_attn_inputs(cfg))
+    grids = [(1, 45, 57), (1, 20, 45)]  # the same tokens as two requests
+    out, vout = torch.empty_like(q), torch.empty_like(q[0])
+    p = B.self_attn_params(q, k, v, out, grid, split)
+    vp = B.varlen_attn_params(q[0], k[0], v[0], vout, grids, split)
+    need, vneed = B.dit_attn_workspace_bytes(p), B.dit_attn_varlen_workspace_bytes(vp)
+    p.flags = vp.flags = B.DIT_FLAG_SMALL_WORKGROUP
+    assert need > B.dit_attn_workspace_bytes(p) and vneed > B.dit_attn_varlen_workspace_bytes(vp), "meant to be cut"
+    ws, vws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (need, vneed))
+
+    def run(stream=None):
+        B.dit_attn_forward(q, k, v, grid, split, out=out, workspace=ws, stream=stream)
+        B.dit_attn_varlen_forward(q[0], k[0], v[0], grids, split, out=vout, workspace=vws, stream=stream)
+
+    run()
+    ref, vref = out.clone(), vout.clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            run(side)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        out.fill_(7.0)
+        vout.fill_(7.0)
+        ws.fill_(rep)
+        vws.fill_(255 - rep)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), "self-attention in pieces, replay %d" % rep
+        assert torch.equal(vout, vref), "packed requests in pieces, replay %d" % rep

@@ -155,8 +155,8 @@ def test_several_tiles_per_workgroup_exact(K, out):
 ])
 @pytest.mark.parametrize("out", ["f32", "bf16"])
 def test_small_tiles(M, N, K, out):
-    """Shapes at which tiles smaller than 256 x 256 are taken, ragged on both sides, from one step to more steps than
-    LDS stages; all elements."""
+    """Shapes at which tiles smaller than 256 x 256 are taken, ragged on both sides, from one step on (more steps
+    than twice the LDS stages: test_small_tiles_reuse_their_stages); all elements."""
     import torch
 
     cfg = dict(M=M, N=N, K=K, seed=61 + M)
@@ -165,3 +165,26 @@ def test_small_tiles(M, N, K, out):
     B.dit_linear_forward(to_dev(x), to_dev(w), to_dev(b), out=y[:, :N])
     compare(to_f64(y[:, :N]), oracle.linear(x, w, b), bf16_out=out == "bf16", tol=tol(K), what="M=%d N=%d K=%d" % (M, N, K))
     assert torch.all(y[:, N:] == 7.0)
+
+
+# every small tile with at least twice as many steps as LDS stages, plus one: each stage is refilled and read again
+# (tile as choose_linear_form names it, stages, M, N, K; test_layout_host.py checks that the shapes run on these tiles)
+STAGE_REUSE = [(11, 6, 2, 760, 832), (21, 5, 130, 3664, 704), (22, 3, 897, 4136, 448), (42, 5, 513, 3624, 704),
+               (34, 3, 3603, 1048, 448), (44, 3, 3468, 1544, 448), (54, 3, 2500, 3336, 576)]
+
+
+@pytest.mark.parametrize("form,stages,M,N,K", STAGE_REUSE)
+def test_small_tiles_reuse_their_stages(form, stages, M, N, K):
+    """Integer-valued inputs whose sums fit 24 bits: a fragment read before its stage has arrived, or after the next step
+    has been written over it, cannot hide in a tolerance."""
+    import torch
+
+    rng = np.random.default_rng(K + M)
+    x = rng.integers(-8, 9, size=(M, K)).astype(np.float32)
+    w = rng.integers(-8, 9, size=(N, K)).astype(np.float32)
+    bias = rng.integers(-64, 65, size=N).astype(np.float32)
+    xb, wb, bb = (wl.f32_to_bf16_bits(a) for a in (x, w, bias))
+    y = torch.full((M + 1, N), -77.0, dtype=torch.float32, device="cuda")
+    B.dit_linear_forward(to_dev(xb), to_dev(wb), to_dev(bb), out=y[:M])
+    assert np.array_equal(to_f64(y[:M]), oracle.linear(xb, wb, bb))
+    assert torch.all(y[M] == -77.0)

@@ -69,3 +69,19 @@ def test_layouts_follow_the_compute_units_of_the_device():
         assert nw.value == 8
         lengths.append(chain.value)
     assert 1 <= lengths[0] < lengths[1] <= 16
+
+
+def test_projection_shapes_of_the_gpu_tests_run_on_the_tiles_they_are_meant_for():
+    from test_gpu_linear import STAGE_REUSE
+
+    assert [s[0] for s in STAGE_REUSE] == [11, 21, 22, 42, 34, 44, 54]  # all that are built
+    for form, stages, M, N, K in STAGE_REUSE:
+        bytes_per_step = (32 * (form // 10) + 64 * (form % 10)) * 128
+        room = 80 if bytes_per_step <= 26 * 1024 else 160  # two workgroups per compute unit, or one
+        assert stages == min(6, room * 1024 // bytes_per_step) and K // 64 >= 2 * stages + 1
+        assert linear_form(M, N, K) == form
+    # and those of test_small_tiles, from one step on
+    for form, M, N, K in [(11, 33, 72, 64), (11, 1, 4104, 448), (21, 2783, 144, 64), (21, 130, 3664, 704),
+                          (22, 1031, 3592, 64), (22, 1031, 3592, 256), (42, 1025, 3080, 320), (34, 1250, 4104, 256),
+                          (44, 3502, 1560, 64), (54, 2500, 3336, 576)]:
+        assert linear_form(M, N, K) == form
