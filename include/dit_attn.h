@@ -64,7 +64,9 @@ typedef enum { DIT_BF16 = 0, DIT_F32 = 1 } dit_dtype;
  * fp64 definition at 32,760 tokens; bf16 operands (8 bits) give about 2e-2.  Both run at
  * the same MFMA rate.  fp16 operands SATURATE: where |scale*log2(e)*q'|, |k'| or |v| exceeds 65504, the
  * largest finite fp16 number, the operand becomes +-65504 (bf16 inputs can hold such values; the result is
- * then that of the clamped operands: finite and deterministic, but not the definition's).  A caller whose
+ * then that of the clamped operands: deterministic, but not the definition's).  Self-attention computed in whole
+ * tiles on the default kernel needs scores (scale*log2(e)*<q', k'>) whose running maximum rises by at most 65504 from
+ * one 64-key tile to the next: a row in which it rises further comes out NaN.  A caller whose
  * activations can be that large opts out with DIT_FLAG_QK_BF16 | DIT_FLAG_PV_BF16, which keep the full
  * bf16 range at bf16 precision.
  */

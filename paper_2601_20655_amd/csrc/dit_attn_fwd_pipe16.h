@@ -270,10 +270,15 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // m += shift, and everything expressed relative to m moves with it.  mx_new holds full row maxima.
     // The scores and the chain seed are moved ON THE MATRIX CORES: S -= shift is one more accumulation step
     // S += 1 * (-shift) per key block, with an all-ones A operand and a B operand that holds -shift of the
-    // lane's query in its first two contraction slots (shift = hi + lo in the operand type, exact for every
-    // shift that matters) and zeros elsewhere.  Every definition of S in the loop is then an MFMA that
+    // lane's query in its first two contraction slots (shift = hi + lo in the operand type) and zeros
+    // elsewhere.  Every definition of S in the loop is then an MFMA that
     // accumulates in place; vector-ALU subtractions here made the register allocator give the changed scores
     // new registers and copy all 32 of them on the common path that changes none.
+    // hi + lo ends where the operand type does: an fp16 pair holds no shift past 65504 (the row became NaN), a bf16 pair
+    // is off by more than the threshold past 2^20, and scores of saturated operands reach 5e11.  A piece of the keys meets
+    // such rises wherever it starts, so the forms with pieces, and the chained one, shift by all of it past there, on
+    // fp32 MFMAs (an all-ones A operand, -shift in the first contraction slot of B): level in both, while the whole-tile
+    // forms, which keep their key loop, took 2 to 5 % longer for what the compiler then made of it.
     auto shift_rows = [&](f32x16 (&S)[2]) {
         constexpr uint32_t kOnes = QK_OP == OP_F16 ? 0x3c003c00u : 0x3f803f80u;
         const u32x4 ones = mk4(kOnes, kOnes, kOnes, kOnes);
@@ -286,7 +291,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const float hi = QK_OP == OP_F16 ? (float)__builtin_bit_cast(f16x2, hi_bits)[0] : bf16_lo(hi_bits);
             const uint32_t lo_bits = pack2<QK_OP>(want - hi, 0.f) & 0xffffu;
             const float lo = QK_OP == OP_F16 ? (float)__builtin_bit_cast(f16x2, lo_bits)[0] : bf16_lo(lo_bits);
-            const float shift = hi + lo;
+            constexpr bool WIDE = PIECES || CHAIN;
+            const float shift = WIDE && fabsf(want) > (QK_OP == OP_F16 ? 65504.0f : 131072.0f) ? want : hi + lo;
             float alpha = __builtin_amdgcn_exp2f(-shift);
             if constexpr (EMPTY_ROWS) {
                 if (empty_thr[qb] != kRescaleThr) alpha = 1.f;  // (nothing to rescale; exp2 may be infinite)
@@ -294,12 +300,24 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             }
             m_run[qb] += shift;
             l_run[qb] *= alpha;
-            // B operand: contraction slots 0 and 1 (lanes of row g = 0) = -hi, -lo
-            const uint32_t neg = ((hi_bits | (lo_bits << 16)) ^ 0x80008000u);
-            const u32x4 bsh = mk4(g4 == 0 ? neg : 0u, 0u, 0u, 0u);
-            negm[qb] = mfma16<QK_OP>(ones, bsh, negm[qb]);
+            if constexpr (WIDE) {
+                const float bsh = g4 == 0 ? -shift : 0.f;
+                negm[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, bsh, negm[qb], 0, 0, 0);
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) S[qb] = mfma16_q<QK_OP>(ones, bsh, S[qb], kb);
+                for (int kb = 0; kb < 4; ++kb) {
+                    f32x4 x = {S[qb][4 * kb], S[qb][4 * kb + 1], S[qb][4 * kb + 2], S[qb][4 * kb + 3]};
+                    x = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, bsh, x, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) S[qb][4 * kb + r] = x[r];
+                }
+            } else {
+                // B operand: contraction slots 0 and 1 (lanes of row g = 0) = -hi, -lo
+                const uint32_t neg = ((hi_bits | (lo_bits << 16)) ^ 0x80008000u);
+                const u32x4 bsh = mk4(g4 == 0 ? neg : 0u, 0u, 0u, 0u);
+                negm[qb] = mfma16<QK_OP>(ones, bsh, negm[qb]);
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) S[qb] = mfma16_q<QK_OP>(ones, bsh, S[qb], kb);
+            }
 #pragma unroll
             for (int og = 0; og < NOG; ++og)
 #pragma unroll

@@ -123,3 +123,40 @@ def test_infinities_saturate_and_nan_stays(dtype):
     assert np.all(np.isnan(got[..., 33]))
     keep = [c for c in range(64) if c != 33]
     compare(got[..., keep], ref[..., keep], what="infinities in v (%s)" % dtype)
+
+
+@pytest.mark.parametrize("flags", [0, B.DIT_FLAG_QK_BF16, BF16_ALL, B.DIT_FLAG_BIG_WORKGROUP])
+def test_scores_that_rise_by_millions_from_tile_to_tile(flags):
+    """Scores far beyond fp16 itself, whose running maximum rises (for some rows falls) by up to 6e7 with every key tile:
+    a row's softmax has then one key, whatever the tile or piece of the keys it is found in, and rows beside it keep theirs.
+    Self-attention in pieces (the latent grid has one frame, so the first rotary section is not rotated) and chained
+    cross-attention."""
+    import torch
+
+    grid, H, D, split = (1, 45, 77), 3, 128, (44, 42, 42)
+    L = grid[1] * grid[2]
+    cfg = dict(B=1, grid=grid, H=H, D=D, split=split, dtype="f32", seed=81)
+    q, k, v = wl.self_attn_inputs(cfg)
+    q[..., :2] = 0.0
+    k[..., :2] = 0.0
+    for t in range(L // 64):
+        k[:, 64 * t + 5 + t % 7, :, 0] = 1000.0 * (t + 1)
+    q[:, ::3, :, 0] = np.resize(np.float32([1.0, 30.0, -30.0, 3e4, -3e4, 5e5]), L // 3)[None, :, None]
+    qn, kn, vn = (wl.f32_to_bf16_bits(a) for a in (q, k, v))
+    picks = np.arange(0, 600)
+    ref, ref_lse = oracle.self_attn(qn, kn, vn, grid, split, rows=picks, want_lse=True)
+    qd, kd, vd = to_dev(qn), to_dev(kn), to_dev(vn)
+    p = B.self_attn_params(qd, kd, vd, qd, grid, split, flags=flags)
+    need = B.dit_attn_workspace_bytes(p)
+    p.flags = (flags & ~B.DIT_FLAG_BIG_WORKGROUP) | B.DIT_FLAG_SMALL_WORKGROUP
+    assert need > B.dit_attn_workspace_bytes(p), "this shape is meant to be computed in pieces"
+    out, lse = B.dit_attn_forward(qd, kd, vd, grid, split, out_dtype=torch.float32, want_lse=True, flags=flags)
+    tol = 4e-2 if flags & B.DIT_FLAG_QK_BF16 else 2e-2
+    compare(to_f64(out[:, :600]), ref, tol=tol, what="rising scores, self, flags=%d" % flags)
+    # (a score's operand rounding: 2^-12 of it in fp16, 2^-9 in bf16, on either side)
+    rel = 2.0 ** -8 if flags & B.DIT_FLAG_QK_BF16 else 2.0 ** -11
+    assert np.all(np.abs(to_f64(lse[..., :600]) - ref_lse) <= 0.1 + rel * np.abs(ref_lse))
+    valid = np.ones((1, L), dtype=np.uint8)
+    cref = oracle.cross_attn(qn[:, :600], kn, vn, valid)
+    cout = B.dit_cross_attn_forward(qd[:, :600], kd, vd, None, out_dtype=torch.float32, flags=flags)
+    compare(to_f64(cout), cref, tol=tol, what="rising scores, cross, flags=%d" % flags)
