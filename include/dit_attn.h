@@ -88,7 +88,8 @@ enum {
     /* Self-attention with pre-packed K/V normally runs a software-pipelined kernel (scores of
      * tile j+1 on the matrix pipe while tile j's softmax runs on the vector ALU, tiles streamed
      * global->LDS directly).  This flag selects the plain one-tile-at-a-time kernel instead
-     * (the one cross-attention and FUSED always use); same results up to rounding order. */
+     * (FUSED, the decoupled form of cross-attention and fp32 query rows there always use it), for
+     * cross-attention too; same results up to rounding order. */
     DIT_FLAG_SIMPLE_SCHEDULE = 1u << 7,
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
@@ -97,16 +98,15 @@ enum {
      * of a partly filled last round, or of whole requests, in pieces along the keys.  SMALL: never in pieces. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,
     DIT_FLAG_SMALL_WORKGROUP = 1u << 9,
-    /* Cross-attention runs the plain kernel by default: with a dozen key tiles per query tile its
-     * shorter prologue beats the pipelined kernel's better steady state (measured).  This flag
-     * selects the pipelined kernel there too (at most 64 key tiles, i.e. Lk <= 4096 for the joint
-     * form, else DIT_ERR_UNSUPPORTED).  No effect on self-attention. */
+    /* Cross-attention with one joint softmax and bf16 rows runs a kernel that chains several query tiles
+     * per workgroup.  This flag selects the 32x32x16 pipelined kernel there instead (at most 64 key tiles,
+     * i.e. Lk <= 4096, else DIT_ERR_UNSUPPORTED).  No effect on self-attention. */
     DIT_FLAG_PIPELINED_SCHEDULE = 1u << 10,
     /* The workspace still holds the rotated, pre-packed K'/V^T tile images (and the rotation table,
      * the key tile lists and masks) that an earlier forward call of the SAME entry point wrote for the
      * same k, v, kv_valid, shapes, grid(s), origin, rope_base, norm (mode, eps, k_gamma), key split,
-     * operand-type flags and, for self-attention, the flags that choose the matrix-instruction shape the
-     * tiles are laid out for (MFMA_32X32, WIDE_QTILE, SIMPLE_SCHEDULE, QK_FP8); that call must precede
+     * operand-type flags and the flags that choose the matrix-instruction shape the tiles are laid out for
+     * (MFMA_32X32, WIDE_QTILE, SIMPLE_SCHEDULE, QK_FP8, PIPELINED_SCHEDULE); that call must precede
      * this one in stream order.  The key-side passes are skipped: k, v and kv_valid are not read and may
      * be NULL.  q, scale, q_gamma, the output and the workgroup-size flags may differ from call to call.
      * This is the K/V cache of a denoising loop: the conditioning keys and values of cross-attention are
@@ -129,8 +129,8 @@ enum {
      * they deliver more flops per joule than 32x32x16 ones (measured: the kernel is 8 % faster on N(0,1) inputs).
      * This flag selects the 32x32x16 form of the same pipeline instead; same results up to rounding order.  It
      * decides the key order inside the pre-packed V^T tiles, so it belongs to the flags that may not change
-     * between the calls that share tiles under DIT_FLAG_KV_RESIDENT.  No effect on cross-attention and on the
-     * forms that only exist on 32x32x16 instructions (QK_FP8, WIDE_QTILE, SIMPLE_SCHEDULE, KV_FUSED). */
+     * between the calls that share tiles under DIT_FLAG_KV_RESIDENT.  Cross-attention: the plain kernel.  No
+     * effect on the forms that only exist on 32x32x16 instructions (QK_FP8, WIDE_QTILE, SIMPLE_SCHEDULE, KV_FUSED). */
     DIT_FLAG_MFMA_32X32 = 1u << 13
 };
 
@@ -210,8 +210,8 @@ dit_status dit_attn_forward(const void *q, const void *k, const void *v, void *o
  * while the second is accumulated.  lse must be NULL and PIPELINED_SCHEDULE / WIDE_QTILE are
  * not available in this form (DIT_ERR_UNSUPPORTED).  kv_valid (nullable): uint8 [B, Lk] dense, 1 = key attends, 0 = padding.
  * A request with no valid key yields out = 0 and lse = -inf.
- * Flags: QK_*, PV_*, WIDE_QTILE, PIPELINED_SCHEDULE and (with it) the workgroup-size flags apply; K/V are
- * always pre-packed.  With kv_valid, the valid keys of a request (of each sequence in the decoupled form)
+ * Flags: QK_*, PV_*, WIDE_QTILE, SIMPLE_SCHEDULE, PIPELINED_SCHEDULE and, except with the plain kernel, the
+ * workgroup-size flags apply; K/V are always pre-packed.  With kv_valid, the valid keys of a request (of each sequence in the decoupled form)
  * are packed densely, in ascending order, into 64-key tiles: a request costs ceil(valid keys / 64)
  * tiles per sequence wherever its padding sits, and only the last of them is partly filled.
  */

@@ -532,7 +532,8 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
     for (int r = 0; r < n; ++r)
         if (pieces[r] > 1) n_pieces += (int64_t)pieces[r] * p->H * ((vt.r[r].L + 255) / 256);
     if (n_pieces > 0)
-        pl->total = pl->base + round_up(dit::part_o_bytes(n_pieces, p->D), kAlign) + round_up(dit::part_ml_bytes(n_pieces), kAlign);
+        pl->total = pl->base + round_up(dit::part_o_bytes(n_pieces, p->D), kAlign) +
+                    round_up(dit::part_ml_bytes(n_pieces), kAlign);
     pl->part_ml_off = pl->base + round_up(dit::part_o_bytes(n_pieces, p->D), kAlign);
     if (n_pieces > 0 && workspace_bytes < pl->total) {  // no room for the pieces: whole tiles
         for (int r = 0; r < n; ++r) pieces[r] = 1;
@@ -581,8 +582,8 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
 // Wavefronts per workgroup and query tiles per workgroup (1 .. 16) of the chained cross-attention kernel.  Estimate in
 // microseconds: rounds of workgroups x (start + query tiles x (what a query tile costs once + its key tiles)), fitted to
 // every chain length from 1 to 16 in both workgroup sizes at 18 shapes of 144 to 32,760 queries and 1 to 9 key tiles.
-// A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles attend is on the
-// device; three quarters of the capacity are taken for it.  Measured against the rule before (8 wavefronts from 512
+// A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles
+// attend is on the device; three quarters of the capacity are taken for it.  Measured against the rule before (8 wavefronts from 512
 // workgroups on, five workgroups per compute unit), us: 7,800 queries x 12 heads, 3 key tiles 30.2 -> 23.8;
 // 12,473 x 9, 2 tiles 33.3 -> 21.9; 3,600 x 40, 7 tiles 56.2 -> 50.3; 32,760 x 12, 9 tiles 136.2 -> 128.9.  Chains
 // longer than 16 lose to requests of different lengths in the last round.
@@ -734,8 +735,8 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
-    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D, p->in_dtype == DIT_F32,
-                    ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
+    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
+                    p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
     if (!pl.fl.fused && !pl.fl.resident) {
@@ -833,7 +834,8 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     pa.tile_list = reinterpret_cast<int*>(ws + pl.list_off);
     pa.tile_count = reinterpret_cast<int*>(ws + pl.count_off);
     pa.tile_count_a = pl.split > 0 ? reinterpret_cast<int*>(ws + pl.count_a_off) : nullptr;
-    pa.key_src = kv_valid && dit::mask_needs_key_list(p->B, p->H, p->Lk, pl.split) ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
+    const bool listed = kv_valid && dit::mask_needs_key_list(p->B, p->H, p->Lk, pl.split);
+    pa.key_src = listed ? reinterpret_cast<int*>(ws + pl.keysrc_off) : nullptr;
     pa.kv_len = use_len ? kv_len : nullptr;
     pa.second_start = second_start;
     pa.split = pl.split;
@@ -933,8 +935,8 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     dit::NormArgs qn, kn;
     dit_strides sq1 = p->sq, sk1 = p->sk;
     sq1.batch = sk1.batch = 0;
-    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, sq1, sk1, 1, pl.vt.total_tokens, pl.vt.total_tokens, p->H, p->D,
-                    p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
+    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, sq1, sk1, 1, pl.vt.total_tokens, pl.vt.total_tokens,
+                    p->H, p->D, p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
     dit::PackArgs pa;

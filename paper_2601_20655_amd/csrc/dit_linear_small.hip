@@ -5,10 +5,11 @@
 // Same operand roles as the big kernel: w rows ride the A operand of v_mfma_f32_16x16x32_bf16, token rows the B
 // operand; a lane (i, g) ends with token i of a block and features 4g .. 4g+3.
 //
-// What bounds it: the LDS.  A step of a 128 x 256 tile reads 128 KiB of fragments (a wavefront's 64 x 64 corner takes
-// 8 fragments for 16 MFMAs) and writes 48 KiB, 1,410 clocks at 128 bytes a clock, against 1,024 clocks of MFMAs on
-// each SIMD and 1,530 measured (one workgroup on an idle chip); the big kernel's tile needs as many clocks of either.  So a small tile costs more per
-// flop, and is taken only where it fills the chip better (choose_linear_form).
+// What bounds it: no one unit.  769 x 10,240 x 5,120 in 160 x 256 tiles (counters, on the 200 compute units that have
+// one): 171,500 clocks for 80 steps, the matrix cores busy in 60 % of them (the big kernel: 82 to 85 %), the LDS serving
+// fragment reads in 28 % (4 clocks for a wavefront's 1 KiB; 32 %), a quarter of the wavefronts' time in waits: LDS holds
+// three stages of so large a tile, and a step has one barrier.  So a small tile costs more per flop than a big one, and
+// is taken only where it fills the chip better (choose_linear_form).
 #include <type_traits>
 
 #include "dit_attn_device.h"
@@ -241,7 +242,9 @@ hipError_t launch_tile(LinearArgs a, hipStream_t s) {
 
 // Every tile that is built, with the microseconds of one step where workgroups have a compute unit to themselves and
 // where two share one (0: they cannot), and those of a workgroup's start and store.  Fitted to runs over 31 shapes
-// (M 1 .. 32,760, N 256 .. 15,360, K 256 .. 5,120); the big kernel: 1.0 to 1.2 a step, 3.5 a tile and 4 a call.
+// (M 1 .. 32,760, N 256 .. 15,360, K 256 .. 5,120) before the reads and loads of a step were spread over its token
+// blocks, which took up to 12 % off the larger ones: they decide for the big kernel a little too often.  The big kernel:
+// 1.0 to 1.2 a step, 3.5 a tile and 4 a call.
 struct Form {
     int tb, fb;
     double step, step2, ends;
@@ -252,10 +255,10 @@ constexpr Form kForms[] = {{1, 1, 0.20, 0.35, 2.5}, {2, 1, 0.215, 0.36, 2.5}, {2
 }  // namespace
 
 // The tile the estimate says is fastest (10 TB + FB), 0 for the big kernel, which keeps what is not 5 % slower there.
-// Measured, us: M x N x K = 769 x 10,240 x 5,120: 110 in 256 x 256 tiles (160 of them), 91 in 160 x 256;
-// 769 x 5,120 x 5,120: 82 and 55 (96 x 256); 512 x 3,072 x 1,536: 28 and 10 (64 x 128); 172 x 3,664 x 3,072: 51 and 12
-// (64 x 64); 1 x 15,360 x 5,120: 97 and 26; 3,600 x 5,120 x 5,120: 191 and 174 (160 x 256); kept:
-// 14,040 x 1,536 x 1,536 (66 against 70), 3,600 x 15,360 x 5,120 (440 against 519).
+// Measured, us a call one after the other on the same operands: M x N x K = 769 x 10,240 x 5,120: 98 in 256 x 256 tiles
+// (160 of them), 80 in 160 x 256 (with other work between the calls 98 and 88); 769 x 5,120 x 5,120: 82 and 56 (96 x 256);
+// 512 x 3,072 x 1,536: 28 and 9 (64 x 128); 172 x 3,664 x 3,072: 51 and 11 (64 x 64); 1 x 15,360 x 5,120: 80 and 23;
+// 3,600 x 5,120 x 5,120: 193 and 161 (160 x 256); kept: 14,040 x 1,536 x 1,536 (66), 3,600 x 15,360 x 5,120 (430).
 int choose_linear_form(int M, int N, int K, int cus) {
     const double nK = K / kLinBK;
     auto tiles_of = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
