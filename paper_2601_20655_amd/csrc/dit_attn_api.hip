@@ -579,29 +579,29 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
 
 }  // namespace
 
-// Wavefronts per workgroup and query tiles per workgroup (1 .. 16) of the chained cross-attention kernel.  Estimate in
-// microseconds: rounds of workgroups x (start + query tiles x (what a query tile costs once + its key tiles)), fitted to
-// every chain length from 1 to 16 in both workgroup sizes at 18 shapes of 144 to 32,760 queries and 1 to 9 key tiles.
-// A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4 wavefronts: two).  How many key tiles
-// attend is on the device; three quarters of the capacity are taken for it.  Measured against the rule before (8 wavefronts from 512
-// workgroups on, five workgroups per compute unit), us: 7,800 queries x 12 heads, 3 key tiles 30.2 -> 23.8;
-// 12,473 x 9, 2 tiles 33.3 -> 21.9; 3,600 x 40, 7 tiles 56.2 -> 50.3; 32,760 x 12, 9 tiles 136.2 -> 128.9.  Chains
-// longer than 16 lose to requests of different lengths in the last round.
-void dit::choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int* qch) {
-    const double n = 0.75 * nKT + 0.5;
+// Wavefronts per workgroup and query tiles per workgroup (1 .. 32, from one head on into the next, of one request) of the
+// chained cross-attention kernel.  Estimate in microseconds: rounds of workgroups x (start + query tiles x (what a query
+// tile costs once + its key tiles)), fitted to chain lengths of 1 to 32 in both workgroup sizes at 11 shapes of 800 to
+// 32,760 queries and 1 to 9 key tiles.  A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4
+// wavefronts: two).  How many key tiles attend is on the device; three fifths of the capacity are taken for it.
+// Measured, us, lengths that fill the rounds and their neighbours: 32,760 queries x 12 heads, 5 key tiles: 4 query tiles a
+// workgroup 98, 6 (one round) 77, 8 92; 32,760 x 40, 9 key tiles: 1 459, 4 416, 10 408, 16 549, 20 (one round) 416; 7,800 x
+// 12, 3 key tiles: 1 25.0, 2 21.9; with 4 wavefronts 3 24.5; 1,105 x 7 x 3 requests, 7 key tiles: 18.1, with 4 14.1.
+void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* nw, int* qch) {
+    const double n = 0.6 * nKT + 0.5;
     double best = 0.0;
     int best_nw = 0;
     for (int w : {8, 4}) {
         if (*nw != 0 && *nw != w) continue;
-        const int64_t nQT = (Lq + 32 * w - 1) / (32 * w);
+        const int64_t tiles = (Lq + 32 * w - 1) / (32 * w) * H;  // of one request
         const int slots = D == 64 && w == 4 ? 2 * cus : cus;
-        const double start = D == 64 ? 1.5 : 2.0;
-        const double tile = D == 64 ? (w == 8 ? 5.0 : 4.0) + n : w == 8 ? 7.0 + 1.4 * n : 4.5 + n;
-        for (int ch = 1; ch <= 16 && ch <= nQT; ++ch) {
-            const int64_t wgs = (nQT + ch - 1) / ch * BH;
+        const double start = D == 64 ? 1.0 : 2.5;
+        const double tile = D == 64 ? (w == 8 ? 5.0 : 4.0) + n : w == 8 ? 4.0 + 1.85 * n : 5.0 + 0.8 * n;
+        for (int ch = 1; ch <= 32 && ch <= tiles; ++ch) {
+            const int64_t wgs = (tiles + ch - 1) / ch * B;
             const int64_t full = wgs / slots, left = wgs % slots;
-            // (one of two workgroups alone on its compute unit: 0.65 of a pair's time)
-            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > cus ? 0.65 : 1.0);
+            // (one of two workgroups alone on its compute unit: half of a pair's time)
+            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > cus ? 0.5 : 1.0);
             const double t = full * (start + ch * tile) + last;
             if (best_nw == 0 || t < best) {
                 best = t;
@@ -611,6 +611,10 @@ void dit::choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int
         }
     }
     *nw = best_nw;
+}
+
+void dit::choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int* qch) {
+    choose_chain(Lq, 1, BH, nKT, D, cus, nw, qch);
 }
 
 namespace {
@@ -655,7 +659,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
                   p->in_dtype == DIT_BF16;
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
-        dit::choose_chain(p->Lq, (int64_t)p->B * p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
+        dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
     } else if (pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;
     } else if (pl->fl.nw == 0) {
@@ -811,7 +815,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
         if (cus != kCUs) {
             pl.fl.nw = (p->flags & DIT_FLAG_BIG_WORKGROUP) ? 8 : (p->flags & DIT_FLAG_SMALL_WORKGROUP) ? 4 : 0;
-            dit::choose_chain(p->Lq, (int64_t)p->B * p->H, pl.nKT, p->D, cus, &pl.fl.nw, &pl.qch);
+            dit::choose_chain(p->Lq, p->B, p->H, pl.nKT, p->D, cus, &pl.fl.nw, &pl.qch);
             pl.nQT = (p->Lq + 32 * pl.fl.nw - 1) / (32 * pl.fl.nw);
         }
     }

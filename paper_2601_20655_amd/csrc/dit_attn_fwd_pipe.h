@@ -75,9 +75,9 @@ struct PipeView {
     int64_t lse_off;       // index of row 0 in lse
     int64_t stat_off;      // index of row 0 in the per-token normalisation table
     int Hg, Wg;            // latent grid of this sequence
-    int qt_count;          // chained form (attn_pipe16_body<.., CHAIN>): consecutive query tiles taken, from qt
+    // chained form (attn_pipe16_body<.., CHAIN>): consecutive query tiles taken from (h, qt) on, on into the next heads
+    int qt_count;
     int piece;             // attn_pipe16_body<.., PIECES>: index of the piece this workgroup computes, < 0: a whole tile
-    uint64_t last_mask;    // chained form: key mask of the sequence's last tile
 };
 
 // NW = wavefronts per workgroup (4 or 8); the workgroup owns NW*QB*32 query rows that share every

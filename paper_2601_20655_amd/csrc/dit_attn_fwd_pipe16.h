@@ -68,15 +68,20 @@ __device__ __forceinline__ float sum_across_rows16(float x) {
 template <int D>
 constexpr int chain_stage_bytes() { return 32 * D * 2; }
 template <int D, int NW>
-constexpr int chain_lds_bytes() { return 4 * TileGeom<D>::PART_KIB * 1024 + NW * chain_stage_bytes<D>(); }
+constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_stage_bytes<D>(); }
 
-// CHAIN: the workgroup takes pv.qt_count consecutive query tiles of its (sequence, head), one after the other,
-// against ONE stream of key tiles that wraps around at the end of the sequence: the tiles of the next query
-// tile's first steps arrive during the last steps of the one before, and between two query tiles there is
-// only the store of the output, the conversion of the next query rows (requested before the store) and the
-// first score tile.  For sequences of a few key tiles (cross-attention: 8 to 13) the start-up of a workgroup
-// -- query rows and first tiles from memory, one after the other -- is otherwise as long as its loop.  The
-// chained form keeps every wavefront on the same side of the barrier (no stagger).
+// CHAIN: the workgroup takes pv.qt_count consecutive query tiles of one sequence, one after the other and on into the
+// next heads, as ONE stream of key-tile steps: the last step of a query tile multiplies the NEXT one's rows, converted
+// just ahead of it, with its first key tile where the other steps multiply the key tile to come, so that between two
+// query tiles there is only the store of the output and the first maxima, no first-score stage and no barrier of its
+// own, and the two staggered halves stay half a step apart through it (one stores while the other is in its last
+// product).  For sequences of a few key tiles (cross-attention: 3 to 13) all this is otherwise as long as the loop.
+// Each half has the whole chain as code of its own: where only the key loop was doubled, the registers' roles did not
+// agree behind it (660 bytes of spills a lane).  In-kernel stamps, 8 wavefronts, 7.75 key tiles on average: 38,600 ->
+// 32,300 clocks a query tile (lock step, first scores and their barrier 3,400 of it -> none).  Whole calls of 4 x
+// 32,760 queries x 40 heads 1,622 -> 1,488 us, kernel alone at 1 x 32,760 x 40, 9 key tiles 440 -> 386, 7,800 x 12, 3 key
+// tiles 24 -> 22.  What bounds it now: the vector work of a step (as in the plain loop, 3,000 to 3,200 clocks a step
+// where the matrix cores take 2,048), and 8,000 clocks a query tile of conversion, maxima and store.
 //
 // PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
 // leaves its unnormalised output, running maxima and row sums in piece pv.piece of a.part_o / a.part_ml.
@@ -96,7 +101,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     static_assert(G::PART_KIB - NW * NI == 2, "two odd pieces per tile part");
     static_assert(QK_OP != OP_FP8, "16-bit score operands only");
 
-    constexpr bool STAG = pipe_staggered<NW>() && !CHAIN;
+    constexpr bool STAG = pipe_staggered<NW>();
     constexpr int VST = STAG ? 3 : 2;  // V^T buffers
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint8_t* const kbuf = smem;  // K buffers 0/1, then the V buffers
@@ -106,13 +111,13 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g4 = lane >> 4;
-    int qt = pv.qt;
+    int qt = pv.qt, h = pv.h;
     RopeGeom rg = a.rg;
     rg.Hg = pv.Hg;
     rg.Wg = pv.Wg;
 
     u32x4 Qf[2][NKS];
-    uint8_t* const qarea = smem + 4 * G::K_BYTES + wave * chain_stage_bytes<D>();  // chained form only
+    uint8_t* const qarea = smem + (2 + VST) * G::K_BYTES + wave * chain_stage_bytes<D>();  // chained form only
     constexpr int QPR = D / 8;  // 16-byte pieces per 16-bit query row
     // chained form: this wavefront's 32 rows of query tile `qtile` -> its area, piece p of row r in slot
     // p ^ (r % QPR) (the copy fills LDS in lane order, so the swizzle is in which piece a lane fetches)
@@ -125,19 +130,19 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         asm volatile("" : "+v"(l));
         return l;
     };
-    auto request_q_lds = [&](int qtile) {
+    auto request_q_lds = [&](int head, int qtile) {
         const int ln = opaque_lane();
+        const uint16_t* const q = static_cast<const uint16_t*>(a.q) + (int64_t)pv.b * a.sq_b + (int64_t)head * a.sq_h;
 #pragma unroll
         for (int k = 0; k < 32 * QPR / 64; ++k) {
             const int r = k * (64 / QPR) + ln / QPR, slot = ln % QPR;
             const int row = qtile * BQ + wave * 32 + r;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
-            const uint16_t* src = static_cast<const uint16_t*>(a.q) + pv.q_off + (int64_t)qr * a.sq_t +
-                                  8 * (slot ^ (r & (QPR - 1)));
+            const uint16_t* src = q + (int64_t)qr * a.sq_t + 8 * (slot ^ (r & (QPR - 1)));
             __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, 0);
         }
     };
-    if constexpr (CHAIN) request_q_lds(qt);
+    if constexpr (CHAIN) request_q_lds(h, qt);
 
     // ---- tile streaming (as in attn_pipe_body): a tile part is PART_KIB pieces of 1 KiB; wavefront w moves
     // pieces w, w+NW, ... of both parts; the two odd pieces of the K part go to wavefronts 0 and 1, those of
@@ -146,17 +151,11 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     const int n_steps = pv.nKT;
     const int last = n_steps - 1;
     const int tail = pv.Lk - (pv.nKT - 1) * kBK;  // valid keys of the last tile (1..64)
-    // past the end: the last tile again; chained: the stream wraps around to the sequence's first tiles
-    auto tile_of = [&](int j) -> int {
-        if constexpr (CHAIN) {
-            j = j >= n_steps ? j - n_steps : j;
-            return j >= n_steps ? j - n_steps : j;  // j <= n_steps + 1, and a sequence may have one tile
-        } else {
-            return j < last ? j : last;
-        }
-    };
+    // past the end: the last tile again
+    auto tile_of = [&](int j) -> int { return j < last ? j : last; };
+    uint64_t last_mask = 0;  // chained: of the last tile
     auto mask_of = [&](int j) -> uint64_t {
-        if constexpr (CHAIN) return j == last ? pv.last_mask : ~0ull;
+        if constexpr (CHAIN) return j == last ? last_mask : ~0ull;
         else return (j == last && tail < kBK) ? ((1ull << tail) - 1ull) : ~0ull;
     };
     constexpr int NDMA = 2 * NI + 1;
@@ -186,6 +185,25 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         asm volatile("" : "+v"(lane_off));
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) dma_piece(i, tk, kb_, tv, vb_, lane_off);
+    };
+    // chained: the stream of key tiles.  Behind the last tile of a query tile comes the first of the next one, which may
+    // be of the next head (past the last head of the sequence: the last one again, for loads that nobody uses).  stream_k
+    // is the tile whose K' part the next interval requests, stream_v the one before it, whose V^T part it requests.
+    int stream_head = 0, stream_k = 0, stream_v = 0;  // tile images, from the chain's first one
+    int stream_idx = 0, stream_qt = pv.qt, stream_h = pv.h;
+    // (selections, no branches: it runs among the MFMAs)
+    auto stream_advance = [&]() {
+        stream_v = stream_k;
+        ++stream_k;
+        ++stream_idx;
+        const int wrap = stream_idx >= pv.nKT;  // (a sequence without a key: its first tile again)
+        stream_idx = wrap ? 0 : stream_idx;
+        stream_qt += wrap;
+        const int turn = stream_qt == a.nQT;
+        stream_qt = turn ? 0 : stream_qt;
+        stream_h += turn;
+        stream_head += (turn & (stream_h < a.H)) ? a.nKT : 0;
+        stream_k = wrap ? stream_head : stream_k;
     };
     auto dma_wait_and_sync = [&]() {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -328,12 +346,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #ifndef DIT_PIPE16_LA
 #define DIT_PIPE16_LA 6
 #endif
-    // LDS fragment reads issued this many fragments ahead of their MFMAs (chained form: one fewer, which is what
-    // keeps its loop free of spilled registers)
-#ifndef DIT_CHAIN_LA
-#define DIT_CHAIN_LA (DIT_PIPE16_LA - 1)
-#endif
-    constexpr int LA = CHAIN ? DIT_CHAIN_LA : DIT_PIPE16_LA;
+    constexpr int LA = DIT_PIPE16_LA;  // LDS fragment reads issued this many fragments ahead of their MFMAs
     constexpr int NCH = 16;            // softmax slices: two scores -> one dword of P
     constexpr int CPA = NCH / NKF;     // slices per K' fragment (pair of score MFMAs): 1 at d128, 2 at d64
     constexpr int CPB = NCH / NVF;     // maxima slices per V^T fragment
@@ -354,16 +367,25 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         if constexpr (CHAIN) return (j + par) & 1;
         else return j & 1;
     };
-    auto dma_interval = [&](int j, int vs) { dma_tiles(tile_of(j + 2), kslot(j), tile_of(j + 1), next_vslot(vs)); };
+    auto dma_interval = [&](int j, int vs) {
+        if constexpr (CHAIN) {
+            dma_tiles(stream_k, kslot(j), stream_v, next_vslot(vs));
+            stream_advance();
+        } else {
+            dma_tiles(tile_of(j + 2), kslot(j), tile_of(j + 1), next_vslot(vs));
+        }
+    };
 
     // One pipelined iteration: Sc holds the relative scores of tile j (all <= threshold), Sn receives those of
     // tile j + 1.  vs = j % VST, the buffer V^T(j) sits in.  LATE (compile-time) selects where the barrier sits.
     // MASKED (compile-time): tile j + 1 may be the ragged last tile, or lie past the end.  The loop proper runs
     // the unmasked form; the last iterations of a sequence are separate copies, so that the steady state holds
-    // no conditional change of the pending scores at all.
-    auto iteration = [&](auto late_tag, auto masked_tag, f32x16 (&Sc)[2], f32x16 (&Sn)[2], int j, int vs) {
+    // no conditional change of the pending scores at all.  LAST (chained): the last key tile of a query tile; Sn receives
+    // the first scores of the next one, from zero, and stays as it is.
+    auto iteration = [&](auto late_tag, auto kind_tag, f32x16 (&Sc)[2], f32x16 (&Sn)[2], int j, int vs) {
         constexpr bool LATE = decltype(late_tag)::value;
-        constexpr bool MASKED = decltype(masked_tag)::value;
+        constexpr bool MASKED = decltype(kind_tag)::value == 1;
+        constexpr bool LAST = decltype(kind_tag)::value == 2;
         const uint8_t* kt = kbuf + kslot(j + 1) * G::K_BYTES + kread_off;
         const uint8_t* vt = vbuf + vs * G::V_BYTES + vread_off;
 
@@ -476,6 +498,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         else
             need = __any(fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) > kRescaleThr);
         if constexpr (!LATE) dma_wait_and_sync();
+        if constexpr (LAST) return;
         if constexpr (MASKED) {
             const uint64_t mnext = mask_of(j + 1);
             // A ragged tile takes the rescale path whatever its maxima say.  It need not (the maxima above were
@@ -488,7 +511,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 if constexpr (!CHAIN) need = true;
             }
             // after the last tile these are scores of a stale buffer: never let them touch the state
-            need = need && j < last;
+            if constexpr (!CHAIN) need = need && j < last;
         }
         // (rows whose maximum stays under the threshold are shifted by zero)
         if (need) {
@@ -499,7 +522,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 
     // ---- prologue: tiles 0 (K, V) and 1 (K) start streaming, then Q is converted while they fly ----
     auto first_tiles = [&]() {
-        if (n_steps > 0) {
+        if constexpr (CHAIN) {
+            dma_tiles(0, 0, 0, 0);  // (there if the sequence has no key too: read and not used)
+            stream_advance();
+            dma_tiles(stream_k, 1, stream_v, 1);  // (its V part: as below)
+            stream_advance();
+        } else if (n_steps > 0) {
             const int t1 = last > 0 ? 1 : 0;
             dma_tiles(0, 0, 0, 0);
             dma_tiles(t1, 1, 0, 1);  // K'(1); its V part lands in a buffer iteration 0 refills anyway
@@ -618,14 +646,14 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         else start_q(std::false_type{});
     }
 
-    int vs_run = 0;  // chained: the V^T buffer of the stream's current step
-    const int n_qt = CHAIN ? pv.qt_count : 1;
+    constexpr std::integral_constant<int, 0> plain{};  // kinds of iteration
+    constexpr std::integral_constant<int, 1> masked{};
+    constexpr std::integral_constant<int, 2> last_of_tile{};
     // chained form: the rows of query tile `qtile` in this wavefront's area -> operand registers.  It takes 16-bit
     // query rows (the host sends fp32 rows and rotations to the other kernels): widen, normalise if asked to, scale,
     // round.  A row's four lanes (i, 0..3) hold its channels; the per-head statistic is their sum, the per-token one
     // comes from the table.
-    auto convert_q_area = [&](int qtile) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copy into the area (long done, except at the start)
+    auto convert_q_area = [&](int head, int qtile) {
         const int ln = opaque_lane();
         auto chunk = [&](int qb, int ks, float x[8]) {
             const int r = 16 * qb + (ln & 15);
@@ -658,24 +686,16 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             for (int ks = 0; ks < NKS; ++ks) {
                 float x[8];
                 chunk(qb, ks, x);
-                if (a.qn.mode) norm8(x, a.qn, rs[qb], pv.h, D, 4 * ks + (ln >> 4));
+                if (a.qn.mode) norm8(x, a.qn, rs[qb], head, D, 4 * ks + (ln >> 4));
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] *= a.qscale;
                 Qf[qb][ks] = pack8<QK_OP>(x);
             }
     };
-    for (int it = 0; it < n_qt; ++it) {  // one pass unless chained
-    if constexpr (CHAIN) {
-        // the operands of this query tile were converted at the end of the one before; its area is free for
-        // the rows of the next one, which arrive while this one is in its loop
-        if (it == 0) convert_q_area(qt);
-        else reset_state();
-        if (it + 1 < n_qt) request_q_lds(qt + 1);
-    }
+    if constexpr (!CHAIN) {
     if (n_steps > 0) {
         // scores of tile 0 become the first running maximum
-        // (chained, later query tiles: the tiles are there, and the barrier that ended the step before has been passed)
-        if (!CHAIN || it == 0) dma_wait_and_sync();
+        dma_wait_and_sync();
         f32x16 S0[2], S1[2];
         qk_tile(S0, kslot(0));
         __syncthreads();  // every wavefront has read K'(0) before iteration 0 streams K'(2) over it
@@ -700,30 +720,29 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         }
 
         auto key_loop = [&](auto late_tag) {
-            int j = 0, vs = CHAIN ? vs_run : 0;
+            int j = 0, vs = 0;
             // iteration j produces the scores of tile j + 1: unmasked while j + 1 < last
             for (; j + 3 < n_steps; j += 2) {
-                iteration(late_tag, std::false_type{}, S0, S1, j, vs);
+                iteration(late_tag, plain, S0, S1, j, vs);
                 vs = next_vslot(vs);
-                iteration(late_tag, std::false_type{}, S1, S0, j + 1, vs);
+                iteration(late_tag, plain, S1, S0, j + 1, vs);
                 vs = next_vslot(vs);
             }
             // the last one to three iterations
             if (j < n_steps) {
-                iteration(late_tag, std::true_type{}, S0, S1, j, vs);
+                iteration(late_tag, masked, S0, S1, j, vs);
                 vs = next_vslot(vs);
                 ++j;
             }
             if (j < n_steps) {
-                iteration(late_tag, std::true_type{}, S1, S0, j, vs);
+                iteration(late_tag, masked, S1, S0, j, vs);
                 vs = next_vslot(vs);
                 ++j;
             }
             if (j < n_steps) {
-                iteration(late_tag, std::true_type{}, S0, S1, j, vs);
+                iteration(late_tag, masked, S0, S1, j, vs);
                 vs = next_vslot(vs);
             }
-            if constexpr (CHAIN) vs_run = vs;
         };
         if (late) {
             key_loop(std::true_type{});
@@ -733,8 +752,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         }
     }
 
+    }
     // ---- epilogue: the lane holds channels 16 cb + 4 g + r of its two queries ----
     if constexpr (CHAIN) {
+    auto store_rows = [&]() __attribute__((always_inline)) {
         // Stored from the accumulators a wavefront instruction writes sixteen 32-byte pieces of sixteen rows; with
         // an output as large as the input and a loop of eight steps that was a third of a query tile's time.  The
         // wavefront passes its 32 rows through a staging area of its own behind the tile buffers, STG bytes at a
@@ -751,9 +772,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const int row = qt * BQ + wave * 32 + qb * 16 + li;
             if (a.lse && lg == 0 && row < pv.Lq) {
                 const float v = l > 0.f ? (m_run[qb] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
-                a.lse[pv.lse_off + row] = v;
+                a.lse[((int64_t)pv.b * a.H + h) * a.Lq + row] = v;
             }
         }
+        const int64_t o_off = (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h;
         auto stage_and_store = [&](auto es_tag) {
             constexpr int ES = decltype(es_tag)::value;  // bytes per output element
             constexpr int RB = D * ES;                   // bytes per staged row
@@ -799,7 +821,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                         asm volatile("" : "+v"(v[k]), "+v"(v[k + 1]), "+v"(v[k + 2]), "+v"(v[k + 3])::"memory");
                 }
                 uint8_t* const obase = static_cast<uint8_t*>(a.out) +
-                                       (pv.o_off + (int64_t)(row0 + pass * RPP + ln / PR) * a.so_t) * ES + (ln % PR) * 16;
+                                       (o_off + (int64_t)(row0 + pass * RPP + ln / PR) * a.so_t) * ES + (ln % PR) * 16;
                 const int64_t kstride = (int64_t)(64 / PR) * a.so_t * ES;
                 if (full) {
 #pragma unroll
@@ -812,10 +834,107 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
             }
         };
-        // the next query tile's operands out of the area, then the area is the staging area
-        if (it + 1 < n_qt) convert_q_area(qt + 1);
         if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
         else stage_and_store(std::integral_constant<int, 2>());
+    };
+    // query tiles of the chain, and the one after (h, qt)
+    const int n_qt = pv.qt_count;
+    int next_h = h, next_qt = qt;
+    auto next_tile = [&]() {
+        if (++next_qt == a.nQT) {
+            next_qt = 0;
+            ++next_h;
+        }
+    };
+    auto query_tiles = [&](auto late_tag) __attribute__((always_inline)) {
+        constexpr bool LATE = decltype(late_tag)::value;
+        f32x16 S0[2], S1[2];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // rows and first tiles
+        convert_q_area(h, qt);
+        next_tile();
+        if (n_qt > 1) request_q_lds(next_h, next_qt);
+        __syncthreads();
+        qk_tile(S0, 0);
+        __syncthreads();  // every wavefront has read K'(0) before iteration 0 streams K'(2) over it
+        if constexpr (LATE) dma_interval(0, 0);
+        last_mask = a.tile_mask[(size_t)pv.b * a.nKT + last];
+        int vs = 0, left = n_qt;
+        while (left > 0) {
+            // S0 = scores of the first key tile, from zero: they become the first running maximum
+            if (mask_of(0) != ~0ull) mask_apply(S0, mask_of(0));
+            row_max(S0);
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                m_run[qb] = mx_new[qb];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) negm[qb][r] = -m_run[qb];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) S0[qb][r] -= m_run[qb];
+            }
+            int j = 0;
+            for (; j + 3 < n_steps; j += 2) {
+                iteration(late_tag, plain, S0, S1, j, vs);
+                vs = next_vslot(vs);
+                iteration(late_tag, plain, S1, S0, j + 1, vs);
+                vs = next_vslot(vs);
+            }
+            // two to go from here, the scores of the last one in S1 (copies, so that the registers' roles agree)
+            if (j + 3 == n_steps) {
+                iteration(late_tag, plain, S0, S1, j, vs);
+                vs = next_vslot(vs);
+                ++j;
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) S0[qb] = S1[qb];
+            }
+            if (j + 2 == n_steps) {
+                iteration(late_tag, masked, S0, S1, j, vs);
+                vs = next_vslot(vs);
+                ++j;
+            } else {
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) S1[qb] = S0[qb];
+            }
+            if (left > 1) {  // the rows of the next query tile (the last one's first scores are not used)
+                // (with two key tiles or more the copy has been waited for at a barrier)
+                if (pv.nKT == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                convert_q_area(next_h, next_qt);
+            }
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) negm[qb][r] = 0.f;
+            iteration(late_tag, last_of_tile, S1, S0, j, vs);
+            vs = next_vslot(vs);
+            par ^= n_steps & 1;
+            store_rows();
+            h = next_h;
+            qt = next_qt;
+            --left;
+            if (left > 1) {
+                next_tile();
+                request_q_lds(next_h, next_qt);
+            }
+            reset_state();
+        }
+        if constexpr (LATE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    if (n_steps > 0) {
+        if constexpr (STAG) {
+            if (late) query_tiles(std::true_type{});
+            else query_tiles(std::false_type{});
+        } else {
+            query_tiles(std::false_type{});
+        }
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the first rows, into the area the store stages in
+        next_tile();
+        for (int it = 0; it < n_qt; ++it) {
+            store_rows();
+            h = next_h;
+            qt = next_qt;
+            next_tile();
+        }
+    }
     } else {
     const int ln = opaque_lane();  // (nothing of the epilogue's addresses is held through the key loop)
     const int li = ln & 15, lg = ln >> 4;
@@ -863,11 +982,6 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         }
     }
     }
-    if constexpr (CHAIN) {
-        ++qt;
-        par ^= n_steps & 1;
-    }
-    }  // query tiles
 }
 
 // One sequence per batch entry, all of the same length.
@@ -1008,32 +1122,28 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(cons
     attn_pipe16_body<D, QK_OP, PV_OP, NW, false, PIECES>(a, pv);
 }
 
-// Cross-attention with one joint softmax per request: workgroups chain `qch` query tiles of one (request, head).
+// Cross-attention with one joint softmax per request: workgroups chain `qch` query tiles of one request, head by head.
 // The pre-pack leaves a request's attending keys densely in its tiles 0 .. count-1 (without a mask or counts all keys
 // attend), so only the last of them is partial; count and that tile's mask come from the
-// workspace.  Workgroup order: request fastest, then chunk, then head, so that the workgroups an XCD holds at a
-// time share a handful of (request, head) tile sets in its L2 and requests of different lengths are interleaved.
+// workspace.  Workgroup order: request fastest, then the chains in the order of their query tiles, so that the workgroups
+// an XCD holds at a time share a handful of (request, head) tile sets in its L2 and requests of different lengths are
+// interleaved.  (Workgroups that walk a 256th of ALL query tiles each, in one round, have 20 heads in work on an XCD at a
+// time: 1,530 us where this order takes 1,480; striding them over the XCD's share so that they stay together costs a start
+// per request and index arithmetic that small calls feel.)
 template <int D, int QK_OP, int PV_OP, int NW>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const AttnArgs a, int qch) {
     const int logical = xcd_contiguous_block();
-    const int nch = (a.nQT + qch - 1) / qch;
     PipeView pv;
-    pv.b = logical % a.B;
-    const int rest = logical / a.B;
-    const int ch = rest % nch;
-    pv.h = rest / nch;
-    pv.qt = ch * qch;
-    pv.qt_count = a.nQT - pv.qt < qch ? a.nQT - pv.qt : qch;
-    const int bh = pv.b * a.H + pv.h;
-    const int count = a.tile_count[pv.b];
+    const int chain = logical / a.B;
+    pv.b = logical - chain * a.B;
+    const int tile0 = chain * qch;
+    pv.h = tile0 / a.nQT;
+    pv.qt = tile0 - pv.h * a.nQT;
+    pv.qt_count = a.H * a.nQT - tile0 < qch ? a.H * a.nQT - tile0 : qch;
     pv.Lq = a.Lq;
     pv.Lk = a.Lk;
-    pv.nKT = count;
-    pv.last_mask = count > 0 ? a.tile_mask[(size_t)pv.b * a.nKT + count - 1] : 0ull;
-    pv.tiles = a.tiles + (size_t)bh * a.nKT * TileGeom<D>::TILE_BYTES;
-    pv.q_off = (int64_t)pv.b * a.sq_b + (int64_t)pv.h * a.sq_h;
-    pv.o_off = (int64_t)pv.b * a.so_b + (int64_t)pv.h * a.so_h;
-    pv.lse_off = ((int64_t)pv.b * a.H + pv.h) * a.Lq;
+    pv.nKT = a.tile_count[pv.b];
+    pv.tiles = a.tiles + ((size_t)(pv.b * a.H + pv.h) * a.nKT) * TileGeom<D>::TILE_BYTES;
     pv.stat_off = (int64_t)pv.b * a.Lq;
     pv.Hg = a.rg.Hg;
     pv.Wg = a.rg.Wg;
@@ -1048,8 +1158,8 @@ hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
-    const int64_t nch = (a.nQT + qch - 1) / qch;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(nch * a.B * a.H)), dim3(64 * NW), smem, s, a, qch);
+    const int64_t chains = ((int64_t)a.H * a.nQT + qch - 1) / qch;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(chains * a.B)), dim3(64 * NW), smem, s, a, qch);
     return hipGetLastError();
 }
 

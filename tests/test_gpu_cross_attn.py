@@ -321,3 +321,32 @@ def test_many_heads_with_listed_masks_of_moderate_length(split):
     many = [t.repeat(1, 1, H // few, 1) for t in (qd, kd, vd)]
     out = B.dit_cross_attn_forward(*many, vald, out_dtype=torch.float32, split=split)
     assert torch.equal(out, alone.repeat(1, 1, H // few, 1))
+
+
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_chains_run_on_into_the_next_heads(D, big):
+    """More query tiles than compute units and few of them a head, so that a workgroup's chain goes from one head to the
+    next, with requests of 1, 2, 4 and 5 key tiles (every way through the step loop) whose last tiles hold one key, some
+    and all; normalised rows (their weights differ from head to head).  Every row against the oracle."""
+    import torch
+
+    nw = 8 if big else 4
+    H, Lq, Lk = 24, 32 * nw * 6 + 11, 320
+    cfg = dict(B=4, Lq=Lq, n_text=Lk, n_image=0, H=H, D=D, dtype="bf16", min_text=5, seed=91 + D)
+    q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
+    keys = (1, 128, 255, 257)
+    valid[:] = 0
+    for b, n in enumerate(keys):
+        valid[b, :n] = 1
+    rng = np.random.default_rng(5)
+    gq, gk = (1.0 + 0.25 * rng.standard_normal(H * D).astype(np.float32) for _ in range(2))
+    qn, kn = (oracle.qk_rmsnorm(x, g.reshape(H, D), 1e-6, "head") for x, g in ((q, gq), (k, gk)))
+    ref, ref_lse = oracle.cross_attn(qn, kn, oracle.as_f64(v), valid, want_lse=True)
+    flags = B.DIT_FLAG_BIG_WORKGROUP if big else B.DIT_FLAG_SMALL_WORKGROUP
+    norm = ("head", 1e-6, torch.from_numpy(gq).cuda(), torch.from_numpy(gk).cuda())
+    out, lse = run_cross(q, k, v, valid, flags=flags, norm=norm, out_dtype=torch.float32, want_lse=True)
+    o = to_f64(out)
+    for b in range(4):
+        compare(o[b], ref[b], what="%d keys, %d wavefronts" % (keys[b], nw))
+    assert np.allclose(to_f64(lse), ref_lse, rtol=0, atol=2e-3)
