@@ -88,8 +88,8 @@ enum {
     /* Self-attention with pre-packed K/V normally runs a software-pipelined kernel (scores of
      * tile j+1 on the matrix pipe while tile j's softmax runs on the vector ALU, tiles streamed
      * global->LDS directly).  This flag selects the plain one-tile-at-a-time kernel instead
-     * (FUSED, the decoupled form of cross-attention and fp32 query rows there always use it), for
-     * cross-attention too; same results up to rounding order. */
+     * (FUSED always uses it, cross-attention with fp32 rows and, in the decoupled form, with bf16 operands
+     * or many query tiles of few keys), for cross-attention too; same results up to rounding order. */
     DIT_FLAG_SIMPLE_SCHEDULE = 1u << 7,
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
@@ -98,13 +98,14 @@ enum {
      * of a partly filled last round, or of whole requests, in pieces along the keys.  SMALL: never in pieces. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,
     DIT_FLAG_SMALL_WORKGROUP = 1u << 9,
-    /* Cross-attention with one joint softmax and bf16 rows runs a kernel that chains several query tiles
-     * per workgroup.  This flag selects the 32x32x16 pipelined kernel there instead (at most 64 key tiles,
-     * i.e. Lk <= 4096, else DIT_ERR_UNSUPPORTED).  No effect on self-attention. */
+    /* Cross-attention of bf16 rows runs a kernel that chains several query tiles per workgroup (both forms; the
+     * decoupled one with fp16 operands, the default).  With one joint softmax this flag selects the
+     * 32x32x16 pipelined kernel instead (at most 64 key tiles, i.e. Lk <= 4096, else DIT_ERR_UNSUPPORTED).  No
+     * effect on self-attention. */
     DIT_FLAG_PIPELINED_SCHEDULE = 1u << 10,
     /* The workspace still holds the rotated, pre-packed K'/V^T tile images (and the rotation table,
      * the key tile lists and masks) that an earlier forward call of the SAME entry point wrote for the
-     * same k, v, kv_valid, shapes, grid(s), origin, rope_base, norm (mode, eps, k_gamma), key split,
+     * same k, v, kv_valid, in_dtype, shapes, grid(s), origin, rope_base, norm (mode, eps, k_gamma), key split,
      * operand-type flags and the flags that choose the matrix-instruction shape the tiles are laid out for
      * (MFMA_32X32, WIDE_QTILE, SIMPLE_SCHEDULE, QK_FP8, PIPELINED_SCHEDULE); that call must precede
      * this one in stream order.  The key-side passes are skipped: k, v and kv_valid are not read and may
@@ -207,7 +208,7 @@ dit_status dit_attn_forward(const void *q, const void *k, const void *v, void *o
  * conditioning sequences with a softmax each, and the two attention outputs are added:
  *     out = softmax(scale q k_A^T) v_A + softmax(scale q k_B^T) v_B;
  * a sequence without a valid key contributes zero.  The first partial result is held in fp16
- * while the second is accumulated.  lse must be NULL and PIPELINED_SCHEDULE / WIDE_QTILE are
+ * while the second is accumulated, in part in the rows of out (which are written twice then).  lse must be NULL and PIPELINED_SCHEDULE / WIDE_QTILE are
  * not available in this form (DIT_ERR_UNSUPPORTED).  kv_valid (nullable): uint8 [B, Lk] dense, 1 = key attends, 0 = padding.
  * A request with no valid key yields out = 0 and lse = -inf.
  * Flags: QK_*, PV_*, WIDE_QTILE, SIMPLE_SCHEDULE, PIPELINED_SCHEDULE and, except with the plain kernel, the

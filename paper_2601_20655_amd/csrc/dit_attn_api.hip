@@ -107,10 +107,10 @@ dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused,
     const bool timed = g_ev_before && g_ev_after;
     hipError_t e;
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    if (aa.tile_count_a) {
-        e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
-    } else if (chain16) {
+    if (chain16) {
         e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, chain16, s);
+    } else if (aa.tile_count_a) {
+        e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (mfma16 && aa.split.n_tail > 0) {
         e = dit::launch_attn_pipe16_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (mfma16) {
@@ -621,12 +621,27 @@ namespace {
 
 struct CrossPlan {
     Flags fl;
-    bool chain16;  // the chained 16x16x32 kernel (joint softmax, default)
+    bool chain16;  // the chained 16x16x32 kernel (default)
     int qch;       // with it: query tiles per workgroup
     int nKT, nQT;
     int split, nTA;  // decoupled form: first key of the second sequence, tiles of the first (0, 0: joint)
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
+
+// Whether two softmaxes run on the chained kernel.  Not with bf16 score operands, whose scores can be -inf (a row's second
+// pass would start from them), nor with bf16 probabilities, which the plain kernel sums as rounded.  Where 256-row query
+// tiles fill the chip more than twice, a pass over a range costs more than the plain kernel's step from one range into the
+// next, and the steps have to make up for it: head_dim 128 does from 8 key tiles on (us, plain -> chained, 9,000 queries x
+// 30 heads: 3 + 5 tiles 105 -> 99, 5 + 5 123 -> 113, 7 + 5 141 -> 127; fp32 rows 125 -> 127, 136 -> 134, 149 -> 143, but
+// 106 -> 112 where only 2 of 8 tiles of the first range hold keys), head_dim 64 does not (9,000 x 30, 5 + 5 tiles 66.7 ->
+// 68.0, 20,000 x 30, 1 + 5 102 -> 115).  Fewer tiles: 1,500 x 12, 5 + 5 tiles 21.2 -> 19.5, head_dim 64 14.4 -> 13.2, 4,000
+// x 30 35.0 -> 31.6.
+// (The tile images are laid out for the kernel: nothing here may change between calls that share them.)
+bool chain_two(const dit_cross_attn_params* p, const Flags& fl, int nKT) {
+    if (fl.qk_op != dit::OP_F16 || fl.pv_op != dit::OP_F16) return false;
+    const int64_t tiles = (int64_t)(p->Lq + 255) / 256 * p->H * p->B;
+    return tiles <= 2 * kCUs || (p->D == 128 && nKT >= 8);
+}
 
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -651,12 +666,12 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (pl->fl.nw == 8 && pl->fl.qb == 2) return DIT_ERR_UNSUPPORTED;
     // the pipelined kernel keeps the list of non-empty tiles in the 64 lanes of a wavefront
     if (pl->fl.pipelined && pl->nKT > 64) return DIT_ERR_UNSUPPORTED;
-    // Default for one joint softmax: the pipelined 16x16x32 kernel, each workgroup chaining several query tiles.
-    // The plain kernel serves the decoupled form and DIT_FLAG_SIMPLE_SCHEDULE (also with DIT_FLAG_MFMA_32X32
+    // Default: the pipelined 16x16x32 kernel, each workgroup chaining several query tiles.
+    // The plain kernel serves DIT_FLAG_SIMPLE_SCHEDULE (also with DIT_FLAG_MFMA_32X32
     // or 64 rows per wavefront); DIT_FLAG_PIPELINED_SCHEDULE asks for the listed 32x32x16 pipelined kernel.
     // (the chained kernel takes 16-bit query rows, normalised or not: fp32 rows go to the plain kernel)
-    pl->chain16 = pl->split == 0 && !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 &&
-                  p->in_dtype == DIT_BF16;
+    pl->chain16 = !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 && p->in_dtype == DIT_BF16 &&
+                  (pl->split == 0 || chain_two(p, pl->fl, pl->nKT));
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
         dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
@@ -869,6 +884,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     aa.tile_list = pa.tile_list;
     aa.tile_count = pa.tile_count;
     aa.tile_count_a = pa.tile_count_a;
+    aa.nTA = pl.nTA;
     aa.tab = nullptr;
     aa.B = p->B; aa.H = p->H; aa.Lq = p->Lq; aa.Lk = p->Lk; aa.nKT = pl.nKT; aa.nQT = pl.nQT;
     aa.in_f32 = p->in_dtype == DIT_F32; aa.out_f32 = p->out_dtype == DIT_F32;

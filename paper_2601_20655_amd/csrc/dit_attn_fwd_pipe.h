@@ -77,6 +77,8 @@ struct PipeView {
     int Hg, Wg;            // latent grid of this sequence
     // chained form (attn_pipe16_body<.., CHAIN>): consecutive query tiles taken from (h, qt) on, on into the next heads
     int qt_count;
+    // two softmaxes in one chain: tiles of the first pass, and what leads from a step's number to its tile image in either pass
+    int n_first, skip_first, skip_second;
     int piece;             // attn_pipe16_body<.., PIECES>: index of the piece this workgroup computes, < 0: a whole tile
 };
 

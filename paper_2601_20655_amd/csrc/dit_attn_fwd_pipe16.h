@@ -89,7 +89,17 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 // START with a tile of nothing else.  Such a row is `empty` until a tile has a score for it: its scores are taken as
 // they are (relative to 0: probabilities, sums and output stay 0) and its first finite maximum, above or below 0,
 // moves them whatever the threshold (empty_thr).
-template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false>
+//
+// TWO (chained): decoupled cross-attention, one softmax over the tiles of each conditioning sequence, their results added.
+// A query tile goes through the stream twice: the last step of its first pass multiplies the SAME rows with the first key
+// tile of the second sequence, and the first result, normalised, waits as fp16 pairs in the output rows themselves (each
+// lane in the row it will write: 16-bit rows are as wide, fp32 rows wider) until the last step of the second pass brings
+// it into the wavefront's LDS area, free by then.  In registers (the plain kernel's way) there is no room for it here, in
+// LDS beside the next rows neither.  Row sums in fp32 over the unrounded probabilities, as in the plain kernel.  What the
+// form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
+// and loads 337) and the second pass's first maxima.  570.8 -> 509 us at 32,760 queries x 40 heads, 5 + 5 key tiles (plain
+// kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
+template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
     constexpr int NKS = D / 32;        // MFMAs of one score chain
@@ -100,6 +110,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     constexpr int NI = G::PART_KIB / NW;  // full rounds of wavefront-wide 1 KiB loads per tile part
     static_assert(G::PART_KIB - NW * NI == 2, "two odd pieces per tile part");
     static_assert(QK_OP != OP_FP8, "16-bit score operands only");
+    static_assert(!TWO || (CHAIN && QK_OP == OP_F16 && PV_OP == OP_F16),
+                  "a pass takes its first maxima as they are: finite scores only; its row sums are those of unrounded probabilities");
 
     constexpr bool STAG = pipe_staggered<NW>();
     constexpr int VST = STAG ? 3 : 2;  // V^T buffers
@@ -148,12 +160,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // pieces w, w+NW, ... of both parts; the two odd pieces of the K part go to wavefronts 0 and 1, those of
     // the V part to wavefronts 2 and 3.
     const uint8_t* const tiles = pv.tiles;  // wavefront-uniform
-    const int n_steps = pv.nKT;
-    const int last = n_steps - 1;
+    int n_steps = TWO ? pv.n_first : pv.nKT;  // of this pass
+    int last = n_steps - 1;
     const int tail = pv.Lk - (pv.nKT - 1) * kBK;  // valid keys of the last tile (1..64)
     // past the end: the last tile again
     auto tile_of = [&](int j) -> int { return j < last ? j : last; };
-    uint64_t last_mask = 0;  // chained: of the last tile
+    uint64_t last_mask = 0;  // chained: of the last tile (of the pass)
     auto mask_of = [&](int j) -> uint64_t {
         if constexpr (CHAIN) return j == last ? last_mask : ~0ull;
         else return (j == last && tail < kBK) ? ((1ull << tail) - 1ull) : ~0ull;
@@ -189,7 +201,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // chained: the stream of key tiles.  Behind the last tile of a query tile comes the first of the next one, which may
     // be of the next head (past the last head of the sequence: the last one again, for loads that nobody uses).  stream_k
     // is the tile whose K' part the next interval requests, stream_v the one before it, whose V^T part it requests.
-    int stream_head = 0, stream_k = 0, stream_v = 0;  // tile images, from the chain's first one
+    int stream_head = 0, stream_k = TWO ? pv.skip_first : 0, stream_v = stream_k;  // tile images, from the chain's first one
     int stream_idx = 0, stream_qt = pv.qt, stream_h = pv.h;
     // (selections, no branches: it runs among the MFMAs)
     auto stream_advance = [&]() {
@@ -203,7 +215,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         stream_qt = turn ? 0 : stream_qt;
         stream_h += turn;
         stream_head += (turn & (stream_h < a.H)) ? a.nKT : 0;
-        stream_k = wrap ? stream_head : stream_k;
+        if constexpr (TWO) stream_k = stream_head + stream_idx + (stream_idx < pv.n_first ? pv.skip_first : pv.skip_second);
+        else stream_k = wrap ? stream_head : stream_k;
     };
     auto dma_wait_and_sync = [&]() {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -402,7 +415,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         // w < 2: scores 2w, 2w+1 of key block 2m; w >= 2: scores 2(w-2), 2(w-2)+1 of key block 2m+1
         uint32_t Pd[2][2][4];
         float ls[2][2];
-        constexpr bool PKSUM = PV_OP == OP_F16;  // row sums over the rounded pairs, packed fp16 (see attn_pipe_body)
+        constexpr bool PKSUM = PV_OP == OP_F16 && !TWO;  // row sums over the rounded pairs, packed fp16 (see attn_pipe_body)
         f16x2 lsp[2][2];
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -420,6 +433,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             Pd[qb][m][w] = pack2<PV_OP>(e0, e1);
             if constexpr (PKSUM) {
                 lsp[qb][w & 1] += __builtin_bit_cast(f16x2, Pd[qb][m][w]);
+            } else if constexpr (TWO) {
+                l_run[qb] += e0 + e1;
             } else {
                 ls[qb][0] += e0;
                 ls[qb][1] += e1;
@@ -485,7 +500,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             if constexpr (PKSUM) {
                 const f16x2 t2 = lsp[qb][0] + lsp[qb][1];
                 l_run[qb] += (float)t2[0] + (float)t2[1];
-            } else {
+            } else if constexpr (!TWO) {
                 l_run[qb] += ls[qb][0] + ls[qb][1];
             }
             asm volatile("" : "+v"(l_run[qb]));  // keeps the row-sum chain here (it would sink past the barrier)
@@ -523,7 +538,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // ---- prologue: tiles 0 (K, V) and 1 (K) start streaming, then Q is converted while they fly ----
     auto first_tiles = [&]() {
         if constexpr (CHAIN) {
-            dma_tiles(0, 0, 0, 0);  // (there if the sequence has no key too: read and not used)
+            dma_tiles(stream_k, 0, stream_v, 0);  // (there if the sequence has no key too: read and not used)
             stream_advance();
             dma_tiles(stream_k, 1, stream_v, 1);  // (its V part: as below)
             stream_advance();
@@ -692,6 +707,49 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 Qf[qb][ks] = pack8<QK_OP>(x);
             }
     };
+    // two softmaxes: the first result of query tile (h, qt) -> the output rows: the lane's 8 channels of blocks 2k, 2k + 1 go to
+    // 16-byte piece 4k + g of its row, and from there into its own 16 bytes of LDS piece (qb, k)
+    constexpr int NPK = D / 32;
+    auto park_piece = [&](int ln, int qb, int k, bool& inside) -> uint8_t* {
+        const int row = qt * BQ + wave * 32 + 16 * qb + (ln & 15);
+        inside = row < pv.Lq;
+        const int64_t off = (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h + (int64_t)(inside ? row : pv.Lq - 1) * a.so_t;
+        return static_cast<uint8_t*>(a.out) + off * (a.out_f32 ? 4 : 2) + k * 64 + (ln >> 4) * 16;
+    };
+    auto park_rows = [&]() __attribute__((always_inline)) {
+        const int ln = opaque_lane();
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const float l = sum_across_rows16(l_run[qb]);
+            const float inv = l > 0.f ? 1.0f / l : 0.f;
+            bool inside;
+            uint8_t* const dst = park_piece(ln, qb, 0, inside);
+            if (inside) {
+#pragma unroll
+                for (int k = 0; k < NPK; ++k) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int cb = 2 * k + (i >> 1), e = 4 * (cb % 4) + 2 * (i & 1);
+                        w[i] = pack2<OP_F16>(O[cb / 4][qb][e] * inv, O[cb / 4][qb][e + 1] * inv);
+                    }
+                    *reinterpret_cast<u32x4*>(dst + k * 64) = mk4(w[0], w[1], w[2], w[3]);
+                }
+            }
+        }
+    };
+    auto request_parked = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows that the area held have been read
+        const int ln = opaque_lane();
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            bool inside;
+            const uint8_t* const src = park_piece(ln, qb, 0, inside);  // (past the end: some row, not used)
+#pragma unroll
+            for (int k = 0; k < NPK; ++k)
+                __builtin_amdgcn_global_load_lds((gptr_t)(src + k * 64), (lptr_t)(qarea + (qb * NPK + k) * 1024), 16, 0, 0);
+        }
+    };
     if constexpr (!CHAIN) {
     if (n_steps > 0) {
         // scores of tile 0 become the first running maximum
@@ -755,7 +813,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     }
     // ---- epilogue: the lane holds channels 16 cb + 4 g + r of its two queries ----
     if constexpr (CHAIN) {
-    auto store_rows = [&]() __attribute__((always_inline)) {
+    auto store_rows = [&](bool parked) __attribute__((always_inline)) {
         // Stored from the accumulators a wavefront instruction writes sixteen 32-byte pieces of sixteen rows; with
         // an output as large as the input and a loop of eight steps that was a third of a query tile's time.  The
         // wavefront passes its 32 rows through a staging area of its own behind the tile buffers, STG bytes at a
@@ -785,16 +843,40 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                           "staging geometry");
             const int row0 = qt * BQ + wave * 32;
             const bool full = row0 + 32 <= pv.Lq;  // wavefront-uniform
+            // the first softmax's result, zero without one; read before rows are staged over it: 16-bit rows, whose first
+            // 16 rows take only the half that held theirs, block by block
+            constexpr bool BOTH = RPP * RB > STG / 2;
+            u32x4 first[TWO ? 2 : 1][TWO ? NPK : 1];
+            auto read_first = [&](int qb) {
+#pragma unroll
+                for (int k = 0; k < NPK; ++k) {
+                    first[qb][k] = *reinterpret_cast<const u32x4*>(region + (qb * NPK + k) * 1024 + ln * 16);
+                    if (!parked) first[qb][k] = mk4(0u, 0u, 0u, 0u);
+                }
+                asm volatile("" ::: "memory");
+            };
+            if constexpr (TWO && BOTH) {
+                read_first(0);
+                read_first(1);
+            }
 #pragma unroll
             for (int pass = 0; pass < 32 / RPP; ++pass) {
                 const int qb = pass * RPP / 16;
+                if constexpr (TWO && !BOTH) read_first(qb);
+                auto value = [&](int cb, int e) {
+                    if constexpr (TWO) {
+                        const uint32_t pair = first[qb][cb / 2][2 * (cb & 1) + (e >> 1)];  // (bit_cast of the element itself reads element 0)
+                        const f16x2 t = __builtin_bit_cast(f16x2, pair);
+                        return O[cb / 4][qb][4 * (cb % 4) + e] * inv[qb] + (float)t[e & 1];
+                    } else {
+                        return O[cb / 4][qb][4 * (cb % 4) + e] * inv[qb];
+                    }
+                };
                 const int rr = li - (pass * RPP) % 16;  // this lane's row within the pass, if it has one
                 if (rr >= 0 && rr < RPP) {
 #pragma unroll
                     for (int cb = 0; cb < NCB; ++cb) {
-                        const int e = 4 * (cb % 4);
-                        const float o0 = O[cb / 4][qb][e] * inv[qb], o1 = O[cb / 4][qb][e + 1] * inv[qb];
-                        const float o2 = O[cb / 4][qb][e + 2] * inv[qb], o3 = O[cb / 4][qb][e + 3] * inv[qb];
+                        const float o0 = value(cb, 0), o1 = value(cb, 1), o2 = value(cb, 2), o3 = value(cb, 3);
                         const int col = (16 * cb + 4 * lg) * ES;
                         uint8_t* const dst = region + rr * RB + (((col >> 4) ^ (rr & (PR - 1))) << 4) + (col & 15);
                         if constexpr (ES == 4) *reinterpret_cast<float4*>(dst) = make_float4(o0, o1, o2, o3);
@@ -857,8 +939,13 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         qk_tile(S0, 0);
         __syncthreads();  // every wavefront has read K'(0) before iteration 0 streams K'(2) over it
         if constexpr (LATE) dma_interval(0, 0);
-        last_mask = a.tile_mask[(size_t)pv.b * a.nKT + last];
+        const uint64_t* const masks = a.tile_mask + (size_t)pv.b * a.nKT;
+        const uint64_t mask_first = masks[TWO ? pv.skip_first + last : last];
+        uint64_t mask_second = 0;
+        if constexpr (TWO) mask_second = masks[pv.skip_second + pv.nKT - 1];
+        last_mask = mask_first;
         int vs = 0, left = n_qt;
+        bool second = false;  // two softmaxes: this pass is over the second sequence, the first result is parked
         while (left > 0) {
             // S0 = scores of the first key tile, from zero: they become the first running maximum
             if (mask_of(0) != ~0ull) mask_apply(S0, mask_of(0));
@@ -894,10 +981,17 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) S1[qb] = S0[qb];
             }
-            if (left > 1) {  // the rows of the next query tile (the last one's first scores are not used)
+            const bool again = TWO && !second && pv.n_first < pv.nKT;  // the second sequence follows, same rows
+            if (!again && left > 1) {  // the rows of the next query tile (the last one's first scores are not used)
                 // (with two key tiles or more the copy has been waited for at a barrier)
                 if (pv.nKT == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 convert_q_area(next_h, next_qt);
+            }
+            if constexpr (TWO) {
+                if (second) {  // (in the area at the barrier of the step below)
+                    if (n_steps == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // its rows are written
+                    request_parked();
+                }
             }
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
@@ -906,13 +1000,23 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             iteration(late_tag, last_of_tile, S1, S0, j, vs);
             vs = next_vslot(vs);
             par ^= n_steps & 1;
-            store_rows();
-            h = next_h;
-            qt = next_qt;
-            --left;
-            if (left > 1) {
-                next_tile();
-                request_q_lds(next_h, next_qt);
+            if (again) {
+                park_rows();
+            } else {
+                store_rows(second);
+                h = next_h;
+                qt = next_qt;
+                --left;
+                if (left > 1) {
+                    next_tile();
+                    request_q_lds(next_h, next_qt);
+                }
+            }
+            if constexpr (TWO) {
+                second = again;
+                n_steps = again ? pv.nKT - pv.n_first : pv.n_first;
+                last = n_steps - 1;
+                last_mask = again ? mask_second : mask_first;
             }
             reset_state();
         }
@@ -929,7 +1033,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the first rows, into the area the store stages in
         next_tile();
         for (int it = 0; it < n_qt; ++it) {
-            store_rows();
+            store_rows(false);
             h = next_h;
             qt = next_qt;
             next_tile();
@@ -1130,7 +1234,9 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(cons
 // interleaved.  (Workgroups that walk a 256th of ALL query tiles each, in one round, have 20 heads in work on an XCD at a
 // time: 1,530 us where this order takes 1,480; striding them over the XCD's share so that they stay together costs a start
 // per request and index arithmetic that small calls feel.)
-template <int D, int QK_OP, int PV_OP, int NW>
+// TWO: the tiles of the two sequences stand from image 0 and from image nTA on, the tile counts of both together and of
+// the first come from the workspace; a sequence without a key has no pass.
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const AttnArgs a, int qch) {
     const int logical = xcd_contiguous_block();
     PipeView pv;
@@ -1147,13 +1253,19 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const
     pv.stat_off = (int64_t)pv.b * a.Lq;
     pv.Hg = a.rg.Hg;
     pv.Wg = a.rg.Wg;
-    attn_pipe16_body<D, QK_OP, PV_OP, NW, true>(a, pv);
+    if constexpr (TWO) {
+        const int first = a.tile_count_a[pv.b];
+        pv.n_first = first > 0 ? first : pv.nKT;
+        pv.skip_first = first > 0 || pv.nKT == 0 ? 0 : a.nTA;
+        pv.skip_second = first < pv.nKT ? a.nTA - first : 0;
+    }
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, true, false, TWO>(a, pv);
 }
 
 // qch: query tiles per workgroup
-template <int D, int QK_OP, int PV_OP, int NW>
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO>
 hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW>;
+    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW, TWO>;
     constexpr int smem = chain_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);

@@ -115,6 +115,7 @@ struct AttnArgs {
     const int* tile_list;       // with tile_mask: [B, nKT] indices of the tiles with any valid key, ascending
     const int* tile_count;      // with tile_mask: [B] how many entries of tile_list are used
     const int* tile_count_a;    // decoupled cross-attention: [B] how many of them form the first softmax
+    int nTA;                    // with it: tile images of the first key group
     const float2* tab;          // nullable: no rotation of q
     // raw K/V for the fused staging path
     const void* k;
@@ -200,6 +201,7 @@ hipError_t launch_attn_pipe16(const AttnArgs& a, int D, int qk_op, int pv_op, in
 hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_op, hipStream_t s);
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
+// (AttnArgs::tile_count_a set: two softmaxes, fp16 operands only)
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s);
 // whether the masks of such a call (split: first key of the second group, 0 = one group) are listed beforehand (the next
 // two passes); launch_prepack sorts out the others by itself

@@ -350,3 +350,38 @@ def test_chains_run_on_into_the_next_heads(D, big):
     for b in range(4):
         compare(o[b], ref[b], what="%d keys, %d wavefronts" % (keys[b], nw))
     assert np.allclose(to_f64(lse), ref_lse, rtol=0, atol=2e-3)
+
+
+@pytest.mark.parametrize("out_f32", [False, True])
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_chains_with_two_softmaxes(D, big, out_f32):
+    """Two passes per query tile in chains over several heads: requests with nothing in one range, with one tile in
+    either, and with 1 to 5 tiles whose last ones hold one key, some and all; a ragged last query tile, output rows
+    that stand apart (the first pass's result waits in them: nothing between them may change).  Every row against the
+    oracle; per-token normalised rows."""
+    import torch
+
+    nw = 8 if big else 4
+    H, Lq, n_text, n_image = 20, 32 * nw * 3 + 11, 270, 320  # (few enough tiles for head_dim 64 to take that kernel too)
+    counts = [(0, 65), (128, 0), (1, 1), (65, 130), (192, 64), (257, 320)]
+    cfg = dict(B=len(counts), Lq=Lq, n_text=n_text, n_image=n_image, H=H, D=D, dtype="bf16", min_text=5, seed=17 + D)
+    q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
+    valid[:] = 0
+    for b, (n, m) in enumerate(counts):
+        valid[b, :n] = 1
+        valid[b, n_text:n_text + m] = 1
+    rng = np.random.default_rng(6)
+    gq, gk = (1.0 + 0.25 * rng.standard_normal(H * D).astype(np.float32) for _ in range(2))
+    qn, kn = (oracle.qk_rmsnorm(x, g.reshape(H, D), 1e-6, "token") for x, g in ((q, gq), (k, gk)))
+    ref = oracle.cross_attn_decoupled(qn, kn, oracle.as_f64(v), n_text, valid)
+    flags = B.DIT_FLAG_BIG_WORKGROUP if big else B.DIT_FLAG_SMALL_WORKGROUP
+    norm = ("token", 1e-6, torch.from_numpy(gq).cuda(), torch.from_numpy(gk).cuda())
+    rows = torch.full((len(counts), Lq, H, D + 8), 7.0, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+    B.dit_cross_attn_forward(to_dev(q), to_dev(k), to_dev(v), torch.from_numpy(valid).cuda(), flags=flags, norm=norm,
+                             split=n_text, out=rows[..., :D])
+    torch.cuda.synchronize()
+    assert bool((rows[..., D:] == 7.0).all())
+    o = to_f64(rows[..., :D])
+    for b, c in enumerate(counts):
+        compare(o[b], ref[b], bf16_out=not out_f32, what="%d + %d keys, %d wavefronts" % (c + (nw,)))
