@@ -583,10 +583,14 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
 // chained cross-attention kernel.  Estimate in microseconds: rounds of workgroups x (start + query tiles x (what a query
 // tile costs once + its key tiles)), fitted to chain lengths of 1 to 32 in both workgroup sizes at 11 shapes of 800 to
 // 32,760 queries and 1 to 9 key tiles.  A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4
-// wavefronts: two).  How many key tiles attend is on the device; three fifths of the capacity are taken for it.
+// wavefronts: two, each a third slower per key tile than alone).  How many key tiles attend is on the device; three
+// fifths of the capacity are taken for it.
 // Measured, us, lengths that fill the rounds and their neighbours: 32,760 queries x 12 heads, 5 key tiles: 4 query tiles a
 // workgroup 98, 6 (one round) 77, 8 92; 32,760 x 40, 9 key tiles: 1 459, 4 416, 10 408, 16 549, 20 (one round) 416; 7,800 x
 // 12, 3 key tiles: 1 25.0, 2 21.9; with 4 wavefronts 3 24.5; 1,105 x 7 x 3 requests, 7 key tiles: 18.1, with 4 14.1.
+// head_dim 64 (13 shapes of 300 to 30,000 queries, 1 to 10 key tiles): 9,000 x 30, 10 key tiles: 8 wavefronts 1 72.9, 4 94.6, 5 (one
+// round) 60.5, 6 70.5, 4 wavefronts 3 67.7, 4 85.2, 5 68.9; 3 key tiles: 5 32.2, with 4 33.5; 1,500 x 12, 10 key tiles:
+// 14.6, with 4 12.9.  (With figures that held 8 wavefronts dear it was 4 wavefronts everywhere: 9,000 x 30 82, 39.6 with 3.)
 void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* nw, int* qch) {
     const double n = 0.6 * nKT + 0.5;
     double best = 0.0;
@@ -595,13 +599,13 @@ void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* n
         if (*nw != 0 && *nw != w) continue;
         const int64_t tiles = (Lq + 32 * w - 1) / (32 * w) * H;  // of one request
         const int slots = D == 64 && w == 4 ? 2 * cus : cus;
-        const double start = D == 64 ? 1.0 : 2.5;
-        const double tile = D == 64 ? (w == 8 ? 5.0 : 4.0) + n : w == 8 ? 4.0 + 1.85 * n : 5.0 + 0.8 * n;
+        const double start = 2.5;
+        const double tile = D == 64 ? (w == 8 ? 1.35 + 0.88 * n : 1.6 + n) : w == 8 ? 4.0 + 1.85 * n : 5.0 + 0.8 * n;
+        const double alone = slots > cus ? 1.6 + 0.68 * n : tile;
         for (int ch = 1; ch <= 32 && ch <= tiles; ++ch) {
             const int64_t wgs = (tiles + ch - 1) / ch * B;
             const int64_t full = wgs / slots, left = wgs % slots;
-            // (one of two workgroups alone on its compute unit: half of a pair's time)
-            const double last = left == 0 ? 0.0 : start + ch * tile * (2 * left <= slots && slots > cus ? 0.5 : 1.0);
+            const double last = left == 0 ? 0.0 : start + ch * (2 * left <= slots ? alone : tile);
             const double t = full * (start + ch * tile) + last;
             if (best_nw == 0 || t < best) {
                 best = t;
