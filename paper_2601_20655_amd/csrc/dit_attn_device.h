@@ -210,4 +210,47 @@ __device__ __forceinline__ void rope8(float x[8], int c, const RopeGeom& rg, con
     }
 }
 
+// The same in two stages, for code that requests the entries of several rows before it uses the first: two pairs a load
+// (a load of scattered entries costs the address unit some thirty clocks whatever its width).
+struct RopeRow {
+    int b[3];  // axis a's table row at the token's position, less the axis's first pair: entry of pair i = tab[b[a] + i]
+};
+
+__device__ __forceinline__ RopeRow rope_row(const RopeGeom& rg, int pt, int ph, int pw) {
+    RopeRow r;
+    r.b[0] = rg.off[0] + pt * rg.hd[0];
+    r.b[1] = rg.off[1] + ph * rg.hd[1] - rg.hd[0];
+    r.b[2] = rg.off[2] + pw * rg.hd[2] - rg.hd[0] - rg.hd[1];
+    return r;
+}
+
+__device__ __forceinline__ float2 rope_one(const float2* tab, const RopeGeom& rg, const RopeRow& r, int ip) {
+    return tab[(uint32_t)((ip < rg.hd[0] ? r.b[0] : ip < rg.hd[0] + rg.hd[1] ? r.b[1] : r.b[2]) + ip)];
+}
+
+typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+
+// Entries of pairs ip, ip + 1 (ip even) as if both were of ip's axis.  Where they are not (an axis ends behind an odd
+// number of pairs) the second one is whatever stands behind the row -- the next position's or the next axis's row, which
+// has entries or ip + 1 would be past the last pair -- and rope_mend puts the right one there.
+__device__ __forceinline__ void rope_two(const float2* tab, const RopeGeom& rg, const RopeRow& r, int ip, float2 cs[2]) {
+    const int b = ip < rg.hd[0] ? r.b[0] : ip < rg.hd[0] + rg.hd[1] ? r.b[1] : r.b[2];
+    const f32x4_a8 e = *reinterpret_cast<const f32x4_a8*>(tab + (uint32_t)(b + ip));
+    cs[0] = make_float2(e[0], e[1]);
+    cs[1] = make_float2(e[2], e[3]);
+}
+
+// Entries of the pairs that the second and third axis begin with, where those numbers are odd.
+__device__ __forceinline__ void rope_edges(const float2* tab, const RopeGeom& rg, const RopeRow& r, float2 edge[2]) {
+    const int h0 = rg.hd[0], h01 = rg.hd[0] + rg.hd[1];
+    edge[0] = edge[1] = make_float2(1.f, 0.f);
+    if (h0 & 1) edge[0] = tab[(uint32_t)((h0 < h01 ? r.b[1] : r.b[2]) + h0)];
+    if (h01 & 1) edge[1] = tab[(uint32_t)(r.b[2] + h01)];
+}
+
+__device__ __forceinline__ void rope_mend(const RopeGeom& rg, const float2 edge[2], int ip, float2 cs[2]) {
+    if (ip + 1 == rg.hd[0]) cs[1] = edge[0];
+    if (ip + 1 == rg.hd[0] + rg.hd[1]) cs[1] = edge[1];
+}
+
 }  // namespace dit

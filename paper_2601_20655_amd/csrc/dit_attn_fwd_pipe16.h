@@ -555,11 +555,14 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // a test of the input type, the normalisation and the rotation around every 16 bytes and a compare-and-select
     // saturation a workgroup of 8 wavefronts took 17,800 clocks from its start to its first scores (21,000 with the
     // normalisation), now 15,300 (16,700); 123.3 -> 119.5 us at 6,240 tokens x 4 heads, 333 -> 328 us at
-    // 3,600 tokens x 40 heads, long sequences level.
+    // 3,600 tokens x 40 heads, long sequences level.  Rotation entries two pairs a load (was one): 1,760 tokens x 9 heads 45.3 ->
+    // 44.0 us, 6,240 x 4 101.7 -> 100.2, five packed requests x 12 4,137 -> 3,999, 3,600 x 40 326 -> 323 (with the
+    // pre-pack's entries requested ahead; half of it each).
     auto start_q = [&](auto f32_tag) {
         constexpr bool F32 = decltype(f32_tag)::value;
         u32x4 raw[2][NKS][F32 ? 2 : 1];
         float2 cs[2][NKS][4];  // (cos, sin) of the lane's channel pairs at the row's position
+        float2 edge[2][2];
         float rs[2] = {1.f, 1.f};
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -578,18 +581,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             }
             int pt, ph, pw;
             token_pos(qr, rg, pt, ph, pw);
-            const int h0 = rg.hd[0], h01 = rg.hd[0] + rg.hd[1];
-            const int bt = rg.off[0] + pt * rg.hd[0];
-            const int bh = rg.off[1] + ph * rg.hd[1] - h0;
-            const int bw = rg.off[2] + pw * rg.hd[2] - h01;
+            const RopeRow rr = rope_row(rg, pt, ph, pw);
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int pp = 0; pp < 4; ++pp) {
-                    const int ip = 16 * ks + 4 * g4 + pp;
-                    const uint32_t idx = ip + (ip < h0 ? bt : ip < h01 ? bh : bw);
-                    cs[qb][ks][pp] = a.tab[idx];
-                }
+                for (int pp = 0; pp < 4; pp += 2) rope_two(a.tab, rg, rr, 16 * ks + 4 * g4 + pp, &cs[qb][ks][pp]);
+            rope_edges(a.tab, rg, rr, edge[qb]);
             if (a.qn.mode == 2) rs[qb] = a.qn.rstd[pv.stat_off + qr];
         }
         first_tiles();
@@ -638,6 +635,16 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                         const float w = (e & 3) == 0 ? ge.x : (e & 3) == 1 ? ge.y : (e & 3) == 2 ? ge.z : ge.w;
                         x[qb][ks][e] *= rs[qb] * w;
                     }
+        }
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {  // (uniform: only the group of 16 pairs that holds an odd boundary is looked at)
+            const int h0 = rg.hd[0], h01 = rg.hd[0] + rg.hd[1];
+            if (((h0 & 1) && (h0 >> 4) == ks) || ((h01 & 1) && (h01 >> 4) == ks)) {
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                    for (int pp = 0; pp < 4; pp += 2) rope_mend(rg, edge[qb], 16 * ks + 4 * g4 + pp, &cs[qb][ks][pp]);
+            }
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)

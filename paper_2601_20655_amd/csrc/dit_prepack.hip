@@ -182,11 +182,14 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
 
     // All rows of the tile are requested before the first is used: at sizes that leave the chip to a few workgroups
     // each, row by row, was four trips to memory one after the other (4 heads of 6,240 tokens 10.4 -> 9.1 us; 12 heads
-    // of 32,760 99 -> 90, 40 heads 284 -> 270).
+    // of 32,760 99 -> 90, 40 heads 284 -> 270).  So are their rotation entries and factors (92 -> 122 registers, level at
+    // 32,760 tokens, 1 us a call less at 1,760 x 9).
     auto rows = [&](auto f32_tag) __attribute__((always_inline)) {
         constexpr bool F32 = decltype(f32_tag)::value;
         u32x4 rk[NI][F32 ? 2 : 1], rv[NI][F32 ? 2 : 1];
         int keys[NI];
+        float2 cs[NI][4];  // rotation entries of the lane's four pairs
+        float rstd[NI];
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int r = tid / CPR + i * ROWS_PER_PASS;
@@ -210,6 +213,15 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
                     rv[i][w] = vsrc[w];
                 }
             }
+            const int kc = key >= 0 ? key : 0;
+            if (a.tab) {
+                int pt, ph, pw;
+                token_pos(kc, t.rg, pt, ph, pw);
+                const RopeRow rr = rope_row(t.rg, pt, ph, pw);
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) cs[i][pp] = rope_one(a.tab, t.rg, rr, 4 * c + pp);
+            }
+            if (a.kn.mode == 2) rstd[i] = a.kn.rstd[t.stat_off + kc];
         }
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -230,7 +242,7 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
             if (a.kn.mode) {  // the CPR neighbouring lanes that share a row add up its squares
                 float rs;
                 if (a.kn.mode == 2) {
-                    rs = ok ? a.kn.rstd[t.stat_off + key] : 0.f;
+                    rs = rstd[i];
                 } else {
                     float ss = 0.f;
 #pragma unroll
@@ -243,9 +255,12 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
             }
             if (ok) {
                 if (a.tab) {
-                    int pt, ph, pw;
-                    token_pos(key, t.rg, pt, ph, pw);
-                    rope8(xk, c, t.rg, a.tab, pt, ph, pw);
+#pragma unroll
+                    for (int pp = 0; pp < 4; ++pp) {
+                        const float x0 = xk[2 * pp], x1 = xk[2 * pp + 1];
+                        xk[2 * pp] = x0 * cs[i][pp].x - x1 * cs[i][pp].y;
+                        xk[2 * pp + 1] = x0 * cs[i][pp].y + x1 * cs[i][pp].x;
+                    }
                 }
             }
             if constexpr (QK_OP == OP_FP8) {

@@ -217,3 +217,19 @@ def test_rotation_table_against_extended_precision(base, origin):
     for got, want in ((tab[:, 0], np.cos(phi)), (tab[:, 1], np.sin(phi))):
         err = np.abs(got.astype(ext) - want)
         assert np.all(err <= allow), "entry %d: off by %g, allowed %g" % (int(np.argmax(err / allow)), err.max(), allow[np.argmax(err / allow)])
+
+
+@pytest.mark.parametrize("split", [(44, 42, 42), (2, 2, 124), (126, 2, 0), (2, 0, 126), (62, 0, 66), (0, 30, 98), (64, 32, 32)])
+def test_axes_that_end_behind_odd_numbers_of_pairs(split):
+    """The prologue fetches rotation entries two pairs at a time; the second is of the next axis where one ends behind an
+    odd number of pairs (first, second, both, neighbouring ends, empty axes).  Last positions of every axis included."""
+    import torch
+
+    cfg = dict(B=1, grid=(3, 5, 19), H=2, D=128, split=split, dtype="bf16", seed=sum(split[:2]))
+    q, k, v = wl.self_attn_inputs(cfg)
+    ref = oracle.self_attn(q, k, v, cfg["grid"], split)
+    for flags in (0, B.DIT_FLAG_SMALL_WORKGROUP):
+        out = B.dit_attn_forward(to_dev(q), to_dev(k), to_dev(v), cfg["grid"], split, flags=flags,
+                                 out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        compare(to_f64(out), ref, what="split %s flags %d" % (split, flags))
