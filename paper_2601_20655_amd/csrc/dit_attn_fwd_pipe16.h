@@ -115,6 +115,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 
     constexpr bool STAG = pipe_staggered<NW>();
     constexpr int VST = STAG ? 3 : 2;  // V^T buffers
+    // whole output rows through an LDS area of the wavefront's own (store_rows); 4 wavefronts without a chain keep the room
+    // for a second workgroup on the compute unit instead.  8 wavefronts of self-attention stored from the accumulators before:
+    // 3,600 x 40 317.6 -> 312.6 us, 14,040 x 12 1,033 -> 1,025, 6,240 x 4 105.5 -> 103.0, full clips level.
+    constexpr bool STAGED = CHAIN || NW == 8;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint8_t* const kbuf = smem;  // K buffers 0/1, then the V buffers
     uint8_t* const vbuf = smem + 2 * G::K_BYTES;
@@ -129,7 +133,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     rg.Wg = pv.Wg;
 
     u32x4 Qf[2][NKS];
-    uint8_t* const qarea = smem + (2 + VST) * G::K_BYTES + wave * chain_stage_bytes<D>();  // chained form only
+    uint8_t* const qarea = smem + (2 + VST) * G::K_BYTES + wave * chain_stage_bytes<D>();  // STAGED only
     constexpr int QPR = D / 8;  // 16-byte pieces per 16-bit query row
     // chained form: this wavefront's 32 rows of query tile `qtile` -> its area, piece p of row r in slot
     // p ^ (r % QPR) (the copy fills LDS in lane order, so the swizzle is in which piece a lane fetches)
@@ -819,7 +823,6 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 
     }
     // ---- epilogue: the lane holds channels 16 cb + 4 g + r of its two queries ----
-    if constexpr (CHAIN) {
     auto store_rows = [&](bool parked) __attribute__((always_inline)) {
         // Stored from the accumulators a wavefront instruction writes sixteen 32-byte pieces of sixteen rows; with
         // an output as large as the input and a loop of eight steps that was a third of a query tile's time.  The
@@ -837,10 +840,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const int row = qt * BQ + wave * 32 + qb * 16 + li;
             if (a.lse && lg == 0 && row < pv.Lq) {
                 const float v = l > 0.f ? (m_run[qb] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
-                a.lse[((int64_t)pv.b * a.H + h) * a.Lq + row] = v;
+                a.lse[CHAIN ? ((int64_t)pv.b * a.H + h) * a.Lq + row : pv.lse_off + row] = v;
             }
         }
-        const int64_t o_off = (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h;
+        const int64_t o_off = CHAIN ? (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h : pv.o_off;
         auto stage_and_store = [&](auto es_tag) {
             constexpr int ES = decltype(es_tag)::value;  // bytes per output element
             constexpr int RB = D * ES;                   // bytes per staged row
@@ -926,6 +929,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
         else stage_and_store(std::integral_constant<int, 2>());
     };
+    if constexpr (CHAIN) {
     // query tiles of the chain, and the one after (h, qt)
     const int n_qt = pv.qt_count;
     int next_h = h, next_qt = qt;
@@ -1070,6 +1074,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 continue;
             }
         }
+        if constexpr (STAGED) continue;
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         if (row < pv.Lq) {
             const int64_t obase = pv.o_off + (int64_t)row * a.so_t;
@@ -1091,6 +1096,9 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 a.lse[pv.lse_off + row] = v;
             }
         }
+    }
+    if constexpr (STAGED) {
+        if (!PIECES || pv.piece < 0) store_rows(false);
     }
     }
 }
@@ -1285,7 +1293,7 @@ hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t
 template <int D, int QK_OP, int PV_OP, int NW>
 hipError_t launch_attn_pipe16_inst(const AttnArgs& a, hipStream_t s) {
     auto kern = attn_fwd_pipe16_kernel<D, QK_OP, PV_OP, NW>;
-    constexpr int smem = pipe_lds_bytes<D, NW>();
+    constexpr int smem = NW == 8 ? chain_lds_bytes<D, NW>() : pipe_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
@@ -1297,7 +1305,7 @@ hipError_t launch_attn_pipe16_inst(const AttnArgs& a, hipStream_t s) {
 template <int D, int QK_OP, int PV_OP>
 hipError_t launch_attn_pipe16_split_inst(const AttnArgs& a, hipStream_t s) {
     auto kern = attn_fwd_pipe16_split_kernel<D, QK_OP, PV_OP>;
-    constexpr int smem = pipe_lds_bytes<D, 8>();
+    constexpr int smem = chain_lds_bytes<D, 8>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;
@@ -1310,7 +1318,7 @@ hipError_t launch_attn_pipe16_split_inst(const AttnArgs& a, hipStream_t s) {
 template <int D, int QK_OP, int PV_OP, int NW, bool PIECES>
 hipError_t launch_attn_pipe16_varlen_inst(const AttnArgs& a, const VarlenTable& vt, hipStream_t s) {
     auto kern = attn_fwd_pipe16_varlen_kernel<D, QK_OP, PV_OP, NW, PIECES>;
-    constexpr int smem = pipe_lds_bytes<D, NW>();
+    constexpr int smem = NW == 8 ? chain_lds_bytes<D, NW>() : pipe_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
     if (e != hipSuccess) return e;

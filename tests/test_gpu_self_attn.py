@@ -233,3 +233,25 @@ def test_axes_that_end_behind_odd_numbers_of_pairs(split):
                                  out_dtype=torch.float32)
         torch.cuda.synchronize()
         compare(to_f64(out), ref, what="split %s flags %d" % (split, flags))
+
+
+@pytest.mark.parametrize("out_f32", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L", [1, 31, 33, 255, 257, 304])
+def test_staged_output_rows_at_tile_edges(L, D, out_f32):
+    """8 wavefronts stage their output rows: sequences that end one row either side of a wavefront's 32 rows and of a
+    query tile, in rows that stand apart (nothing between them may change), with the log-sum-exp."""
+    import torch
+
+    split = (22, 20, 22) if D == 64 else (44, 42, 42)
+    cfg = dict(B=2, grid=(1, 1, L), H=3, D=D, split=split, dtype="bf16", seed=L + D)
+    q, k, v = wl.self_attn_inputs(cfg)
+    ref, ref_lse = oracle.self_attn(q, k, v, cfg["grid"], split, want_lse=True)
+    rows = torch.full((2, L, 3, D + 8), 7.0, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+    lse = torch.full((2, 3, L), 7.0, dtype=torch.float32, device="cuda")
+    B.dit_attn_forward(to_dev(q), to_dev(k), to_dev(v), cfg["grid"], split, flags=B.DIT_FLAG_BIG_WORKGROUP,
+                       out=rows[..., :D], lse=lse)
+    torch.cuda.synchronize()
+    assert bool((rows[..., D:] == 7.0).all())
+    compare(to_f64(rows[..., :D]), ref, bf16_out=not out_f32, what="L=%d D=%d" % (L, D))
+    assert np.max(np.abs(to_f64(lse) - ref_lse)) < 5e-3
