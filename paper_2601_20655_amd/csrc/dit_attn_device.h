@@ -188,8 +188,14 @@ __device__ __forceinline__ void token_pos(int n, const RopeGeom& rg, int& pt, in
     pw = rem - ph * rg.Wg;
 }
 
+// A pair (x0, x1) becomes (x0 cos - x1 sin, x1 cos + x0 sin); all in fp32.  Which product is rounded by itself is stated and
+// not left to the compiler, whose choice differs from kernel to kernel: rows that the projection's epilogue rotates are
+// to have the bits of those that the pre-pack rotates.
+__device__ __forceinline__ float2 rotate_pair(float x0, float x1, float2 cs) {
+    return make_float2(__builtin_fmaf(x0, cs.x, -(x1 * cs.y)), __builtin_fmaf(x1, cs.x, x0 * cs.y));
+}
+
 // Rotate channels [8c, 8c+8) = pairs 4c..4c+3 of a token at position indices (pt, ph, pw).
-// A pair (x0, x1) becomes (x0 cos - x1 sin, x0 sin + x1 cos); all in fp32.
 __device__ __forceinline__ void rope8(float x[8], int c, const RopeGeom& rg, const float2* tab,
                                       int pt, int ph, int pw) {
 #pragma unroll
@@ -203,10 +209,9 @@ __device__ __forceinline__ void rope8(float x[8], int c, const RopeGeom& rg, con
         } else {
             idx = rg.off[2] + pw * rg.hd[2] + (ip - rg.hd[0] - rg.hd[1]);
         }
-        const float2 cs = tab[idx];
-        const float x0 = x[2 * pp], x1 = x[2 * pp + 1];
-        x[2 * pp] = x0 * cs.x - x1 * cs.y;
-        x[2 * pp + 1] = x0 * cs.y + x1 * cs.x;
+        const float2 y = rotate_pair(x[2 * pp], x[2 * pp + 1], tab[idx]);
+        x[2 * pp] = y.x;
+        x[2 * pp + 1] = y.y;
     }
 }
 

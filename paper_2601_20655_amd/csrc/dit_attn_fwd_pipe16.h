@@ -657,10 +657,9 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 float y[8];
 #pragma unroll
                 for (int pp = 0; pp < 4; ++pp) {
-                    const float2 c = cs[qb][ks][pp];
-                    const float x0 = x[qb][ks][2 * pp], x1 = x[qb][ks][2 * pp + 1];
-                    y[2 * pp] = (x0 * c.x - x1 * c.y) * a.qscale;
-                    y[2 * pp + 1] = (x0 * c.y + x1 * c.x) * a.qscale;
+                    const float2 r = rotate_pair(x[qb][ks][2 * pp], x[qb][ks][2 * pp + 1], cs[qb][ks][pp]);
+                    y[2 * pp] = r.x * a.qscale;
+                    y[2 * pp + 1] = r.y * a.qscale;
                 }
                 Qf[qb][ks] = pack8<QK_OP>(y);
             }

@@ -477,12 +477,11 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
                             if (ip < rg.hd[0]) idx = rg.off[0] + pt * rg.hd[0] + ip;
                             else if (ip < rg.hd[0] + rg.hd[1]) idx = rg.off[1] + ph * rg.hd[1] + (ip - rg.hd[0]);
                             else idx = rg.off[2] + pw * rg.hd[2] + (ip - rg.hd[0] - rg.hd[1]);
-                            const float2 cs = a.qkv_tab[idx];
                             float& x0 = pp ? y2 : y0;
                             float& x1 = pp ? y3 : y1;
-                            const float r0 = x0 * cs.x - x1 * cs.y, r1 = x0 * cs.y + x1 * cs.x;
-                            x0 = r0;
-                            x1 = r1;
+                            const float2 r = rotate_pair(x0, x1, a.qkv_tab[idx]);
+                            x0 = r.x;
+                            x1 = r.y;
                         }
                     }
                     if (part != 0 && tok >= a.M) y0 = y1 = y2 = y3 = 0.f;

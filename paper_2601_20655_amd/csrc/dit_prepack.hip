@@ -257,9 +257,9 @@ __device__ __forceinline__ void pack_tile(const PackArgs& a, const PackTile& t, 
                 if (a.tab) {
 #pragma unroll
                     for (int pp = 0; pp < 4; ++pp) {
-                        const float x0 = xk[2 * pp], x1 = xk[2 * pp + 1];
-                        xk[2 * pp] = x0 * cs[i][pp].x - x1 * cs[i][pp].y;
-                        xk[2 * pp + 1] = x0 * cs[i][pp].y + x1 * cs[i][pp].x;
+                        const float2 y = rotate_pair(xk[2 * pp], xk[2 * pp + 1], cs[i][pp]);
+                        xk[2 * pp] = y.x;
+                        xk[2 * pp + 1] = y.y;
                     }
                 }
             }

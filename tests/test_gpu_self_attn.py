@@ -255,3 +255,62 @@ def test_staged_output_rows_at_tile_edges(L, D, out_f32):
     assert bool((rows[..., D:] == 7.0).all())
     compare(to_f64(rows[..., :D]), ref, bf16_out=not out_f32, what="L=%d D=%d" % (L, D))
     assert np.max(np.abs(to_f64(lse) - ref_lse)) < 5e-3
+
+
+@pytest.mark.parametrize("flags", [B.DIT_FLAG_BIG_WORKGROUP, B.DIT_FLAG_SMALL_WORKGROUP])
+@pytest.mark.parametrize("side", ["q", "k"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_rotated_pairs_are_rounded_as_stated(D, dtype, side, flags):
+    """A rotated pair is (fma(x0, cos, -(x1 sin)), fma(x1, cos, x0 sin)) in fp32, in q as in k: pairs are drawn until
+    there are some at every place in the row whose fp16 operand is another one if the other product is rounded by itself.
+    Sequences of one token whose rows hold such a pair and zeros: the log-sum-exp is the score itself.  Its error beside
+    the operands': a sum of two exact products and a product with ln 2, rounded or truncated to fp32, and ln 2 in
+    fp32, 2^-23 of the terms' magnitudes each."""
+    import torch
+
+    ext = np.longdouble
+    split, origin = ((22, 20, 22) if D == 64 else (44, 42, 42)), (3, 17, 29)
+    z = torch.zeros((1, 1, 1, D), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(B.dit_attn_workspace_bytes(B.self_attn_params(z, z, z, z, (1, 1, 1), split, origin=origin)),
+                     dtype=torch.uint8, device="cuda")
+    B.dit_attn_forward(z, z, z, (1, 1, 1), split, origin=origin, workspace=ws)  # the table stands at the start of it
+    tab = ws[:4 * D].view(torch.float32).cpu().numpy().reshape(D // 2, 2).astype(ext)
+    qscale = ext(np.float32(np.float32(1.0) / np.sqrt(np.float32(D))) * np.float32(1.4426950408889634))
+
+    def f32(x):
+        return x.astype(np.float32).astype(ext)
+
+    def operands(x0, x1, i, scale, other):
+        """fp16 operands of the pairs (x0, x1) at place i; other: the other products rounded by themselves."""
+        c, s = tab[i, 0], tab[i, 1]
+        y0 = f32(f32(x0 * c) - x1 * s) if other else f32(x0 * c - f32(x1 * s))
+        y1 = f32(f32(x1 * c) + x0 * s) if other else f32(x1 * c + f32(x0 * s))
+        return np.stack([f32(y * scale).astype(np.float16).astype(np.float64) for y in (y0, y1)], axis=-1)
+
+    rng = np.random.default_rng(D)
+    bits = 16 if dtype == "bf16" else 0  # low bits of an fp32 number that are zero
+    rows, want, allow = [], [], []
+    for i in range(D // 2):
+        x = rng.uniform(0.5, 2.0, (2, 1 << 16)).astype(np.float32) * np.float32(1 - 2 * (i & 1))
+        x = (x.view(np.uint32) >> bits << bits).view(np.float32).astype(ext)
+        scale = qscale if side == "q" else ext(1)
+        a, b = (operands(x[0], x[1], i, scale, other) for other in (False, True))
+        y = rng.uniform(0.5, 2.0, 2).astype(np.float32)
+        y = (y.view(np.uint32) >> bits << bits).view(np.float32).astype(ext)
+        o = operands(y[0], y[1], i, qscale if side == "k" else ext(1), False)
+        terms = a * o * np.log(2.0)
+        room = 3 * 2.0 ** -23 * np.abs(terms).sum(-1)
+        for n in np.nonzero(np.abs(((a - b) * o).sum(-1)) * np.log(2.0) > 4 * room)[0][:4]:
+            pair = np.zeros((2, D), dtype=np.float32)
+            pair[0, 2 * i:2 * i + 2], pair[1, 2 * i:2 * i + 2] = x[:, n], y
+            rows.append(pair if side == "q" else pair[::-1])
+            want.append(terms[n].sum())
+            allow.append(room[n])
+    assert len(rows) >= D // 2
+    rows = torch.from_numpy(np.stack(rows, axis=1)).to("cuda", torch.float32 if dtype == "f32" else torch.bfloat16)
+    q, k = (r[:, None, None, :].contiguous() for r in rows)
+    _, lse = B.dit_attn_forward(q, k, k, (1, 1, 1), split, origin=origin, flags=flags, want_lse=True)
+    torch.cuda.synchronize()
+    off = np.abs(to_f64(lse)[:, 0, 0] - np.array(want)) > np.array(allow)
+    assert not off.any(), "%d of %d scores are not of the operands stated" % (off.sum(), off.size)
