@@ -105,11 +105,12 @@ enum {
     DIT_FLAG_PIPELINED_SCHEDULE = 1u << 10,
     /* The workspace still holds the rotated, pre-packed K'/V^T tile images (and the rotation table,
      * the key tile lists and masks) that an earlier forward call of the SAME entry point wrote for the
-     * same k, v, kv_valid, in_dtype, shapes, grid(s), origin, rope_base, norm (mode, eps, k_gamma), key split,
+     * same k, v, kv_valid, shapes, grid(s), origin, rope_base, norm (mode, eps, k_gamma), key split,
      * operand-type flags and the flags that choose the matrix-instruction shape the tiles are laid out for
      * (MFMA_32X32, WIDE_QTILE, SIMPLE_SCHEDULE, QK_FP8, PIPELINED_SCHEDULE); that call must precede
      * this one in stream order.  The key-side passes are skipped: k, v and kv_valid are not read and may
-     * be NULL.  q, scale, q_gamma, the output and the workgroup-size flags may differ from call to call.
+     * be NULL.  q (its type, in_dtype, too but for cross-attention with one joint softmax; in cross-attention the
+     * number of its rows, Lq), scale, q_gamma, the output and the workgroup-size flags may differ from call to call.
      * This is the K/V cache of a denoising loop: the conditioning keys and values of cross-attention are
      * the same at every step, and a caller that evaluates several query sets against one K, V pays for
      * one pre-pack.  Nothing records what the workspace holds: the caller vouches for it.  Not with

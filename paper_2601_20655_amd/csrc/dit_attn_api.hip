@@ -625,6 +625,7 @@ namespace {
 
 struct CrossPlan {
     Flags fl;
+    bool layout16;  // tile images in the layout of the 16x16x32 kernels
     bool chain16;  // the chained 16x16x32 kernel (default)
     int qch;       // with it: query tiles per workgroup
     int nKT, nQT;
@@ -632,17 +633,14 @@ struct CrossPlan {
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
 
-// Whether two softmaxes run on the chained kernel.  Not with bf16 score operands, whose scores can be -inf (a row's second
-// pass would start from them), nor with bf16 probabilities, which the plain kernel sums as rounded.  Where 256-row query
+// Whether two softmaxes run on the chained kernel.  Where 256-row query
 // tiles fill the chip more than twice, a pass over a range costs more than the plain kernel's step from one range into the
 // next, and the steps have to make up for it: head_dim 128 does from 8 key tiles on (us, plain -> chained, 9,000 queries x
 // 30 heads: 3 + 5 tiles 105 -> 99, 5 + 5 123 -> 113, 7 + 5 141 -> 127; fp32 rows 125 -> 127, 136 -> 134, 149 -> 143, but
 // 106 -> 112 where only 2 of 8 tiles of the first range hold keys), head_dim 64 does not (9,000 x 30, 5 + 5 tiles 66.7 ->
 // 68.0, 20,000 x 30, 1 + 5 102 -> 115).  Fewer tiles: 1,500 x 12, 5 + 5 tiles 21.2 -> 19.5, head_dim 64 14.4 -> 13.2, 4,000
 // x 30 35.0 -> 31.6.
-// (The tile images are laid out for the kernel: nothing here may change between calls that share them.)
-bool chain_two(const dit_cross_attn_params* p, const Flags& fl, int nKT) {
-    if (fl.qk_op != dit::OP_F16 || fl.pv_op != dit::OP_F16) return false;
+bool chain_two(const dit_cross_attn_params* p, int nKT) {
     const int64_t tiles = (int64_t)(p->Lq + 255) / 256 * p->H * p->B;
     return tiles <= 2 * kCUs || (p->D == 128 && nKT >= 8);
 }
@@ -674,8 +672,14 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     // The plain kernel serves DIT_FLAG_SIMPLE_SCHEDULE (also with DIT_FLAG_MFMA_32X32
     // or 64 rows per wavefront); DIT_FLAG_PIPELINED_SCHEDULE asks for the listed 32x32x16 pipelined kernel.
     // (the chained kernel takes 16-bit query rows, normalised or not: fp32 rows go to the plain kernel)
-    pl->chain16 = !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 && p->in_dtype == DIT_BF16 &&
-                  (pl->split == 0 || chain_two(p, pl->fl, pl->nKT));
+    const bool bf16 = p->in_dtype == DIT_BF16;
+    // Two softmaxes are not chained with bf16 score operands, whose scores can be -inf (a row's second pass would start from
+    // them), nor with bf16 probabilities, which the plain kernel sums as rounded.  Wherever one of the calls that may share
+    // resident tiles can be chained, all of them lay the tiles out for it: operand types and flags decide, not the
+    // number or the type of the query rows or the type of the output.  The plain kernel reads either layout.
+    const bool f16 = pl->fl.qk_op == dit::OP_F16 && pl->fl.pv_op == dit::OP_F16;
+    pl->layout16 = !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 && (pl->split == 0 ? bf16 : f16);
+    pl->chain16 = pl->layout16 && bf16 && (pl->split == 0 || chain_two(p, pl->nKT));
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
         dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
@@ -864,7 +868,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     pa.split = pl.split;
     pa.nTA = pl.nTA;
     pa.tab = nullptr;
-    pa.v_layout = pl.chain16 ? 1 : 0;
+    pa.v_layout = pl.layout16 ? 1 : 0;
     pa.B = p->B; pa.H = p->H; pa.Lk = p->Lk; pa.nKT = pl.nKT;
     pa.in_f32 = p->in_dtype == DIT_F32;
     pa.sk_b = p->sk.batch; pa.sk_t = p->sk.token; pa.sk_h = p->sk.head;
@@ -889,6 +893,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     aa.tile_count = pa.tile_count;
     aa.tile_count_a = pa.tile_count_a;
     aa.nTA = pl.nTA;
+    aa.layout16 = pl.layout16;
     aa.tab = nullptr;
     aa.B = p->B; aa.H = p->H; aa.Lq = p->Lq; aa.Lk = p->Lk; aa.nKT = pl.nKT; aa.nQT = pl.nQT;
     aa.in_f32 = p->in_dtype == DIT_F32; aa.out_f32 = p->out_dtype == DIT_F32;

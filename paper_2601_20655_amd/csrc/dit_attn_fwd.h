@@ -21,7 +21,9 @@ constexpr float kRescaleThr = 8.0f;
 // SPLIT: decoupled cross-attention.  The first tile_count_a[b] listed tiles form one softmax, the
 // rest a second one; when the loop crosses over, the first result is normalised, parked in
 // registers as fp16 and added back in the epilogue.
-template <int D, int QB, int QK_OP, int PV_OP, bool FUSED, bool SPLIT = false>
+// LAYOUT16: the tile images are laid out for the 16x16x32 kernels (v_layout 1 of the pre-pack): a V^T chunk holds another
+// pair of the four 4-key pieces that a lane has of 32 keys, so the probabilities are paired alike.
+template <int D, int QB, int QK_OP, int PV_OP, bool FUSED, bool SPLIT = false, bool LAYOUT16 = false>
 __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(const AttnArgs a) {
     using G = TileGeom<D>;
     constexpr int NKS = D / 16;           // contraction steps of the score product
@@ -32,7 +34,7 @@ __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(con
     constexpr int NI_K = kBK / KROWS_PER_PASS;
     constexpr int NI_V = D / 32;          // V^T: 8 chunks per row, 32 rows per pass
     static_assert(!FUSED || (PV_OP == OP_BF16 && D == 128), "fused staging keeps V in bf16, D = 128");
-    static_assert(!SPLIT || !FUSED, "the decoupled form works on pre-packed tiles");
+    static_assert(!(SPLIT || LAYOUT16) || !FUSED, "on pre-packed tiles");
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
@@ -70,6 +72,11 @@ __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(con
     // ---- staging of K/V tiles ----
     const int kchunk_off = (tid / CPR) * G::KROW + (tid % CPR) * 16;
     const int vchunk_off = G::K_BYTES + (tid >> 3) * G::VROW + (tid & 7) * 16;
+    // (LAYOUT16: chunks of rows 4..11 of every 16 have changed places in pairs; put back on the way into LDS.  A pass steps
+    // over whole sixteens of rows.)
+    const auto chunk = [](int c, int row) { return LAYOUT16 ? c ^ (((row >> 2) ^ (row >> 3)) & 1) : c; };
+    const int klds_off = (tid / CPR) * G::KROW + chunk(tid % CPR, tid / CPR) * 16;
+    const int vlds_off = G::K_BYTES + (tid >> 3) * G::VROW + chunk(tid & 7, tid >> 3) * 16;
     const uint8_t* tiles = FUSED ? nullptr : a.tiles + (size_t)bh * a.nKT * G::TILE_BYTES;
     u32x4 preK[NI_K];
     u32x4 preV[NI_V];       // pre-packed path: V^T chunks
@@ -118,10 +125,10 @@ __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(con
         if constexpr (!FUSED) {
 #pragma unroll
             for (int i = 0; i < NI_K; ++i)
-                *reinterpret_cast<u32x4*>(dst + kchunk_off + i * KROWS_PER_PASS * G::KROW) = preK[i];
+                *reinterpret_cast<u32x4*>(dst + klds_off + i * KROWS_PER_PASS * G::KROW) = preK[i];
 #pragma unroll
             for (int i = 0; i < NI_V; ++i)
-                *reinterpret_cast<u32x4*>(dst + vchunk_off + i * 32 * G::VROW) = preV[i];
+                *reinterpret_cast<u32x4*>(dst + vlds_off + i * 32 * G::VROW) = preV[i];
         } else {
 #pragma unroll
             for (int i = 0; i < NI_K; ++i) {
@@ -353,13 +360,13 @@ __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(con
                 float lsum4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kg = 0; kg < 4; ++kg) {
-                    const int o = 8 * (kg & 1);
+                    const int o = (LAYOUT16 ? 4 : 8) * (kg & 1), o2 = o + (LAYOUT16 ? 8 : 4);
                     const f32x16& s = S[kg >> 1][qb];
                     P[kg][qb] = mk4(pack2<PV_OP>(s[o + 0], s[o + 1]), pack2<PV_OP>(s[o + 2], s[o + 3]),
-                                    pack2<PV_OP>(s[o + 4], s[o + 5]), pack2<PV_OP>(s[o + 6], s[o + 7]));
+                                    pack2<PV_OP>(s[o2 + 0], s[o2 + 1]), pack2<PV_OP>(s[o2 + 2], s[o2 + 3]));
                     if constexpr (PV_OP == OP_F16) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) lsum4[e & 3] += s[o + e];
+                        for (int e = 0; e < 8; ++e) lsum4[e & 3] += s[(e < 4 ? o : o2 - 4) + e];
                     } else {  // bf16 P: sum the rounded values, which cancels their (8-bit) rounding error
                         lsum4[0] = sum2<PV_OP>(P[kg][qb].x, lsum4[0]);
                         lsum4[1] = sum2<PV_OP>(P[kg][qb].y, lsum4[1]);
@@ -424,9 +431,9 @@ __global__ void __launch_bounds__(kThreads, QB == 1 ? 2 : 1) attn_fwd_kernel(con
     }
 }
 
-template <int D, int QB, int QK_OP, int PV_OP, bool FUSED, bool SPLIT = false>
+template <int D, int QB, int QK_OP, int PV_OP, bool FUSED, bool SPLIT = false, bool LAYOUT16 = false>
 hipError_t launch_attn_inst(const AttnArgs& a, hipStream_t s) {
-    auto kern = attn_fwd_kernel<D, QB, QK_OP, PV_OP, FUSED, SPLIT>;
+    auto kern = attn_fwd_kernel<D, QB, QK_OP, PV_OP, FUSED, SPLIT, LAYOUT16>;
     constexpr int smem = 2 * TileGeom<D>::TILE_BYTES;
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);

@@ -116,6 +116,7 @@ struct AttnArgs {
     const int* tile_count;      // with tile_mask: [B] how many entries of tile_list are used
     const int* tile_count_a;    // decoupled cross-attention: [B] how many of them form the first softmax
     int nTA;                    // with it: tile images of the first key group
+    int layout16;               // with it: whether the tile images are in the layout of the 16x16x32 kernels
     const float2* tab;          // nullable: no rotation of q
     // raw K/V for the fused staging path
     const void* k;

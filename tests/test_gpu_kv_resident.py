@@ -134,3 +134,34 @@ def test_packed_requests_second_query_set():
         L = int(np.prod(g))
         compare(to_f64(out)[n0:n0 + L], ref[n0:n0 + L], what="request of %d tokens" % L)
         n0 += L
+
+
+@pytest.mark.parametrize("n_text,n_image", [(100, 65), (300, 257)])
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_cross_attention_tiles_serve_any_queries(D, two, n_text, n_image):
+    """Tiles packed by a call with few or many query rows, with two softmaxes of either type, and with either output type,
+    serve calls of every other kind: the same bits as a call that packs for itself, and the oracle's values for the few rows."""
+    import torch
+
+    H, few, many = 8, 300, 17000  # (many: more 256-row tiles than two rounds over the chip)
+    split = n_text if two else 0
+    cfg = dict(B=1, Lq=few, n_text=n_text, n_image=n_image, H=H, D=D, dtype="bf16", min_text=16, seed=D + n_text)
+    q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
+    ref = oracle.cross_attn_decoupled(q, k, v, split, valid) if two else oracle.cross_attn(q, k, v, valid)
+    qs = {few: to_dev(q)}
+    qs[many] = qs[few].repeat(1, many // few + 1, 1, 1)[:, :many].contiguous()
+    kd, vd, md = to_dev(k), to_dev(v), to_dev(valid)
+    both = (torch.bfloat16, torch.float32)
+    kinds = [(n, t, o) for n in (few, many) for t in (both if two else both[:1]) for o in both]
+    alone = {}
+    for n, t, o in kinds:
+        alone[n, t, o] = B.dit_cross_attn_forward(qs[n].to(t), kd.to(t), vd.to(t), md, split=split, out_dtype=o)
+        compare(to_f64(alone[n, t, o][:, :few]), ref, bf16_out=o == torch.bfloat16, what="%d rows %s" % (n, t))
+    ws = workspace(32 << 20)
+    for n, t, o in kinds:
+        B.dit_cross_attn_forward(qs[n].to(t), kd.to(t), vd.to(t), md, split=split, out_dtype=o, workspace=ws)
+        for kind in kinds:
+            out = B.dit_cross_attn_forward(qs[kind[0]].to(kind[1]), poisoned_like(kd).to(kind[1]), poisoned_like(vd).to(kind[1]),
+                                           None, split=split, out_dtype=kind[2], workspace=ws, flags=RES)
+            assert torch.equal(out, alone[kind]), "packed for %s, asked by %s" % ((n, t, o), kind)
