@@ -88,8 +88,8 @@ enum {
     /* Self-attention with pre-packed K/V normally runs a software-pipelined kernel (scores of
      * tile j+1 on the matrix pipe while tile j's softmax runs on the vector ALU, tiles streamed
      * global->LDS directly).  This flag selects the plain one-tile-at-a-time kernel instead
-     * (FUSED always uses it, cross-attention with fp32 rows and, in the decoupled form, with bf16 operands
-     * or many query tiles of few keys), for cross-attention too; same results up to rounding order. */
+     * (FUSED always uses it, cross-attention with fp32 rows and, in the decoupled form, with bf16 operands,
+     * fp32 output or head_dim 64), for cross-attention too; same results up to rounding order. */
     DIT_FLAG_SIMPLE_SCHEDULE = 1u << 7,
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
@@ -98,8 +98,8 @@ enum {
      * of a partly filled last round, or of whole requests, in pieces along the keys.  SMALL: never in pieces. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,
     DIT_FLAG_SMALL_WORKGROUP = 1u << 9,
-    /* Cross-attention of bf16 rows runs a kernel that chains several query tiles per workgroup (both forms; the
-     * decoupled one with fp16 operands, the default).  With one joint softmax this flag selects the
+    /* Cross-attention of bf16 rows runs a kernel that chains several query tiles per workgroup (the decoupled
+     * form: at head_dim 128 with fp16 operands and bf16 output).  With one joint softmax this flag selects the
      * 32x32x16 pipelined kernel instead (at most 64 key tiles, i.e. Lk <= 4096, else DIT_ERR_UNSUPPORTED).  No
      * effect on self-attention. */
     DIT_FLAG_PIPELINED_SCHEDULE = 1u << 10,

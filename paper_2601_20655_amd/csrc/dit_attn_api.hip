@@ -633,18 +633,6 @@ struct CrossPlan {
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
 
-// Whether two softmaxes run on the chained kernel.  Where 256-row query
-// tiles fill the chip more than twice, a pass over a range costs more than the plain kernel's step from one range into the
-// next, and the steps have to make up for it: head_dim 128 does from 8 key tiles on (us, plain -> chained, 9,000 queries x
-// 30 heads: 3 + 5 tiles 105 -> 99, 5 + 5 123 -> 113, 7 + 5 141 -> 127; fp32 rows 125 -> 127, 136 -> 134, 149 -> 143, but
-// 106 -> 112 where only 2 of 8 tiles of the first range hold keys), head_dim 64 does not (9,000 x 30, 5 + 5 tiles 66.7 ->
-// 68.0, 20,000 x 30, 1 + 5 102 -> 115).  Fewer tiles: 1,500 x 12, 5 + 5 tiles 21.2 -> 19.5, head_dim 64 14.4 -> 13.2, 4,000
-// x 30 35.0 -> 31.6.
-bool chain_two(const dit_cross_attn_params* p, int nKT) {
-    const int64_t tiles = (int64_t)(p->Lq + 255) / 256 * p->H * p->B;
-    return tiles <= 2 * kCUs || (p->D == 128 && nKT >= 8);
-}
-
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
     if (p->B < 1 || p->H < 1 || p->D < 1 || p->Lq < 1 || p->Lk < 1) return DIT_ERR_INVALID_ARG;
@@ -673,13 +661,18 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     // or 64 rows per wavefront); DIT_FLAG_PIPELINED_SCHEDULE asks for the listed 32x32x16 pipelined kernel.
     // (the chained kernel takes 16-bit query rows, normalised or not: fp32 rows go to the plain kernel)
     const bool bf16 = p->in_dtype == DIT_BF16;
-    // Two softmaxes are not chained with bf16 score operands, whose scores can be -inf (a row's second pass would start from
-    // them), nor with bf16 probabilities, which the plain kernel sums as rounded.  Wherever one of the calls that may share
-    // resident tiles can be chained, all of them lay the tiles out for it: operand types and flags decide, not the
-    // number or the type of the query rows or the type of the output.  The plain kernel reads either layout.
-    const bool f16 = pl->fl.qk_op == dit::OP_F16 && pl->fl.pv_op == dit::OP_F16;
-    pl->layout16 = !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 && (pl->split == 0 ? bf16 : f16);
-    pl->chain16 = pl->layout16 && bf16 && (pl->split == 0 || chain_two(p, pl->nKT));
+    // Two softmaxes are chained where the form as a whole gains by it, and by nothing that depends on the rest of the call: a
+    // row has the bits of its own kernel in a batch as alone.  Not with bf16 score operands, whose scores can be -inf (a
+    // row's second pass would start from them), nor with bf16 probabilities, which the plain kernel sums as rounded.  At 45
+    // shapes of 75 to 32,760 queries x 2 to 40 heads, 1 to 8 + 5 key tiles, resident keys, time of the plain kernel over
+    // that of the chained one: head_dim 128 with bf16 output 1.07 (0.96 to 1.20; 32,760 x 40, 5 + 5 tiles 585 -> 489 us, 9,000
+    // x 30, 1 + 5 tiles 86 -> 82), with fp32 output 1.02 (0.93 to 1.15: a pass over one or two tiles does not pay for parking
+    // and wider rows), head_dim 64 0.95 (0.80 to 1.13).
+    const bool two = p->D == 128 && pl->fl.qk_op == dit::OP_F16 && pl->fl.pv_op == dit::OP_F16;
+    // Wherever one of the calls that may share resident tiles can be chained, all of them lay the tiles out for it: not
+    // the number or the type of the query rows or the type of the output decides.  The plain kernel reads either layout.
+    pl->layout16 = !pl->fl.simple && !pl->fl.pipelined && !pl->fl.mfma32 && pl->fl.qb == 1 && (pl->split == 0 ? bf16 : two);
+    pl->chain16 = pl->layout16 && bf16 && (pl->split == 0 || p->out_dtype == DIT_BF16);
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
         dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);

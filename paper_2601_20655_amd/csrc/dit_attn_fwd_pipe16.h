@@ -93,9 +93,9 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 // TWO (chained): decoupled cross-attention, one softmax over the tiles of each conditioning sequence, their results added.
 // A query tile goes through the stream twice: the last step of its first pass multiplies the SAME rows with the first key
 // tile of the second sequence, and the first result, normalised, waits as fp16 pairs in the output rows themselves (each
-// lane in the row it will write: 16-bit rows are as wide, fp32 rows wider) until the last step of the second pass brings
+// lane in the row it will write; 16-bit rows, which are as wide) until the last step of the second pass brings
 // it into the wavefront's LDS area, free by then.  In registers (the plain kernel's way) there is no room for it here, in
-// LDS beside the next rows neither.  Row sums in fp32 over the unrounded probabilities, as in the plain kernel.  What the
+// LDS beside the next rows neither with 8 wavefronts (154 KiB are taken; with 4 there would be).  Row sums in fp32 over the unrounded probabilities, as in the plain kernel.  What the
 // form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
 // and loads 337) and the second pass's first maxima.  570.8 -> 509 us at 32,760 queries x 40 heads, 5 + 5 key tiles (plain
 // kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
@@ -110,7 +110,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     constexpr int NI = G::PART_KIB / NW;  // full rounds of wavefront-wide 1 KiB loads per tile part
     static_assert(G::PART_KIB - NW * NI == 2, "two odd pieces per tile part");
     static_assert(QK_OP != OP_FP8, "16-bit score operands only");
-    static_assert(!TWO || (CHAIN && QK_OP == OP_F16 && PV_OP == OP_F16),
+    static_assert(!TWO || (CHAIN && D == 128 && QK_OP == OP_F16 && PV_OP == OP_F16),
                   "a pass takes its first maxima as they are: finite scores only; its row sums are those of unrounded probabilities");
 
     constexpr bool STAG = pipe_staggered<NW>();
@@ -724,7 +724,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         const int row = qt * BQ + wave * 32 + 16 * qb + (ln & 15);
         inside = row < pv.Lq;
         const int64_t off = (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h + (int64_t)(inside ? row : pv.Lq - 1) * a.so_t;
-        return static_cast<uint8_t*>(a.out) + off * (a.out_f32 ? 4 : 2) + k * 64 + (ln >> 4) * 16;
+        return static_cast<uint8_t*>(a.out) + off * 2 + k * 64 + (ln >> 4) * 16;
     };
     auto park_rows = [&]() __attribute__((always_inline)) {
         const int ln = opaque_lane();
@@ -852,9 +852,9 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                           "staging geometry");
             const int row0 = qt * BQ + wave * 32;
             const bool full = row0 + 32 <= pv.Lq;  // wavefront-uniform
-            // the first softmax's result, zero without one; read before rows are staged over it: 16-bit rows, whose first
-            // 16 rows take only the half that held theirs, block by block
-            constexpr bool BOTH = RPP * RB > STG / 2;
+            // the first softmax's result, zero without one: read block by block before rows are staged over it (16 staged rows
+            // take only the half of the area that held theirs)
+            static_assert(!TWO || RPP * RB <= STG / 2, "the second block's first result stays in place");
             u32x4 first[TWO ? 2 : 1][TWO ? NPK : 1];
             auto read_first = [&](int qb) {
 #pragma unroll
@@ -864,14 +864,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
                 asm volatile("" ::: "memory");
             };
-            if constexpr (TWO && BOTH) {
-                read_first(0);
-                read_first(1);
-            }
 #pragma unroll
             for (int pass = 0; pass < 32 / RPP; ++pass) {
                 const int qb = pass * RPP / 16;
-                if constexpr (TWO && !BOTH) read_first(qb);
+                if constexpr (TWO) read_first(qb);
                 auto value = [&](int cb, int e) {
                     if constexpr (TWO) {
                         const uint32_t pair = first[qb][cb / 2][2 * (cb & 1) + (e >> 1)];  // (bit_cast of the element itself reads element 0)
@@ -925,8 +921,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
             }
         };
-        if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
-        else stage_and_store(std::integral_constant<int, 2>());
+        if constexpr (TWO) {
+            stage_and_store(std::integral_constant<int, 2>());
+        } else {
+            if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
+            else stage_and_store(std::integral_constant<int, 2>());
+        }
     };
     if constexpr (CHAIN) {
     // query tiles of the chain, and the one after (h, qt)

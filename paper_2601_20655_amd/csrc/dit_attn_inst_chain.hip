@@ -1,5 +1,5 @@
 // Instantiations of the chained cross-attention kernel on 16x16x32 MFMAs: one joint softmax, and one softmax for each of
-// two conditioning sequences (fp16 operands).
+// two conditioning sequences (head_dim 128, fp16 operands, 16-bit output rows).
 #include "dit_attn_fwd_pipe16.h"
 
 namespace dit {
@@ -18,7 +18,6 @@ hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_
     DIT_CASE(false, 64, OP_BF16, OP_F16)
     DIT_CASE(false, 64, OP_BF16, OP_BF16)
     DIT_CASE(true, 128, OP_F16, OP_F16)
-    DIT_CASE(true, 64, OP_F16, OP_F16)
 #undef DIT_CASE
     return hipErrorInvalidValue;
 }

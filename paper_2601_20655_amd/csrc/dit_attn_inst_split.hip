@@ -17,8 +17,6 @@ hipError_t launch_attn_split(const AttnArgs& a, int D, int qk_op, int pv_op, hip
 #undef DIT_SPLIT_CASE
     if (a.layout16 && D == 128 && qk_op == OP_F16 && pv_op == OP_F16)
         return launch_attn_inst<128, 1, OP_F16, OP_F16, false, true, true>(a, s);
-    if (a.layout16 && D == 64 && qk_op == OP_F16 && pv_op == OP_F16)
-        return launch_attn_inst<64, 1, OP_F16, OP_F16, false, true, true>(a, s);
     return hipErrorInvalidValue;
 }
 

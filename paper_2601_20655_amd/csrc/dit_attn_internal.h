@@ -202,7 +202,7 @@ hipError_t launch_attn_pipe16(const AttnArgs& a, int D, int qk_op, int pv_op, in
 hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_op, hipStream_t s);
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
-// (AttnArgs::tile_count_a set: two softmaxes, fp16 operands only)
+// (AttnArgs::tile_count_a set: two softmaxes, head_dim 128, fp16 operands and 16-bit output rows only)
 hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s);
 // whether the masks of such a call (split: first key of the second group, 0 = one group) are listed beforehand (the next
 // two passes); launch_prepack sorts out the others by itself

@@ -385,3 +385,40 @@ def test_chains_with_two_softmaxes(D, big, out_f32):
     o = to_f64(rows[..., :D])
     for b, c in enumerate(counts):
         compare(o[b], ref[b], bf16_out=not out_f32, what="%d + %d keys, %d wavefronts" % (c + (nw,)))
+
+
+@pytest.mark.parametrize("out_f32", [False, True])
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_rows_do_not_depend_on_the_rest_of_the_call(D, two, out_f32):
+    """A request has the same bits alone as with more query rows behind its own, in a batch, with more heads, and with keys
+    padded to a larger capacity: calls of 16 to 2,000 query tiles of 256 rows, either side of every line by which
+    calls are laid over the chip."""
+    import torch
+
+    H, Lq, n_text, n_image = 8, 300, 100, 65
+    cfg = dict(B=1, Lq=Lq, n_text=n_text, n_image=n_image, H=H, D=D, dtype="bf16", min_text=16, seed=3 * D)
+    q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
+    valid[:] = 1
+    valid[:, 83:n_text] = 0
+    qd, kd, vd = (to_dev(x) for x in (q, k, v))
+    md = torch.from_numpy(valid).cuda()
+    dt = torch.float32 if out_f32 else torch.bfloat16
+
+    def run(q, k, v, m, n=n_text):
+        return B.dit_cross_attn_forward(q, k, v, m, split=n if two else 0, out_dtype=dt)[:1, :Lq, :H]
+
+    alone = run(qd, kd, vd, md)
+    others = [x.flip(1).expand(5, -1, -1, -1) for x in (qd, kd, vd)]  # five requests with rows of their own
+    for n_q in (Lq, 2000, 17000):
+        many = torch.cat([qd] + [qd.flip(1)] * (n_q // Lq), dim=1)[:, :n_q].contiguous()
+        assert torch.equal(run(many, kd, vd, md), alone), "%d query rows" % n_q
+        batch = torch.cat([many, many.flip(1).expand(5, -1, -1, -1)])
+        assert torch.equal(run(batch, *(torch.cat([x, o]) for x, o in zip((kd, vd), others[1:])), md.expand(6, -1).contiguous()),
+                           alone), "%d query rows in a batch of 6" % n_q
+        heads = [torch.cat([x] + [x.flip(2)] * 4, dim=2) for x in (many, kd, vd)]
+        assert torch.equal(run(*heads, md), alone), "%d query rows, %d heads" % (n_q, 5 * H)
+        pad = lambda x: torch.cat([x[:, :n_text], x[:, :1].expand(-1, 412, *x.shape[2:]), x[:, n_text:]], dim=1).contiguous()
+        wide = pad(md)
+        wide[:, n_text:512] = 0
+        assert torch.equal(run(many, pad(kd), pad(vd), wide, 512), alone), "%d query rows, room for 512 keys" % n_q
