@@ -583,7 +583,7 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
 // chained cross-attention kernel.  Estimate in microseconds: rounds of workgroups x (start + query tiles x (what a query
 // tile costs once + its key tiles)), fitted to chain lengths of 1 to 32 in both workgroup sizes at 11 shapes of 800 to
 // 32,760 queries and 1 to 9 key tiles.  A compute unit (the device has `cus`) holds one workgroup (head_dim 64 with 4
-// wavefronts: two, each a third slower per key tile than alone).  How many key tiles attend is on the device; three
+// wavefronts: two, each half as slow again per key tile as alone).  How many key tiles attend is on the device; three
 // fifths of the capacity are taken for it.
 // Measured, us, lengths that fill the rounds and their neighbours: 32,760 queries x 12 heads, 5 key tiles: 4 query tiles a
 // workgroup 98, 6 (one round) 77, 8 92; 32,760 x 40, 9 key tiles: 1 459, 4 416, 10 408, 16 549, 20 (one round) 416; 7,800 x
@@ -615,10 +615,6 @@ void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* n
         }
     }
     *nw = best_nw;
-}
-
-void dit::choose_chain(int Lq, int64_t BH, int nKT, int D, int cus, int* nw, int* qch) {
-    choose_chain(Lq, 1, BH, nKT, D, cus, nw, qch);
 }
 
 namespace {

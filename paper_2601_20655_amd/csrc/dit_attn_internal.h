@@ -179,9 +179,9 @@ inline hipError_t compute_units(int* n) {
     return e == hipSuccess ? hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev) : e;
 }
 
-// Layout of the chained cross-attention kernel on `cus` compute units.  *nw: 4 or 8 if asked for, 0 to choose.
+// Layout of the chained cross-attention kernel on `cus` compute units (the host tests read it).  *nw: 4 or 8 if asked for, 0
+// to choose.
 void choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* nw, int* qch);
-void choose_chain(int Lq, int64_t H, int nKT, int D, int cus, int* nw, int* qch);  // one request (the host tests read it)
 
 // How a packed call (params: dit_varlen_attn_params) with this workspace is laid over the chip: wavefronts per workgroup
 // (0: it is refused) and query tiles computed in pieces.  No device is touched; the host tests read it.

@@ -323,6 +323,11 @@ def test_many_heads_with_listed_masks_of_moderate_length(split):
     assert torch.equal(out, alone.repeat(1, 1, H // few, 1))
 
 
+# requests, heads, query tiles a head (the last one of 11 rows), keys of either range: of the next two tests, whose chains are
+# to cross from head to head in the middle of a chain (a host test holds them to that)
+CHAINS_ONE, CHAINS_TWO = (4, 24, 7, (320,)), (7, 20, 4, (270, 320))
+
+
 @pytest.mark.parametrize("big", [False, True])
 @pytest.mark.parametrize("D", [64, 128])
 def test_chains_run_on_into_the_next_heads(D, big):
@@ -332,8 +337,9 @@ def test_chains_run_on_into_the_next_heads(D, big):
     import torch
 
     nw = 8 if big else 4
-    H, Lq, Lk = 24, 32 * nw * 6 + 11, 320
-    cfg = dict(B=4, Lq=Lq, n_text=Lk, n_image=0, H=H, D=D, dtype="bf16", min_text=5, seed=91 + D)
+    nb, H, tiles, (Lk,) = CHAINS_ONE
+    Lq = 32 * nw * (tiles - 1) + 11
+    cfg = dict(B=nb, Lq=Lq, n_text=Lk, n_image=0, H=H, D=D, dtype="bf16", min_text=5, seed=91 + D)
     q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
     keys = (1, 128, 255, 257)
     valid[:] = 0
@@ -356,16 +362,17 @@ def test_chains_run_on_into_the_next_heads(D, big):
 @pytest.mark.parametrize("big", [False, True])
 @pytest.mark.parametrize("D", [64, 128])
 def test_chains_with_two_softmaxes(D, big, out_f32):
-    """Two passes per query tile in chains over several heads: requests with nothing in one range, with one tile in
-    either, and with 1 to 5 tiles whose last ones hold one key, some and all; a ragged last query tile, output rows
-    that stand apart (the first pass's result waits in them: nothing between them may change).  Every row against the
-    oracle; per-token normalised rows."""
+    """Two passes per query tile in chains over several heads (bf16 rows of head_dim 128; the others run on the plain
+    kernel): requests with nothing in one range or in both, with one tile in either, and with 1 to 5 tiles whose last ones
+    hold one key, some and all; a ragged last query tile, output rows that stand apart (the first pass's result
+    waits in them: nothing between them may change).  Every row against the oracle; per-token normalised rows."""
     import torch
 
     nw = 8 if big else 4
-    H, Lq, n_text, n_image = 20, 32 * nw * 3 + 11, 270, 320  # (few enough tiles for head_dim 64 to take that kernel too)
-    counts = [(0, 65), (128, 0), (1, 1), (65, 130), (192, 64), (257, 320)]
-    cfg = dict(B=len(counts), Lq=Lq, n_text=n_text, n_image=n_image, H=H, D=D, dtype="bf16", min_text=5, seed=17 + D)
+    nb, H, tiles, (n_text, n_image) = CHAINS_TWO
+    Lq = 32 * nw * (tiles - 1) + 11
+    counts = [(0, 65), (128, 0), (1, 1), (65, 130), (0, 0), (192, 64), (257, 320)]
+    cfg = dict(B=nb, Lq=Lq, n_text=n_text, n_image=n_image, H=H, D=D, dtype="bf16", min_text=5, seed=17 + D)
     q, k, v, valid, _ = wl.cross_attn_inputs(cfg)
     valid[:] = 0
     for b, (n, m) in enumerate(counts):

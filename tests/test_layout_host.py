@@ -56,19 +56,47 @@ def linear_form(M, N, K, cus=256):
     return f(M, N, K, cus)
 
 
+def chain_layout(Lq, nb, H, nKT, D, nw=0, cus=256):
+    """Wavefronts per workgroup (nw: as asked for, 0: chosen) and query tiles per workgroup of chained cross-attention."""
+    f = B.lib()._ZN3dit12choose_chainEiiliiiPiS0_
+    f.restype = None
+    f.argtypes = 2 * [ctypes.c_int] + [ctypes.c_int64] + 3 * [ctypes.c_int] + 2 * [ctypes.POINTER(ctypes.c_int)]
+    w, chain = ctypes.c_int(nw), ctypes.c_int(0)
+    f(Lq, nb, H, nKT, D, cus, ctypes.byref(w), ctypes.byref(chain))
+    assert w.value in (4, 8) and nw in (0, w.value)
+    assert 1 <= chain.value <= min(32, (Lq + 32 * w.value - 1) // (32 * w.value) * H)  # (of one request)
+    return w.value, chain.value
+
+
 def test_layouts_follow_the_compute_units_of_the_device():
     """A partition of the chip has fewer compute units: 256 x 256 tiles fill it earlier, and cross-attention chains more
     query tiles per workgroup on it."""
     assert linear_form(769, 10240, 5120) == 54 and linear_form(769, 10240, 5120, cus=32) == 0
-    f = B.lib()._ZN3dit12choose_chainEiliiiPiS0_
-    f.argtypes = [ctypes.c_int, ctypes.c_int64] + 3 * [ctypes.c_int] + 2 * [ctypes.POINTER(ctypes.c_int)]
-    lengths = []
-    for cus in (256, 32):
-        nw, chain = ctypes.c_int(8), ctypes.c_int(0)
-        f(7800, 12, 3, 128, cus, ctypes.byref(nw), ctypes.byref(chain))
-        assert nw.value == 8
-        lengths.append(chain.value)
-    assert 1 <= lengths[0] < lengths[1] <= 16
+    whole, part = (chain_layout(7800, 1, 12, 3, 128, nw=8, cus=cus)[1] for cus in (256, 32))
+    assert whole < part
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("nw", [0, 4, 8])
+def test_chains_stay_inside_a_request(D, nw):
+    """Chains are cut per request, whatever the batch: one query tile in all, chains longer than a head has tiles, the cap."""
+    assert chain_layout(1, 1, 1, 1, D, nw)[1] == 1
+    assert chain_layout(1, 500, 1, 1, D, nw)[1] == 1
+    w, chain = chain_layout(300, 1, 1 << 20, 1, D, nw)  # (many heads of a few tiles each)
+    assert (300 + 32 * w - 1) // (32 * w) < chain
+    for nb, Lq, H in ((1, 32760, 40), (4, 32760, 40), (3, 1105, 7), (64, 77, 3)):
+        for nKT in (1, 3, 13, 1000):
+            chain_layout(Lq, nb, H, nKT, D, nw)
+
+
+def test_chained_shapes_of_the_gpu_tests_cross_from_head_to_head():
+    from test_gpu_cross_attn import CHAINS_ONE, CHAINS_TWO
+
+    for (nb, H, tiles, keys), dims in ((CHAINS_ONE, (64, 128)), (CHAINS_TWO, (128,))):
+        for D in dims:
+            for nw in (4, 8):
+                _, chain = chain_layout(32 * nw * (tiles - 1) + 11, nb, H, sum((n + 63) // 64 for n in keys), D, nw)
+                assert chain > 1 and tiles % chain != 0
 
 
 def test_projection_shapes_of_the_gpu_tests_run_on_the_tiles_they_are_meant_for():
