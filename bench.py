@@ -263,7 +263,9 @@ def other_workload(args):
         io_bytes = 2.0 * q.numel() * q.element_size() + 2.0 * float(valid.sum()) * H * D * k.element_size()
         what = "%s cross-attention, B=%d, %d queries x (512 text masked to %s + 257 image) keys, %d heads, d%d" % (
             "decoupled" if split else "joint", cfg["B"], Lq, list(map(int, text_len)), H, D)
-        plain = split or args.flags & (B.DIT_FLAG_SIMPLE_SCHEDULE | B.DIT_FLAG_MFMA_32X32 | B.DIT_FLAG_WIDE_QTILE)
+        plain = args.flags & (B.DIT_FLAG_SIMPLE_SCHEDULE | B.DIT_FLAG_MFMA_32X32 | B.DIT_FLAG_WIDE_QTILE)
+        if split:  # two softmaxes are chained with fp16 operands only
+            plain |= args.flags & (B.DIT_FLAG_QK_BF16 | B.DIT_FLAG_PV_BF16)
         kernel = ("attn_fwd_pipe_kernel" if args.flags & B.DIT_FLAG_PIPELINED_SCHEDULE else
                   "attn_fwd_kernel" if plain else "attn_fwd_pipe16_chain_kernel")
         # --key-counts: the same keys as two counts per request (text keys, image keys) instead of the byte mask

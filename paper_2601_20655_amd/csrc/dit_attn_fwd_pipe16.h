@@ -80,8 +80,9 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 // agree behind it (660 bytes of spills a lane).  In-kernel stamps, 8 wavefronts, 7.75 key tiles on average: 38,600 ->
 // 32,300 clocks a query tile (lock step, first scores and their barrier 3,400 of it -> none).  Whole calls of 4 x
 // 32,760 queries x 40 heads 1,622 -> 1,488 us, kernel alone at 1 x 32,760 x 40, 9 key tiles 440 -> 386, 7,800 x 12, 3 key
-// tiles 24 -> 22.  What bounds it now: the vector work of a step (as in the plain loop, 3,000 to 3,200 clocks a step
-// where the matrix cores take 2,048), and 8,000 clocks a query tile of conversion, maxima and store.
+// tiles 24 -> 22.  What bounds it now, by counters at 4 to 12 key tiles (32,760 x 40): 14,800 clocks a query tile, of start
+// and end of the pass, conversion, maxima and store, and 2,610 a key tile, where the matrix cores take 2,048; at 8 key tiles
+// they are busy 44 % of the time, the vector ALU 49 %, and wavefronts wait a quarter of theirs.
 //
 // PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
 // leaves its unnormalised output, running maxima and row sums in piece pv.piece of a.part_o / a.part_ml.
@@ -97,8 +98,8 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 // it into the wavefront's LDS area, free by then.  In registers (the plain kernel's way) there is no room for it here, in
 // LDS beside the next rows neither with 8 wavefronts (154 KiB are taken; with 4 there would be).  Row sums in fp32 over the unrounded probabilities, as in the plain kernel.  What the
 // form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
-// and loads 337) and the second pass's first maxima.  570.8 -> 509 us at 32,760 queries x 40 heads, 5 + 5 key tiles (plain
-// kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
+// and loads 337) and the second pass's first maxima: 24,000 clocks a query tile and 2,690 a key tile.  585 -> 489 us at
+// 32,760 queries x 40 heads, 5 + 5 key tiles, resident keys (plain kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
 template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
@@ -116,8 +117,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     constexpr bool STAG = pipe_staggered<NW>();
     constexpr int VST = STAG ? 3 : 2;  // V^T buffers
     // whole output rows through an LDS area of the wavefront's own (store_rows); 4 wavefronts without a chain keep the room
-    // for a second workgroup on the compute unit instead.  8 wavefronts of self-attention stored from the accumulators before:
-    // 3,600 x 40 317.6 -> 312.6 us, 14,040 x 12 1,033 -> 1,025, 6,240 x 4 105.5 -> 103.0, full clips level.
+    // for a second workgroup on the compute unit instead.  8 wavefronts of self-attention stored from the accumulators before;
+    // the gain is in the figures of start_q.
     constexpr bool STAGED = CHAIN || NW == 8;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint8_t* const kbuf = smem;  // K buffers 0/1, then the V buffers
@@ -559,9 +560,10 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // a test of the input type, the normalisation and the rotation around every 16 bytes and a compare-and-select
     // saturation a workgroup of 8 wavefronts took 17,800 clocks from its start to its first scores (21,000 with the
     // normalisation), now 15,300 (16,700); 123.3 -> 119.5 us at 6,240 tokens x 4 heads, 333 -> 328 us at
-    // 3,600 tokens x 40 heads, long sequences level.  Rotation entries two pairs a load (was one): 1,760 tokens x 9 heads 45.3 ->
-    // 44.0 us, 6,240 x 4 101.7 -> 100.2, five packed requests x 12 4,137 -> 3,999, 3,600 x 40 326 -> 323 (with the
-    // pre-pack's entries requested ahead; half of it each).
+    // 3,600 tokens x 40 heads, long sequences level.  Rotation entries two pairs a load (was one), the
+    // pre-pack's requested ahead and, with 8 wavefronts, whole output rows at the end, whole calls, all three: 6,240 x 4
+    // 100.0 -> 97.9 us, 3,600 x 40 318.6 -> 311.6, five packed requests x 12 3,997 -> 3,892, 32,760 x 12 5,139 -> 5,088, toy
+    // grids level.
     auto start_q = [&](auto f32_tag) {
         constexpr bool F32 = decltype(f32_tag)::value;
         u32x4 raw[2][NKS][F32 ? 2 : 1];
