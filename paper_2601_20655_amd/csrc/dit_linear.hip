@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // per-token normalisation's first half (weights applied, sums of squares left for k_rescale_kernel)
     static_assert(!(OUT_F32 && QKV), "the fused q/k/v form writes 16-bit rows and tiles");
     static_assert(kLinBM == 256 && kLinBN == 256 && kLinBK == 64, "tile shape");
-    constexpr int SX = kLinSX, SW = kLinSW, NW = kLinWaves;
+    constexpr int SX = kLinSX;
     constexpr int BR = 16;       // rows of an MFMA block
     constexpr int FB = 4;        // 16-feature blocks per wavefront
     constexpr int TB = 8;        // 16-token blocks per wavefront
@@ -180,11 +180,9 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // {1,2,4,7}, {8,11,13,14}, {9,10,12,15}), and with piece (4 ks + lg) ^ ((row >> 1) & 7) each of those
     // cycles touches 16 different 16-byte bank groups.
     const int sw = (lr >> 1) & 7;
-    int koff[NKS];
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) koff[ks] = ((4 * ks + lg) ^ sw) * 16;
-    int xread = (wt * BR * TB + lr) * ROWB;
-    int wread = kWBase + (wf * BR * FB + lr) * ROWB;
+    // (one register for both operands and slices: slice 1 differs in bit 6, the wavefront's first row is uniform)
+    int lane_read = lr * ROWB + (lg ^ sw) * 16;
+    const uint32_t xread = wt * BR * TB * ROWB, wread = kWBase + wf * BR * FB * ROWB;
 
     f32x4 acc[FB][TB];
 #pragma unroll
@@ -195,34 +193,38 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
             for (int r = 0; r < 4; ++r) acc[fb][tb][r] = 0.f;
 
     // Operand fragments.  A slice (32 contraction indices) takes FB fragments of w and TB of x and feeds
-    // FB x TB MFMAs, walked token block by token block.  The w fragments are double-buffered and requested
-    // a slice ahead; an x fragment is used by the FB MFMAs of its token block and refilled IN PLACE one
-    // block later (an LDS return into registers whose MFMAs have issued is safe), so only one set is held.
+    // FB x TB MFMAs, walked by pairs of token blocks, both blocks of a pair on one w fragment before the next: of the
+    // orders a power-limited MFMA loop was timed in (random operands), the A operand held for two products draws least
+    // (1,938 TFLOP/s; B held for four or eight 1,887; neither 1,880).  Block by block, w fragment by w fragment, 32,760 x
+    // 5,120 x 5,120 took 1,189 us, in pairs 1,180.
+    // The w fragments are double-buffered and requested
+    // a slice ahead; the x fragments of a pair are refilled IN PLACE during the next
+    // pair (an LDS return into registers whose MFMAs have issued is safe), so only one set is held.
     // The reads are inline assembly so that the waits can be counted: LDS returns in order, and the number
-    // of reads issued behind the one a block needs is a constant of the block's place in the step, so a
-    // fragment is asked for 5 to 10 reads (2 to 9 token blocks) before its use.  The compiler itself waits
+    // of reads issued behind the ones a pair needs is a constant of the pair's place in the slice, so a
+    // fragment is asked for 4 to 8 reads before its use.  The compiler itself waits
     // for LDS reads with lgkmcnt(0), which would drain that queue at every use.
     //
-    // Everything that is not an MFMA -- one or two LDS reads, at most one load, their address arithmetic --
-    // is placed BETWEEN the four MFMAs of a token block (scheduling barriers pin the order), so that it
-    // issues while the matrix pipe works on the MFMA in front of it: a wavefront issues in order, and four
+    // Everything that is not an MFMA -- one or two LDS reads, at most two loads, their address arithmetic --
+    // is placed BETWEEN the eight MFMAs of a pair (scheduling barriers pin the order), so that it
+    // issues while the matrix pipe works on the MFMA in front of it: a wavefront issues in order, and
     // MFMAs back to back followed by the rest leave the pipe idle for as long as the rest takes to issue.
     u32x4 W[2][FB], X[TB];
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
     auto read_w = [&](u32x4& w, auto fb, int buf, int ks) __attribute__((always_inline)) {
-        const uint32_t wa = lds0 + buf * kLinTileBytes + wread + koff[ks];
+        const uint32_t wa = (lane_read ^ (ks * 64)) + (lds0 + buf * kLinTileBytes + wread);
         asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(w) : "v"(wa), "n"(decltype(fb)::value * BR * ROWB));
     };
     auto read_x = [&](u32x4& x, auto tb, int buf, int ks) __attribute__((always_inline)) {
-        const uint32_t xa = lds0 + buf * kLinTileBytes + xread + koff[ks];
+        const uint32_t xa = (lane_read ^ (ks * 64)) + (lds0 + buf * kLinTileBytes + xread);
         asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(x) : "v"(xa), "n"(decltype(tb)::value * BR * ROWB));
     };
-    // The barrier that opens step k sits in the last slice of step k-1, in its second token block: by then
+    // The barrier that opens step k sits in the last slice of step k-1, in its first pair: by then
     // every wavefront has asked for all fragments of step k-1 (the wait in front of the barrier completes
     // the reads), so behind it the buffers of step k-1 may be refilled and the tiles of step k, which the loading
     // wavefronts have waited for, may be read.  The loads of one barrier period go out between the MFMAs:
-    // the w tile of step k+1 in the first four blocks behind the barrier (two chunks a block), the x tile
-    // of step k+2 one chunk a block in the first slice of the next step.  The counted wait in front of the
+    // the w tile of step k+1 in the first three pairs, the x tile
+    // of step k+2 one chunk a token block in the first slice of the next step.  The counted wait in front of the
     // barrier leaves exactly that youngest x tile in flight.
     // (the bare barrier instruction: __syncthreads() is a fence too, for which the compiler drains every
     // load in flight -- vmcnt(0) -- in front of the barrier, and the x tile that is meant to stay in
@@ -558,7 +560,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     next_load_step();
     int xb = 0, wb = 0;  // buffers of the step being multiplied
     static_for<0, FB>([&](auto fb) { read_w(W[0][decltype(fb)::value], fb, wb, 0); });
-    static_for<0, TB - 1>([&](auto tb) { read_x(X[decltype(tb)::value], tb, xb, 0); });
+    static_for<0, TB - 2>([&](auto tb) { read_x(X[decltype(tb)::value], tb, xb, 0); });
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     int tile = 0, kt = 0;  // the step being multiplied
     int tm, tn;
@@ -569,59 +571,56 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     for (int step = 0; step < nsteps; ++step) {
         const int xb_next = xb + 1 == SX ? 0 : xb + 1, wb_next = wb ^ 1;
         const int xb_prev = xb == 0 ? SX - 1 : xb - 1;
-        auto block = [&](auto ksc, auto tbc) __attribute__((always_inline)) {
-            constexpr int ks = decltype(ksc)::value, T = decltype(tbc)::value;
+        // two token blocks, T and T + 1, MFMA m: feature block m / 2, token block T + m % 2
+        auto pair = [&](auto ksc, auto pc) __attribute__((always_inline)) {
+            constexpr int ks = decltype(ksc)::value, P = decltype(pc)::value, T = 2 * P;
             constexpr bool last = ks + 1 == NKS;
             constexpr int cur = ks & 1, nxt = cur ^ 1;
             // fragments of the next slice come from this step's buffers, or from the next step's
             const int nxb = last ? xb_next : xb, nwb = last ? wb_next : wb;
             constexpr int nks = last ? 0 : ks + 1;
-            // reads issued behind the youngest fragment this block needs (its x fragment; in the first
-            // block of a slice the slice's last w fragment), from the issue order below
-            constexpr int YOUNGER = last ? (T < 2 ? 6 : T == 2 ? 8 : 10) : (T == 0 ? 5 : 10);
-            if constexpr (T == 0) {
-                asm volatile("s_waitcnt lgkmcnt(%5)"
-                             : "+v"(W[cur][0]), "+v"(W[cur][1]), "+v"(W[cur][2]), "+v"(W[cur][3]), "+v"(X[T])
-                             : "n"(YOUNGER));
+            // reads issued behind the youngest fragment this pair needs (its second x fragment), from the issue order
+            // below: the x fragments of the pairs behind it and, from the second pair on, the next slice's w fragments
+            if constexpr (P == 0) {
+                asm volatile("s_waitcnt lgkmcnt(4)"
+                             : "+v"(W[cur][0]), "+v"(W[cur][1]), "+v"(W[cur][2]), "+v"(W[cur][3]), "+v"(X[T]), "+v"(X[T + 1]));
             } else {
-                asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(X[T]) : "n"(YOUNGER));
+                asm volatile("s_waitcnt lgkmcnt(8)" : "+v"(X[T]), "+v"(X[T + 1]));
             }
-            acc[0][T] = mfma16<OP_BF16>(W[cur][0], X[T], acc[0][T]);
-            __builtin_amdgcn_sched_barrier(0);
-            // (after the last step the loads and reads behind this barrier go to buffers nobody uses:
-            // uniform control flow)
-            if constexpr (last && T == 1) sync_point();
-            // the x fragment of the block before: its MFMAs have issued
-            if constexpr (T == 0) read_x(X[TB - 1], std::integral_constant<int, TB - 1>(), xb, ks);
-            else read_x(X[T - 1], std::integral_constant<int, T - 1>(), nxb, nks);
-            __builtin_amdgcn_sched_barrier(0);
-            acc[1][T] = mfma16<OP_BF16>(W[cur][1], X[T], acc[1][T]);
-            __builtin_amdgcn_sched_barrier(0);
-            // this block's share of the loads (q = token blocks since the barrier); both tiles are those
-            // of the step two ahead
-            // (the w tile, needed a step from now, two chunks a block; the x tile, needed two steps from now, one)
-            constexpr int q = last ? T - 1 : TB - 1 + T;
-            if constexpr (LOADS && q >= 0 && 2 * q < NCH) {
-                dma_w_chunk(wb, 2 * q);
-                dma_w_chunk(wb, 2 * q + 1);
-            } else if constexpr (LOADS && q >= TB - 1 && q - (TB - 1) < NCH) {
-                dma_x_chunk(xb_prev, q - (TB - 1));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            acc[2][T] = mfma16<OP_BF16>(W[cur][2], X[T], acc[2][T]);
-            __builtin_amdgcn_sched_barrier(0);
-            // the next slice's w fragments, two per block (behind the barrier in the last slice)
-            constexpr int wi = last ? T - 1 : T;
-            if constexpr (wi == 0 || wi == 1) {
-                read_w(W[nxt][2 * wi], std::integral_constant<int, 2 * wi>(), nwb, nks);
-                read_w(W[nxt][2 * wi + 1], std::integral_constant<int, 2 * wi + 1>(), nwb, nks);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            acc[3][T] = mfma16<OP_BF16>(W[cur][3], X[T], acc[3][T]);
-            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, 2 * FB>([&](auto mc) __attribute__((always_inline)) {
+                constexpr int m = decltype(mc)::value, fb = m >> 1, tb = T + (m & 1);
+                acc[fb][tb] = mfma16<OP_BF16>(W[cur][fb], X[tb], acc[fb][tb]);
+                __builtin_amdgcn_sched_barrier(0);
+                // the x fragments of the pair before: their MFMAs have issued
+                if constexpr (m < 2) {
+                    if constexpr (P == 0) read_x(X[TB - 2 + m], std::integral_constant<int, TB - 2 + m>(), xb, ks);
+                    else read_x(X[T - 2 + m], std::integral_constant<int, T - 2 + m>(), nxb, nks);
+                }
+                // (after the last step the loads and reads behind this barrier go to buffers nobody uses:
+                // uniform control flow)
+                if constexpr (last && P == 0 && m == 4) sync_point();
+                // the next slice's w fragments, two at a time (behind the barrier in the last slice)
+                if constexpr (P == 0 && (m == 4 || m == 6)) {
+                    constexpr int wi = m - 4;
+                    read_w(W[nxt][wi], std::integral_constant<int, wi>(), nwb, nks);
+                    read_w(W[nxt][wi + 1], std::integral_constant<int, wi + 1>(), nwb, nks);
+                }
+                // the loads (the w tile, needed a step from now, two chunks a token block behind the barrier; the x tile,
+                // needed two steps from now, one a token block of the next slice)
+                if constexpr (LOADS && (m == 3 || m == 5)) {
+                    constexpr int q = 2 * P + (m == 5) - 1;  // token blocks since the barrier
+                    if constexpr (last && q >= 0 && 2 * q < NCH) {
+                        dma_w_chunk(wb, 2 * q);
+                        dma_w_chunk(wb, 2 * q + 1);
+                    } else if constexpr (!last) {
+                        dma_x_chunk(xb_prev, q + 1);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
         };
         static_for<0, NKS>([&](auto ksc) __attribute__((always_inline)) {
-            static_for<0, TB>([&](auto tbc) __attribute__((always_inline)) { block(ksc, tbc); });
+            static_for<0, TB / 2>([&](auto pc) __attribute__((always_inline)) { pair(ksc, pc); });
         });
         xb = xb_next;
         wb = wb_next;
@@ -638,10 +637,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
                 int l = lane;
                 asm volatile("" : "+v"(l));
                 const int r = l & 15, g = l >> 4;
-#pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) koff[ks] = ((4 * ks + g) ^ ((r >> 1) & 7)) * 16;
-                xread = (wt * BR * TB + r) * ROWB;
-                wread = kWBase + (wf * BR * FB + r) * ROWB;
+                lane_read = r * ROWB + (g ^ ((r >> 1) & 7)) * 16;
             }
             kt = 0;
             tile_coords(++tile, tm, tn);
