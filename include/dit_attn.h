@@ -31,6 +31,9 @@
  *    in pieces along the keys; which ones depends on the number of tiles of the whole call, so the bits of a row (not
  *    its error against the definition) may then differ with the batch size, the number of heads, the other packed
  *    requests (their grids, not their order or values) and with whether the workspace has room for the pieces.
+ *    Likewise a short sequence of a small enough call (default operand types, neither workgroup-size flag) is computed
+ *    by one launch that divides its keys among the wavefronts of a workgroup, unless the bytes between the first and
+ *    the last element of out meet those of k or v (which are then packed before the first row of out is written).
  *  - Arithmetic: inputs bf16 (or fp32), q and k rotated and scaled in fp32, then rounded
  *    once (nearest-even) to the 16-bit MFMA operand type chosen by `flags`; scores,
  *    softmax statistics and the output accumulator are fp32; output bf16 or fp32.

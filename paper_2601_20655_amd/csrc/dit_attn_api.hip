@@ -100,14 +100,29 @@ bool self_attn_uses_mfma16(const Flags& fl) {
     return !fl.fused && !fl.simple && fl.qb == 1 && fl.qk_op != dit::OP_FP8 && !fl.mfma32;
 }
 
+// The one-launch kernel has the default operand types only, and asking for a workgroup size asks for the general kernel.
+bool takes_short(const Flags& fl, uint32_t flags) {
+    return self_attn_uses_mfma16(fl) && fl.qk_op == dit::OP_F16 && fl.pv_op == dit::OP_F16 &&
+           !(flags & (DIT_FLAG_BIG_WORKGROUP | DIT_FLAG_SMALL_WORKGROUP));
+}
+
+// What the one-launch kernel takes besides the attention kernel's arguments.
+struct ShortCall {
+    int qb;
+    const dit::TableArgs* table;
+    const dit::NormArgs* kn;
+};
+
 // Attention kernel launch, bracketed by the caller's timing events when the hook is set.  chain16: query tiles per
 // workgroup of the chained cross-attention kernel, 0 for the other kernels.
 dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused, bool mfma16, hipStream_t s,
-                    int chain16 = 0) {
+                    int chain16 = 0, const ShortCall* sc = nullptr) {
     const bool timed = g_ev_before && g_ev_after;
     hipError_t e;
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    if (chain16) {
+    if (sc) {
+        e = dit::launch_attn_short(aa, *sc->table, *sc->kn, D, sc->qb, fl.resident, s);
+    } else if (chain16) {
         e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, chain16, s);
     } else if (aa.tile_count_a) {
         e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
@@ -147,6 +162,16 @@ bool strides_ok(const dit_strides& s, int32_t B, int32_t H, int32_t D, int64_t L
         if (!token_major && !head_major) return false;
     }
     return true;
+}
+
+// Whether the bytes from the first to the last element of two [B, L, H, D] tensors meet.
+bool overlap(const void* x, const dit_strides& sx, int32_t tx, const void* y, const dit_strides& sy, int32_t ty, int32_t B,
+             int32_t H, int32_t D, int64_t L) {
+    auto end = [&](const void* p, const dit_strides& s, int32_t t) {
+        const int64_t n = (int64_t)(B - 1) * s.batch + (L - 1) * s.token + (int64_t)(H - 1) * s.head + D;
+        return reinterpret_cast<uintptr_t>(p) + (uintptr_t)n * (t == DIT_F32 ? 4 : 2);
+    };
+    return reinterpret_cast<uintptr_t>(x) < end(y, sy, ty) && reinterpret_cast<uintptr_t>(y) < end(x, sx, tx);
 }
 
 // eps >= 0, a known mode; the channel weights are read as float4
@@ -212,6 +237,7 @@ struct SelfPlan {
     dit::SplitPlan split;
     int split_nQT;
     size_t total;
+    int short_qb;  // > 0: one launch for everything, in workgroups of 16 short_qb query rows
 };
 
 // How the self-attention kernel on 16x16x32 MFMAs is laid over the chip.  Estimates of its time in key-tile steps of an
@@ -253,6 +279,19 @@ dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int nKT, int nw) {
         }
     }
     return best;
+}
+
+// Whether a short sequence is computed in one launch (dit_attn_short.hip), in workgroups of 16 or 32 query rows (1, 2; 0: no).
+// Every workgroup makes the operands of all keys of its head, so it pays while one round of workgroups takes the call.  us a
+// call one after the other, general path and this (a launch by itself: 9.2), tokens x heads: head_dim 64, 16 rows: 60 x 40 14.3
+// and 9.3, 256 x 8 14.0 and 9.4, 413 x 8 16.6 and 11.1, 1,024 x 2 21.4 and 16.3; two rounds, 770 x 8, 20.7 and 27.0; 32 rows: 256
+// x 24 14.6 and 10.2, 512 x 12 17.0 and 12.6, 1,024 x 8 21.8 and 19.0; two rounds, 770 x 12, 21.5 and 33.4.  head_dim 128, 16
+// rows: 60 x 40 16.1 and 12.6, 256 x 8 19.7 and 15.0, 512 x 8 23.8 and 18.7, 640 x 2 25.3 and 22.9; 1,024 x 2 30.9 and 29.3 (not
+// taken); 32 rows spill there: 413 x 12 24.6 and 25.7.
+int choose_short(int64_t L, int64_t BH, int D, int table_entries) {
+    if (table_entries > dit::kShortTable || L > (D == 64 ? 1024 : 640)) return 0;
+    if (BH * ((L + 15) / 16) <= kCUs) return 1;
+    return D == 64 && BH * ((L + 31) / 32) <= kCUs ? 2 : 0;
 }
 
 dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
@@ -307,6 +346,8 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     if (pl->base == 0) pl->base = kAlign;
     pl->total = pl->base;
     pl->split = dit::SplitPlan{0, 0, 1};
+    pl->short_qb = 0;
+    if (takes_short(pl->fl, p->flags)) pl->short_qb = choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
     if (self_attn_uses_mfma16(pl->fl) && !(p->flags & DIT_FLAG_SMALL_WORKGROUP)) {
         pl->split_nQT = (int)((L + 255) / 256);
         pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H, pl->nKT, pl->fl.nw);
@@ -751,11 +792,14 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
-    st = setup_rows(pl.fl.resident ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
+    const bool one = pl.short_qb > 0 &&
+                     (pl.fl.resident || (!overlap(out, p->so, p->out_dtype, k, p->sk, p->in_dtype, p->B, p->H, p->D, pl.L) &&
+                                         !overlap(out, p->so, p->out_dtype, v, p->sv, p->in_dtype, p->B, p->H, p->D, pl.L)));
+    st = setup_rows(pl.fl.resident || one ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
                     p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
-    if (!pl.fl.fused && !pl.fl.resident) {
+    if (!pl.fl.fused && !pl.fl.resident && !one) {
         dit::PackArgs pa;
         memset(&pa, 0, sizeof(pa));
         pa.kn = kn;
@@ -789,6 +833,11 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     aa.rg = rg;
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
+    if (one) {
+        aa.nQT = (int)((pl.L + 16 * pl.short_qb - 1) / (16 * pl.short_qb));
+        const ShortCall sc{pl.short_qb, &ta, &kn};
+        return run_attn(aa, p->D, pl.fl, false, true, s, 0, &sc);
+    }
     apply_split(&pl, p->D, ws, workspace_bytes, &aa);
     return run_attn(aa, p->D, pl.fl, pl.fl.fused, self_attn_uses_mfma16(pl.fl), s);
 }
@@ -930,6 +979,24 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return DIT_ERR_ALIGNMENT;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.base)
         return DIT_ERR_WORKSPACE;
+
+    // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit; a short one goes there
+    if (pl.vt.n == 1 && takes_short(pl.fl, p->flags) && choose_short(pl.vt.total_tokens, p->H, p->D, pl.table_entries) > 0) {
+        dit_self_attn_params one;
+        memset(&one, 0, sizeof(one));
+        one.B = 1; one.H = p->H; one.D = p->D;
+        one.T = p->grids[0].T; one.Hg = p->grids[0].Hg; one.Wg = p->grids[0].Wg;
+        one.t0 = p->t0; one.h0 = p->h0; one.w0 = p->w0;
+        one.d_t = p->d_t; one.d_h = p->d_h; one.d_w = p->d_w;
+        one.rope_base = p->rope_base; one.scale = p->scale;
+        one.in_dtype = p->in_dtype; one.out_dtype = p->out_dtype; one.flags = p->flags;
+        one.sq = p->sq; one.sk = p->sk; one.sv = p->sv; one.so = p->so;
+        one.sq.batch = one.sk.batch = one.sv.batch = one.so.batch = 0;
+        one.norm = p->norm;
+        SelfPlan sp;
+        if (plan_self(&one, &sp) == DIT_OK && workspace_bytes >= sp.base)  // (rows that overlap are refused there, not here)
+            return dit_attn_forward(q, k, v, out, lse, &one, workspace, workspace_bytes, stream);
+    }
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);

@@ -12,29 +12,6 @@
 
 namespace dit {
 
-// angle = position * base^(-2i/d_a), d_a = 2 * hd.  base^x = 2^(x log2(base)), the exponent in two parts (log2(base) is,
-// and the product's rounding is kept): as exact as pow() for every base and position that is accepted, and it and the
-// joint sine and cosine are a third of the dependent fp64 instructions of pow(), cos() and sin() -- a table is a few
-// hundred to a few thousand entries, so the time is a launch and one thread's latency: 2.8 -> 2.4 us for 212 entries.
-// (In one part the error of the power grows with |x log2(base)|: base 1e-10 at positions 3 to 7 gave four times the
-// error that the last bits of the power and of the product with the position allow.)
-__device__ __forceinline__ void rope_entry(const TableArgs& a, int idx) {
-    if (idx >= a.total) return;
-    int ax = 0;
-    if (idx >= a.rg.off[2]) ax = 2;
-    else if (idx >= a.rg.off[1]) ax = 1;
-    const int local = idx - a.rg.off[ax];
-    const int hd = a.rg.hd[ax];
-    const int p = local / hd, i = local - p * hd;
-    const double x = -(double)i / (double)hd;
-    const double t = x * a.log2_base, rest = fma(x, a.log2_base, -t) + x * a.log2_base_lo;
-    const double y = exp2(t);
-    const double phi = (double)(a.origin[ax] + p) * fma(y, rest * 0.6931471805599453, y);
-    double sn, cs;
-    sincos(phi, &sn, &cs);
-    a.tab[idx] = make_float2((float)cs, (float)sn);
-}
-
 // 1/sqrt(mean of x^2 over all H*D channels + eps) of one token row, by one wavefront.  The order of the sum is fixed:
 // chunk i (16 bytes of 16-bit rows) belongs to column i % 256, the columns 64 u .. 64 u + 63 are added up pairwise by
 // the distances 1, 2, 4 .. 32, then the four sums (0 + 1) + (2 + 3); a lane holds one column of each u.
@@ -82,7 +59,10 @@ __global__ void __launch_bounds__(256) row_stats_kernel(const TableArgs t, const
                                                         int table_blocks, int q_blocks) {
     const int blk = blockIdx.x;
     const int wave = threadIdx.x >> 6;
-    if (blk < table_blocks) rope_entry(t, blk * 256 + threadIdx.x);
+    if (blk < table_blocks) {
+        const int i = blk * 256 + threadIdx.x;
+        if (i < t.total) t.tab[i] = rope_entry(t, i);
+    }
     else if (blk < table_blocks + q_blocks) token_rstd(q, (int64_t)(blk - table_blocks) * 4 + wave);
     else token_rstd(k, (int64_t)(blk - table_blocks - q_blocks) * 4 + wave);
 }
