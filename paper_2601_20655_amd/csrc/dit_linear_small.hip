@@ -177,7 +177,8 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    // ---- store: 16 token rows at a time through an area of the wavefront's own, so that rows leave in 16-byte pieces
+    // ---- store: 16 token rows at a time through an area of the wavefront's own, so that rows leave in 16-byte pieces, past the
+    // caches (769 x 10,240 x 5,120 72.1 -> 70.6 us on the operands of the call before, 89.4 -> 88.7 on new ones)
     constexpr int ES = OUT_F32 ? 4 : 2;
     constexpr int RB = 16 * FB * ES;  // bytes of a staged row: the wavefront's features
     constexpr int PR = RB / 16;       // pieces per row
@@ -218,7 +219,7 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
             // N is a multiple of 8: a piece of a row is inside or outside as a whole
             if ((NP >= 64 || p < NP) && m < a.M && n < a.N) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(area + r * RB + slot(r, c) * 16);
-                *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES) = v;
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES));
             }
         }
         asm volatile("" ::: "memory");
