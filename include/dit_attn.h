@@ -96,7 +96,8 @@ enum {
     DIT_FLAG_SIMPLE_SCHEDULE = 1u << 7,
     /* Workgroup size of the pipelined self-attention kernel.  BIG: 8 wavefronts, 256 query rows
      * share each K/V tile in LDS (half the L2 -> LDS tile traffic).  SMALL: 4 wavefronts, 128
-     * rows, two workgroups per CU.  Neither flag: the one whose rounds of workgroups fill the chip
+     * rows, two workgroups per CU (reshaped, with the same results bit for bit, where there are so few that each has a
+     * compute unit to itself).  Neither flag: the one whose rounds of workgroups fill the chip
      * better; dit_attn_forward and dit_attn_varlen_forward may then (or with BIG) also compute the query tiles
      * of a partly filled last round, or of whole requests, in pieces along the keys.  SMALL: never in pieces. */
     DIT_FLAG_BIG_WORKGROUP = 1u << 8,

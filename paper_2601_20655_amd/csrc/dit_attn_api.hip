@@ -245,26 +245,31 @@ struct SelfPlan {
 // 21 shapes of 320 to 75,600 tokens and 2 to 40 heads, both head dimensions:
 //   - a workgroup's start and end cost 7.5 steps, the end of a piece one more;
 //   - with 4 wavefronts (128 rows) a compute unit holds two workgroups, which together take 1.04 of the 8-wavefront
-//     step; one alone takes 0.83 of it;
+//     step; one alone takes 0.83 of it; where all of them together are one round, in 16 rows a wavefront (short_tile_rows),
+//     0.58 + 0.001 a workgroup (1,600 x 3: 0.61, 1,600 x 9: 0.68, 6,240 x 4: 0.73, 1,600 x 19: 0.84), and in 64-row tiles 0.59;
 //   - combining P pieces costs a launch and 2 x 256 rows of fp32 each: 3 + 0.037 P steps.
 // The measured order of the forms follows these numbers wherever they are more than a few per cent apart: e.g. (tokens,
 // heads) 3,600 x 3: 62.7 us in whole tiles, 40.1 in 5 pieces each; 6,240 x 4: 101.8 and 86.6 (2 pieces); 3,600 x 40:
 // 262 and 258 (last 88 of 600 tiles in 2 pieces); 75,600 x 2: 5,294 and 4,395 (last 80 of 592 in 3 pieces); level or
 // slower in pieces, and left whole: 1,560 x 12 (33.1 and 37.2), 6,307 x 20 (336 and 357), 20,280 x 3 (497 and 518).
-constexpr int kCUs = 256;  // compute units of the chip (workspace sizes go by them, whatever device is current, if any)
+using dit::kCUs;
 constexpr double kEnds = 7.5;
 constexpr int kMaxPieces = 1024;  // 136.3 MB of workspace at head_dim 128
 
-double whole_tile_steps(int64_t tiles, int nKT, int nw) {  // tiles of 32 nw query rows
+// tiles of 32 nw query rows; tiles64: of 64
+double whole_tile_steps(int64_t tiles, int64_t tiles64, int nKT, int nw) {
     if (nw == 8) return (double)((tiles + kCUs - 1) / kCUs) * (nKT + kEnds);
+    if (tiles <= kCUs) return (nKT + kEnds) * (tiles64 <= kCUs ? 0.59 : 0.58 + 0.001 * tiles);
     const int64_t pairs = tiles / (2 * kCUs), rest = tiles - pairs * 2 * kCUs;
     return (nKT + kEnds) * (1.04 * pairs + (rest == 0 ? 0.0 : rest <= kCUs ? 0.83 : 1.04));
 }
 
-// nw: the form that runs the tiles whole; tiles, tiles_nw: query tiles of 256 and of 32 nw rows
-dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int nKT, int nw) {
+// nw: the form that runs the tiles whole; tiles, tiles_nw, tiles64: query tiles of 256, of 32 nw and of 64 rows
+dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int64_t tiles64, int nKT, int nw) {
     dit::SplitPlan best{0, 0, 1};
-    double best_steps = 0.97 * whole_tile_steps(tiles_nw, nKT, nw);
+    // (tiles of 16 rows a wavefront do a little better than their estimate: 3,600 x 8 whole 72.9, in pieces 80.1 at 0.93 of it;
+    // 3,600 x 4 59.8 and 55.5 at 0.91)
+    double best_steps = (nw == 4 && tiles_nw <= kCUs ? 0.92 : 0.97) * whole_tile_steps(tiles_nw, tiles64, nKT, nw);
     const int64_t rounds = tiles / kCUs;
     if (tiles % kCUs == 0 || tiles > (1 << 20)) return best;
     for (int64_t r = rounds; r >= 0 && r >= rounds - 1; --r) {  // rounds of whole tiles
@@ -283,13 +288,13 @@ dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int nKT, int nw) {
 
 // Whether a short sequence is computed in one launch (dit_attn_short.hip), in workgroups of 16 or 32 query rows (1, 2; 0: no).
 // Every workgroup makes the operands of all keys of its head, so it pays while one round of workgroups takes the call.  us a
-// call one after the other, general path and this (a launch by itself: 9.2), tokens x heads: head_dim 64, 16 rows: 60 x 40 14.3
-// and 9.3, 256 x 8 14.0 and 9.4, 413 x 8 16.6 and 11.1, 1,024 x 2 21.4 and 16.3; two rounds, 770 x 8, 20.7 and 27.0; 32 rows: 256
-// x 24 14.6 and 10.2, 512 x 12 17.0 and 12.6, 1,024 x 8 21.8 and 19.0; two rounds, 770 x 12, 21.5 and 33.4.  head_dim 128, 16
-// rows: 60 x 40 16.1 and 12.6, 256 x 8 19.7 and 15.0, 512 x 8 23.8 and 18.7, 640 x 2 25.3 and 22.9; 1,024 x 2 30.9 and 29.3 (not
-// taken); 32 rows spill there: 413 x 12 24.6 and 25.7.
+// call one after the other, general path and this (a launch by itself: 9.2), tokens x heads: head_dim 64, 16 rows: 64 x 40 13.7
+// and 9.3, 413 x 8 14.0 and 11.5, 512 x 2 14.3 and 11.0, 1,020 x 4 18.6 and 16.4; two rounds, 770 x 8, 20.7 and 27.0; 32 rows: 256
+// x 20 13.8 and 10.6, 640 x 10 16.0 and 15.4; two rounds, 770 x 12, 21.5 and 33.4.  head_dim 128, 16
+// rows: 64 x 40 14.8 and 12.6, 256 x 8 17.6 and 15.0; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not
+// taken); 32 rows spill there: 413 x 12 25.7.
 int choose_short(int64_t L, int64_t BH, int D, int table_entries) {
-    if (table_entries > dit::kShortTable || L > (D == 64 ? 1024 : 640)) return 0;
+    if (table_entries > dit::kShortTable || L > (D == 64 ? 1024 : 384)) return 0;
     if (BH * ((L + 15) / 16) <= kCUs) return 1;
     return D == 64 && BH * ((L + 31) / 32) <= kCUs ? 2 : 0;
 }
@@ -328,8 +333,9 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
         pl->fl.nw = 4;  // only the pipelined 32-rows-per-wavefront kernel has the 8-wavefront form
     } else if (pl->fl.nw == 0) {
         const int64_t t8 = ((L + 255) / 256) * p->B * p->H, t4 = ((L + 127) / 128) * p->B * p->H;
+        const int64_t t64 = ((L + 63) / 64) * p->B * p->H;
         if (self_attn_uses_mfma16(pl->fl))
-            pl->fl.nw = whole_tile_steps(t8, pl->nKT, 8) <= whole_tile_steps(t4, pl->nKT, 4) ? 8 : 4;
+            pl->fl.nw = whole_tile_steps(t8, t64, pl->nKT, 8) <= whole_tile_steps(t4, t64, pl->nKT, 4) ? 8 : 4;
         else  // 8 wavefronts when 256-row workgroups still cover the 256 CUs at least twice over
             pl->fl.nw = t8 >= 512 ? 8 : 4;
     }
@@ -350,7 +356,8 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     if (takes_short(pl->fl, p->flags)) pl->short_qb = choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
     if (self_attn_uses_mfma16(pl->fl) && !(p->flags & DIT_FLAG_SMALL_WORKGROUP)) {
         pl->split_nQT = (int)((L + 255) / 256);
-        pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H, pl->nKT, pl->fl.nw);
+        pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H,
+                                 ((L + 63) / 64) * p->B * p->H, pl->nKT, pl->fl.nw);
         if (pl->split.n_tail > 0)
             pl->total = pl->base + round_up(dit::part_o_bytes((int64_t)pl->split.n_tail * pl->split.n_piece, p->D), kAlign) +
                         round_up(dit::part_ml_bytes((int64_t)pl->split.n_tail * pl->split.n_piece), kAlign);
@@ -448,7 +455,8 @@ void choose_packed(const dit::VarlenTable& vt, int H, uint32_t flags, int* nw, i
     const double t8 = work_off(c8, vt.n, kCUs);
     double half4 = 0.0;  // from here on at most one workgroup per compute unit is left
     const double all4 = work_off(c4, vt.n, 2 * kCUs, &half4);
-    const double t4 = 1.04 * half4 + 0.83 * (all4 - half4);
+    // (packed requests are not cut into 64-row tiles)
+    const double t4 = n4 <= kCUs ? (0.58 + 0.001 * n4) * all4 : 1.04 * half4 + 0.83 * (all4 - half4);
     if (*nw == 0) *nw = t8 <= t4 ? 8 : 4;
     if (flags & DIT_FLAG_SMALL_WORKGROUP) return;
     double best = 0.97 * (*nw == 8 ? t8 : t4);
@@ -562,10 +570,10 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
         if (pl->fl.nw == 0) pl->fl.nw = big_blocks >= 512 ? 8 : 4;
     } else if (n == 1) {
         // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit
-        const int64_t t8 = ((total + 255) / 256) * p->H, t4 = ((total + 127) / 128) * p->H;
+        const int64_t t8 = ((total + 255) / 256) * p->H, t4 = ((total + 127) / 128) * p->H, t64 = ((total + 63) / 64) * p->H;
         const int nKT = vt.r[0].nKT;
-        if (pl->fl.nw == 0) pl->fl.nw = whole_tile_steps(t8, nKT, 8) <= whole_tile_steps(t4, nKT, 4) ? 8 : 4;
-        if (!(p->flags & DIT_FLAG_SMALL_WORKGROUP)) pl->single = choose_split(t8, pl->fl.nw == 8 ? t8 : t4, nKT, pl->fl.nw);
+        if (pl->fl.nw == 0) pl->fl.nw = whole_tile_steps(t8, t64, nKT, 8) <= whole_tile_steps(t4, t64, nKT, 4) ? 8 : 4;
+        if (!(p->flags & DIT_FLAG_SMALL_WORKGROUP)) pl->single = choose_split(t8, pl->fl.nw == 8 ? t8 : t4, t64, nKT, pl->fl.nw);
     } else {
         choose_packed(vt, p->H, p->flags, &pl->fl.nw, pieces);
     }

@@ -58,8 +58,15 @@ __device__ __forceinline__ float sum_across_rows16(float x) {
     return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
-// NW = wavefronts per workgroup (4 or 8); a wavefront owns 32 query rows (two blocks of 16), the workgroup's
+// NW = wavefronts per workgroup (4 or 8); a wavefront owns QBN = 2 blocks of 16 query rows, the workgroup's
 // NW * 32 rows share every K/V tile in LDS.
+// QBN = 1: 16 rows a wavefront, for calls whose tiles all fit one round (short_tile_rows).  A fragment read from LDS then
+// feeds one MFMA instead of two, which a full chip pays for (14,040 x 12 1,040 -> 1,340 us); but where compute units have
+// one workgroup each, what counts is how long its steps take: 128 rows by 8 wavefronts, two a SIMD under each other's
+// latencies, instead of 4; 64 rows by 4 where even those fill at most half of the chip.  Whole calls, us, 4 x 32 rows, 8 x 16, 4 x 16,
+// (tokens, heads) head_dim 128: 1,600 x 9 44.1, 38.0, 35.5; 640 x 20 29.3, 26.4, 24.2; 1,020 x 12 34.3, 30.0, 28.2; 640 x 40 33.9,
+// 29.9, (two rounds) 33.0; 3,600 x 8 75.5, 69.7, (79.3); head_dim 64: 1,600 x 9 29.5, 25.9, 25.1; 3,600 x 8 51.1, 44.0.  The same
+// bits in all three.
 // The chained form keeps, behind the tile buffers, one area per wavefront the size of its 32 query rows in 16
 // bits.  The rows of the NEXT query tile are copied into it (global -> LDS) while the current one is in its loop;
 // at the boundary they are converted into operand registers, and the area then serves as the staging area of the
@@ -106,17 +113,19 @@ constexpr int kOnce = 2;
 // form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
 // and loads 337) and the second pass's first maxima: 24,000 clocks a query tile and 2,690 a key tile.  585 -> 489 us at
 // 32,760 queries x 40 heads, 5 + 5 key tiles, resident keys (plain kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
-template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false>
+template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false, int QBN = 2>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
     constexpr int NKS = D / 32;        // MFMAs of one score chain
     constexpr int NCB = D / 16;        // 16-channel blocks of the output
     constexpr int NKF = 4 * NKS;       // K' fragments of a tile: (ks, kb), each feeds the two query blocks
     constexpr int NVF = 2 * NCB;       // V^T fragments of a tile: (m, cb)
-    constexpr int BQ = NW * 32;
+    constexpr int WR = 16 * QBN;  // query rows of a wavefront
+    constexpr int BQ = NW * WR;
     constexpr int NI = G::PART_KIB / NW;  // full rounds of wavefront-wide 1 KiB loads per tile part
     static_assert(G::PART_KIB - NW * NI == 2, "two odd pieces per tile part");
     static_assert(QK_OP != OP_FP8, "16-bit score operands only");
+    static_assert(QBN == 2 || (!CHAIN && !PIECES), "one query block a wavefront: whole tiles of self-attention");
     static_assert(!TWO || (CHAIN && D == 128 && QK_OP == OP_F16 && PV_OP == OP_F16),
                   "a pass takes its first maxima as they are: finite scores only; its row sums are those of unrounded probabilities");
 
@@ -139,7 +148,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     rg.Hg = pv.Hg;
     rg.Wg = pv.Wg;
 
-    u32x4 Qf[2][NKS];
+    u32x4 Qf[QBN][NKS];
     uint8_t* const qarea = smem + (2 + VST) * G::K_BYTES + wave * chain_stage_bytes<D>();  // STAGED only
     constexpr int QPR = D / 8;  // 16-byte pieces per 16-bit query row
     // chained form: this wavefront's 32 rows of query tile `qtile` -> its area, piece p of row r in slot
@@ -159,7 +168,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #pragma unroll
         for (int k = 0; k < 32 * QPR / 64; ++k) {
             const int r = k * (64 / QPR) + ln / QPR, slot = ln % QPR;
-            const int row = qtile * BQ + wave * 32 + r;
+            const int row = qtile * BQ + wave * WR + r;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
             const uint16_t* src = q + (int64_t)qr * a.sq_t + 8 * (slot ^ (r & (QPR - 1)));
             __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, kOnce);
@@ -236,14 +245,14 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 
     // ---- running state ----
     constexpr int NOG = NCB / 4;  // output blocks of 64 channels: quarter cb % 4 of O[cb / 4]
-    f32x16 O[NOG][2];
-    f32x4 negm[2];  // every element = -m_run: the accumulator a score MFMA chain starts from
-    float m_run[2], l_run[2];
+    f32x16 O[NOG][QBN];
+    f32x4 negm[QBN];  // every element = -m_run: the accumulator a score MFMA chain starts from
+    float m_run[QBN], l_run[QBN];
     constexpr bool EMPTY_ROWS = PIECES && QK_OP == OP_BF16;
     float empty_thr[2] = {kRescaleThr, kRescaleThr};  // EMPTY_ROWS: -inf while the row is empty
     auto reset_state = [&]() {
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             m_run[qb] = 0.f;
             l_run[qb] = 0.f;
 #pragma unroll
@@ -270,22 +279,22 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     };
 
     // S^T of one tile from zero (first tile only): S[qb][4 kb + r] = score of key 16 kb + 4 g + r
-    auto qk_tile = [&](f32x16 (&S)[2], int buf) {
+    auto qk_tile = [&](f32x16 (&S)[QBN], int buf) {
         const uint8_t* kt = kbuf + buf * G::K_BYTES + kread_off;
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) S[qb][r] = 0.f;
 #pragma unroll
         for (int f = 0; f < NKF; ++f) {
             const u32x4 ka = k_operand(kt, f);
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) S[qb] = mfma16_q<QK_OP>(ka, Qf[qb][f >> 2], S[qb], f & 3);
+            for (int qb = 0; qb < QBN; ++qb) S[qb] = mfma16_q<QK_OP>(ka, Qf[qb][f >> 2], S[qb], f & 3);
         }
     };
 
     // keys whose mask bit is clear leave the softmax; element 4 kb + r is key 16 kb + 4 g + r of the tile
-    auto mask_apply = [&](f32x16 (&S)[2], uint64_t mask) {
+    auto mask_apply = [&](f32x16 (&S)[QBN], uint64_t mask) {
         const uint64_t mlane = mask >> (4 * g4);
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
@@ -293,15 +302,15 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             for (int r = 0; r < 4; ++r) {
                 const bool ok = (mlane >> (16 * kb + r)) & 1ull;
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) S[qb][4 * kb + r] = ok ? S[qb][4 * kb + r] : -INFINITY;
+                for (int qb = 0; qb < QBN; ++qb) S[qb][4 * kb + r] = ok ? S[qb][4 * kb + r] : -INFINITY;
             }
     };
 
     // Row maxima of a score tile (relative to m_run once the loop runs), over all four lanes of a row.
-    float mx_new[2];
-    auto row_max = [&](const f32x16 (&S)[2]) {
+    float mx_new[QBN];
+    auto row_max = [&](const f32x16 (&S)[QBN]) {
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             float mx = S[qb][0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S[qb][r]);
@@ -321,11 +330,11 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // such rises wherever it starts, so the forms with pieces, and the chained one, shift by all of it past there, on
     // fp32 MFMAs (an all-ones A operand, -shift in the first contraction slot of B): level in both, while the whole-tile
     // forms, which keep their key loop, took 2 to 5 % longer for what the compiler then made of it.
-    auto shift_rows = [&](f32x16 (&S)[2]) {
+    auto shift_rows = [&](f32x16 (&S)[QBN]) {
         constexpr uint32_t kOnes = QK_OP == OP_F16 ? 0x3c003c00u : 0x3f803f80u;
         const u32x4 ones = mk4(kOnes, kOnes, kOnes, kOnes);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             const float thr = EMPTY_ROWS ? empty_thr[qb] : kRescaleThr;
             const float want = mx_new[qb] > thr ? mx_new[qb] : 0.f;
             // hi + lo in the score operand type; what is applied is their exact fp32 sum
@@ -371,15 +380,16 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #define DIT_PIPE16_LA 6
 #endif
     constexpr int LA = DIT_PIPE16_LA;  // LDS fragment reads issued this many fragments ahead of their MFMAs
-    constexpr int NCH = 16;            // softmax slices: two scores -> one dword of P
-    constexpr int CPA = NCH / NKF;     // slices per K' fragment (pair of score MFMAs): 1 at d128, 2 at d64
-    constexpr int CPB = NCH / NVF;     // maxima slices per V^T fragment
+    constexpr int NCH = 8 * QBN;       // softmax slices: two scores -> one dword of P
+    // behind K' fragment f (its QBN score MFMAs) come the slices up to (f + 1) NCH / NKF: one at d128, two at d64 (half as many
+    // with one query block); the maxima behind the V^T fragments likewise
+    constexpr int CPA = (NCH + NKF - 1) / NKF;
 #ifndef DIT_PIPE16_PRE
 #define DIT_PIPE16_PRE 3
 #endif
     // exp2 of a softmax slice runs this many slices ahead of its pack (at least one fragment's worth)
     constexpr int PRE = DIT_PIPE16_PRE < CPA ? CPA : DIT_PIPE16_PRE;
-    static_assert(CPA * NKF == NCH && CPB * NVF == NCH, "slices must divide evenly over fragments");
+    
     static_assert(LA <= NKF && LA <= NVF, "lookahead too deep");
 
     const bool late = STAG && wave >= NW / 2;
@@ -406,7 +416,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // the unmasked form; the last iterations of a sequence are separate copies, so that the steady state holds
     // no conditional change of the pending scores at all.  LAST (chained): the last key tile of a query tile; Sn receives
     // the first scores of the next one, from zero, and stays as it is.
-    auto iteration = [&](auto late_tag, auto kind_tag, f32x16 (&Sc)[2], f32x16 (&Sn)[2], int j, int vs) {
+    auto iteration = [&](auto late_tag, auto kind_tag, f32x16 (&Sc)[QBN], f32x16 (&Sn)[QBN], int j, int vs) {
         constexpr bool LATE = decltype(late_tag)::value;
         constexpr bool MASKED = decltype(kind_tag)::value == 1;
         constexpr bool LAST = decltype(kind_tag)::value == 2;
@@ -424,22 +434,22 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 
         // slice c = (m, qb, w): dword w of the B operand of key group m for query block qb;
         // w < 2: scores 2w, 2w+1 of key block 2m; w >= 2: scores 2(w-2), 2(w-2)+1 of key block 2m+1
-        uint32_t Pd[2][2][4];
-        float ls[2][2];
+        uint32_t Pd[QBN][2][4];
+        float ls[QBN][2];
         constexpr bool PKSUM = PV_OP == OP_F16 && !TWO;  // row sums over the rounded pairs, packed fp16 (see attn_pipe_body)
-        f16x2 lsp[2][2];
+        f16x2 lsp[QBN][2];
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             ls[qb][0] = ls[qb][1] = 0.f;
             lsp[qb][0] = lsp[qb][1] = f16x2{(_Float16)0.f, (_Float16)0.f};
         }
         auto exp_slice = [&](int c) {
-            const int m = c / 8, qb = (c % 8) / 4, w = c % 4, e = 4 * (2 * m + (w >> 1)) + 2 * (w & 1);
+            const int m = c / (4 * QBN), qb = c / 4 % QBN, w = c % 4, e = 4 * (2 * m + (w >> 1)) + 2 * (w & 1);
             Sc[qb][e] = __builtin_amdgcn_exp2f(Sc[qb][e]);
             Sc[qb][e + 1] = __builtin_amdgcn_exp2f(Sc[qb][e + 1]);
         };
         auto pack_slice = [&](int c) {
-            const int m = c / 8, qb = (c % 8) / 4, w = c % 4, e = 4 * (2 * m + (w >> 1)) + 2 * (w & 1);
+            const int m = c / (4 * QBN), qb = c / 4 % QBN, w = c % 4, e = 4 * (2 * m + (w >> 1)) + 2 * (w & 1);
             const float e0 = Sc[qb][e], e1 = Sc[qb][e + 1];
             Pd[qb][m][w] = pack2<PV_OP>(e0, e1);
             if constexpr (PKSUM) {
@@ -463,13 +473,14 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             Sn[0] = ks == 0 ? mfma16_q_init<QK_OP>(kf[f], Qf[0][ks], negm[0], Sn[0], kb)
                             : mfma16_q<QK_OP>(kf[f], Qf[0][ks], Sn[0], kb);
 #pragma unroll
-            for (int cc = 0; cc < CPA; ++cc)
-                if (f * CPA + cc + PRE < NCH) exp_slice(f * CPA + cc + PRE);
+            for (int c = f * NCH / NKF; c < (f + 1) * NCH / NKF; ++c)
+                if (c + PRE < NCH) exp_slice(c + PRE);
             __builtin_amdgcn_sched_barrier(0);
-            Sn[1] = ks == 0 ? mfma16_q_init<QK_OP>(kf[f], Qf[1][ks], negm[1], Sn[1], kb)
-                            : mfma16_q<QK_OP>(kf[f], Qf[1][ks], Sn[1], kb);
+            if constexpr (QBN == 2)
+                Sn[QBN - 1] = ks == 0 ? mfma16_q_init<QK_OP>(kf[f], Qf[QBN - 1][ks], negm[QBN - 1], Sn[QBN - 1], kb)
+                                      : mfma16_q<QK_OP>(kf[f], Qf[QBN - 1][ks], Sn[QBN - 1], kb);
 #pragma unroll
-            for (int cc = 0; cc < CPA; ++cc) pack_slice(f * CPA + cc);
+            for (int c = f * NCH / NKF; c < (f + 1) * NCH / NKF; ++c) pack_slice(c);
             __builtin_amdgcn_sched_barrier(0);
         }
 
@@ -485,29 +496,30 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         float pm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         // slice c of the maxima: the two scores (kb, qb, r..r+1) with c = 8 kb + 4 qb + r / 2 ... any order will do
         auto max_slice = [&](int c) {
-            const int kb = c / 4, qb = (c % 4) / 2, e = 4 * kb + 2 * (c % 2);
+            const int kb = c / (2 * QBN), qb = c / 2 % QBN, e = 4 * kb + 2 * (c % 2);
             pm[c & 3] = max3(pm[c & 3], Sn[qb][e], Sn[qb][e + 1]);
         };
 #pragma unroll
         for (int v = 0; v < NVF; ++v) {
             const int m = v / NCB, cb = v % NCB;
             if (v + LA < NVF) vf[v + LA] = v_operand(vt, v + LA);
-            const u32x4 pb0 = mk4(Pd[0][m][0], Pd[0][m][1], Pd[0][m][2], Pd[0][m][3]);
-            const u32x4 pb1 = mk4(Pd[1][m][0], Pd[1][m][1], Pd[1][m][2], Pd[1][m][3]);
-            O[cb / 4][0] = mfma16_q<PV_OP>(vf[v], pb0, O[cb / 4][0], cb % 4);
+            O[cb / 4][0] = mfma16_q<PV_OP>(vf[v], mk4(Pd[0][m][0], Pd[0][m][1], Pd[0][m][2], Pd[0][m][3]), O[cb / 4][0], cb % 4);
             // the first fragment leaves the last score MFMAs time to retire
             if (v >= 1) {
 #pragma unroll
-                for (int cc = 0; cc < CPB; ++cc) max_slice((v - 1) * CPB + cc);
+                for (int c = (v - 1) * NCH / NVF; c < v * NCH / NVF; ++c) max_slice(c);
             }
             __builtin_amdgcn_sched_barrier(0);
-            O[cb / 4][1] = mfma16_q<PV_OP>(vf[v], pb1, O[cb / 4][1], cb % 4);
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (QBN == 2) {
+                const auto& P1 = Pd[QBN - 1][m];
+                O[cb / 4][QBN - 1] = mfma16_q<PV_OP>(vf[v], mk4(P1[0], P1[1], P1[2], P1[3]), O[cb / 4][QBN - 1], cb % 4);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
 #pragma unroll
-        for (int c = (NVF - 1) * CPB; c < NCH; ++c) max_slice(c);
+        for (int c = (NVF - 1) * NCH / NVF; c < NCH; ++c) max_slice(c);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             if constexpr (PKSUM) {
                 const f16x2 t2 = lsp[qb][0] + lsp[qb][1];
                 l_run[qb] += (float)t2[0] + (float)t2[1];
@@ -572,13 +584,13 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // grids level.
     auto start_q = [&](auto f32_tag) {
         constexpr bool F32 = decltype(f32_tag)::value;
-        u32x4 raw[2][NKS][F32 ? 2 : 1];
-        float2 cs[2][NKS][4];  // (cos, sin) of the lane's channel pairs at the row's position
-        float2 edge[2][2];
+        u32x4 raw[QBN][NKS][F32 ? 2 : 1];
+        float2 cs[QBN][NKS][4];  // (cos, sin) of the lane's channel pairs at the row's position
+        float2 edge[QBN][2];
         float rs[2] = {1.f, 1.f};
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            const int row = qt * BQ + wave * 32 + qb * 16 + i16;
+        for (int qb = 0; qb < QBN; ++qb) {
+            const int row = qt * BQ + wave * WR + qb * 16 + i16;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
             const int64_t base = pv.q_off + (int64_t)qr * a.sq_t + 8 * g4;
 #pragma unroll
@@ -602,9 +614,9 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             if (a.qn.mode == 2) rs[qb] = a.qn.rstd[pv.stat_off + qr];
         }
         first_tiles();
-        float x[2][NKS][8];
+        float x[QBN][NKS][8];
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 if constexpr (F32) {
@@ -617,7 +629,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         if (a.qn.mode) {
             if (a.qn.mode == 1) {  // a row's channels are read by the four lanes (i, 0..3)
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) {
+                for (int qb = 0; qb < QBN; ++qb) {
                     float ss = 0.f;
 #pragma unroll
                     for (int ks = 0; ks < NKS; ++ks)
@@ -638,7 +650,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
             }
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
@@ -653,13 +665,13 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const int h0 = rg.hd[0], h01 = rg.hd[0] + rg.hd[1];
             if (((h0 & 1) && (h0 >> 4) == ks) || ((h01 & 1) && (h01 >> 4) == ks)) {
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb)
+                for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
                     for (int pp = 0; pp < 4; pp += 2) rope_mend(rg, edge[qb], 16 * ks + 4 * g4 + pp, &cs[qb][ks][pp]);
             }
         }
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 float y[8];
@@ -695,13 +707,13 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         float rs[2] = {1.f, 1.f};
         if (a.qn.mode == 2) {
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                const int row = qtile * BQ + wave * 32 + 16 * qb + (ln & 15);
+            for (int qb = 0; qb < QBN; ++qb) {
+                const int row = qtile * BQ + wave * WR + 16 * qb + (ln & 15);
                 rs[qb] = a.qn.rstd[pv.stat_off + (row < pv.Lq ? row : pv.Lq - 1)];
             }
         } else if (a.qn.mode == 1) {
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < QBN; ++qb) {
                 float ss = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks) {
@@ -714,7 +726,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             }
         }
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 float x[8];
@@ -729,7 +741,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     // 16-byte piece 4k + g of its row, and from there into its own 16 bytes of LDS piece (qb, k)
     constexpr int NPK = D / 32;
     auto park_piece = [&](int ln, int qb, int k, bool& inside) -> uint8_t* {
-        const int row = qt * BQ + wave * 32 + 16 * qb + (ln & 15);
+        const int row = qt * BQ + wave * WR + 16 * qb + (ln & 15);
         inside = row < pv.Lq;
         const int64_t off = (int64_t)pv.b * a.so_b + (int64_t)h * a.so_h + (int64_t)(inside ? row : pv.Lq - 1) * a.so_t;
         return static_cast<uint8_t*>(a.out) + off * 2 + k * 64 + (ln >> 4) * 16;
@@ -737,7 +749,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     auto park_rows = [&]() __attribute__((always_inline)) {
         const int ln = opaque_lane();
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             const float l = sum_across_rows16(l_run[qb]);
             const float inv = l > 0.f ? 1.0f / l : 0.f;
             bool inside;
@@ -760,7 +772,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows that the area held have been read
         const int ln = opaque_lane();
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             bool inside;
             const uint8_t* const src = park_piece(ln, qb, 0, inside);  // (past the end: some row, not used)
 #pragma unroll
@@ -772,7 +784,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     if (n_steps > 0) {
         // scores of tile 0 become the first running maximum
         dma_wait_and_sync();
-        f32x16 S0[2], S1[2];
+        f32x16 S0[QBN], S1[QBN];
         qk_tile(S0, kslot(0));
         __syncthreads();  // every wavefront has read K'(0) before iteration 0 streams K'(2) over it
         if constexpr (STAG) {
@@ -781,7 +793,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         if (mask_of(0) != ~0ull) mask_apply(S0, mask_of(0));
         row_max(S0);  // finite: a sequence has at least one key
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             m_run[qb] = mx_new[qb];
             if constexpr (EMPTY_ROWS) {
                 if (mx_new[qb] == -INFINITY) {
@@ -839,12 +851,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         uint8_t* const region = qarea;
         const int ln = opaque_lane();
         const int li = ln & 15, lg = ln >> 4;
-        float inv[2];
+        float inv[QBN];
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QBN; ++qb) {
             const float l = sum_across_rows16(l_run[qb]);
             inv[qb] = l > 0.f ? 1.0f / l : 0.f;
-            const int row = qt * BQ + wave * 32 + qb * 16 + li;
+            const int row = qt * BQ + wave * WR + qb * 16 + li;
             if (a.lse && lg == 0 && row < pv.Lq) {
                 const float v = l > 0.f ? (m_run[qb] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
                 a.lse[CHAIN ? ((int64_t)pv.b * a.H + h) * a.Lq + row : pv.lse_off + row] = v;
@@ -858,8 +870,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             constexpr int RPP = STG / RB < 16 ? STG / RB : 16;  // rows per pass: at most one 16-row block
             static_assert(RPP >= 1 && 16 % RPP == 0 && PR <= 64 && 64 % PR == 0 && (RPP * RB) % 1024 == 0,
                           "staging geometry");
-            const int row0 = qt * BQ + wave * 32;
-            const bool full = row0 + 32 <= pv.Lq;  // wavefront-uniform
+            const int row0 = qt * BQ + wave * WR;
+            const bool full = row0 + WR <= pv.Lq;  // wavefront-uniform
             // the first softmax's result, zero without one: read block by block before rows are staged over it (16 staged rows
             // take only the half of the area that held theirs)
             static_assert(!TWO || RPP * RB <= STG / 2, "the second block's first result stays in place");
@@ -873,7 +885,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 asm volatile("" ::: "memory");
             };
 #pragma unroll
-            for (int pass = 0; pass < 32 / RPP; ++pass) {
+            for (int pass = 0; pass < WR / RPP; ++pass) {
                 const int qb = pass * RPP / 16;
                 if constexpr (TWO) read_first(qb);
                 auto value = [&](int cb, int e) {
@@ -950,7 +962,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     };
     auto query_tiles = [&](auto late_tag) __attribute__((always_inline)) {
         constexpr bool LATE = decltype(late_tag)::value;
-        f32x16 S0[2], S1[2];
+        f32x16 S0[QBN], S1[QBN];
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // rows and first tiles
         convert_q_area(h, qt);
         next_tile();
@@ -971,7 +983,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             if (mask_of(0) != ~0ull) mask_apply(S0, mask_of(0));
             row_max(S0);
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < QBN; ++qb) {
                 m_run[qb] = mx_new[qb];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) negm[qb][r] = -m_run[qb];
@@ -991,7 +1003,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 vs = next_vslot(vs);
                 ++j;
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) S0[qb] = S1[qb];
+                for (int qb = 0; qb < QBN; ++qb) S0[qb] = S1[qb];
             }
             if (j + 2 == n_steps) {
                 iteration(late_tag, masked, S0, S1, j, vs);
@@ -999,7 +1011,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 ++j;
             } else {
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) S1[qb] = S0[qb];
+                for (int qb = 0; qb < QBN; ++qb) S1[qb] = S0[qb];
             }
             const bool again = TWO && !second && pv.n_first < pv.nKT;  // the second sequence follows, same rows
             if (!again && left > 1) {  // the rows of the next query tile (the last one's first scores are not used)
@@ -1014,7 +1026,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
             }
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < QBN; ++qb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) negm[qb][r] = 0.f;
             iteration(late_tag, last_of_tile, S1, S0, j, vs);
@@ -1063,8 +1075,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     const int ln = opaque_lane();  // (nothing of the epilogue's addresses is held through the key loop)
     const int li = ln & 15, lg = ln >> 4;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int row = qt * BQ + wave * 32 + qb * 16 + li;
+    for (int qb = 0; qb < QBN; ++qb) {
+        const int row = qt * BQ + wave * WR + qb * 16 + li;
         float l = l_run[qb];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
@@ -1113,7 +1125,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 }
 
 // One sequence per batch entry, all of the same length.
-template <int D, int QK_OP, int PV_OP, int NW>
+template <int D, int QK_OP, int PV_OP, int NW, int QBN>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_kernel(const AttnArgs a) {
     const int logical = xcd_contiguous_block();
     PipeView pv;
@@ -1131,7 +1143,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_kernel(const AttnA
     pv.stat_off = (int64_t)pv.b * a.Lq;
     pv.Hg = a.rg.Hg;
     pv.Wg = a.rg.Wg;
-    attn_pipe16_body<D, QK_OP, PV_OP, NW>(a, pv);
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, false, false, false, QBN>(a, pv);
 }
 
 // The same with the query tiles of the last, partly filled round cut into pieces along the keys (AttnArgs::split):
@@ -1243,11 +1255,11 @@ __global__ void __launch_bounds__(256) attn_combine_varlen_kernel(const AttnArgs
 
 // Packed requests of different lengths: work distribution in varlen_view.  PIECES: some requests' tiles are computed
 // in pieces (8 wavefronts only).
-template <int D, int QK_OP, int PV_OP, int NW, bool PIECES>
+template <int D, int QK_OP, int PV_OP, int NW, bool PIECES, int QBN>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(const AttnArgs a, const VarlenTable vt) {
     PipeView pv;
     if (!varlen_view<D>(a, vt, pv)) return;  // uniform over the workgroup, before any barrier
-    attn_pipe16_body<D, QK_OP, PV_OP, NW, false, PIECES>(a, pv);
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, false, PIECES, false, QBN>(a, pv);
 }
 
 // Cross-attention with one joint softmax per request: workgroups chain `qch` query tiles of one request, head by head.
@@ -1299,9 +1311,9 @@ hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t
     return hipGetLastError();
 }
 
-template <int D, int QK_OP, int PV_OP, int NW>
+template <int D, int QK_OP, int PV_OP, int NW, int QBN>
 hipError_t launch_attn_pipe16_inst(const AttnArgs& a, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_kernel<D, QK_OP, PV_OP, NW>;
+    auto kern = attn_fwd_pipe16_kernel<D, QK_OP, PV_OP, NW, QBN>;
     constexpr int smem = NW == 8 ? chain_lds_bytes<D, NW>() : pipe_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
@@ -1324,9 +1336,9 @@ hipError_t launch_attn_pipe16_split_inst(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int D, int QK_OP, int PV_OP, int NW, bool PIECES>
+template <int D, int QK_OP, int PV_OP, int NW, bool PIECES, int QBN>
 hipError_t launch_attn_pipe16_varlen_inst(const AttnArgs& a, const VarlenTable& vt, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_varlen_kernel<D, QK_OP, PV_OP, NW, PIECES>;
+    auto kern = attn_fwd_pipe16_varlen_kernel<D, QK_OP, PV_OP, NW, PIECES, QBN>;
     constexpr int smem = NW == 8 ? chain_lds_bytes<D, NW>() : pipe_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);

@@ -179,6 +179,14 @@ inline hipError_t compute_units(int* n) {
     return e == hipSuccess ? hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev) : e;
 }
 
+// Compute units of the chip: layouts and workspace sizes of self-attention go by them, whatever device is current, if any.
+constexpr int kCUs = 256;
+
+// Query rows per workgroup of self-attention in the small form (4 wavefronts of 32 rows, two workgroups a compute unit), whose
+// workgroups are reshaped where they fit one round with a compute unit each: 64 rows (4 wavefronts of 16) if those do, else
+// 128 (8 of 16 where they do, else 4 of 32).
+inline int short_tile_rows(int64_t BH, int64_t L) { return BH * ((L + 63) / 64) <= kCUs ? 64 : 128; }
+
 // Layout of the chained cross-attention kernel on `cus` compute units (the host tests read it).  *nw: 4 or 8 if asked for, 0
 // to choose.
 void choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* nw, int* qch);

@@ -21,10 +21,12 @@ CASES = [  # batch, grid, heads, head_dim, dtype of the inputs, normalisation, h
     (1, (1, 8, 8), 40, 64, "bf16", "head", False),       # 64
     (2, (1, 5, 13), 5, 128, "bf16", None, True),         # 65
     (1, (1, 1, 257), 2, 128, "f32", None, False),        # a long table: 22 + 21 + 257 * 21 entries are too many, general path
+    (1, (3, 7, 11), 9, 128, "f32", "token", False),      # 231
     (1, (1, 7, 59), 12, 64, "bf16", "token", False),     # 413: 32 rows a workgroup
-    (1, (8, 8, 8), 8, 128, "bf16", "head", False),       # 512: every wavefront one tile, the last size in one round
-    (1, (1, 13, 45), 5, 128, "f32", "token", False),     # 585: ten tiles on eight wavefronts, the last one of 9 keys
-    (1, (10, 8, 8), 6, 128, "bf16", None, False),        # 640
+    (1, (8, 8, 8), 8, 64, "bf16", "head", False),        # 512: every wavefront one tile, the last size in one round
+    (1, (1, 13, 45), 6, 64, "f32", "token", False),      # 585: ten tiles on eight wavefronts, the last one of 9 keys
+    (1, (6, 8, 8), 10, 128, "bf16", None, False),        # 384: the longest at head_dim 128
+    (1, (1, 7, 55), 3, 128, "f32", "head", False),       # 385: one more, general path
     (1, (4, 16, 16), 8, 64, "f32", "head", False),       # 1,024: two tiles each, 32 rows
     (1, (7, 11, 13), 4, 64, "bf16", None, True),         # 1,001
 ]
