@@ -79,7 +79,8 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 
 // Cache policy (non-temporal) of bytes that are read once or written and not read again: query rows of the chained form,
 // output rows.  4 x 32,760 queries x 40 heads, 8 key tiles 1,518 -> 1,492 us; 32,760 x 40, 3 key tiles 201 -> 193, 7,800 x 12,
-// 3 key tiles (whole call) 30.9 -> 29.8; self-attention level.  Key and value rows in the pre-pack, and its tile images:
+// 3 key tiles (whole call) 30.9 -> 29.8; self-attention level.  Not for fp32 output rows (4 x 20,572 x 17, 6 key tiles 407, with
+// them 418) nor query rows of head_dim 64 (4 x 128 x 25 22.5, with them 22.7).  Key and value rows in the pre-pack, and its tile images:
 // level, left as they were.
 constexpr int kOnce = 2;
 
@@ -171,7 +172,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const int row = qtile * BQ + wave * WR + r;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
             const uint16_t* src = q + (int64_t)qr * a.sq_t + 8 * (slot ^ (r & (QPR - 1)));
-            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, kOnce);
+            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, D == 128 ? kOnce : 0);
         }
     };
     if constexpr (CHAIN) request_q_lds(h, qt);
@@ -930,16 +931,18 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 uint8_t* const obase = static_cast<uint8_t*>(a.out) +
                                        (o_off + (int64_t)(row0 + pass * RPP + ln / PR) * a.so_t) * ES + (ln % PR) * 16;
                 const int64_t kstride = (int64_t)(64 / PR) * a.so_t * ES;
-                // (past the caches: nobody on the chip reads the rows again, and they push out key tiles; see kOnce)
+                auto put = [&](int k) {
+                    u32x4* const dst = reinterpret_cast<u32x4*>(obase + k * kstride);
+                    if constexpr (ES == 2) __builtin_nontemporal_store(v[k], dst);  // (see kOnce)
+                    else *dst = v[k];
+                };
                 if (full) {
 #pragma unroll
-                    for (int k = 0; k < NK; ++k)
-                        __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4*>(obase + k * kstride));
+                    for (int k = 0; k < NK; ++k) put(k);
                 } else {
 #pragma unroll
                     for (int k = 0; k < NK; ++k)
-                        if (row0 + pass * RPP + k * (64 / PR) + ln / PR < pv.Lq)
-                            __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4*>(obase + k * kstride));
+                        if (row0 + pass * RPP + k * (64 / PR) + ln / PR < pv.Lq) put(k);
                 }
             }
         };
