@@ -69,24 +69,20 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     // A stage is the tile's BN rows of w, then its BM rows of x, 128 bytes each; the DMA moves 8 rows an instruction
     // and fills LDS in lane order, so the bank swizzle (piece p of row r in slot p ^ ((r >> 1) & 7)) is in which piece
     // a lane fetches.  Rows past the end are clamped to the last one; their products are not stored.
-    // A lane's byte offset from the tile's first row is 32 bits (the host checks that a tile's extent fits) and stays the same
-    // from step to step; what moves on is the uniform base.  (64-bit pointers a lane, moved on one by one: 769 x 10,240 x
-    // 5,120 69.5 -> 68.9 us on the operands of the call before, 172 x 3,664 x 3,072 11.7 -> 11.3.)
     const int r8 = lane >> 3;
-    auto offset_of = [&](int chunk) __attribute__((always_inline)) -> uint32_t {  // of 8 rows
+    auto src_of = [&](int chunk) __attribute__((always_inline)) -> const uint8_t* {  // of 8 rows, step 0
         const bool is_w = chunk < T::BN / 8;
         const int r = 8 * (is_w ? chunk : chunk - T::BN / 8) + r8;
         const int piece = (lane & 7) ^ ((r >> 1) & 7);
-        const int last = is_w ? a.N - 1 - tn * T::BN : a.M - 1 - tm * T::BM;
-        return (uint32_t)(r < last ? r : last) * (uint32_t)((is_w ? a.ldw : a.ldx) * 2) + piece * 16;
+        const int row0 = is_w ? tn * T::BN : tm * T::BM, end = is_w ? a.N : a.M;
+        const int row = row0 + r < end ? row0 + r : end - 1;
+        return reinterpret_cast<const uint8_t*>(is_w ? a.w + (int64_t)row * a.ldw : a.x + (int64_t)row * a.ldx) + piece * 16;
     };
     constexpr int FULL = T::FULL;
-    uint32_t off[T::LOADS];
+    const uint8_t* src[T::LOADS];
 #pragma unroll
-    for (int i = 0; i < FULL; ++i) off[i] = offset_of(wave + 8 * i);
-    if constexpr (TB & 1) off[FULL] = offset_of(8 * FULL + (wave >> 1));  // half a chunk per wavefront
-    const uint8_t* wstep = reinterpret_cast<const uint8_t*>(a.w + (int64_t)tn * T::BN * a.ldw);  // the step requested next
-    const uint8_t* xstep = reinterpret_cast<const uint8_t*>(a.x + (int64_t)tm * T::BM * a.ldx);
+    for (int i = 0; i < FULL; ++i) src[i] = src_of(wave + 8 * i);
+    if constexpr (TB & 1) src[FULL] = src_of(8 * FULL + (wave >> 1));  // half a chunk per wavefront
     f32x4 acc[FB][TB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb)
@@ -120,26 +116,18 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     auto request_piece = [&](auto i, int stage) __attribute__((always_inline)) {
         constexpr int I = decltype(i)::value;
         uint8_t* const dst = smem + stage * T::STAGE;
-        // chunk wave + 8 i is of w or of x for all wavefronts alike: w has BN / 8 = 8 FB chunks
-        const uint8_t* const base = I < FB ? wstep : xstep;
-        uint32_t o = off[I];
-        asm volatile("" : "+v"(o));  // (else the compiler keeps base + offset, 64 bits a lane)
+        src[I] += requested > 0 && requested < nK ? 128 : 0;  // on from the step requested before
         if constexpr (I < FULL) {
-            __builtin_amdgcn_global_load_lds((gptr_t)(base + o), (lptr_t)(dst + (wave + 8 * I) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)src[I], (lptr_t)(dst + (wave + 8 * I) * 1024), 16, 0, 0);
         } else {
             if ((lane >> 5) == (wave & 1))
-                __builtin_amdgcn_global_load_lds((gptr_t)(base + o), (lptr_t)(dst + (8 * FULL + (wave >> 1)) * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gptr_t)src[I], (lptr_t)(dst + (8 * FULL + (wave >> 1)) * 1024), 16, 0, 0);
         }
-    };
-    auto requested_step = [&]() __attribute__((always_inline)) {
-        const int64_t on = ++requested < nK ? 128 : 0;
-        wstep += on;
-        xstep += on;
     };
 #pragma unroll
     for (int s = 0; s < S - 1; ++s) {
         static_for<0, T::LOADS>([&](auto i) __attribute__((always_inline)) { request_piece(i, s); });
-        requested_step();
+        ++requested;
     }
     sync_stage();
     u32x4 W0[FB], X0[TB], W1[FB], X1[TB];
@@ -180,7 +168,7 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
             }
         };
         slice(W0, X0, W1, X1, stage, std::integral_constant<int, 1>());
-        requested_step();
+        ++requested;
         slice(W1, X1, W0, X0, next, std::integral_constant<int, 0>());  // (behind the last step: unused)
         free_stage = stage;
         stage = next;
