@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // row are swizzled with the row number.  The accumulators start the next tile at zero.
     // The rows pass the caches (non-temporal stores): nobody on the chip reads them again, and as large as x they pushed
     // operand rows out: 32,760 x 5,120 x 5,120 1,149 -> 1,125 us on the
-    // operands of the call before, level on new ones.
+    // operands of the call before, level on new ones.  Not rows that cut 64-byte sectors (whole_sectors).
     auto store_tile = [&](int tm, int tn, int stage_buf) __attribute__((always_inline)) {
         constexpr int ES = OUT_F32 ? 4 : 2;   // bytes per output element
         constexpr int RB = 64 * ES;           // bytes per staged row (the wavefront's 64 features)
@@ -262,6 +262,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         uint8_t* const region = smem + stage_buf * kLinTileBytes + wave * 4096;
         const int rrow = lane / PR, rp = lane % PR;
         const int n = tn * kLinBN + wf * BR * FB + rp * (16 / ES);
+        const bool sectors = whole_sectors(a.y, a.ldy * ES);
         // (16-bit output only: with fp32 output the extra path costs the step loop a register)
         const bool full = !OUT_F32 && (tm + 1) * kLinBM <= a.M && (tn + 1) * kLinBN <= a.N;  // uniform
 #pragma unroll
@@ -290,7 +291,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
                 const int m = tm * kLinBM + wt * BR * TB + pass * RP + k * (64 / PR) + rrow;
                 // N is a multiple of 8: a piece of a row is inside or outside as a whole
                 if (m < a.M && n < a.N)
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES));
+                    store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v, sectors);
             };
             if (full) {
                 // a tile inside y stores without tests, and all four pieces of the pass are read back before the
@@ -305,7 +306,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int m = tm * kLinBM + wt * BR * TB + pass * RP + k * (64 / PR) + rrow;
-                    __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES));
+                    store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v[k], sectors);
                 }
             } else {
                 // (two at a time: the loop around this leaves few registers free)

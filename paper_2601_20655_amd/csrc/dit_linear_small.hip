@@ -187,6 +187,7 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     uint8_t* const area = smem + wave * 16 * RB;
     // where piece c of staged row r lies: spread over the banks by the row number
     auto slot = [](int r, int c) { return c ^ (r & (PR - 1)); };
+    const bool sectors = RB >= 64 && whole_sectors(a.y, a.ldy * ES);
     float b[FB][4];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
@@ -219,7 +220,7 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
             // N is a multiple of 8: a piece of a row is inside or outside as a whole
             if ((NP >= 64 || p < NP) && m < a.M && n < a.N) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(area + r * RB + slot(r, c) * 16);
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES));
+                store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v, sectors);
             }
         }
         asm volatile("" ::: "memory");
