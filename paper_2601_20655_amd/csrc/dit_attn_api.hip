@@ -678,6 +678,18 @@ struct CrossPlan {
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
 
+// Wavefronts and chain length of a call, nw as its flags ask for (0: either).  One softmax whose 128-row query tiles are one
+// round of workgroups takes those (16 rows a wavefront then, see short_tile_rows), two softmaxes go by the estimate.
+void layout_chain(const dit_cross_attn_params* p, int cus, int nw, CrossPlan* pl) {
+    pl->fl.nw = nw;
+    if (nw != 8 && pl->split == 0 && (int64_t)(p->Lq + 127) / 128 * p->B * p->H <= cus) {
+        pl->fl.nw = 4;
+        pl->qch = 1;
+    } else {
+        dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, cus, &pl->fl.nw, &pl->qch);
+    }
+}
+
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
     if (p->B < 1 || p->H < 1 || p->D < 1 || p->Lq < 1 || p->Lk < 1) return DIT_ERR_INVALID_ARG;
@@ -720,7 +732,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     pl->chain16 = pl->layout16 && bf16 && (pl->split == 0 || p->out_dtype == DIT_BF16);
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
-        dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, kCUs, &pl->fl.nw, &pl->qch);
+        layout_chain(p, kCUs, pl->fl.nw, pl);
     } else if (pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;
     } else if (pl->fl.nw == 0) {
@@ -883,8 +895,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
         const hipError_t e = dit::compute_units(&cus);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
         if (cus != kCUs) {
-            pl.fl.nw = (p->flags & DIT_FLAG_BIG_WORKGROUP) ? 8 : (p->flags & DIT_FLAG_SMALL_WORKGROUP) ? 4 : 0;
-            dit::choose_chain(p->Lq, p->B, p->H, pl.nKT, p->D, cus, &pl.fl.nw, &pl.qch);
+            layout_chain(p, cus, (p->flags & DIT_FLAG_BIG_WORKGROUP) ? 8 : (p->flags & DIT_FLAG_SMALL_WORKGROUP) ? 4 : 0, &pl);
             pl.nQT = (p->Lq + 32 * pl.fl.nw - 1) / (32 * pl.fl.nw);
         }
     }
@@ -1224,6 +1235,6 @@ const char* dit_strerror(dit_status s) {
 
 const char* dit_last_hip_error(void) { return g_hip_error; }
 
-int dit_attn_version(void) { return 10700; }  // 1.7.0
+int dit_attn_version(void) { return 10800; }  // 1.8.0
 
 }  // extern "C"

@@ -66,7 +66,8 @@ __device__ __forceinline__ float sum_across_rows16(float x) {
 // latencies, instead of 4; 64 rows by 4 where even those fill at most half of the chip.  Whole calls, us, 4 x 32 rows, 8 x 16, 4 x 16,
 // (tokens, heads) head_dim 128: 1,600 x 9 44.1, 38.0, 35.5; 640 x 20 29.3, 26.4, 24.2; 1,020 x 12 34.3, 30.0, 28.2; 640 x 40 33.9,
 // 29.9, (two rounds) 33.0; 3,600 x 8 75.5, 69.7, (79.3); head_dim 64: 1,600 x 9 29.5, 25.9, 25.1; 3,600 x 8 51.1, 44.0.  The same
-// bits in all three.
+// bits in all three.  Chained (cross-attention, tiles in one round), whole calls: 1,000 queries x 20 heads, 757 keys 27.8 ->
+// 24.0, on resident keys 18.8 -> 15.5; 200 x 40, 769 keys 31.5 -> 27.0; head_dim 64 19.0 -> 16.8, 21.1 -> 18.9.
 // The chained form keeps, behind the tile buffers, one area per wavefront the size of its 32 query rows in 16
 // bits.  The rows of the NEXT query tile are copied into it (global -> LDS) while the current one is in its loop;
 // at the boundary they are converted into operand registers, and the area then serves as the staging area of the
@@ -80,7 +81,7 @@ constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_st
 // Cache policy (non-temporal) of bytes that are read once or written and not read again: query rows of the chained form,
 // output rows.  4 x 32,760 queries x 40 heads, 8 key tiles 1,518 -> 1,492 us; 32,760 x 40, 3 key tiles 201 -> 193, 7,800 x 12,
 // 3 key tiles (whole call) 30.9 -> 29.8; self-attention level.  Not for fp32 output rows (4 x 20,572 x 17, 6 key tiles 407, with
-// them 418) nor query rows of head_dim 64 (4 x 128 x 25 22.5, with them 22.7).  Key and value rows in the pre-pack, and its tile images:
+// them 418), query rows of head_dim 64 (4 x 128 x 25 22.5, with them 22.7) or calls of one round (4 x 144 x 18 25.0, 25.4).  Key and value rows in the pre-pack, and its tile images:
 // level, left as they were.
 constexpr int kOnce = 2;
 
@@ -126,7 +127,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     constexpr int NI = G::PART_KIB / NW;  // full rounds of wavefront-wide 1 KiB loads per tile part
     static_assert(G::PART_KIB - NW * NI == 2, "two odd pieces per tile part");
     static_assert(QK_OP != OP_FP8, "16-bit score operands only");
-    static_assert(QBN == 2 || (!CHAIN && !PIECES), "one query block a wavefront: whole tiles of self-attention");
+    static_assert(QBN == 2 || (!TWO && !PIECES), "one query block a wavefront: whole tiles, one softmax");
     static_assert(!TWO || (CHAIN && D == 128 && QK_OP == OP_F16 && PV_OP == OP_F16),
                   "a pass takes its first maxima as they are: finite scores only; its row sums are those of unrounded probabilities");
 
@@ -167,12 +168,12 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         const int ln = opaque_lane();
         const uint16_t* const q = static_cast<const uint16_t*>(a.q) + (int64_t)pv.b * a.sq_b + (int64_t)head * a.sq_h;
 #pragma unroll
-        for (int k = 0; k < 32 * QPR / 64; ++k) {
+        for (int k = 0; k < WR * QPR / 64; ++k) {
             const int r = k * (64 / QPR) + ln / QPR, slot = ln % QPR;
             const int row = qtile * BQ + wave * WR + r;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
             const uint16_t* src = q + (int64_t)qr * a.sq_t + 8 * (slot ^ (r & (QPR - 1)));
-            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, D == 128 ? kOnce : 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, D == 128 && QBN == 2 ? kOnce : 0);
         }
     };
     if constexpr (CHAIN) request_q_lds(h, qt);
@@ -933,7 +934,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 const int64_t kstride = (int64_t)(64 / PR) * a.so_t * ES;
                 auto put = [&](int k) {
                     u32x4* const dst = reinterpret_cast<u32x4*>(obase + k * kstride);
-                    if constexpr (ES == 2) __builtin_nontemporal_store(v[k], dst);  // (see kOnce)
+                    if constexpr (ES == 2 && QBN == 2) __builtin_nontemporal_store(v[k], dst);  // (see kOnce)
                     else *dst = v[k];
                 };
                 if (full) {
@@ -1275,7 +1276,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(cons
 // per request and index arithmetic that small calls feel.)
 // TWO: the tiles of the two sequences stand from image 0 and from image nTA on, the tile counts of both together and of
 // the first come from the workspace; a sequence without a key has no pass.
-template <int D, int QK_OP, int PV_OP, int NW, bool TWO>
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN = 2>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const AttnArgs a, int qch) {
     const int logical = xcd_contiguous_block();
     PipeView pv;
@@ -1298,13 +1299,13 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const
         pv.skip_first = first > 0 || pv.nKT == 0 ? 0 : a.nTA;
         pv.skip_second = first < pv.nKT ? a.nTA - first : 0;
     }
-    attn_pipe16_body<D, QK_OP, PV_OP, NW, true, false, TWO>(a, pv);
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, true, false, TWO, QBN>(a, pv);
 }
 
 // qch: query tiles per workgroup
-template <int D, int QK_OP, int PV_OP, int NW, bool TWO>
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN = 2>
 hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW, TWO>;
+    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW, TWO, QBN>;
     constexpr int smem = chain_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);
