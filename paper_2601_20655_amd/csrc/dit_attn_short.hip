@@ -16,8 +16,8 @@
 // them.
 //
 // What bounds it: one wavefront's chain of table entry (fp64), rows from memory, rotation, scores, maximum, products and
-// combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it is shorter than the host needs for
-// a launch.  Whole calls, us, three launches and one: 256 tokens x 4 heads x 64 14.9 and 9.3, 256 x 8 x 128 17.6 and 15.0 (see
+// combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it (9 to 10 us) is what the host needs
+// for a launch.  Whole calls, us, three launches and one: 256 tokens x 4 heads x 64 14.9 and 9.3, 256 x 8 x 128 17.6 and 15.0 (see
 // choose_short).  All eight wavefronts work on the table, whatever the number of key tiles: with as many wavefronts as tiles 60
 // tokens x 128 took 16.5 instead of 12.3.  Tried: the first rows requested ahead of the table (registers: 18.3 -> 20.0 at 512 x 2
 // x 128).
