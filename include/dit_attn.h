@@ -32,8 +32,9 @@
  *    its error against the definition) may then differ with the batch size, the number of heads, the other packed
  *    requests (their grids, not their order or values) and with whether the workspace has room for the pieces.
  *    Likewise a short sequence of a small enough call (default operand types, neither workgroup-size flag) is computed
- *    by one launch that divides its keys among the wavefronts of a workgroup, unless the bytes between the first and
- *    the last element of out meet those of k or v (which are then packed before the first row of out is written).
+ *    by a kernel that divides its keys among the wavefronts of a workgroup.
+ *  - The bits of a result do not depend on where the tensors lie.  Except with DIT_FLAG_KV_FUSED, k, v and the channel
+ *    weights of the k rows have been read before the first row of out or lse is written.
  *  - Arithmetic: inputs bf16 (or fp32), q and k rotated and scaled in fp32, then rounded
  *    once (nearest-even) to the 16-bit MFMA operand type chosen by `flags`; scores,
  *    softmax statistics and the output accumulator are fp32; output bf16 or fp32.
@@ -355,7 +356,8 @@ dit_status dit_linear_forward(const void *x, const void *w, const void *bias, vo
  * Timing hook for benchmarks and profilers (not part of the attention definition): while
  * both handles are non-NULL, every forward call made by the calling thread records the
  * hipEvent_t `before` on the stream just before the attention kernel and `after` just after
- * it, so the dominant kernel can be timed apart from the table and pre-pack kernels.
+ * it, so the dominant kernel can be timed apart from the table and pre-pack kernels (a short sequence's kernel may
+ * do their work itself).
  * The events are the caller's; pass NULL, NULL to switch the hook off.
  */
 void dit_attn_set_timing_events(void *before, void *after);

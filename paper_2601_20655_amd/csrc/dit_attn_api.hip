@@ -106,9 +106,10 @@ bool takes_short(const Flags& fl, uint32_t flags) {
            !(flags & (DIT_FLAG_BIG_WORKGROUP | DIT_FLAG_SMALL_WORKGROUP));
 }
 
-// What the one-launch kernel takes besides the attention kernel's arguments.
+// What the kernel for short sequences takes besides the attention kernel's arguments.
 struct ShortCall {
     int qb;
+    bool packed;  // table and tiles are in the workspace
     const dit::TableArgs* table;
     const dit::NormArgs* kn;
 };
@@ -121,7 +122,7 @@ dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused,
     hipError_t e;
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (sc) {
-        e = dit::launch_attn_short(aa, *sc->table, *sc->kn, D, sc->qb, fl.resident, s);
+        e = dit::launch_attn_short(aa, *sc->table, *sc->kn, D, sc->qb, sc->packed, s);
     } else if (chain16) {
         e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, chain16, s);
     } else if (aa.tile_count_a) {
@@ -164,14 +165,32 @@ bool strides_ok(const dit_strides& s, int32_t B, int32_t H, int32_t D, int64_t L
     return true;
 }
 
-// Whether the bytes from the first to the last element of two [B, L, H, D] tensors meet.
-bool overlap(const void* x, const dit_strides& sx, int32_t tx, const void* y, const dit_strides& sy, int32_t ty, int32_t B,
-             int32_t H, int32_t D, int64_t L) {
-    auto end = [&](const void* p, const dit_strides& s, int32_t t) {
-        const int64_t n = (int64_t)(B - 1) * s.batch + (L - 1) * s.token + (int64_t)(H - 1) * s.head + D;
-        return reinterpret_cast<uintptr_t>(p) + (uintptr_t)n * (t == DIT_F32 ? 4 : 2);
-    };
-    return reinterpret_cast<uintptr_t>(x) < end(y, sy, ty) && reinterpret_cast<uintptr_t>(y) < end(x, sx, tx);
+// Bytes from the first to the last element of a [B, L, H, D] tensor, or of n dense fp32 values.
+struct Span {
+    uintptr_t begin, end;
+    bool meets(const Span& o) const { return begin < o.end && o.begin < end; }
+};
+Span span_of(const void* p, const dit_strides& s, int32_t dtype, int32_t B, int32_t H, int32_t D, int64_t L) {
+    const int64_t n = (int64_t)(B - 1) * s.batch + (L - 1) * s.token + (int64_t)(H - 1) * s.head + D;
+    const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
+    return {begin, begin + (uintptr_t)n * (dtype == DIT_F32 ? 4 : 2)};
+}
+Span span_of(const float* p, int64_t n) {
+    const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
+    return {begin, p ? begin + (uintptr_t)n * 4 : begin};
+}
+
+// Whether what a self-attention call writes (out, lse) meets what its key-side passes read (k, v, the weights of the key
+// rows): those passes then have to be over before the first row of out is written.
+bool writes_over_keys(const dit_self_attn_params* p, int64_t L, const void* k, const void* v, const void* out,
+                      const float* lse) {
+    const Span rows = span_of(out, p->so, p->out_dtype, p->B, p->H, p->D, L);
+    const Span sums = span_of(lse, (int64_t)p->B * p->H * L);
+    for (const Span& in : {span_of(k, p->sk, p->in_dtype, p->B, p->H, p->D, L),
+                           span_of(v, p->sv, p->in_dtype, p->B, p->H, p->D, L),
+                           span_of(p->norm.mode != DIT_NORM_NONE ? p->norm.k_gamma : nullptr, (int64_t)p->H * p->D)})
+        if (rows.meets(in) || sums.meets(in)) return true;
+    return false;
 }
 
 // eps >= 0, a known mode; the channel weights are read as float4
@@ -812,9 +831,8 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     const float scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)p->D);
 
     dit::NormArgs qn, kn;
-    const bool one = pl.short_qb > 0 &&
-                     (pl.fl.resident || (!overlap(out, p->so, p->out_dtype, k, p->sk, p->in_dtype, p->B, p->H, p->D, pl.L) &&
-                                         !overlap(out, p->so, p->out_dtype, v, p->sv, p->in_dtype, p->B, p->H, p->D, pl.L)));
+    // a short sequence in one launch, or, the same bit for bit, in one on tiles that are in the workspace before it
+    const bool one = pl.short_qb > 0 && !pl.fl.resident && !writes_over_keys(p, pl.L, k, v, out, lse);
     st = setup_rows(pl.fl.resident || one ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
                     p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
@@ -853,9 +871,9 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     aa.rg = rg;
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
-    if (one) {
+    if (pl.short_qb > 0) {
         aa.nQT = (int)((pl.L + 16 * pl.short_qb - 1) / (16 * pl.short_qb));
-        const ShortCall sc{pl.short_qb, &ta, &kn};
+        const ShortCall sc{pl.short_qb, !one, &ta, &kn};
         return run_attn(aa, p->D, pl.fl, false, true, s, 0, &sc);
     }
     apply_split(&pl, p->D, ws, workspace_bytes, &aa);

@@ -10,10 +10,10 @@
 // through LDS as those of pieces along the keys are.  Every workgroup works out the rotation table and rotates all keys
 // of its head again, which is the price, and why the sequence has to be short (choose_short).
 //
-// The workspace is left as the general path leaves it: rotation table, and tile images in the layout of the 16x16x32
-// kernels, written from the operand registers by the workgroups of the first query rows.  With RESIDENT the operands are
-// read from such images instead of being made, so that a call on resident tiles gives the bits of the one that packed
-// them.
+// The workspace is left as the general path leaves it, byte for byte: rotation table, and tile images in the layout of
+// the 16x16x32 kernels, written from the operand registers by the workgroups of the first query rows.  With RESIDENT the
+// operands are read from such images instead of being made -- after the table and pre-pack kernels of the same call, where
+// it writes over its keys, or in a call on resident tiles -- with the same bits.
 //
 // What bounds it: one wavefront's chain of table entry (fp64), rows from memory, rotation, scores, maximum, products and
 // combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it (9 to 10 us) is what the host needs
@@ -169,19 +169,34 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
     // Multiplier of a row whose channels the four lanes (i, 0..3) hold.
     // (The empty statement makes the row a new value behind the branch: the compiler otherwise keeps what it widened for
     // the sum, of all rows at once.)
-    auto row_factor = [&](const NormArgs& n, u32x4 (&raw)[NKS][2], bool f32, int64_t stat) __attribute__((always_inline)) {
+    // The order of a per-head sum is that of the kernel that reads the rows on the general path: of q rows the attention
+    // kernel's (a lane's channels one after the other), of k rows the pre-pack's (eight channels, then chunks pairwise), so
+    // that the tile images are the same whoever writes them.
+    auto row_factor = [&](const NormArgs& n, u32x4 (&raw)[NKS][2], bool f32, int64_t stat, auto k_row) __attribute__((always_inline)) {
+        constexpr bool K_ROW = decltype(k_row)::value;
         float rs = 1.f;
         if (n.mode == 2) rs = n.rstd[stat];
         if (n.mode == 1) {
-            float ss = 0.f;
+            float ss[NKS];
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 float x[8];
                 values8(raw[ks], f32, x);
+                ss[ks] = K_ROW || ks == 0 ? 0.f : ss[ks - 1];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
+                for (int e = 0; e < 8; ++e) ss[ks] = fmaf(x[e], x[e], ss[ks]);
             }
-            rs = 1.0f / sqrtf(sum_across_rows16(ss) * (1.0f / D) + n.eps);
+            if constexpr (K_ROW) {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) ss[ks] = sum_across_rows16(ss[ks]);
+#pragma unroll
+                for (int m = 1; m < NKS; m <<= 1)
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ks += 2 * m) ss[ks] += ss[ks + m];
+            } else {
+                ss[0] = sum_across_rows16(ss[NKS - 1]);
+            }
+            rs = 1.0f / sqrtf(ss[0] * (1.0f / D) + n.eps);
         }
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
@@ -205,7 +220,7 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
         int pt, ph, pw;
         token_pos(qrow[qb], a.rg, pt, ph, pw);
         const RopeRow rr = rope_row(a.rg, pt, ph, pw);
-        const float rs = row_factor(a.qn, qraw[qb], q_f32, (int64_t)b * L + qrow[qb]);
+        const float rs = row_factor(a.qn, qraw[qb], q_f32, (int64_t)b * L + qrow[qb], std::false_type{});
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             float x[8];
@@ -268,7 +283,7 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
                 int pt, ph, pw;
                 token_pos(key[kb], a.rg, pt, ph, pw);
                 const RopeRow rr = rope_row(a.rg, pt, ph, pw);
-                const float rs = row_factor(kn, kraw[kb], F32, (int64_t)b * L + key[kb]);
+                const float rs = row_factor(kn, kraw[kb], F32, (int64_t)b * L + key[kb], std::true_type{});
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks) {
                     float x[8];

@@ -87,3 +87,36 @@ def test_packed_requests_ignore_stale_workspace():
 
     (a, la), (b, lb) = twice(call, need, tuple(q.shape), torch.bfloat16)
     assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and torch.equal(la, lb)
+
+
+@pytest.mark.parametrize("grid,H,D,dtype", [((3, 7, 11), 3, 128, "bf16"), ((1, 7, 59), 4, 64, "f32"), ((1, 13, 45), 6, 64, "bf16")])
+@pytest.mark.parametrize("mode", [None, "head", "token"])
+def test_short_self_attention_ignores_stale_workspace(grid, H, D, dtype, mode):
+    """One launch leaves the table and the tile images, their zeros too (rows and columns past the last key, pads), as the
+    general path does: equal byte for byte on stale memory, and good for a call on resident tiles."""
+    import torch
+
+    split = (44, 42, 42) if D == 128 else (22, 20, 22)
+    cfg = dict(B=1, grid=grid, H=H, D=D, split=split, dtype=dtype, seed=37)
+    q, k, v = (to_dev(a) for a in wl.self_attn_inputs(cfg))
+    gq, gk = (to_dev(g) for g in wl.norm_weights(cfg))
+    norm = None if mode is None else (mode, 1e-6, gq, gk)
+    need = B.dit_attn_workspace_bytes(B.self_attn_params(q, k, v, q, grid, split, norm=norm))
+    left = {}
+    for flags in (0, B.DIT_FLAG_SMALL_WORKGROUP):
+
+        def call(ws, out, lse):
+            B.dit_attn_forward(q, k, v, grid, split, out=out, lse=lse.view(1, H, -1), flags=flags, workspace=ws[:need], norm=norm)
+            left.setdefault(flags, []).append(ws[:need].clone())
+            again, lse2 = B.dit_attn_forward(q, None, None, grid, split, flags=flags | B.DIT_FLAG_KV_RESIDENT, workspace=ws[:need],
+                                             norm=norm, out_dtype=out.dtype, want_lse=True)
+            assert torch.equal(again, out) and torch.equal(lse2, lse.view(1, H, -1))
+
+        (a, la), (b, lb) = twice(call, need, tuple(q.shape), torch.float32)
+        assert torch.equal(a, b) and torch.equal(la, lb)
+    written = 8 * (grid[0] * split[0] + grid[1] * split[1] + grid[2] * split[2]) // 2
+    for one, general in zip(left[0], left[B.DIT_FLAG_SMALL_WORKGROUP]):
+        assert torch.equal(one[:written], general[:written])
+        tiles = (written + 255) // 256 * 256
+        end = tiles + H * ((grid[0] * grid[1] * grid[2] + 63) // 64) * 2 * (18 if D == 128 else 10) * 1024
+        assert torch.equal(one[tiles:end], general[tiles:end])

@@ -84,8 +84,7 @@ def test_short_sequence(case):
     if nb == 1:
         packed = B.dit_attn_varlen_forward(q[0], k[0], v[0], [grid], split, out_dtype=torch.float32, norm=norm)
         assert torch.equal(packed, out[0])
-    # the general path: the same results but for rounding, and the same workspace: rotation table, and tile images (whose rows
-    # behind a per-head mean may differ in its last bit)
+    # the general path: the same results but for rounding, and the same workspace: rotation table and tile images
     ws_g = torch.zeros(need, dtype=torch.uint8, device="cuda")
     out_g, lse_g = B.dit_attn_forward(q, k, v, grid, split, out_dtype=torch.float32, want_lse=True, workspace=ws_g, norm=norm,
                                       flags=B.DIT_FLAG_SMALL_WORKGROUP)
@@ -96,9 +95,8 @@ def test_short_sequence(case):
     assert (lse - lse_g).abs().max().item() < 1e-3
     table = 8 * (grid[0] * split[0] + grid[1] * split[1] + grid[2] * split[2]) // 2
     assert torch.equal(ws[:table], ws_g[:table])
-    if mode != "head":
-        n = (table + 255) // 256 * 256 + nb * H * ((L + 63) // 64) * 2 * (18 if D == 128 else 10) * 1024
-        assert torch.equal(ws[:n], ws_g[:n])
+    n = (table + 255) // 256 * 256 + nb * H * ((L + 63) // 64) * 2 * (18 if D == 128 else 10) * 1024
+    assert torch.equal(ws[:n], ws_g[:n])
 
 
 def test_output_over_the_keys():
@@ -111,3 +109,57 @@ def test_output_over_the_keys():
     ref = oracle.self_attn(qn, kn, vn, grid, SPLITS[D])
     B.dit_attn_forward(q, k, v, grid, SPLITS[D], out=k)
     compare(to_f64(k), ref, what="out over k")
+
+
+@pytest.mark.parametrize("place", ["q columns", "k", "v", "lse over k", "lse over the weights"])
+@pytest.mark.parametrize("grid,H,D,dtype,mode", [
+    ((2, 8, 8), 4, 64, "f32", None), ((1, 7, 59), 12, 64, "bf16", "token"), ((4, 9, 16), 6, 64, "f32", "head"),
+    ((3, 7, 9), 4, 128, "f32", "head"), ((6, 8, 8), 10, 128, "bf16", "head"), ((1, 5, 13), 2, 128, "bf16", None),
+])
+def test_place_of_the_results_does_not_change_them(grid, H, D, dtype, mode, place):
+    """out or lse where the key rows or their weights are, or between them (the columns of one q/k/v buffer): the keys are
+    packed before the first row is written, and every bit of out, lse and the workspace is that of the call beside them."""
+    import torch
+
+    split, L = SPLITS[D], grid[0] * grid[1] * grid[2]
+    if place == "lse over the weights" and mode is None:
+        pytest.skip("no weights")
+    cfg = dict(B=1, grid=grid, H=H, D=D, split=split, dtype=dtype, seed=23)
+    rng = np.random.default_rng(6)
+    gq, gk = ((1 + 0.25 * rng.standard_normal(H * D)).astype(np.float32) for _ in range(2))
+    rows = [to_dev(x) for x in wl.self_attn_inputs(cfg)]
+    need = B.dit_attn_workspace_bytes(B.self_attn_params(*rows, rows[0], grid, split, norm=(mode, 1e-6, None, None) if mode else None))
+
+    def call(where):
+        buf = torch.stack(rows, dim=2)  # [1, L, 3, H, D]
+        q, k, v = (buf[:, :, i] for i in range(3)) if where == "q columns" else (x.clone() for x in rows)
+        gamma_k = torch.zeros(max(H * D, H * L), device="cuda")
+        gamma_k[:H * D] = to_dev(gk)
+        norm = None if mode is None else (mode, 1e-6, to_dev(gq), gamma_k[:H * D])
+        out = {"q columns": q, "k": k, "v": v}.get(where, torch.full_like(rows[0], float("nan")))
+        lse = torch.full((1, H, L), float("nan"), device="cuda")
+        if where == "lse over k":
+            lse = k.view(-1).view(torch.float32)[:H * L].view(1, H, L)
+        if where == "lse over the weights":
+            lse = gamma_k[:H * L].view(1, H, L)
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        B.dit_attn_forward(q, k, v, grid, split, out=out, lse=lse, workspace=ws, norm=norm)
+        return out.contiguous(), lse.clone(), ws
+
+    for got, beside in zip(call(place), call("beside")):
+        assert torch.equal(got, beside)
+
+
+@pytest.mark.parametrize("grid,H", [((3, 7, 11), 4), ((6, 8, 8), 10)])
+def test_projection_then_attention_in_place(grid, H):
+    """What the fused projection promises of its tiles, with out over the q columns of the rows of the separate route."""
+    import torch
+
+    D, K, L = 128, 128, grid[0] * grid[1] * grid[2]
+    rng = np.random.default_rng(9)
+    x, w = (to_dev(wl.f32_to_bf16_bits((rng.standard_normal(s) * K ** -0.25).astype(np.float32))) for s in ((L, K), (3 * H * D, K)))
+    q, ws = B.dit_qkv_proj_forward(x, w, None, grid, SPLITS[D], H)
+    fused = B.dit_attn_forward(q, None, None, grid, SPLITS[D], flags=B.DIT_FLAG_KV_RESIDENT, workspace=ws)
+    q, k, v = (B.dit_linear_forward(x, w).view(1, L, 3, H, D)[:, :, i] for i in range(3))
+    B.dit_attn_forward(q, k, v, grid, SPLITS[D], out=q)
+    assert torch.equal(fused, q)
