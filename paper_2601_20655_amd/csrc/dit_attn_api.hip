@@ -305,18 +305,37 @@ dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int64_t tiles64, in
     return best;
 }
 
-// Whether a short sequence is computed in one launch (dit_attn_short.hip), in workgroups of 16 or 32 query rows (1, 2; 0: no).
-// Every workgroup makes the operands of all keys of its head, so it pays while one round of workgroups takes the call.  us a
-// call one after the other, general path and this (a launch by itself: 9.2), tokens x heads: head_dim 64, 16 rows: 64 x 40 13.7
-// and 9.3, 413 x 8 14.0 and 11.5, 512 x 2 14.3 and 11.0, 1,020 x 4 18.6 and 16.4; two rounds, 770 x 8, 20.7 and 27.0; 32 rows: 256
-// x 20 13.8 and 10.6, 640 x 10 16.0 and 15.4; two rounds, 770 x 12, 21.5 and 33.4.  head_dim 128, 16
-// rows: 64 x 40 14.8 and 12.6, 256 x 8 17.6 and 15.0; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not
-// taken); 32 rows spill there: 413 x 12 25.7.
-int choose_short(int64_t L, int64_t BH, int D, int table_entries) {
-    if (table_entries > dit::kShortTable || L > (D == 64 ? 1024 : 384)) return 0;
+}  // namespace
+
+// Every workgroup works on all keys of its head, so this pays while one round of workgroups takes the call.  us a call, one
+// after the other, general path and this (tokens x heads, 16-bit rows): head_dim 64, 16 rows: 256 x 4 16.0 and 9.3, 413 x 8 16.1
+// and 11.4, 512 x 2 16.8 and 10.7, 1,024 x 4 19.3 and 15.7; 32 rows: 512 x 15 16.8 and 13.0, 1,024 x 8 18.2 and 16.0; two
+// rounds, 770 x 8, 20.7 and 27.0 (in one launch).  head_dim 128, 16 rows: 64 x 4 13.7 and 12.0, 256 x 8 16.5 and 15.1, 384 x 10
+// 19.4 and 17.7; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not taken); 32 rows spill there: 413 x 12 25.7.
+int dit::choose_short(int64_t L, int64_t BH, int D, int table_entries) {
+    if (table_entries > kShortTable || L > (D == 64 ? 1024 : 384)) return 0;
     if (BH * ((L + 15) / 16) <= kCUs) return 1;
     return D == 64 && BH * ((L + 31) / 32) <= kCUs ? 2 : 0;
 }
+
+// One launch saves two, about 2 us on the device and 3 more where the host is what a call waits for, and pays with every
+// workgroup's own table and packing.  What makes that longer adds up, each about a microsecond: fp32 rows, per-token factors
+// (a launch of their own ahead of it, which makes the table on the way otherwise), both together past 256 tokens (fp32 512 x 8
+// 15.8 and 13.2 / 17.4 and 16.5), a table of more than two entries a thread,
+// at head_dim 128 twice the work a key and more than three key tiles, at head_dim 64 more tiles than wavefronts (from 769
+// tokens on for most of them) and 32 query rows.  us in one launch and in three, replayed from a graph / called one after
+// the other, at 0 to 2 of these: head_dim 64, 256 x 4 7.8 and 9.9 / 9.3 and 15.0; 512 x 15 12.3 and 13.7 / 13.0 and 15.5; fp32 576
+// x 4 13.6 and 12.2 / 14.0 and 16.3; head_dim 128, 64 x 40 11.8 and 12.9 / 12.4 and 14.0; 256 x 8 14.6 and 13.8 / 15.1 and 15.0;
+// fp32 192 x 20 15.9 and 15.3 / 16.3 and 17.0; at 3 and more: head_dim 64, 1,024 x 4 16.3 and 14.2 / 17.0 and 15.7, fp32 x 8 23.3
+// and 15.5 / 23.7 and 16.7, fp32, per token, 512 x 15 18.3 and 16.2 / 19.5 and 18.0; head_dim 128, 1 x 6 x 64 tokens x 10 18.7 and
+// 16.6 / 19.1 and 18.0, fp32, per token 23.6 and 19.2 / 24.2 and 20.6 (the general path: 20.2 / 21.6).
+bool dit::short_packs_itself(int64_t L, int D, int qb, int table_entries, bool f32_rows, bool token_norm) {
+    const int own = D == 64 ? (L > 512) + 2 * (L > 768) + (qb == 2) : 1 + (L > 192);
+    const int rows = f32_rows + token_norm + (f32_rows && token_norm && L > 256);
+    return own + rows + (table_entries > 1024) < 3;
+}
+
+namespace {
 
 dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -372,7 +391,7 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     pl->total = pl->base;
     pl->split = dit::SplitPlan{0, 0, 1};
     pl->short_qb = 0;
-    if (takes_short(pl->fl, p->flags)) pl->short_qb = choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
+    if (takes_short(pl->fl, p->flags)) pl->short_qb = dit::choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
     if (self_attn_uses_mfma16(pl->fl) && !(p->flags & DIT_FLAG_SMALL_WORKGROUP)) {
         pl->split_nQT = (int)((L + 255) / 256);
         pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H,
@@ -832,7 +851,9 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
 
     dit::NormArgs qn, kn;
     // a short sequence in one launch, or, the same bit for bit, in one on tiles that are in the workspace before it
-    const bool one = pl.short_qb > 0 && !pl.fl.resident && !writes_over_keys(p, pl.L, k, v, out, lse);
+    const bool one = pl.short_qb > 0 && !pl.fl.resident && !writes_over_keys(p, pl.L, k, v, out, lse) &&
+                     dit::short_packs_itself(pl.L, p->D, pl.short_qb, pl.table_entries, p->in_dtype == DIT_F32,
+                                             p->norm.mode == DIT_NORM_TOKEN);
     st = setup_rows(pl.fl.resident || one ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
                     p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
@@ -1018,7 +1039,7 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
         return DIT_ERR_WORKSPACE;
 
     // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit; a short one goes there
-    if (pl.vt.n == 1 && takes_short(pl.fl, p->flags) && choose_short(pl.vt.total_tokens, p->H, p->D, pl.table_entries) > 0) {
+    if (pl.vt.n == 1 && takes_short(pl.fl, p->flags) && dit::choose_short(pl.vt.total_tokens, p->H, p->D, pl.table_entries) > 0) {
         dit_self_attn_params one;
         memset(&one, 0, sizeof(one));
         one.B = 1; one.H = p->H; one.D = p->D;

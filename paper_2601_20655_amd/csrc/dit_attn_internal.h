@@ -220,11 +220,15 @@ bool mask_needs_key_list(int B, int H, int Lk, int split);
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s);
 // after launch_prepack when a.key_src is set: compact the non-empty tiles of every batch entry into tile_list / tile_count
 hipError_t launch_tile_compact(const PackArgs& a, hipStream_t s);
-// Short sequences in one launch (dit_attn_short.hip): a.nQT workgroups of 16 qb query rows a head; resident: on tiles that are
-// packed already, else it writes them, and the rotation table, as the other kernels do.
+// Short sequences (dit_attn_short.hip): a.nQT workgroups of 16 qb query rows a head; packed: the rotation table and the tiles
+// are in the workspace, else the launch makes them for itself and leaves them there.
 constexpr int kShortWaves = 8;     // wavefronts of a workgroup, at most
 constexpr int kShortTable = 2048;  // entries of the rotation table, at most
-hipError_t launch_attn_short(const AttnArgs& a, const TableArgs& ta, const NormArgs& kn, int D, int qb, bool resident,
+// Whether a call takes that kernel, in workgroups of 16 or 32 query rows (1, 2; 0: no), BH sequences and heads; and whether
+// in the one launch (the host tests read both).
+int choose_short(int64_t L, int64_t BH, int D, int table_entries);
+bool short_packs_itself(int64_t L, int D, int qb, int table_entries, bool f32_rows, bool token_norm);
+hipError_t launch_attn_short(const AttnArgs& a, const TableArgs& ta, const NormArgs& kn, int D, int qb, bool packed,
                              hipStream_t s);
 // qb = 32-row query blocks per wavefront (1 or 2)
 hipError_t launch_attn(const AttnArgs& a, int D, int qb, int qk_op, int pv_op, bool fused,

@@ -13,7 +13,7 @@
 // The workspace is left as the general path leaves it, byte for byte: rotation table, and tile images in the layout of
 // the 16x16x32 kernels, written from the operand registers by the workgroups of the first query rows.  With RESIDENT the
 // operands are read from such images instead of being made -- after the table and pre-pack kernels of the same call, where
-// it writes over its keys, or in a call on resident tiles -- with the same bits.
+// it writes over its keys or that is faster (short_packs_itself), or in a call on resident tiles -- with the same bits.
 //
 // What bounds it: one wavefront's chain of table entry (fp64), rows from memory, rotation, scores, maximum, products and
 // combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it (9 to 10 us) is what the host needs

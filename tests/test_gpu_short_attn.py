@@ -29,6 +29,8 @@ CASES = [  # batch, grid, heads, head_dim, dtype of the inputs, normalisation, h
     (1, (1, 7, 55), 3, 128, "f32", "head", False),       # 385: one more, general path
     (1, (4, 16, 16), 8, 64, "f32", "head", False),       # 1,024: two tiles each, 32 rows
     (1, (7, 11, 13), 4, 64, "bf16", None, True),         # 1,001
+    (1, (1, 7, 59), 12, 64, "f32", None, True),          # 413: 32 fp32 rows a workgroup in one launch
+    (1, (1, 3, 43), 4, 128, "f32", None, False),         # 129: three key tiles, the last one of a single key
 ]
 
 

@@ -113,3 +113,50 @@ def test_projection_shapes_of_the_gpu_tests_run_on_the_tiles_they_are_meant_for(
                           (22, 1031, 3592, 64), (22, 1031, 3592, 256), (42, 1025, 3080, 320), (34, 1250, 4104, 256),
                           (44, 3502, 1560, 64), (54, 2500, 3336, 576)]:
         assert linear_form(M, N, K) == form
+
+
+def short_form(L, heads, D, table_entries, f32=False, token=False):
+    """Query rows a workgroup of the kernel for short sequences (0: another kernel) and whether one launch does everything."""
+    f = B.lib()._ZN3dit12choose_shortEllii
+    f.restype = ctypes.c_int
+    f.argtypes = 2 * [ctypes.c_int64] + 2 * [ctypes.c_int]
+    g = B.lib()._ZN3dit18short_packs_itselfEliiibb
+    g.restype = ctypes.c_bool
+    g.argtypes = [ctypes.c_int64] + 3 * [ctypes.c_int] + 2 * [ctypes.c_bool]
+    qb = f(L, heads, D, table_entries)
+    return 16 * qb, qb > 0 and g(L, D, qb, table_entries, f32, token)
+
+
+@pytest.mark.parametrize("L,heads,D,table,rows", [
+    (1024, 4, 64, 300, 16), (1025, 1, 64, 300, 0), (1024, 5, 64, 300, 32), (1024, 8, 64, 300, 32), (1024, 9, 64, 300, 0),
+    (16, 256, 64, 300, 16), (16, 257, 64, 300, 0), (17, 128, 64, 300, 16), (17, 129, 64, 300, 32), (32, 256, 64, 300, 32), (1, 1, 64, 2048, 16),
+    (1, 1, 64, 2049, 0), (384, 10, 128, 468, 16), (384, 11, 128, 468, 0), (385, 1, 128, 468, 0), (1, 1, 128, 2049, 0),
+])
+def test_short_sequences_take_their_kernel_while_one_round_holds_them(L, heads, D, table, rows):
+    assert short_form(L, heads, D, table)[0] == rows
+
+
+@pytest.mark.parametrize("L,heads,D,table,f32,token,itself", [
+    (256, 4, 64, 212, True, True, True), (257, 4, 64, 212, True, True, False), (512, 15, 64, 256, True, False, True), (512, 15, 64, 256, True, True, False),
+    (576, 4, 64, 267, True, False, True), (768, 5, 64, 300, False, True, True), (768, 10, 64, 300, True, False, False),
+    (769, 1, 64, 300, False, False, False), (64, 40, 128, 358, True, False, True), (64, 8, 128, 1387, True, False, False),
+    (192, 20, 128, 402, True, False, True), (193, 8, 128, 402, True, False, False), (256, 8, 128, 694, False, False, True),
+    (256, 8, 128, 1450, False, False, False), (384, 10, 128, 468, False, True, False),
+])
+def test_one_launch_where_it_is_faster_than_three(L, heads, D, table, f32, token, itself):
+    rows, one = short_form(L, heads, D, table, f32, token)
+    assert rows > 0 and one == itself
+
+
+def test_short_shapes_of_the_gpu_tests_reach_every_form():
+    from test_gpu_short_attn import CASES, SPLITS
+
+    seen = set()
+    for nb, grid, H, D, dtype, mode, _ in CASES:
+        L = grid[0] * grid[1] * grid[2]
+        table = sum(n * s // 2 for n, s in zip(grid, SPLITS[D]))
+        seen.add((D, dtype) + short_form(L, nb * H, D, table, dtype == "f32", mode == "token"))
+    for D, rows in ((64, 16), (64, 32), (128, 16)):
+        for dtype in ("bf16", "f32"):
+            assert (D, dtype, rows, True) in seen, (D, dtype, rows)
+        assert any((D, dtype, rows, False) in seen for dtype in ("bf16", "f32"))
