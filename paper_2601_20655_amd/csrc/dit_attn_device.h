@@ -80,17 +80,6 @@ __device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
     }
 }
 
-// Output rows of a projection pass the caches (non-temporal) where a wavefront's part of a row is whole 64-byte sectors: a
-// sector that two of them write is put together in the L2, and past it costs a write each (26,783 x 15,144 x 2,432 1,468 us
-// with the caches, 1,502 past them; 341 x 880 x 3,584 12.0 and 13.2).
-__device__ __forceinline__ bool whole_sectors(const void* y, int64_t row_bytes) {
-    return ((reinterpret_cast<uintptr_t>(y) | (uintptr_t)row_bytes) & 63u) == 0;
-}
-__device__ __forceinline__ void store_row_piece(u32x4* dst, u32x4 v, bool past_caches) {
-    if (past_caches) __builtin_nontemporal_store(v, dst);
-    else *dst = v;
-}
-
 // ---- 8-bit (OCP e4m3) score operands ----
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 

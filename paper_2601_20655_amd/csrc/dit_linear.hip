@@ -243,9 +243,8 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // loads that refill it are issued in the next step -- behind the barrier that ends the store, so that a
     // loading wavefront that has stored cannot overwrite what another one still stages.  Pieces of a staged
     // row are swizzled with the row number.  The accumulators start the next tile at zero.
-    // The rows pass the caches (non-temporal stores): nobody on the chip reads them again, and as large as x they pushed
-    // operand rows out: 32,760 x 5,120 x 5,120 1,149 -> 1,125 us on the
-    // operands of the call before, level on new ones.  Not rows that cut 64-byte sectors (whole_sectors).
+    // (Tried: non-temporal stores.  Level on new operands and for the kernel that reads the rows next: 32,760 x 5,120 x 5,120
+    // 1,172 and 1,171 us, fused rows of 3,600 x 40 and the attention on them 743 and 744.)
     auto store_tile = [&](int tm, int tn, int stage_buf) __attribute__((always_inline)) {
         constexpr int ES = OUT_F32 ? 4 : 2;   // bytes per output element
         constexpr int RB = 64 * ES;           // bytes per staged row (the wavefront's 64 features)
@@ -262,7 +261,6 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         uint8_t* const region = smem + stage_buf * kLinTileBytes + wave * 4096;
         const int rrow = lane / PR, rp = lane % PR;
         const int n = tn * kLinBN + wf * BR * FB + rp * (16 / ES);
-        const bool sectors = whole_sectors(a.y, a.ldy * ES);
         // (16-bit output only: with fp32 output the extra path costs the step loop a register)
         const bool full = !OUT_F32 && (tm + 1) * kLinBM <= a.M && (tn + 1) * kLinBN <= a.N;  // uniform
 #pragma unroll
@@ -291,7 +289,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
                 const int m = tm * kLinBM + wt * BR * TB + pass * RP + k * (64 / PR) + rrow;
                 // N is a multiple of 8: a piece of a row is inside or outside as a whole
                 if (m < a.M && n < a.N)
-                    store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v, sectors);
+                    *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES) = v;
             };
             if (full) {
                 // a tile inside y stores without tests, and all four pieces of the pass are read back before the
@@ -306,7 +304,7 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int m = tm * kLinBM + wt * BR * TB + pass * RP + k * (64 / PR) + rrow;
-                    store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v[k], sectors);
+                    *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES) = v[k];
                 }
             } else {
                 // (two at a time: the loop around this leaves few registers free)

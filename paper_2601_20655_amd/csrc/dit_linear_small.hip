@@ -177,8 +177,9 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    // ---- store: 16 token rows at a time through an area of the wavefront's own, so that rows leave in 16-byte pieces, past the
-    // caches (769 x 10,240 x 5,120 72.1 -> 70.6 us on the operands of the call before, 89.4 -> 88.7 on new ones)
+    // ---- store: 16 token rows at a time through an area of the wavefront's own, so that rows leave in 16-byte pieces
+    // (Tried: non-temporal stores.  769 x 10,240 x 5,120 72.1 -> 70.6 us on the operands of the call before, 89.4 -> 88.7 on
+    // new ones, but level with the kernel that reads the rows next: cross-attention of 256 queries on them 92.7 and 92.8.)
     constexpr int ES = OUT_F32 ? 4 : 2;
     constexpr int RB = 16 * FB * ES;  // bytes of a staged row: the wavefront's features
     constexpr int PR = RB / 16;       // pieces per row
@@ -187,7 +188,6 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     uint8_t* const area = smem + wave * 16 * RB;
     // where piece c of staged row r lies: spread over the banks by the row number
     auto slot = [](int r, int c) { return c ^ (r & (PR - 1)); };
-    const bool sectors = RB >= 64 && whole_sectors(a.y, a.ldy * ES);
     float b[FB][4];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
             // N is a multiple of 8: a piece of a row is inside or outside as a whole
             if ((NP >= 64 || p < NP) && m < a.M && n < a.N) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(area + r * RB + slot(r, c) * 16);
-                store_row_piece(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES), v, sectors);
+                *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.y) + ((int64_t)m * a.ldy + n) * ES) = v;
             }
         }
         asm volatile("" ::: "memory");
