@@ -195,11 +195,11 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // Operand fragments.  A slice (32 contraction indices) takes FB fragments of w and TB of x and feeds
     // FB x TB MFMAs, walked by pairs of token blocks, both blocks of a pair on one w fragment before the next: of the
     // orders a power-limited MFMA loop was timed in (random operands), the A operand held for two products draws least
-    // (1,938 TFLOP/s; B held for four or eight 1,887; neither 1,880).  Block by block, w fragment by w fragment, 32,760 x
-    // 5,120 x 5,120 took 1,189 us, in pairs 1,180.
-    // The w fragments are double-buffered and requested
-    // a slice ahead; the x fragments of a pair are refilled IN PLACE during the next
-    // pair (an LDS return into registers whose MFMAs have issued is safe), so only one set is held.
+    // (1,938 TFLOP/s; B held for four or eight 1,887; neither 1,880).  Block by block, w fragment by w fragment, and in pairs,
+    // us, new operands: 32,760 x 5,120 x 5,120 1,185 and 1,178 (medians 1,190 and 1,187: within what runs differ), fp32 rows
+    // 1,243 and 1,230, fused with per-head norms 3,823 and 3,804 (N = 15,360), 3,600 x 15,360 x 5,120 level.
+    // The w fragments are double-buffered and requested a slice ahead; the x fragments of a pair are refilled IN PLACE
+    // during the next pair (an LDS return into registers whose MFMAs have issued is safe), so only one set is held.
     // The reads are inline assembly so that the waits can be counted: LDS returns in order, and the number
     // of reads issued behind the ones a pair needs is a constant of the pair's place in the slice, so a
     // fragment is asked for 4 to 8 reads before its use.  The compiler itself waits
@@ -251,6 +251,12 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         constexpr int PR = RB / 16;           // 16-byte pieces per row
         constexpr int RP = 4096 / RB;         // rows per pass
         constexpr int TBP = RP / BR;          // token blocks per pass
+        uint8_t* const region = smem + stage_buf * kLinTileBytes + wave * 4096;
+        // (lane numbers the compiler cannot see through: what the store derives from them is not held through the step loop)
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int lr = l & 15, lg = l >> 4, rrow = l / PR, rp = l % PR;
+        const int n = tn * kLinBN + wf * BR * FB + rp * (16 / ES);
         uint2 bb[FB];
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
@@ -258,9 +264,6 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
             bb[fb] = make_uint2(0u, 0u);
             if (a.bias && n0 < a.N) bb[fb] = *reinterpret_cast<const uint2*>(a.bias + n0);
         }
-        uint8_t* const region = smem + stage_buf * kLinTileBytes + wave * 4096;
-        const int rrow = lane / PR, rp = lane % PR;
-        const int n = tn * kLinBN + wf * BR * FB + rp * (16 / ES);
         // (16-bit output only: with fp32 output the extra path costs the step loop a register)
         const bool full = !OUT_F32 && (tm + 1) * kLinBM <= a.M && (tn + 1) * kLinBN <= a.N;  // uniform
 #pragma unroll
@@ -630,12 +633,13 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         if (++kt == nK) {
             if constexpr (QKV) store_tile_qkv(tm, tn, xb == 0 ? SX - 1 : xb - 1);
             else store_tile(tm, tn, xb == 0 ? SX - 1 : xb - 1);
-            if constexpr (QKV != 0) {
-                // The fused forms work the per-lane fragment offsets out again behind every store of a tile, from
-                // a lane number the compiler cannot see through: they are then new values here, not values that
-                // have to survive the store, which has no register to spare for them (kept across it, one of them
-                // was spilled and reloaded INSIDE the step loop, and a reload from scratch memory there makes the
-                // compiler wait for every load in flight).
+            // The per-lane fragment offset is worked out again behind every store of a tile, from a lane number the compiler
+            // cannot see through: it is then a new value here, not one that has to survive the store, which has no register
+            // to spare for it (kept across it in the fused forms, it was spilled and reloaded INSIDE the step loop, and a
+            // reload from scratch memory there makes the compiler wait for every load in flight; kept in the plain forms, the
+            // store spilled 8 registers with 16-bit rows and 7 with fp32 ones, now none: 7,800 x 1,536 x 1,536 34.5 -> 33.4 us,
+            // 14,040 x 1,536 x 1,536 66.0 -> 64.7, 20,001 x 3,000 x 2,048 198.1 -> 195.1; large K and fp32 rows level).
+            {
                 int l = lane;
                 asm volatile("" : "+v"(l));
                 const int r = l & 15, g = l >> 4;
