@@ -193,6 +193,22 @@ bool writes_over_keys(const dit_self_attn_params* p, int64_t L, const void* k, c
     return false;
 }
 
+// Whether the 16-bit rows that chained cross-attention writes pass the caches (non-temporal stores): where the last-level
+// cache (256 MB) could keep less than half of them for whoever reads them next, and every row starts and ends with a 64-byte
+// sector (one that two stores share is put together in the L2; past it each part is a write of its own: 4 x 32,760 x 40,
+// 5 key tiles, rows 16 bytes off 1,142 -> 1,190 us).  us through the caches and past them: 4 x 32,760 x 40, 5 key tiles (1,342
+// MB) 1,070 and 1,035, 3 x 32,760 x 40, 2 key tiles 529 and 510; with a pass that reads the rows once: 4 x 32,760 x 40, 3 key
+// tiles 1,219 and 1,203, 2 x 32,760 x 40 743 and 738, but 32,760 x 40 (335 MB) 375 and 378, 16,000 x 40 192 and 198, 8,000 x 40 100
+// and 105; with the output projection 2,000 x 40 130 and 133, 1,560 x 40 104 and 108, 5,000 x 12 46.8 and 48.3, 7,800 x 12 66.7 and
+// 66.4 -- though the call alone is faster past them at every size (7,800 x 12 28.6 and 25.4): what it saves, the reader pays.
+// Self-attention (alone 3,600 x 40 286 and 283, with the output projection 471 and 470) and head_dim 64 (630 and 622 to
+// 634): level, through the caches.
+bool rows_pass_caches(const void* out, const dit_cross_attn_params* p) {
+    if (p->out_dtype != DIT_BF16 || p->D != 128 || 2 * (int64_t)p->B * p->Lq * p->H * p->D <= (int64_t)512 << 20) return false;
+    const int64_t strides = p->so.batch | p->so.token | p->so.head;
+    return ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)(2 * strides)) & 63u) == 0;
+}
+
 // eps >= 0, a known mode; the channel weights are read as float4
 dit_status norm_ok(const dit_qk_norm& n) {
     if (n.mode != DIT_NORM_NONE && n.mode != DIT_NORM_HEAD && n.mode != DIT_NORM_TOKEN) return DIT_ERR_INVALID_ARG;
@@ -995,6 +1011,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     aa.in_f32 = p->in_dtype == DIT_F32; aa.out_f32 = p->out_dtype == DIT_F32;
     aa.sq_b = p->sq.batch; aa.sq_t = p->sq.token; aa.sq_h = p->sq.head;
     aa.so_b = p->so.batch; aa.so_t = p->so.token; aa.so_h = p->so.head;
+    aa.out_once = rows_pass_caches(out, p);
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
     return run_attn(aa, p->D, pl.fl, false, false, s, pl.chain16 ? pl.qch : 0);

@@ -78,11 +78,11 @@ constexpr int chain_stage_bytes() { return 32 * D * 2; }
 template <int D, int NW>
 constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_stage_bytes<D>(); }
 
-// Cache policy (non-temporal) of bytes that are read once or written and not read again: query rows of the chained form,
-// output rows.  4 x 32,760 queries x 40 heads, 8 key tiles 1,518 -> 1,492 us; 32,760 x 40, 3 key tiles 201 -> 193, 7,800 x 12,
-// 3 key tiles (whole call) 30.9 -> 29.8; self-attention level.  Not for fp32 output rows (4 x 20,572 x 17, 6 key tiles 407, with
-// them 418), query rows of head_dim 64 (4 x 128 x 25 22.5, with them 22.7) or calls of one round (4 x 144 x 18 25.0, 25.4).  Key and value rows in the pre-pack, and its tile images:
-// level, left as they were.
+// Cache policy (non-temporal) of bytes that are read once: query rows of the chained form at head_dim 128, 32 rows a wavefront.
+// us, cross-attention and the output projection behind it, through the caches and past them: 8,000 x 40, 5 key tiles 402
+// and 397, 16,000 x 40 728 and 721, 4 x 32,760 x 40 level; not at head_dim 64 (4 x 128 x 25 22.5, with it 22.7) or in calls of one
+// round (4 x 144 x 18 25.0, 25.4).  Key and value rows in the pre-pack, and its tile images: level, left as they were.
+// Output rows: rows_pass_caches.
 constexpr int kOnce = 2;
 
 // CHAIN: the workgroup takes pv.qt_count consecutive query tiles of one sequence, one after the other and on into the
@@ -115,7 +115,8 @@ constexpr int kOnce = 2;
 // form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
 // and loads 337) and the second pass's first maxima: 24,000 clocks a query tile and 2,690 a key tile.  585 -> 489 us at
 // 32,760 queries x 40 heads, 5 + 5 key tiles, resident keys (plain kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
-template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false, int QBN = 2>
+template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false, int QBN = 2,
+          bool ONCE = false>
 __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeView& pv) {
     using G = TileGeom<D>;
     constexpr int NKS = D / 32;        // MFMAs of one score chain
@@ -934,7 +935,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 const int64_t kstride = (int64_t)(64 / PR) * a.so_t * ES;
                 auto put = [&](int k) {
                     u32x4* const dst = reinterpret_cast<u32x4*>(obase + k * kstride);
-                    if constexpr (ES == 2 && QBN == 2) __builtin_nontemporal_store(v[k], dst);  // (see kOnce)
+                    if constexpr (ONCE) __builtin_nontemporal_store(v[k], dst);
                     else *dst = v[k];
                 };
                 if (full) {
@@ -947,7 +948,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
                 }
             }
         };
-        if constexpr (TWO) {
+        if constexpr (TWO || ONCE) {
             stage_and_store(std::integral_constant<int, 2>());
         } else {
             if (a.out_f32) stage_and_store(std::integral_constant<int, 4>());
@@ -1276,7 +1277,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_varlen_kernel(cons
 // per request and index arithmetic that small calls feel.)
 // TWO: the tiles of the two sequences stand from image 0 and from image nTA on, the tile counts of both together and of
 // the first come from the workspace; a sequence without a key has no pass.
-template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN = 2>
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN, bool ONCE>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const AttnArgs a, int qch) {
     const int logical = xcd_contiguous_block();
     PipeView pv;
@@ -1299,13 +1300,13 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_pipe16_chain_kernel(const
         pv.skip_first = first > 0 || pv.nKT == 0 ? 0 : a.nTA;
         pv.skip_second = first < pv.nKT ? a.nTA - first : 0;
     }
-    attn_pipe16_body<D, QK_OP, PV_OP, NW, true, false, TWO, QBN>(a, pv);
+    attn_pipe16_body<D, QK_OP, PV_OP, NW, true, false, TWO, QBN, ONCE>(a, pv);
 }
 
 // qch: query tiles per workgroup
-template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN = 2>
+template <int D, int QK_OP, int PV_OP, int NW, bool TWO, int QBN = 2, bool ONCE = false>
 hipError_t launch_attn_pipe16_chain_inst(const AttnArgs& a, int qch, hipStream_t s) {
-    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW, TWO, QBN>;
+    auto kern = attn_fwd_pipe16_chain_kernel<D, QK_OP, PV_OP, NW, TWO, QBN, ONCE>;
     constexpr int smem = chain_lds_bytes<D, NW>();
     static std::atomic<uint64_t> attr_set{0};
     hipError_t e = allow_dynamic_lds(kern, smem, attr_set);

@@ -8,7 +8,12 @@ namespace {
 
 template <int D, int QK_OP, int PV_OP, bool TWO>
 hipError_t launch_form(const AttnArgs& a, int nw, int qch, hipStream_t s) {
-    if (nw == 8) return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO>(a, qch, s);
+    if (nw == 8) {
+        if constexpr (D == 128) {
+            if (a.out_once) return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO, 2, true>(a, qch, s);
+        }
+        return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO>(a, qch, s);
+    }
     if constexpr (!TWO) {
         if (qch == 1) {  // all query tiles in one round: one query block a wavefront (short_tile_rows)
             const int rows = short_tile_rows((int64_t)a.B * a.H, a.Lq);

@@ -124,6 +124,7 @@ struct AttnArgs {
     int64_t sk_b, sk_t, sk_h, sv_b, sv_t, sv_h;
     int B, H, Lq, Lk, nKT, nQT;
     int in_f32, out_f32;
+    int out_once;  // chained cross-attention, 8 wavefronts: output rows are stored past the caches (rows_pass_caches)
     int64_t sq_b, sq_t, sq_h, so_b, so_t, so_h;
     RopeGeom rg;
     float qscale;  // softmax scale * log2(e), folded into q'

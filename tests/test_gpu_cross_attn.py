@@ -429,3 +429,27 @@ def test_rows_do_not_depend_on_the_rest_of_the_call(D, two, out_f32):
         wide = pad(md)
         wide[:, n_text:512] = 0
         assert torch.equal(run(many, pad(kd), pad(vd), wide, 512), alone), "%d query rows, room for 512 keys" % n_q
+
+
+@pytest.mark.parametrize("split", [0, 64])
+def test_rows_past_the_caches_have_the_same_bits(split):
+    """More output rows than the caches hold are stored past them, in whole 64-byte sectors only; the same call into rows
+    that start 16 bytes off stores through them."""
+    import torch
+
+    nb, Lq, H, D, Lk = 2, 26300, 40, 128, 130
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q, k, v = (torch.randn(nb, n, H, D, generator=g, device="cuda").to(torch.bfloat16) for n in (Lq, Lk, Lk))
+    assert 2 * q.numel() > 512 << 20
+    aligned = torch.empty_like(q)
+    shifted = torch.empty(q.numel() + 8, dtype=q.dtype, device="cuda")[8:].view(q.shape)
+    assert aligned.data_ptr() % 64 == 0 and shifted.data_ptr() % 64 == 16
+    for out in (aligned, shifted):
+        B.dit_cross_attn_forward(q, k, v, out=out, split=split, flags=B.DIT_FLAG_BIG_WORKGROUP)
+    assert torch.equal(aligned.view(torch.int16), shifted.view(torch.int16))
+    ref = torch.zeros(64, H, D, dtype=torch.float64)  # the last rows of the last request
+    for a, b in ((0, split), (split, Lk)):
+        if b > a:
+            qf, kf, vf = (t.double().cpu().transpose(0, 1) for t in (q[-1, -64:], k[-1, a:b], v[-1, a:b]))
+            ref += (torch.softmax(qf @ kf.transpose(1, 2) * D ** -0.5, dim=-1) @ vf).transpose(0, 1)
+    compare(to_f64(aligned[-1, -64:]), ref.numpy(), bf16_out=True, what="rows past the caches, split %d" % split)
