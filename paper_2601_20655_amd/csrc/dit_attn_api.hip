@@ -114,17 +114,17 @@ struct ShortCall {
     const dit::NormArgs* kn;
 };
 
-// Attention kernel launch, bracketed by the caller's timing events when the hook is set.  chain16: query tiles per
-// workgroup of the chained cross-attention kernel, 0 for the other kernels.
+// Attention kernel launch, bracketed by the caller's timing events when the hook is set.  chain: layout of the chained
+// cross-attention kernel, null for the other kernels.
 dit_status run_attn(const dit::AttnArgs& aa, int D, const Flags& fl, bool fused, bool mfma16, hipStream_t s,
-                    int chain16 = 0, const ShortCall* sc = nullptr) {
+                    const dit::ChainLayout* chain = nullptr, const ShortCall* sc = nullptr) {
     const bool timed = g_ev_before && g_ev_after;
     hipError_t e;
     if (timed && (e = hipEventRecord(g_ev_before, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (sc) {
         e = dit::launch_attn_short(aa, *sc->table, *sc->kn, D, sc->qb, sc->packed, s);
-    } else if (chain16) {
-        e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, fl.nw, chain16, s);
+    } else if (chain) {
+        e = dit::launch_attn_pipe16_chain(aa, D, fl.qk_op, fl.pv_op, *chain, s);
     } else if (aa.tile_count_a) {
         e = dit::launch_attn_split(aa, D, fl.qk_op, fl.pv_op, s);
     } else if (mfma16 && aa.split.n_tail > 0) {
@@ -720,29 +720,30 @@ void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* n
     *nw = best_nw;
 }
 
+// One softmax whose 128-row query tiles are one round of workgroups takes those, or 64-row ones where they are too, in 16 rows
+// a wavefront (see attn_pipe16_body); everything else goes by the estimate.
+dit::ChainLayout dit::layout_chain(int Lq, int B, int64_t H, int nKT, int D, bool two, int cus, int nw) {
+    ChainLayout c{nw, 32, 1};
+    if (nw != 8 && !two && (int64_t)(Lq + 127) / 128 * B * H <= cus) {
+        c.nw = short_tile_rows(B * H, Lq, cus) / 16;
+        c.rows = 16;
+    } else {
+        choose_chain(Lq, B, H, nKT, D, cus, &c.nw, &c.qch);
+    }
+    return c;
+}
+
 namespace {
 
 struct CrossPlan {
     Flags fl;
     bool layout16;  // tile images in the layout of the 16x16x32 kernels
     bool chain16;  // the chained 16x16x32 kernel (default)
-    int qch;       // with it: query tiles per workgroup
+    dit::ChainLayout chain;  // with it
     int nKT, nQT;
     int split, nTA;  // decoupled form: first key of the second sequence, tiles of the first (0, 0: joint)
     size_t mask_off, list_off, count_off, count_a_off, keysrc_off, tiles_off, rstd_off, total;
 };
-
-// Wavefronts and chain length of a call, nw as its flags ask for (0: either).  One softmax whose 128-row query tiles are one
-// round of workgroups takes those (16 rows a wavefront then, see short_tile_rows), two softmaxes go by the estimate.
-void layout_chain(const dit_cross_attn_params* p, int cus, int nw, CrossPlan* pl) {
-    pl->fl.nw = nw;
-    if (nw != 8 && pl->split == 0 && (int64_t)(p->Lq + 127) / 128 * p->B * p->H <= cus) {
-        pl->fl.nw = 4;
-        pl->qch = 1;
-    } else {
-        dit::choose_chain(p->Lq, p->B, p->H, pl->nKT, p->D, cus, &pl->fl.nw, &pl->qch);
-    }
-}
 
 dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     if (!p) return DIT_ERR_INVALID_ARG;
@@ -786,7 +787,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
     pl->chain16 = pl->layout16 && bf16 && (pl->split == 0 || p->out_dtype == DIT_BF16);
     if (!pl->fl.pipelined && !pl->chain16) pl->fl.simple = true;
     if (pl->chain16) {
-        layout_chain(p, kCUs, pl->fl.nw, pl);
+        pl->chain = dit::layout_chain(p->Lq, p->B, p->H, pl->nKT, p->D, pl->split > 0, kCUs, pl->fl.nw);
     } else if (pl->fl.simple || pl->fl.qb == 2) {
         pl->fl.nw = 4;
     } else if (pl->fl.nw == 0) {
@@ -794,7 +795,7 @@ dit_status plan_cross(const dit_cross_attn_params* p, CrossPlan* pl) {
         // prologue and epilogue better than one large workgroup saves on tile traffic (measured)
         pl->fl.nw = 4;
     }
-    const int bq = 32 * pl->fl.nw * pl->fl.qb;
+    const int bq = pl->chain16 ? pl->chain.nw * pl->chain.rows : 32 * pl->fl.nw * pl->fl.qb;
     pl->nQT = (p->Lq + bq - 1) / bq;
     if ((int64_t)pl->nQT * p->B * p->H > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
     if ((int64_t)pl->nKT * p->B * p->H > 0x7fffffffLL) return DIT_ERR_UNSUPPORTED;
@@ -911,7 +912,7 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     if (pl.short_qb > 0) {
         aa.nQT = (int)((pl.L + 16 * pl.short_qb - 1) / (16 * pl.short_qb));
         const ShortCall sc{pl.short_qb, !one, &ta, &kn};
-        return run_attn(aa, p->D, pl.fl, false, true, s, 0, &sc);
+        return run_attn(aa, p->D, pl.fl, false, true, s, nullptr, &sc);
     }
     apply_split(&pl, p->D, ws, workspace_bytes, &aa);
     return run_attn(aa, p->D, pl.fl, pl.fl.fused, self_attn_uses_mfma16(pl.fl), s);
@@ -950,8 +951,8 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
         const hipError_t e = dit::compute_units(&cus);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
         if (cus != kCUs) {
-            layout_chain(p, cus, (p->flags & DIT_FLAG_BIG_WORKGROUP) ? 8 : (p->flags & DIT_FLAG_SMALL_WORKGROUP) ? 4 : 0, &pl);
-            pl.nQT = (p->Lq + 32 * pl.fl.nw - 1) / (32 * pl.fl.nw);
+            pl.chain = dit::layout_chain(p->Lq, p->B, p->H, pl.nKT, p->D, pl.split > 0, cus, pl.fl.nw);
+            pl.nQT = (p->Lq + pl.chain.nw * pl.chain.rows - 1) / (pl.chain.nw * pl.chain.rows);
         }
     }
 
@@ -1014,7 +1015,7 @@ dit_status cross_forward(const void* q, const void* k, const void* v, const uint
     aa.out_once = rows_pass_caches(out, p);
     aa.qscale = scale * dit::kLog2e;
     aa.qn = qn;
-    return run_attn(aa, p->D, pl.fl, false, false, s, pl.chain16 ? pl.qch : 0);
+    return run_attn(aa, p->D, pl.fl, false, false, s, pl.chain16 ? &pl.chain : nullptr);
 }
 
 }  // namespace

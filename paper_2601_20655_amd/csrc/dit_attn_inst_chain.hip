@@ -7,32 +7,25 @@ namespace dit {
 namespace {
 
 template <int D, int QK_OP, int PV_OP, bool TWO>
-hipError_t launch_form(const AttnArgs& a, int nw, int qch, hipStream_t s) {
-    if (nw == 8) {
-        if constexpr (D == 128) {
-            if (a.out_once) return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO, 2, true>(a, qch, s);
-        }
-        return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO>(a, qch, s);
-    }
+hipError_t launch_form(const AttnArgs& a, const ChainLayout& c, hipStream_t s) {
     if constexpr (!TWO) {
-        if (qch == 1) {  // all query tiles in one round: one query block a wavefront (short_tile_rows)
-            const int rows = short_tile_rows((int64_t)a.B * a.H, a.Lq);
-            AttnArgs b = a;
-            b.nQT = (a.Lq + rows - 1) / rows;
-            if ((int64_t)b.nQT * a.B * a.H <= kCUs)
-                return rows == 64 ? launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 4, false, 1>(b, 1, s)
-                                  : launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, false, 1>(b, 1, s);
-        }
+        if (c.rows == 16)
+            return c.nw == 8 ? launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, false, 1>(a, c.qch, s)
+                             : launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 4, false, 1>(a, c.qch, s);
     }
-    return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 4, TWO>(a, qch, s);
+    if (c.nw != 8) return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 4, TWO>(a, c.qch, s);
+    if constexpr (D == 128) {
+        if (a.out_once) return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO, 2, true>(a, c.qch, s);
+    }
+    return launch_attn_pipe16_chain_inst<D, QK_OP, PV_OP, 8, TWO>(a, c.qch, s);
 }
 
 }  // namespace
 
-hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s) {
+hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c, hipStream_t s) {
 #define DIT_CASE(TWO, DD, QK, PV)                                                                 \
     if ((a.tile_count_a != nullptr) == TWO && D == DD && qk_op == QK && pv_op == PV)               \
-        return launch_form<DD, QK, PV, TWO>(a, nw, qch, s);
+        return launch_form<DD, QK, PV, TWO>(a, c, s);
     DIT_CASE(false, 128, OP_F16, OP_F16)
     DIT_CASE(false, 128, OP_F16, OP_BF16)
     DIT_CASE(false, 128, OP_BF16, OP_F16)

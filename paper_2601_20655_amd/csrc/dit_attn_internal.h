@@ -186,11 +186,18 @@ constexpr int kCUs = 256;
 // Query rows per workgroup of self-attention in the small form (4 wavefronts of 32 rows, two workgroups a compute unit), whose
 // workgroups are reshaped where they fit one round with a compute unit each: 64 rows (4 wavefronts of 16) if those do, else
 // 128 (8 of 16 where they do, else 4 of 32).
-inline int short_tile_rows(int64_t BH, int64_t L) { return BH * ((L + 63) / 64) <= kCUs ? 64 : 128; }
+inline int short_tile_rows(int64_t BH, int64_t L, int cus = kCUs) { return BH * ((L + 63) / 64) <= cus ? 64 : 128; }
 
 // Layout of the chained cross-attention kernel on `cus` compute units (the host tests read it).  *nw: 4 or 8 if asked for, 0
 // to choose.
 void choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* nw, int* qch);
+struct ChainLayout {
+    int nw;    // wavefronts per workgroup
+    int rows;  // query rows per wavefront, 32 or 16
+    int qch;   // query tiles (of nw * rows rows) per workgroup
+};
+// The layout of a call: that one, or 16 rows a wavefront.  two: one softmax for each of two key groups.  nw as above.
+ChainLayout layout_chain(int Lq, int B, int64_t H, int nKT, int D, bool two, int cus, int nw);
 
 // How a packed call (params: dit_varlen_attn_params) with this workspace is laid over the chip: wavefronts per workgroup
 // (0: it is refused) and query tiles computed in pieces.  No device is touched; the host tests read it.
@@ -212,7 +219,7 @@ hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
 // (AttnArgs::tile_count_a set: two softmaxes, head_dim 128, fp16 operands and 16-bit output rows only)
-hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, int nw, int qch, hipStream_t s);
+hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c, hipStream_t s);
 // whether the masks of such a call (split: first key of the second group, 0 = one group) are listed beforehand (the next
 // two passes); launch_prepack sorts out the others by itself
 bool mask_needs_key_list(int B, int H, int Lk, int split);

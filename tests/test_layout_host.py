@@ -76,6 +76,35 @@ def test_layouts_follow_the_compute_units_of_the_device():
     assert whole < part
 
 
+class ChainLayout(ctypes.Structure):
+    _fields_ = [("nw", ctypes.c_int), ("rows", ctypes.c_int), ("qch", ctypes.c_int)]
+
+
+def call_layout(Lq, nb, H, nKT, D, two=False, cus=256, nw=0):
+    """Wavefronts per workgroup, query rows per wavefront and query tiles per workgroup that a cross-attention call gets."""
+    f = B.lib()._ZN3dit12layout_chainEiiliibii
+    f.restype = ChainLayout
+    f.argtypes = 2 * [ctypes.c_int] + [ctypes.c_int64] + 2 * [ctypes.c_int] + [ctypes.c_bool] + 2 * [ctypes.c_int]
+    c = f(Lq, nb, H, nKT, D, two, cus, nw)
+    return c.nw, c.rows, c.qch
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("cus", [256, 64, 32])
+def test_one_round_of_query_tiles_takes_16_rows_a_wavefront(D, cus):
+    """On however many compute units the device has: 64-row tiles while those are one round, then 128-row ones."""
+    for nb, H in ((1, 1), (2, 3), (1, 20)):
+        per = cus // (nb * H)  # tiles a head in one round
+        assert call_layout(64 * per, nb, H, 5, D, cus=cus) == (4, 16, 1)
+        assert call_layout(64 * per + 1, nb, H, 5, D, cus=cus) == (8, 16, 1)
+        assert call_layout(128 * per, nb, H, 5, D, cus=cus, nw=4) == (8, 16, 1)
+        for asked in (0, 4, 8):
+            c = call_layout(128 * per + 1, nb, H, 5, D, cus=cus, nw=asked)
+            assert c[1] == 32 and c[0::2] == chain_layout(128 * per + 1, nb, H, 5, D, asked, cus)
+        # two softmaxes and 256-row workgroups have no such form
+        assert call_layout(64, nb, H, 5, D, two=True, cus=cus)[1] == call_layout(64, nb, H, 5, D, cus=cus, nw=8)[1] == 32
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("nw", [0, 4, 8])
 def test_chains_stay_inside_a_request(D, nw):
