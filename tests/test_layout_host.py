@@ -124,8 +124,10 @@ def test_chained_shapes_of_the_gpu_tests_cross_from_head_to_head():
     for (nb, H, tiles, keys), dims in ((CHAINS_ONE, (64, 128)), (CHAINS_TWO, (128,))):
         for D in dims:
             for nw in (4, 8):
-                _, chain = chain_layout(32 * nw * (tiles - 1) + 11, nb, H, sum((n + 63) // 64 for n in keys), D, nw)
+                Lq, nKT = 32 * nw * (tiles - 1) + 11, sum((n + 63) // 64 for n in keys)
+                _, chain = chain_layout(Lq, nb, H, nKT, D, nw)
                 assert chain > 1 and tiles % chain != 0
+                assert call_layout(Lq, nb, H, nKT, D, two=len(keys) > 1 and dims == (128,), nw=nw) == (nw, 32, chain)
 
 
 def test_projection_shapes_of_the_gpu_tests_run_on_the_tiles_they_are_meant_for():
