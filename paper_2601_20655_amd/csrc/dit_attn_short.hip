@@ -130,7 +130,8 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
     };
 
     // ---- rotation table and channel weights, in LDS; the first workgroup leaves the table in the workspace too ----
-    for (int i = tid; i < 2 * D; i += 64 * kShortWaves) {
+    // (RESIDENT: the weights of the k rows are in the tiles; their array is not read, it may be gone)
+    for (int i = tid; i < (RESIDENT ? D : 2 * D); i += 64 * kShortWaves) {
         const float* const src = i < D ? a.qn.gamma : kn.gamma;
         gamma[i] = src ? src[(int64_t)h * D + (i & (D - 1))] : 1.f;
     }
