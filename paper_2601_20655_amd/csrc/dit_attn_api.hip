@@ -100,7 +100,8 @@ bool self_attn_uses_mfma16(const Flags& fl) {
     return !fl.fused && !fl.simple && fl.qb == 1 && fl.qk_op != dit::OP_FP8 && !fl.mfma32;
 }
 
-// The one-launch kernel has the default operand types only, and asking for a workgroup size asks for the general kernel.
+// The one-launch kernel has the default operand types only, and asking for a workgroup size asks for the general
+// kernel.
 bool takes_short(const Flags& fl, uint32_t flags) {
     return self_attn_uses_mfma16(fl) && fl.qk_op == dit::OP_F16 && fl.pv_op == dit::OP_F16 &&
            !(flags & (DIT_FLAG_BIG_WORKGROUP | DIT_FLAG_SMALL_WORKGROUP));
@@ -180,8 +181,8 @@ Span span_of(const float* p, int64_t n) {
     return {begin, p ? begin + (uintptr_t)n * 4 : begin};
 }
 
-// Whether what a self-attention call writes (out, lse) meets what its key-side passes read (k, v, the weights of the key
-// rows): those passes then have to be over before the first row of out is written.
+// Whether what a self-attention call writes (out, lse) meets what its key-side passes read (k, v, the weights of the
+// key rows): those passes then have to be over before the first row of out is written.
 bool writes_over_keys(const dit_self_attn_params* p, int64_t L, const void* k, const void* v, const void* out,
                       const float* lse) {
     const Span rows = span_of(out, p->so, p->out_dtype, p->B, p->H, p->D, L);
@@ -193,18 +194,19 @@ bool writes_over_keys(const dit_self_attn_params* p, int64_t L, const void* k, c
     return false;
 }
 
-// Whether the 16-bit rows that chained cross-attention writes pass the caches (non-temporal stores): where the last-level
-// cache (256 MB) could keep less than half of them for whoever reads them next, and every row starts and ends with a 64-byte
-// sector (one that two stores share is put together in the L2; past it each part is a write of its own: 4 x 32,760 x 40,
-// 5 key tiles, rows 16 bytes off 1,142 -> 1,190 us).  us through the caches and past them: 4 x 32,760 x 40, 5 key tiles (1,342
-// MB) 1,070 and 1,035, 3 x 32,760 x 40, 2 key tiles 529 and 510; with a pass that reads the rows once: 4 x 32,760 x 40, 3 key
-// tiles 1,219 and 1,203, 2 x 32,760 x 40 743 and 738, but 32,760 x 40 (335 MB) 375 and 378, 16,000 x 40 192 and 198, 8,000 x 40 100
-// and 105; with the output projection 2,000 x 40 130 and 133, 1,560 x 40 104 and 108, 5,000 x 12 46.8 and 48.3, 7,800 x 12 66.7 and
-// 66.4 -- though the call alone is faster past them at every size (7,800 x 12 28.6 and 25.4): what it saves, the reader pays.
-// Self-attention (alone 3,600 x 40 286 and 283, with the output projection 471 and 470) and head_dim 64 (630 and 622 to
-// 634): level, through the caches.
+// Whether the 16-bit rows that chained cross-attention writes pass the caches (non-temporal stores): where the
+// last-level cache (256 MB) could keep less than half of them for whoever reads them next, and every row starts and
+// ends with a 64-byte sector (one that two stores share is put together in the L2; past it each part is a write of its
+// own: 4 x 32,760 x 40, 5 key tiles, rows 16 bytes off 1,142 -> 1,190 us).  us through the caches and past them: 4 x
+// 32,760 x 40, 5 key tiles (1,342 MB) 1,070 and 1,035, 3 x 32,760 x 40, 2 key tiles 529 and 510; with a pass that reads
+// the rows once: 4 x 32,760 x 40, 3 key tiles 1,219 and 1,203, 2 x 32,760 x 40 743 and 738, but 32,760 x 40 (335 MB)
+// 375 and 378, 16,000 x 40 192 and 198, 8,000 x 40 100 and 105; with the output projection 2,000 x 40 130 and 133,
+// 1,560 x 40 104 and 108, 5,000 x 12 46.8 and 48.3, 7,800 x 12 66.7 and 66.4 -- though the call alone is faster past
+// them at every size (7,800 x 12 28.6 and 25.4): what it saves, the reader pays.  Self-attention (alone 3,600 x 40 286
+// and 283, with the output projection 471 and 470) and head_dim 64 (630 and 622 to 634): level, through the caches.
 bool rows_pass_caches(const void* out, const dit_cross_attn_params* p) {
-    if (p->out_dtype != DIT_BF16 || p->D != 128 || 2 * (int64_t)p->B * p->Lq * p->H * p->D <= (int64_t)512 << 20) return false;
+    const int64_t bytes = 2 * (int64_t)p->B * p->Lq * p->H * p->D;
+    if (p->out_dtype != DIT_BF16 || p->D != 128 || bytes <= (int64_t)512 << 20) return false;
     const int64_t strides = p->so.batch | p->so.token | p->so.head;
     return ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)(2 * strides)) & 63u) == 0;
 }
@@ -272,7 +274,7 @@ struct SelfPlan {
     dit::SplitPlan split;
     int split_nQT;
     size_t total;
-    int short_qb;  // > 0: one launch for everything, in workgroups of 16 short_qb query rows
+    int short_qb;  // > 0: the kernel for short sequences, in workgroups of 16 short_qb query rows
 };
 
 // How the self-attention kernel on 16x16x32 MFMAs is laid over the chip.  Estimates of its time in key-tile steps of an
@@ -280,13 +282,18 @@ struct SelfPlan {
 // 21 shapes of 320 to 75,600 tokens and 2 to 40 heads, both head dimensions:
 //   - a workgroup's start and end cost 7.5 steps, the end of a piece one more;
 //   - with 4 wavefronts (128 rows) a compute unit holds two workgroups, which together take 1.04 of the 8-wavefront
-//     step; one alone takes 0.83 of it; where all of them together are one round, in 16 rows a wavefront (short_tile_rows),
-//     0.58 + 0.001 a workgroup (1,600 x 3: 0.61, 1,600 x 9: 0.68, 6,240 x 4: 0.73, 1,600 x 19: 0.84), and in 64-row tiles 0.59;
+//     step; one alone takes 0.83 of it; where all of them together are one round, in 16 rows a wavefront
+//     (short_tile_rows), 0.58 + 0.001 a workgroup (1,600 x 3: 0.61, 1,600 x 9: 0.68, 6,240 x 4: 0.73, 1,600 x 19:
+//     0.84), and in 64-row tiles 0.59;
 //   - combining P pieces costs a launch and 2 x 256 rows of fp32 each: 3 + 0.037 P steps.
 // The measured order of the forms follows these numbers wherever they are more than a few per cent apart: e.g. (tokens,
 // heads) 3,600 x 3: 62.7 us in whole tiles, 40.1 in 5 pieces each; 6,240 x 4: 101.8 and 86.6 (2 pieces); 3,600 x 40:
 // 262 and 258 (last 88 of 600 tiles in 2 pieces); 75,600 x 2: 5,294 and 4,395 (last 80 of 592 in 3 pieces); level or
 // slower in pieces, and left whole: 1,560 x 12 (33.1 and 37.2), 6,307 x 20 (336 and 357), 20,280 x 3 (497 and 518).
+// The figures of 16 rows a wavefront, and the 0.92 below, come from few shapes; at 50 of 640 to 10,125 tokens x 2 to 40
+// heads, 39 to 247 tiles, both head dimensions, the choice was never more than 2 % slower than the better of whole
+// tiles and pieces (3,600 x 6 65.3 whole, 67.9 in pieces, x 4 57.8 and 52.8; 4,800 x 6 88.4 and 86.9; 2,400 x 12 55.8,
+// 62.4).
 using dit::kCUs;
 constexpr double kEnds = 7.5;
 constexpr int kMaxPieces = 1024;  // 136.3 MB of workspace at head_dim 128
@@ -302,8 +309,8 @@ double whole_tile_steps(int64_t tiles, int64_t tiles64, int nKT, int nw) {
 // nw: the form that runs the tiles whole; tiles, tiles_nw, tiles64: query tiles of 256, of 32 nw and of 64 rows
 dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int64_t tiles64, int nKT, int nw) {
     dit::SplitPlan best{0, 0, 1};
-    // (tiles of 16 rows a wavefront do a little better than their estimate: 3,600 x 8 whole 72.9, in pieces 80.1 at 0.93 of it;
-    // 3,600 x 4 59.8 and 55.5 at 0.91)
+    // (tiles of 16 rows a wavefront do a little better than their estimate: 3,600 x 8 whole 72.9, in pieces 80.1 at
+    // 0.93 of it; 3,600 x 4 59.8 and 55.5 at 0.91)
     double best_steps = (nw == 4 && tiles_nw <= kCUs ? 0.92 : 0.97) * whole_tile_steps(tiles_nw, tiles64, nKT, nw);
     const int64_t rounds = tiles / kCUs;
     if (tiles % kCUs == 0 || tiles > (1 << 20)) return best;
@@ -323,28 +330,30 @@ dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int64_t tiles64, in
 
 }  // namespace
 
-// Every workgroup works on all keys of its head, so this pays while one round of workgroups takes the call.  us a call, one
-// after the other, general path and this (tokens x heads, 16-bit rows): head_dim 64, 16 rows: 256 x 4 16.0 and 9.3, 413 x 8 16.1
-// and 11.4, 512 x 2 16.8 and 10.7, 1,024 x 4 19.3 and 15.7; 32 rows: 512 x 15 16.8 and 13.0, 1,024 x 8 18.2 and 16.0; two
-// rounds, 770 x 8, 20.7 and 27.0 (in one launch).  head_dim 128, 16 rows: 64 x 4 13.7 and 12.0, 256 x 8 16.5 and 15.1, 384 x 10
-// 19.4 and 17.7; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not taken); 32 rows spill there: 413 x 12 25.7.
+// Every workgroup works on all keys of its head, so this pays while one round of workgroups takes the call.  us a call,
+// one after the other, general path and this (tokens x heads, 16-bit rows): head_dim 64, 16 rows: 256 x 4 16.0 and 9.3,
+// 413 x 8 16.1 and 11.4, 512 x 2 16.8 and 10.7, 1,024 x 4 19.3 and 15.7; 32 rows: 512 x 15 16.8 and 13.0, 1,024 x 8
+// 18.2 and 16.0; two rounds, 770 x 8, 20.7 and 27.0 (in one launch).  head_dim 128, 16 rows: 64 x 4 13.7 and 12.0, 256
+// x 8 16.5 and 15.1, 384 x 10 19.4 and 17.7; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not taken); 32 rows spill
+// there: 413 x 12 25.7.
 int dit::choose_short(int64_t L, int64_t BH, int D, int table_entries) {
     if (table_entries > kShortTable || L > (D == 64 ? 1024 : 384)) return 0;
     if (BH * ((L + 15) / 16) <= kCUs) return 1;
     return D == 64 && BH * ((L + 31) / 32) <= kCUs ? 2 : 0;
 }
 
-// One launch saves two, about 2 us on the device and 3 more where the host is what a call waits for, and pays with every
-// workgroup's own table and packing.  What makes that longer adds up, each about a microsecond: fp32 rows, per-token factors
-// (a launch of their own ahead of it, which makes the table on the way otherwise), both together past 256 tokens (fp32 512 x 8
-// 15.8 and 13.2 / 17.4 and 16.5), a table of more than two entries a thread,
-// at head_dim 128 twice the work a key and more than three key tiles, at head_dim 64 more tiles than wavefronts (from 769
-// tokens on for most of them) and 32 query rows.  us in one launch and in three, replayed from a graph / called one after
-// the other, at 0 to 2 of these: head_dim 64, 256 x 4 7.8 and 9.9 / 9.3 and 15.0; 512 x 15 12.3 and 13.7 / 13.0 and 15.5; fp32 576
-// x 4 13.6 and 12.2 / 14.0 and 16.3; head_dim 128, 64 x 40 11.8 and 12.9 / 12.4 and 14.0; 256 x 8 14.6 and 13.8 / 15.1 and 15.0;
-// fp32 192 x 20 15.9 and 15.3 / 16.3 and 17.0; at 3 and more: head_dim 64, 1,024 x 4 16.3 and 14.2 / 17.0 and 15.7, fp32 x 8 23.3
-// and 15.5 / 23.7 and 16.7, fp32, per token, 512 x 15 18.3 and 16.2 / 19.5 and 18.0; head_dim 128, 1 x 6 x 64 tokens x 10 18.7 and
-// 16.6 / 19.1 and 18.0, fp32, per token 23.6 and 19.2 / 24.2 and 20.6 (the general path: 20.2 / 21.6).
+// One launch saves two, about 2 us on the device and 3 more where the host is what a call waits for, and pays with
+// every workgroup's own table and packing.  What makes that longer adds up, each about a microsecond: fp32 rows,
+// per-token factors (a launch of their own ahead of it, which makes the table on the way otherwise), both together past
+// 256 tokens (fp32 512 x 8 15.8 and 13.2 / 17.4 and 16.5), a table of more than two entries a thread,
+// at head_dim 128 twice the work a key and more than three key tiles, at head_dim 64 more tiles than wavefronts (from
+// 769 tokens on for most of them) and 32 query rows.  us in one launch and in three, replayed from a graph / called one
+// after the other, at 0 to 2 of these: head_dim 64, 256 x 4 7.8 and 9.9 / 9.3 and 15.0; 512 x 15 12.3 and 13.7 / 13.0
+// and 15.5; fp32 576 x 4 13.6 and 12.2 / 14.0 and 16.3; head_dim 128, 64 x 40 11.8 and 12.9 / 12.4 and 14.0; 256 x 8
+// 14.6 and 13.8 / 15.1 and 15.0; fp32 192 x 20 15.9 and 15.3 / 16.3 and 17.0; at 3 and more: head_dim 64, 1,024 x 4
+// 16.3 and 14.2 / 17.0 and 15.7, fp32 x 8 23.3 and 15.5 / 23.7 and 16.7, fp32, per token, 512 x 15 18.3 and 16.2 / 19.5
+// and 18.0; head_dim 128, 1 x 6 x 64 tokens x 10 18.7 and 16.6 / 19.1 and 18.0, fp32, per token 23.6 and 19.2 / 24.2
+// and 20.6 (the general path: 20.2 / 21.6).
 bool dit::short_packs_itself(int64_t L, int D, int qb, int table_entries, bool f32_rows, bool token_norm) {
     const int own = D == 64 ? (L > 512) + 2 * (L > 768) + (qb == 2) : 1 + (L > 192);
     const int rows = f32_rows + token_norm + (f32_rows && token_norm && L > 256);
@@ -407,7 +416,8 @@ dit_status plan_self(const dit_self_attn_params* p, SelfPlan* pl) {
     pl->total = pl->base;
     pl->split = dit::SplitPlan{0, 0, 1};
     pl->short_qb = 0;
-    if (takes_short(pl->fl, p->flags)) pl->short_qb = dit::choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
+    if (takes_short(pl->fl, p->flags))
+        pl->short_qb = dit::choose_short(L, (int64_t)p->B * p->H, p->D, pl->table_entries);
     if (self_attn_uses_mfma16(pl->fl) && !(p->flags & DIT_FLAG_SMALL_WORKGROUP)) {
         pl->split_nQT = (int)((L + 255) / 256);
         pl->split = choose_split((int64_t)pl->split_nQT * p->B * p->H, (int64_t)pl->nQT * p->B * p->H,
@@ -624,10 +634,12 @@ dit_status plan_varlen(const dit_varlen_attn_params* p, size_t workspace_bytes, 
         if (pl->fl.nw == 0) pl->fl.nw = big_blocks >= 512 ? 8 : 4;
     } else if (n == 1) {
         // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit
-        const int64_t t8 = ((total + 255) / 256) * p->H, t4 = ((total + 127) / 128) * p->H, t64 = ((total + 63) / 64) * p->H;
+        const int64_t t8 = ((total + 255) / 256) * p->H, t4 = ((total + 127) / 128) * p->H;
+        const int64_t t64 = ((total + 63) / 64) * p->H;
         const int nKT = vt.r[0].nKT;
         if (pl->fl.nw == 0) pl->fl.nw = whole_tile_steps(t8, t64, nKT, 8) <= whole_tile_steps(t4, t64, nKT, 4) ? 8 : 4;
-        if (!(p->flags & DIT_FLAG_SMALL_WORKGROUP)) pl->single = choose_split(t8, pl->fl.nw == 8 ? t8 : t4, t64, nKT, pl->fl.nw);
+        if (!(p->flags & DIT_FLAG_SMALL_WORKGROUP))
+            pl->single = choose_split(t8, pl->fl.nw == 8 ? t8 : t4, t64, nKT, pl->fl.nw);
     } else {
         choose_packed(vt, p->H, p->flags, &pl->fl.nw, pieces);
     }
@@ -720,8 +732,8 @@ void dit::choose_chain(int Lq, int B, int64_t H, int nKT, int D, int cus, int* n
     *nw = best_nw;
 }
 
-// One softmax whose 128-row query tiles are one round of workgroups takes those, or 64-row ones where they are too, in 16 rows
-// a wavefront (see attn_pipe16_body); everything else goes by the estimate.
+// One softmax whose 128-row query tiles are one round of workgroups takes those, or 64-row ones where they are too, in
+// 16 rows a wavefront (see attn_pipe16_body); everything else goes by the estimate.
 dit::ChainLayout dit::layout_chain(int Lq, int B, int64_t H, int nKT, int D, bool two, int cus, int nw) {
     ChainLayout c{nw, 32, 1};
     if (nw != 8 && !two && (int64_t)(Lq + 127) / 128 * B * H <= cus) {
@@ -871,8 +883,8 @@ dit_status dit_attn_forward(const void* q, const void* k, const void* v, void* o
     const bool one = pl.short_qb > 0 && !pl.fl.resident && !writes_over_keys(p, pl.L, k, v, out, lse) &&
                      dit::short_packs_itself(pl.L, p->D, pl.short_qb, pl.table_entries, p->in_dtype == DIT_F32,
                                              p->norm.mode == DIT_NORM_TOKEN);
-    st = setup_rows(pl.fl.resident || one ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L, p->H, p->D,
-                    p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
+    st = setup_rows(pl.fl.resident || one ? nullptr : &ta, p->norm, q, k, p->sq, p->sk, p->B, (int)pl.L, (int)pl.L,
+                    p->H, p->D, p->in_dtype == DIT_F32, ws + pl.rstd_off, &qn, &kn, pl.fl.resident, s);
     if (st != DIT_OK) return st;
 
     if (!pl.fl.fused && !pl.fl.resident && !one) {
@@ -1056,8 +1068,10 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || workspace_bytes < pl.base)
         return DIT_ERR_WORKSPACE;
 
-    // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit; a short one goes there
-    if (pl.vt.n == 1 && takes_short(pl.fl, p->flags) && dit::choose_short(pl.vt.total_tokens, p->H, p->D, pl.table_entries) > 0) {
+    // one request is laid out as dit_attn_forward does it, so that its result is the same bit for bit; a short one goes
+    // there
+    if (pl.vt.n == 1 && takes_short(pl.fl, p->flags) &&
+        dit::choose_short(pl.vt.total_tokens, p->H, p->D, pl.table_entries) > 0) {
         dit_self_attn_params one;
         memset(&one, 0, sizeof(one));
         one.B = 1; one.H = p->H; one.D = p->D;
@@ -1070,7 +1084,8 @@ dit_status dit_attn_varlen_forward(const void* q, const void* k, const void* v, 
         one.sq.batch = one.sk.batch = one.sv.batch = one.so.batch = 0;
         one.norm = p->norm;
         SelfPlan sp;
-        if (plan_self(&one, &sp) == DIT_OK && workspace_bytes >= sp.base)  // (rows that overlap are refused there, not here)
+        // (rows that overlap are refused there, not here)
+        if (plan_self(&one, &sp) == DIT_OK && workspace_bytes >= sp.base)
             return dit_attn_forward(q, k, v, out, lse, &one, workspace, workspace_bytes, stream);
     }
 

@@ -179,12 +179,12 @@ __device__ __forceinline__ void norm8(float x[8], const NormArgs& n, float rs, i
     }
 }
 
-// angle = position * base^(-2i/d_a), d_a = 2 * hd.  base^x = 2^(x log2(base)), the exponent in two parts (log2(base) is,
-// and the product's rounding is kept): as exact as pow() for every base and position that is accepted, and it and the
-// joint sine and cosine are a third of the dependent fp64 instructions of pow(), cos() and sin() -- a table is a few
-// hundred to a few thousand entries, so the time is a launch and one thread's latency: 2.8 -> 2.4 us for 212 entries.
-// (In one part the error of the power grows with |x log2(base)|: base 1e-10 at positions 3 to 7 gave four times the
-// error that the last bits of the power and of the product with the position allow.)
+// angle = position * base^(-2i/d_a), d_a = 2 * hd.  base^x = 2^(x log2(base)), the exponent in two parts (log2(base)
+// is, and the product's rounding is kept): as exact as pow() for every base and position that is accepted, and it and
+// the joint sine and cosine are a third of the dependent fp64 instructions of pow(), cos() and sin() -- a table is a
+// few hundred to a few thousand entries, so the time is a launch and one thread's latency: 2.8 -> 2.4 us for 212
+// entries. (In one part the error of the power grows with |x log2(base)|: base 1e-10 at positions 3 to 7 gave four
+// times the error that the last bits of the power and of the product with the position allow.)
 __device__ __forceinline__ float2 rope_entry(const TableArgs& a, int idx) {
     int ax = 0;
     if (idx >= a.rg.off[2]) ax = 2;

@@ -58,16 +58,17 @@ __device__ __forceinline__ float sum_across_rows16(float x) {
     return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
-// NW = wavefronts per workgroup (4 or 8); a wavefront owns QBN = 2 blocks of 16 query rows, the workgroup's
-// NW * 32 rows share every K/V tile in LDS.
-// QBN = 1: 16 rows a wavefront, for calls whose tiles all fit one round (short_tile_rows).  A fragment read from LDS then
-// feeds one MFMA instead of two, which a full chip pays for (14,040 x 12 1,040 -> 1,340 us); but where compute units have
-// one workgroup each, what counts is how long its steps take: 128 rows by 8 wavefronts, two a SIMD under each other's
-// latencies, instead of 4; 64 rows by 4 where even those fill at most half of the chip.  Whole calls, us, 4 x 32 rows, 8 x 16, 4 x 16,
-// (tokens, heads) head_dim 128: 1,600 x 9 44.1, 38.0, 35.5; 640 x 20 29.3, 26.4, 24.2; 1,020 x 12 34.3, 30.0, 28.2; 640 x 40 33.9,
-// 29.9, (two rounds) 33.0; 3,600 x 8 75.5, 69.7, (79.3); head_dim 64: 1,600 x 9 29.5, 25.9, 25.1; 3,600 x 8 51.1, 44.0.  The same
-// bits in all three.  Chained (cross-attention, tiles in one round), whole calls: 1,000 queries x 20 heads, 757 keys 27.8 ->
-// 24.0, on resident keys 18.8 -> 15.5; 200 x 40, 769 keys 31.5 -> 27.0; head_dim 64 19.0 -> 16.8, 21.1 -> 18.9.
+// NW = wavefronts per workgroup (4 or 8); a wavefront owns QBN (2 or 1) blocks of 16 query rows, the workgroup's
+// NW * 16 QBN rows share every K/V tile in LDS.
+// QBN = 1: 16 rows a wavefront, for calls whose tiles all fit one round (short_tile_rows).  A fragment read from LDS
+// then feeds one MFMA instead of two, which a full chip pays for (14,040 x 12 1,040 -> 1,340 us); but where compute
+// units have one workgroup each, what counts is how long its steps take: 128 rows by 8 wavefronts, two a SIMD under
+// each other's latencies, instead of 4; 64 rows by 4 where even those fill at most half of the chip.  Whole calls, us,
+// 4 x 32 rows, 8 x 16, 4 x 16, (tokens, heads) head_dim 128: 1,600 x 9 44.1, 38.0, 35.5; 640 x 20 29.3, 26.4, 24.2;
+// 1,020 x 12 34.3, 30.0, 28.2; 640 x 40 33.9, 29.9, (two rounds) 33.0; 3,600 x 8 75.5, 69.7, (79.3); head_dim 64: 1,600
+// x 9 29.5, 25.9, 25.1; 3,600 x 8 51.1, 44.0.  The same bits in all three.  Chained (cross-attention, tiles in one
+// round), whole calls: 1,000 queries x 20 heads, 757 keys 27.8 -> 24.0, on resident keys 18.8 -> 15.5; 200 x 40, 769
+// keys 31.5 -> 27.0; head_dim 64 19.0 -> 16.8, 21.1 -> 18.9.
 // The chained form keeps, behind the tile buffers, one area per wavefront the size of its 32 query rows in 16
 // bits.  The rows of the NEXT query tile are copied into it (global -> LDS) while the current one is in its loop;
 // at the boundary they are converted into operand registers, and the area then serves as the staging area of the
@@ -78,11 +79,11 @@ constexpr int chain_stage_bytes() { return 32 * D * 2; }
 template <int D, int NW>
 constexpr int chain_lds_bytes() { return pipe_lds_bytes<D, NW>() + NW * chain_stage_bytes<D>(); }
 
-// Cache policy (non-temporal) of bytes that are read once: query rows of the chained form at head_dim 128, 32 rows a wavefront.
-// us, cross-attention and the output projection behind it, through the caches and past them: 8,000 x 40, 5 key tiles 402
-// and 397, 16,000 x 40 728 and 721, 4 x 32,760 x 40 level; not at head_dim 64 (4 x 128 x 25 22.5, with it 22.7) or in calls of one
-// round (4 x 144 x 18 25.0, 25.4).  Key and value rows in the pre-pack, and its tile images: level, left as they were.
-// Output rows: rows_pass_caches.
+// Cache policy (non-temporal) of bytes that are read once: query rows of the chained form at head_dim 128, 32 rows a
+// wavefront.  us, cross-attention and the output projection behind it, through the caches and past them: 8,000 x 40, 5
+// key tiles 402 and 397, 16,000 x 40 728 and 721, 4 x 32,760 x 40 level; not at head_dim 64 (4 x 128 x 25 22.5, with it
+// 22.7) or in calls of one round (4 x 144 x 18 25.0, 25.4).  Key and value rows in the pre-pack, and its tile images:
+// level, left as they were.  Output rows: rows_pass_caches.
 constexpr int kOnce = 2;
 
 // CHAIN: the workgroup takes pv.qt_count consecutive query tiles of one sequence, one after the other and on into the
@@ -121,7 +122,7 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
     using G = TileGeom<D>;
     constexpr int NKS = D / 32;        // MFMAs of one score chain
     constexpr int NCB = D / 16;        // 16-channel blocks of the output
-    constexpr int NKF = 4 * NKS;       // K' fragments of a tile: (ks, kb), each feeds the two query blocks
+    constexpr int NKF = 4 * NKS;       // K' fragments of a tile: (ks, kb), each feeds the QBN query blocks
     constexpr int NVF = 2 * NCB;       // V^T fragments of a tile: (m, cb)
     constexpr int WR = 16 * QBN;  // query rows of a wavefront
     constexpr int BQ = NW * WR;
@@ -174,7 +175,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             const int row = qtile * BQ + wave * WR + r;
             const int qr = row < pv.Lq ? row : pv.Lq - 1;
             const uint16_t* src = q + (int64_t)qr * a.sq_t + 8 * (slot ^ (r & (QPR - 1)));
-            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0, D == 128 && QBN == 2 ? kOnce : 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(qarea + k * 1024), 16, 0,
+                                             D == 128 && QBN == 2 ? kOnce : 0);
         }
     };
     if constexpr (CHAIN) request_q_lds(h, qt);
@@ -384,15 +386,15 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
 #endif
     constexpr int LA = DIT_PIPE16_LA;  // LDS fragment reads issued this many fragments ahead of their MFMAs
     constexpr int NCH = 8 * QBN;       // softmax slices: two scores -> one dword of P
-    // behind K' fragment f (its QBN score MFMAs) come the slices up to (f + 1) NCH / NKF: one at d128, two at d64 (half as many
-    // with one query block); the maxima behind the V^T fragments likewise
+    // behind K' fragment f (its QBN score MFMAs) come the slices up to (f + 1) NCH / NKF: one at d128, two at d64 (half
+    // as many with one query block); the maxima behind the V^T fragments likewise
     constexpr int CPA = (NCH + NKF - 1) / NKF;
 #ifndef DIT_PIPE16_PRE
 #define DIT_PIPE16_PRE 3
 #endif
     // exp2 of a softmax slice runs this many slices ahead of its pack (at least one fragment's worth)
     constexpr int PRE = DIT_PIPE16_PRE < CPA ? CPA : DIT_PIPE16_PRE;
-    
+    static_assert(CPA * NKF >= NCH && PRE >= CPA, "every slice behind a fragment, its exponentials at least one ahead");
     static_assert(LA <= NKF && LA <= NVF, "lookahead too deep");
 
     const bool late = STAG && wave >= NW / 2;
@@ -506,7 +508,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
         for (int v = 0; v < NVF; ++v) {
             const int m = v / NCB, cb = v % NCB;
             if (v + LA < NVF) vf[v + LA] = v_operand(vt, v + LA);
-            O[cb / 4][0] = mfma16_q<PV_OP>(vf[v], mk4(Pd[0][m][0], Pd[0][m][1], Pd[0][m][2], Pd[0][m][3]), O[cb / 4][0], cb % 4);
+            const auto& P0 = Pd[0][m];
+            O[cb / 4][0] = mfma16_q<PV_OP>(vf[v], mk4(P0[0], P0[1], P0[2], P0[3]), O[cb / 4][0], cb % 4);
             // the first fragment leaves the last score MFMAs time to retire
             if (v >= 1) {
 #pragma unroll
@@ -515,7 +518,8 @@ __device__ __forceinline__ void attn_pipe16_body(const AttnArgs& a, const PipeVi
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (QBN == 2) {
                 const auto& P1 = Pd[QBN - 1][m];
-                O[cb / 4][QBN - 1] = mfma16_q<PV_OP>(vf[v], mk4(P1[0], P1[1], P1[2], P1[3]), O[cb / 4][QBN - 1], cb % 4);
+                O[cb / 4][QBN - 1] =
+                    mfma16_q<PV_OP>(vf[v], mk4(P1[0], P1[1], P1[2], P1[3]), O[cb / 4][QBN - 1], cb % 4);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

@@ -22,7 +22,8 @@ hipError_t launch_form(const AttnArgs& a, const ChainLayout& c, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c, hipStream_t s) {
+hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c,
+                                    hipStream_t s) {
 #define DIT_CASE(TWO, DD, QK, PV)                                                                 \
     if ((a.tile_count_a != nullptr) == TWO && D == DD && qk_op == QK && pv_op == PV)               \
         return launch_form<DD, QK, PV, TWO>(a, c, s);

@@ -180,12 +180,13 @@ inline hipError_t compute_units(int* n) {
     return e == hipSuccess ? hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev) : e;
 }
 
-// Compute units of the chip: layouts and workspace sizes of self-attention go by them, whatever device is current, if any.
+// Compute units of the chip: layouts and workspace sizes of self-attention go by them, whatever device is current, if
+// any.
 constexpr int kCUs = 256;
 
-// Query rows per workgroup of self-attention in the small form (4 wavefronts of 32 rows, two workgroups a compute unit), whose
-// workgroups are reshaped where they fit one round with a compute unit each: 64 rows (4 wavefronts of 16) if those do, else
-// 128 (8 of 16 where they do, else 4 of 32).
+// Query rows per workgroup of self-attention in the small form (4 wavefronts of 32 rows, two workgroups a compute
+// unit), whose workgroups are reshaped where they fit one round with a compute unit each: 64 rows (4 wavefronts of 16)
+// if those do, else 128 (8 of 16 where they do, else 4 of 32).
 inline int short_tile_rows(int64_t BH, int64_t L, int cus = kCUs) { return BH * ((L + 63) / 64) <= cus ? 64 : 128; }
 
 // Layout of the chained cross-attention kernel on `cus` compute units (the host tests read it).  *nw: 4 or 8 if asked for, 0
@@ -219,7 +220,8 @@ hipError_t launch_attn_pipe16_split(const AttnArgs& a, int D, int qk_op, int pv_
 hipError_t launch_attn_pipe16_varlen(const AttnArgs& a, const VarlenTable& vt, int D, int qk_op, int pv_op, int nw,
                                      hipStream_t s);
 // (AttnArgs::tile_count_a set: two softmaxes, head_dim 128, fp16 operands and 16-bit output rows only)
-hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c, hipStream_t s);
+hipError_t launch_attn_pipe16_chain(const AttnArgs& a, int D, int qk_op, int pv_op, const ChainLayout& c,
+                                    hipStream_t s);
 // whether the masks of such a call (split: first key of the second group, 0 = one group) are listed beforehand (the next
 // two passes); launch_prepack sorts out the others by itself
 bool mask_needs_key_list(int B, int H, int Lk, int split);
@@ -228,12 +230,12 @@ bool mask_needs_key_list(int B, int H, int Lk, int split);
 hipError_t launch_key_compact(const PackArgs& a, hipStream_t s);
 // after launch_prepack when a.key_src is set: compact the non-empty tiles of every batch entry into tile_list / tile_count
 hipError_t launch_tile_compact(const PackArgs& a, hipStream_t s);
-// Short sequences (dit_attn_short.hip): a.nQT workgroups of 16 qb query rows a head; packed: the rotation table and the tiles
-// are in the workspace, else the launch makes them for itself and leaves them there.
+// Short sequences (dit_attn_short.hip): a.nQT workgroups of 16 qb query rows a head; packed: the rotation table and the
+// tiles are in the workspace, else the launch makes them for itself and leaves them there.
 constexpr int kShortWaves = 8;     // wavefronts of a workgroup, at most
 constexpr int kShortTable = 2048;  // entries of the rotation table, at most
-// Whether a call takes that kernel, in workgroups of 16 or 32 query rows (1, 2; 0: no), BH sequences and heads; and whether
-// in the one launch (the host tests read both).
+// Whether a call takes that kernel, in workgroups of 16 or 32 query rows (1, 2; 0: no), BH sequences and heads; and
+// whether in the one launch (the host tests read both).
 int choose_short(int64_t L, int64_t BH, int D, int table_entries);
 bool short_packs_itself(int64_t L, int D, int qb, int table_entries, bool f32_rows, bool token_norm);
 hipError_t launch_attn_short(const AttnArgs& a, const TableArgs& ta, const NormArgs& kn, int D, int qb, bool packed,

@@ -3,24 +3,26 @@
 //
 // Sequences of a few hundred tokens are all latency on the general path: three launches one behind the other (rotation
 // table, pre-pack, attention), each of which fills a small part of the chip, and in the last one a wavefront walks the
-// key tiles one by one.  Here the wavefronts of a workgroup take one 64-key tile each (further ones in turn), all at the
-// same time: K rows come from memory straight into the layout of the score MFMA's A operand, where a lane holds eight
-// consecutive channels of a key, that is four whole rotation pairs; V rows go through LDS in rows and come back
+// key tiles one by one.  Here the wavefronts of a workgroup take one 64-key tile each (further ones in turn), all at
+// the same time: K rows come from memory straight into the layout of the score MFMA's A operand, where a lane holds
+// eight consecutive channels of a key, that is four whole rotation pairs; V rows go through LDS in rows and come back
 // transposed (ds_read_b64_tr_b16); each wavefront keeps its own running maximum, and the results are put together
 // through LDS as those of pieces along the keys are.  Every workgroup works out the rotation table and rotates all keys
 // of its head again, which is the price, and why the sequence has to be short (choose_short).
 //
 // The workspace is left as the general path leaves it, byte for byte: rotation table, and tile images in the layout of
-// the 16x16x32 kernels, written from the operand registers by the workgroups of the first query rows.  With RESIDENT the
-// operands are read from such images instead of being made -- after the table and pre-pack kernels of the same call, where
-// it writes over its keys or that is faster (short_packs_itself), or in a call on resident tiles -- with the same bits.
+// the 16x16x32 kernels, written from the operand registers by the workgroups of the first query rows.  With RESIDENT
+// the operands are read from such images instead of being made -- after the table and pre-pack kernels of the same
+// call, where it writes over its keys or that is faster (short_packs_itself), or in a call on resident tiles -- with
+// the same bits.
 //
-// What bounds it: one wavefront's chain of table entry (fp64), rows from memory, rotation, scores, maximum, products and
-// combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it (9 to 10 us) is what the host needs
-// for a launch.  Whole calls, us, three launches and one: 256 tokens x 4 heads x 64 14.9 and 9.3, 256 x 8 x 128 17.6 and 15.0 (see
-// choose_short).  All eight wavefronts work on the table, whatever the number of key tiles: with as many wavefronts as tiles 60
-// tokens x 128 took 16.5 instead of 12.3.  Tried: the first rows requested ahead of the table (registers: 18.3 -> 20.0 at 512 x 2
-// x 128).
+// What bounds it: one wavefront's chain of table entry (fp64), rows from memory, rotation, scores, maximum, products
+// and combination, two wavefronts per SIMD; at head_dim 64 with up to four key tiles all of it (9 to 10 us) is what the
+// host needs for a launch (per-token factors are a launch of their own ahead of it).  Whole calls, us, the general
+// path and this: 256 tokens (4 x 8 x 8) x 4 heads x 64 16.0 and 9.3, 256 (16 x 16) x 8 x 128 16.5 and 15.1, on resident
+// tiles 7.6 and 4.2, 11.3 and 6.5 (more at choose_short and short_packs_itself).  All eight wavefronts work on the
+// table, whatever the number of key tiles: with as many wavefronts as tiles 60 tokens x 128 took 16.5 instead of 12.3.
+// Tried: the first rows requested ahead of the table (registers: 18.3 -> 20.0 at 512 x 2 x 128).
 #include "dit_attn_fwd_pipe16.h"
 
 namespace dit {
@@ -40,7 +42,8 @@ struct ShortGeom {
 
 // IN: 0 bf16 rows, 1 fp32 rows, 2 resident tiles (query rows of either type)
 template <int D, int QB, int IN>
-__global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const AttnArgs a, const TableArgs ta, const NormArgs kn) {
+__global__ void __launch_bounds__(64 * kShortWaves)
+    attn_short_kernel(const AttnArgs a, const TableArgs ta, const NormArgs kn) {
     using G = TileGeom<D>;
     using S = ShortGeom<D>;
     constexpr int NKS = D / 32, NCB = D / 16;
@@ -48,7 +51,8 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
     const bool q_f32 = RESIDENT ? a.in_f32 != 0 : F32;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = a.nKT < kShortWaves ? a.nKT : kShortWaves;  // nt: wavefronts that have key tiles
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = a.nKT < kShortWaves ? a.nKT : kShortWaves;  // wavefronts that have key tiles
     const int i16 = lane & 15, g4 = lane >> 4;
     uint8_t* const area = smem + wave * S::AREA;
     float2* const stats = reinterpret_cast<float2*>(smem + nt * S::AREA);  // [wavefront][16 QB]: maximum, row sum
@@ -74,11 +78,13 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 if constexpr (decltype(f32_tag)::value) {
-                    const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.q) + off + 32 * ks);
+                    const float* const row = static_cast<const float*>(a.q) + off + 32 * ks;
+                    const u32x4* const src = reinterpret_cast<const u32x4*>(row);
                     qraw[qb][ks][0] = src[0];
                     qraw[qb][ks][1] = src[1];
                 } else {
-                    qraw[qb][ks][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.q) + off + 32 * ks);
+                    const uint16_t* const src = static_cast<const uint16_t*>(a.q) + off + 32 * ks;
+                    qraw[qb][ks][0] = *reinterpret_cast<const u32x4*>(src);
                 }
             }
         }
@@ -86,41 +92,42 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
     if (q_f32) request_q(std::true_type{});
     else request_q(std::false_type{});
 
-                // ---- key and value rows of a tile.  Rows past the end: the last one, and zeros in its place as operands. ----
-                u32x4 kraw[4][NKS][2];
-                int key[4];
-                auto request_k = [&](int j, int kb) __attribute__((always_inline)) {
-                    const int n = j * kBK + 16 * kb + i16;
-                    key[kb] = n < L ? n : L - 1;
-                    const int64_t off = (int64_t)b * a.sk_b + (int64_t)h * a.sk_h + (int64_t)key[kb] * a.sk_t + 8 * g4;
-    #pragma unroll
-                    for (int ks = 0; ks < NKS; ++ks) {
-                        if constexpr (F32) {
-                            const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.k) + off + 32 * ks);
-                            kraw[kb][ks][0] = src[0];
-                            kraw[kb][ks][1] = src[1];
-                        } else {
-                            kraw[kb][ks][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.k) + off + 32 * ks);
-                        }
-                    }
-                };
-                // V rows, CPR lanes a row, 64 / CPR rows a pass, NVB passes at a time: into LDS as operands
-                constexpr int CPR = D / 8, NVP = kBK * CPR / 64, NVB = F32 ? 4 : 8, NB = NVP / NVB;
-                u32x4 vraw[NVB][2];
-                auto request_v = [&](int j, int batch) __attribute__((always_inline)) {
-    #pragma unroll
-                    for (int p = 0; p < NVB; ++p) {
-                        const int n = j * kBK + (batch * NVB + p) * (64 / CPR) + lane / CPR;
-                        const int64_t off = (int64_t)b * a.sv_b + (int64_t)h * a.sv_h + (int64_t)(n < L ? n : L - 1) * a.sv_t + 8 * (lane % CPR);
-                        if constexpr (F32) {
-                            const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.v) + off);
-                            vraw[p][0] = src[0];
-                            vraw[p][1] = src[1];
-                        } else {
-                            vraw[p][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.v) + off);
-                        }
-                    }
-                };
+    // ---- key and value rows of a tile.  Rows past the end: the last one, and zeros in its place as operands. ----
+    u32x4 kraw[4][NKS][2];
+    int key[4];
+    auto request_k = [&](int j, int kb) __attribute__((always_inline)) {
+        const int n = j * kBK + 16 * kb + i16;
+        key[kb] = n < L ? n : L - 1;
+        const int64_t off = (int64_t)b * a.sk_b + (int64_t)h * a.sk_h + (int64_t)key[kb] * a.sk_t + 8 * g4;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            if constexpr (F32) {
+                const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.k) + off + 32 * ks);
+                kraw[kb][ks][0] = src[0];
+                kraw[kb][ks][1] = src[1];
+            } else {
+                kraw[kb][ks][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.k) + off + 32 * ks);
+            }
+        }
+    };
+    // V rows, CPR lanes a row, 64 / CPR rows a pass, NVB passes at a time: into LDS as operands
+    constexpr int CPR = D / 8, NVP = kBK * CPR / 64, NVB = F32 ? 4 : 8, NB = NVP / NVB;
+    u32x4 vraw[NVB][2];
+    auto request_v = [&](int j, int batch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < NVB; ++p) {
+            const int n = j * kBK + (batch * NVB + p) * (64 / CPR) + lane / CPR;
+            const int64_t off = (int64_t)b * a.sv_b + (int64_t)h * a.sv_h + (int64_t)(n < L ? n : L - 1) * a.sv_t +
+                                8 * (lane % CPR);
+            if constexpr (F32) {
+                const u32x4* const src = reinterpret_cast<const u32x4*>(static_cast<const float*>(a.v) + off);
+                vraw[p][0] = src[0];
+                vraw[p][1] = src[1];
+            } else {
+                vraw[p][0] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.v) + off);
+            }
+        }
+    };
     // as much in flight as the registers hold (fp32 rows at head_dim 128: half of the keys)
     constexpr int KAHEAD = F32 && D == 128 ? 2 : 4;
     auto request_tile = [&](int j) __attribute__((always_inline)) {
@@ -168,12 +175,13 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
         }
     };
     // Multiplier of a row whose channels the four lanes (i, 0..3) hold.
-    // (The empty statement makes the row a new value behind the branch: the compiler otherwise keeps what it widened for
-    // the sum, of all rows at once.)
-    // The order of a per-head sum is that of the kernel that reads the rows on the general path: of q rows the attention
-    // kernel's (a lane's channels one after the other), of k rows the pre-pack's (eight channels, then chunks pairwise), so
-    // that the tile images are the same whoever writes them.
-    auto row_factor = [&](const NormArgs& n, u32x4 (&raw)[NKS][2], bool f32, int64_t stat, auto k_row) __attribute__((always_inline)) {
+    // (The empty statement makes the row a new value behind the branch: the compiler otherwise keeps what it widened
+    // for the sum, of all rows at once.)
+    // The order of a per-head sum is that of the kernel that reads the rows on the general path: of q rows the
+    // attention kernel's (a lane's channels one after the other), of k rows the pre-pack's (eight channels, then chunks
+    // pairwise), so that the tile images are the same whoever writes them.
+    auto row_factor = [&](const NormArgs& n, u32x4 (&raw)[NKS][2], bool f32, int64_t stat,
+                          auto k_row) __attribute__((always_inline)) {
         constexpr bool K_ROW = decltype(k_row)::value;
         float rs = 1.f;
         if (n.mode == 2) rs = n.rstd[stat];
@@ -254,9 +262,11 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks)
-                    Kf[kb][ks] = *reinterpret_cast<const u32x4*>(image + (16 * kb + i16) * G::KROW + ks * 64 + gsw * 16);
+                    Kf[kb][ks] =
+                        *reinterpret_cast<const u32x4*>(image + (16 * kb + i16) * G::KROW + ks * 64 + gsw * 16);
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) Vf[cb] = *reinterpret_cast<const u32x4*>(image + G::K_BYTES + (16 * cb + i16) * G::VROW + gsw * 16);
+            for (int cb = 0; cb < NCB; ++cb)
+                Vf[cb] = *reinterpret_cast<const u32x4*>(image + G::K_BYTES + (16 * cb + i16) * G::VROW + gsw * 16);
         } else {
             auto stage_v = [&](int batch) __attribute__((always_inline)) {
 #pragma unroll
@@ -292,7 +302,8 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
                     scale8(x, rs, gamma + D, ks);
                     rotate8(x, rr, ks);
                     u32x4 p = pack8<OP_F16>(x);
-                    asm volatile("" : "+v"(p));  // (here, not where it is used: the values ahead of it take twice the registers)
+                    // (here, not where it is used: the values ahead of it take twice the registers)
+                    asm volatile("" : "+v"(p));
                     Kf[kb][ks] = inside ? p : mk4(0u, 0u, 0u, 0u);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -352,8 +363,9 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
                     for (int r = 0; r < 4; ++r) O[cb][qb][r] *= alpha;
             }
         }
-        // O^T += V^T P^T.  The transposing read: of 16 lanes, lane s names 8 bytes of row s / 4, columns 4 (s % 4) .. + 3, and
-        // lane i gets column i of the four rows.  Group g takes keys 32 m + 16 g' + 4 g .. + 3 of channels 16 cb .. + 15.
+        // O^T += V^T P^T.  The transposing read: of 16 lanes, lane s names 8 bytes of row s / 4, columns 4 (s % 4) .. +
+        // 3, and lane i gets column i of the four rows.  Group g takes keys 32 m + 16 g' + 4 g .. + 3 of channels 16 cb
+        // .. + 15.
         asm volatile("" ::: "memory");  // (one wavefront's LDS accesses complete in order)
         const uint8_t* const tr = area + (4 * g4 + (i16 >> 2)) * S::VPITCH + (i16 & 3) * 8;
 #pragma unroll
@@ -361,17 +373,17 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
                 u32x4 vf;
+                uint8_t* const chunk = image + G::K_BYTES + (16 * cb + i16) * G::VROW + gsw * 16;
                 if constexpr (RESIDENT) {
                     vf = Vf[cb];
-                    if (m == 0) Vf[cb] = *reinterpret_cast<const u32x4*>(image + G::K_BYTES + (16 * cb + i16) * G::VROW + 64 + gsw * 16);
+                    if (m == 0) Vf[cb] = *reinterpret_cast<const u32x4*>(chunk + 64);
                 } else {
-                    const uint2 lo = __builtin_bit_cast(
-                        uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(tr + 32 * m * S::VPITCH + cb * 32)));
+                    const uint8_t* const src = tr + 32 * m * S::VPITCH + cb * 32;
+                    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)src));
                     const uint2 hi = __builtin_bit_cast(
-                        uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(tr + (32 * m + 16) * S::VPITCH + cb * 32)));
+                        uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(src + 16 * S::VPITCH)));
                     vf = mk4(lo.x, lo.y, hi.x, hi.y);
-                    if (rb == 0)
-                        *reinterpret_cast<u32x4*>(image + G::K_BYTES + (16 * cb + i16) * G::VROW + m * 64 + gsw * 16) = vf;
+                    if (rb == 0) *reinterpret_cast<u32x4*>(chunk + m * 64) = vf;
                 }
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) O[cb][qb] = mfma16<OP_F16>(vf, P[qb][m], O[cb][qb]);
@@ -380,7 +392,8 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
             if (rb == 0) {
 #pragma unroll
                 for (int d = 0; d < D; d += 64)
-                    *reinterpret_cast<u32x4*>(image + G::K_BYTES + (d + lane) * G::VROW + kBK * 2) = mk4(0u, 0u, 0u, 0u);
+                    *reinterpret_cast<u32x4*>(image + G::K_BYTES + (d + lane) * G::VROW + kBK * 2) =
+                        mk4(0u, 0u, 0u, 0u);
             }
         }
         asm volatile("" ::: "memory");
@@ -415,7 +428,8 @@ __global__ void __launch_bounds__(64 * kShortWaves) attn_short_kernel(const Attn
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         const int64_t off = (int64_t)b * a.so_b + (int64_t)h * a.so_h + (int64_t)row * a.so_t + 4 * c;
         if (a.out_f32)
-            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) =
+                make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
         else
             *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + off) =
                 make_uint2(pack2<OP_BF16>(o[0] * inv, o[1] * inv), pack2<OP_BF16>(o[2] * inv, o[3] * inv));
@@ -449,7 +463,8 @@ hipError_t launch_rows(const AttnArgs& a, const TableArgs& ta, const NormArgs& k
 hipError_t launch_attn_short(const AttnArgs& a, const TableArgs& ta, const NormArgs& kn, int D, int qb, bool resident,
                              hipStream_t s) {
     if (D == 128 && qb == 1) return launch_rows<128, 1>(a, ta, kn, resident, s);
-    if (D == 64) return qb == 1 ? launch_rows<64, 1>(a, ta, kn, resident, s) : launch_rows<64, 2>(a, ta, kn, resident, s);
+    if (D == 64)
+        return qb == 1 ? launch_rows<64, 1>(a, ta, kn, resident, s) : launch_rows<64, 2>(a, ta, kn, resident, s);
     return hipErrorInvalidValue;
 }
 

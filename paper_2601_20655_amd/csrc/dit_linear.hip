@@ -195,13 +195,13 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // Operand fragments.  A slice (32 contraction indices) takes FB fragments of w and TB of x and feeds
     // FB x TB MFMAs, walked by pairs of token blocks, both blocks of a pair on one w fragment before the next: of the
     // orders a power-limited MFMA loop was timed in (random operands), the A operand held for two products draws least
-    // (1,938 TFLOP/s; B held for four or eight 1,887; neither 1,880).  Block by block, w fragment by w fragment, and in pairs,
-    // us, new operands: 32,760 x 5,120 x 5,120 1,185 and 1,178 (medians 1,190 and 1,187: within what runs differ), fp32 rows
-    // 1,243 and 1,230, fused with per-head norms 3,823 and 3,804 (N = 15,360), 3,600 x 15,360 x 5,120 level.
-    // The w fragments are double-buffered and requested a slice ahead; the x fragments of a pair are refilled IN PLACE
-    // during the next pair (an LDS return into registers whose MFMAs have issued is safe), so only one set is held.
-    // The reads are inline assembly so that the waits can be counted: LDS returns in order, and the number
-    // of reads issued behind the ones a pair needs is a constant of the pair's place in the slice, so a
+    // (1,938 TFLOP/s; B held for four or eight 1,887; neither 1,880).  Block by block, w fragment by w fragment, and in
+    // pairs, us, new operands: 32,760 x 5,120 x 5,120 1,185 and 1,178 (medians 1,190 and 1,187: within what runs
+    // differ), fp32 rows 1,243 and 1,230, fused with per-head norms 3,823 and 3,804 (N = 15,360), 3,600 x 15,360 x
+    // 5,120 level. The w fragments are double-buffered and requested a slice ahead; the x fragments of a pair are
+    // refilled IN PLACE during the next pair (an LDS return into registers whose MFMAs have issued is safe), so only
+    // one set is held. The reads are inline assembly so that the waits can be counted: LDS returns in order, and the
+    // number of reads issued behind the ones a pair needs is a constant of the pair's place in the slice, so a
     // fragment is asked for 4 to 8 reads before its use.  The compiler itself waits
     // for LDS reads with lgkmcnt(0), which would drain that queue at every use.
     //
@@ -243,8 +243,8 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
     // loads that refill it are issued in the next step -- behind the barrier that ends the store, so that a
     // loading wavefront that has stored cannot overwrite what another one still stages.  Pieces of a staged
     // row are swizzled with the row number.  The accumulators start the next tile at zero.
-    // (Tried: non-temporal stores.  Level on new operands and for the kernel that reads the rows next: 32,760 x 5,120 x 5,120
-    // 1,172 and 1,171 us, fused rows of 3,600 x 40 and the attention on them 743 and 744.)
+    // (Tried: non-temporal stores.  Level on new operands and for the kernel that reads the rows next: 32,760 x 5,120 x
+    // 5,120 1,172 and 1,171 us, fused rows of 3,600 x 40 and the attention on them 743 and 744.)
     auto store_tile = [&](int tm, int tn, int stage_buf) __attribute__((always_inline)) {
         constexpr int ES = OUT_F32 ? 4 : 2;   // bytes per output element
         constexpr int RB = 64 * ES;           // bytes per staged row (the wavefront's 64 features)
@@ -252,7 +252,8 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         constexpr int RP = 4096 / RB;         // rows per pass
         constexpr int TBP = RP / BR;          // token blocks per pass
         uint8_t* const region = smem + stage_buf * kLinTileBytes + wave * 4096;
-        // (lane numbers the compiler cannot see through: what the store derives from them is not held through the step loop)
+        // (lane numbers the compiler cannot see through: what the store derives from them is not held through the step
+        // loop)
         int l = lane;
         asm volatile("" : "+v"(l));
         const int lr = l & 15, lg = l >> 4, rrow = l / PR, rp = l % PR;
@@ -588,7 +589,8 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
             // below: the x fragments of the pairs behind it and, from the second pair on, the next slice's w fragments
             if constexpr (P == 0) {
                 asm volatile("s_waitcnt lgkmcnt(4)"
-                             : "+v"(W[cur][0]), "+v"(W[cur][1]), "+v"(W[cur][2]), "+v"(W[cur][3]), "+v"(X[T]), "+v"(X[T + 1]));
+                             : "+v"(W[cur][0]), "+v"(W[cur][1]), "+v"(W[cur][2]), "+v"(W[cur][3]), "+v"(X[T]),
+                               "+v"(X[T + 1]));
             } else {
                 asm volatile("s_waitcnt lgkmcnt(8)" : "+v"(X[T]), "+v"(X[T + 1]));
             }
@@ -610,8 +612,8 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
                     read_w(W[nxt][wi], std::integral_constant<int, wi>(), nwb, nks);
                     read_w(W[nxt][wi + 1], std::integral_constant<int, wi + 1>(), nwb, nks);
                 }
-                // the loads (the w tile, needed a step from now, two chunks a token block behind the barrier; the x tile,
-                // needed two steps from now, one a token block of the next slice)
+                // the loads (the w tile, needed a step from now, two chunks a token block behind the barrier; the x
+                // tile, needed two steps from now, one a token block of the next slice)
                 if constexpr (LOADS && (m == 3 || m == 5)) {
                     constexpr int q = 2 * P + (m == 5) - 1;  // token blocks since the barrier
                     if constexpr (last && q >= 0 && 2 * q < NCH) {
@@ -633,12 +635,13 @@ __global__ void __launch_bounds__(64 * kLinWaves, 1) linear_kernel(const LinearA
         if (++kt == nK) {
             if constexpr (QKV) store_tile_qkv(tm, tn, xb == 0 ? SX - 1 : xb - 1);
             else store_tile(tm, tn, xb == 0 ? SX - 1 : xb - 1);
-            // The per-lane fragment offset is worked out again behind every store of a tile, from a lane number the compiler
-            // cannot see through: it is then a new value here, not one that has to survive the store, which has no register
-            // to spare for it (kept across it in the fused forms, it was spilled and reloaded INSIDE the step loop, and a
-            // reload from scratch memory there makes the compiler wait for every load in flight; kept in the plain forms, the
-            // store spilled 8 registers with 16-bit rows and 7 with fp32 ones, now none: 7,800 x 1,536 x 1,536 34.5 -> 33.4 us,
-            // 14,040 x 1,536 x 1,536 66.0 -> 64.7, 20,001 x 3,000 x 2,048 198.1 -> 195.1; large K and fp32 rows level).
+            // The per-lane fragment offset is worked out again behind every store of a tile, from a lane number the
+            // compiler cannot see through: it is then a new value here, not one that has to survive the store, which
+            // has no register to spare for it (kept across it in the fused forms, it was spilled and reloaded INSIDE
+            // the step loop, and a reload from scratch memory there makes the compiler wait for every load in flight;
+            // kept in the plain forms, the store spilled 8 registers with 16-bit rows and 7 with fp32 ones, now none:
+            // 7,800 x 1,536 x 1,536 34.5 -> 33.4 us, 14,040 x 1,536 x 1,536 66.0 -> 64.7, 20,001 x 3,000 x 2,048 198.1
+            // -> 195.1; large K and fp32 rows level).
             {
                 int l = lane;
                 asm volatile("" : "+v"(l));

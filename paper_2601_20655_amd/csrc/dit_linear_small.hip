@@ -178,8 +178,9 @@ __global__ void __launch_bounds__(512, (LinTile<TB, FB>::PAIR ? 4 : 2)) linear_t
     asm volatile("" ::: "memory");
 
     // ---- store: 16 token rows at a time through an area of the wavefront's own, so that rows leave in 16-byte pieces
-    // (Tried: non-temporal stores.  769 x 10,240 x 5,120 72.1 -> 70.6 us on the operands of the call before, 89.4 -> 88.7 on
-    // new ones, but level with the kernel that reads the rows next: cross-attention of 256 queries on them 92.7 and 92.8.)
+    // (Tried: non-temporal stores.  769 x 10,240 x 5,120 72.1 -> 70.6 us on the operands of the call before, 89.4 ->
+    // 88.7 on new ones, but level with the kernel that reads the rows next: cross-attention of 256 queries on them 92.7
+    // and 92.8.)
     constexpr int ES = OUT_F32 ? 4 : 2;
     constexpr int RB = 16 * FB * ES;  // bytes of a staged row: the wavefront's features
     constexpr int PR = RB / 16;       // pieces per row
