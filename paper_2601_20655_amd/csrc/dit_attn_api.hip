@@ -1307,6 +1307,6 @@ const char* dit_strerror(dit_status s) {
 
 const char* dit_last_hip_error(void) { return g_hip_error; }
 
-int dit_attn_version(void) { return 10700; }  // 1.7.0
+int dit_attn_version(void) { return 10800; }  // 1.8.0
 
 }  // extern "C"

@@ -96,8 +96,8 @@ constexpr int kOnce = 2;
 // agree behind it (660 bytes of spills a lane).  In-kernel stamps, 8 wavefronts, 7.75 key tiles on average: 38,600 ->
 // 32,300 clocks a query tile (lock step, first scores and their barrier 3,400 of it -> none).  Whole calls of 4 x
 // 32,760 queries x 40 heads 1,622 -> 1,488 us, kernel alone at 1 x 32,760 x 40, 9 key tiles 440 -> 386, 7,800 x 12, 3 key
-// tiles 24 -> 22.  What bounds it now, by counters at 4 to 12 key tiles (32,760 x 40): 14,800 clocks a query tile, of start
-// and end of the pass, conversion, maxima and store, and 2,610 a key tile, where the matrix cores take 2,048; at 8 key tiles
+// tiles 24 -> 22.  What bounds it now, by counters at 4 to 12 key tiles (32,760 x 40): 15,200 clocks a query tile, of start
+// and end of the pass, conversion, maxima and store, and 2,480 a key tile, where the matrix cores take 2,048; at 8 key tiles
 // they are busy 44 % of the time, the vector ALU 49 %, and wavefronts wait a quarter of theirs.
 //
 // PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
@@ -114,7 +114,7 @@ constexpr int kOnce = 2;
 // it into the wavefront's LDS area, free by then.  In registers (the plain kernel's way) there is no room for it here, in
 // LDS beside the next rows neither with 8 wavefronts (154 KiB are taken; with 4 there would be).  Row sums in fp32 over the unrounded probabilities, as in the plain kernel.  What the
 // form costs beside its steps: a tenth of the call for parking (2 x 32,760 x 12, 11 key tiles: 376 us, without its stores
-// and loads 337) and the second pass's first maxima: 24,000 clocks a query tile and 2,690 a key tile.  585 -> 489 us at
+// and loads 337) and the second pass's first maxima: 23,500 clocks a query tile and 2,670 a key tile.  585 -> 489 us at
 // 32,760 queries x 40 heads, 5 + 5 key tiles, resident keys (plain kernel before).  With all of O rewritten before the rows are staged 42 registers spilled: 532.
 template <int D, int QK_OP, int PV_OP, int NW, bool CHAIN = false, bool PIECES = false, bool TWO = false, int QBN = 2,
           bool ONCE = false>
