@@ -333,9 +333,10 @@ dit::SplitPlan choose_split(int64_t tiles, int64_t tiles_nw, int64_t tiles64, in
 // Every workgroup works on all keys of its head, so this pays while one round of workgroups takes the call.  us a call,
 // one after the other, general path and this (tokens x heads, 16-bit rows): head_dim 64, 16 rows: 256 x 4 16.0 and 9.3,
 // 413 x 8 16.1 and 11.4, 512 x 2 16.8 and 10.7, 1,024 x 4 19.3 and 15.7; 32 rows: 512 x 15 16.8 and 13.0, 1,024 x 8
-// 18.2 and 16.0; two rounds, 770 x 8, 20.7 and 27.0 (in one launch).  head_dim 128, 16 rows: 64 x 4 13.7 and 12.0, 256
-// x 8 16.5 and 15.1, 384 x 10 19.4 and 17.7; 413 x 8 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not taken); 32 rows spill
-// there: 413 x 12 25.7.
+// 18.2 and 16.0.  head_dim 128, 16 rows: 64 x 4 13.7 and 12.0, 256 x 8 16.5 and 15.1, 384 x 10 19.4 and 17.7; 413 x 8
+// 19.0 and 20.3, 640 x 2 21.1 and 24.0 (not taken); 32 rows spill there: 413 x 12 25.7.  In more than one round, on
+// packed tiles: head_dim 64, 1,024 x 12 19.2 and 24.4, 256 x 40 12.6 and 16.5; 128, 256 x 24 17.2 and 21.5, 256 x 160
+// 31.5 and 76.1.
 int dit::choose_short(int64_t L, int64_t BH, int D, int table_entries) {
     if (table_entries > kShortTable || L > (D == 64 ? 1024 : 384)) return 0;
     if (BH * ((L + 15) / 16) <= kCUs) return 1;

@@ -96,9 +96,9 @@ constexpr int kOnce = 2;
 // agree behind it (660 bytes of spills a lane).  In-kernel stamps, 8 wavefronts, 7.75 key tiles on average: 38,600 ->
 // 32,300 clocks a query tile (lock step, first scores and their barrier 3,400 of it -> none).  Whole calls of 4 x
 // 32,760 queries x 40 heads 1,622 -> 1,488 us, kernel alone at 1 x 32,760 x 40, 9 key tiles 440 -> 386, 7,800 x 12, 3 key
-// tiles 24 -> 22.  What bounds it now, by counters at 4 to 12 key tiles (32,760 x 40): 15,200 clocks a query tile, of start
-// and end of the pass, conversion, maxima and store, and 2,480 a key tile, where the matrix cores take 2,048; at 8 key tiles
-// they are busy 44 % of the time, the vector ALU 49 %, and wavefronts wait a quarter of theirs.
+// tiles 24 -> 22.  What bounds it now, by counters at 4 to 12 key tiles (32,760 x 40): 15,200 clocks a query tile, of
+// start and end of the pass, conversion, maxima and store, and 2,480 a key tile, where the matrix cores take 2,048; at
+// 8 key tiles they are busy 44 % of the time, the vector ALU 49 %, and wavefronts wait a quarter of theirs.
 //
 // PIECES: the sequence of keys that pv describes may be a range of the real one (pv.piece >= 0); the workgroup then
 // leaves its unnormalised output, running maxima and row sums in piece pv.piece of a.part_o / a.part_ml.
